@@ -49,6 +49,7 @@ typedef enum {
 
 #define SIP_MAX_V (1 << 19)        /* largest vocabulary the kernels support            */
 #define SIP_MAX_B (1 << 20)        /* most rows of one call                             */
+#define SIP_MAX_RESIDENT_V 32768   /* largest row that one workgroup holds in registers */
 #define SIP_MAX_K_LOGPROBS 64      /* largest k_logprobs                                */
 #define SIP_MAX_SHARDS 8           /* most vocabulary shards sip_sample_sharded() takes */
 #define SIP_MAX_SLOTS (1 << 20)    /* most slots a sampler state can have               */
@@ -82,15 +83,16 @@ typedef struct {
  *
  * Diagnostic: after a call has completed, the first 2 * B int32 of the workspace say, per row,
  * which code path finished it (path[B]) and what the finishing kernel made of it (why[B]).
- *   path: 1 = settled from the candidate list the one pass over the logits left behind; any
+ *   path: 1 = settled from the candidate list the one pass over the logits left behind, or, up to
+ *   SIP_MAX_RESIDENT_V entries, from the row held in registers; any
  *   other value = finished after reading the row again (normally from cache): 15 = from a second,
  *   longer candidate list (one more read of that row); 16 = by the row's workgroup over the whole
  *   row (plain temperature sampling without any filter: two more reads; a nucleus that reaches
  *   below the candidate list: four to six); anything else = the exact multi-pass path, the value
  *   naming the reason (2 top_k too large for any candidate list, 3-13 the candidate list could
- *   not prove the answer, 17-29 nor could the longer one, 14 vocabulary size outside the
- *   single-pass kernels).
- *   why: 1 = the finishing kernel settled the row; else why it passed the row on: 2 no list was
+ *   not prove the answer, 17-29 nor could the longer one), or 14: vocabulary size outside the
+ *   single-pass kernels (why = 1: settled from registers all the same).
+ *   why: 1 = the finishing kernel (or the one that holds the row) settled it; else why it passed the row on: 2 no list was
  *   made, 3 a chunk's list overflowed, 4 more distinct history tokens than the table of
  *   multiplicities holds, 5 list too long, 6 maximum not proven, 7 value span not representable,
  *   8 k-th / n-th largest not in the list, 9 too many equal values in one bin, 10 top_p <= 0,
@@ -98,7 +100,8 @@ typedef struct {
  *   14 no mass / exact-only shape.
  * Results mean the same whichever path ran.
  *
- * Kernels of a call (names as a profiler shows them): stream_kernel (the one pass over the
+ * Kernels of a call (names as a profiler shows them): resident_kernel alone up to
+ * SIP_MAX_RESIDENT_V entries; else stream_kernel (the one pass over the
  * logits), then finish_rescue_kernel for batches of no more rows than the device has compute
  * units, else finish_kernel followed by rescue_kernel (which returns at once when no row was
  * passed on); exact_kernel alone for vocabulary sizes outside the single-pass kernels.

@@ -17,6 +17,7 @@
 #include "sip_finish.h"
 #include "sip_fused.h"
 #include "sip_handoff.h"
+#include "sip_resident.h"
 #include "sip_state.h"
 #include "sip_stream.h"
 
@@ -32,6 +33,14 @@ struct Plan {
   size_t final_lds;
 };
 
+// Rows up to here are held in registers by one workgroup (sip_resident.h).  At the line both ways
+// cost the same on an easy row (bf16 V = 31931, 67 rows: 20.4 us against 13.0 + 13.0 us for the
+// streaming and the finishing kernel; fp32 V = 28520, 43 rows: 27.6 against 11.5 + 17.8 us), below
+// it the one kernel wins (fp32 V = 23702 greedy: 6.8 against 14.5 us), and on rows whose nucleus
+// outgrows a candidate list it wins everywhere (V = 32000, 4 rows: 25.7 against 77.6 us).  Beyond,
+// the row no longer fits 16 waves x 128 registers.
+constexpr int kResidentMaxV = SIP_MAX_RESIDENT_V;
+static_assert(kResidentMaxV == 1024 * 32, "the largest variant launched below");
 constexpr int kFastMinV = 16384;
 constexpr int kFastMaxV = 262144;
 constexpr int kFastMinPiece = 8192;      // smallest vocabulary shard: its sample blocks (at most 32 of 256 elements) must fit
@@ -289,6 +298,30 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
   const DeviceSetup* dev = device_setup();
   if (!dev) return SIP_ERR_HIP;
   sip::Args a = a_in;
+  hipEvent_t ev[6];
+  for (int i = 0; i < 6; ++i) { ev[i] = g_prof[i]; g_prof[i] = nullptr; }
+  const bool timed = ev[0] || ev[1] || ev[2] || ev[3] || ev[4] || ev[5];
+  if (a.V <= kResidentMaxV) {
+    // a workgroup holds its whole row in registers: one kernel
+    if (state) {
+      a.call_tick = a.rescue_tick;
+      hipLaunchKernelGGL(sip::state_take_tick_kernel, dim3(1), dim3(64), 0, stream, head, a.call_tick);
+    }
+    const bool f32 = dtype == SIP_F32;
+    auto kern = a.V <= 4096    ? (f32 ? sip::resident_kernel<SIP_F32, 512, 8> : sip::resident_kernel<SIP_BF16, 512, 8>)
+                : a.V <= 8192  ? (f32 ? sip::resident_kernel<SIP_F32, 1024, 8> : sip::resident_kernel<SIP_BF16, 1024, 8>)
+                : a.V <= 16384 ? (f32 ? sip::resident_kernel<SIP_F32, 1024, 16> : sip::resident_kernel<SIP_BF16, 1024, 16>)
+                               : (f32 ? sip::resident_kernel<SIP_F32, 1024, 32> : sip::resident_kernel<SIP_BF16, 1024, 32>);
+    const dim3 threads(a.V <= 4096 ? 512 : 1024);
+    if (timed) {
+      hipExtLaunchKernelGGL(kern, dim3(B), threads, 0, stream, ev[0], ev[1], 0, a);
+      for (int i = 2; i < 6; ++i)
+        if (ev[i]) (void)hipEventRecord(ev[i], stream);     // no second and third kernel: empty intervals
+    } else {
+      hipLaunchKernelGGL(kern, dim3(B), threads, 0, stream, a);
+    }
+    return hipGetLastError() == hipSuccess ? SIP_OK : SIP_ERR_HIP;
+  }
   const size_t words = ((size_t)a.V + 31) / 32;
   if (!plan.fast) {
     // every row takes the exact multi-pass path
@@ -306,9 +339,6 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
   auto k_stream = dtype == SIP_F32 ? sip::stream_kernel<SIP_F32, SH> : sip::stream_kernel<SIP_BF16, SH>;
   auto k_rescue = dtype == SIP_F32 ? sip::rescue_kernel<SIP_F32, SH> : sip::rescue_kernel<SIP_BF16, SH>;
   const size_t dyn = std::max(plan.final_lds, 2 * words * sizeof(uint32_t));
-  hipEvent_t ev[6];
-  for (int i = 0; i < 6; ++i) { ev[i] = g_prof[i]; g_prof[i] = nullptr; }
-  const bool timed = ev[0] || ev[1] || ev[2] || ev[3] || ev[4] || ev[5];
   // The pass over the logits, then one workgroup per row on what it left.  A batch of no more rows
   // than the device has compute units: the workgroup also takes its row through the heavier logic
   // if the list does not settle it (sip_fused.h).  Larger batches: the lean finishing kernel, two

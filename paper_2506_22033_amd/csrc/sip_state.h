@@ -115,5 +115,10 @@ __global__ __launch_bounds__(kStateThreads) void state_assign_kernel(StateHeader
 __global__ void state_tick_kernel(StateHeader* head) {
   if (blockIdx.x == 0 && threadIdx.x == 0) head->tick += 1;
 }
+// A call that one kernel serves whole takes its number before that kernel: every row needs it, and
+// calls in flight at once on one state each get their own.
+__global__ void state_take_tick_kernel(StateHeader* head, unsigned long long* call_tick) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *call_tick = atomicAdd(&head->tick, 1ull);
+}
 
 }  // namespace sip

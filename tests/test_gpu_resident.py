@@ -1,0 +1,88 @@
+"""Rows that one workgroup holds in registers (vocabularies up to 32768): sizes at the edges of the
+kernel's variants and of its loads, every kind of row, pieces, a separate prompt, a state."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2506_22033_amd as sip
+import workloads
+from oracle import sip_oracle as O
+from tests import sip_harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(rng, B, V):
+    kind = np.arange(B) % 10
+    params = dict(temperature=np.choose(kind, [0.0, 1.0, 0.7, 1.3, 0.9, 1.0, 0.3, 0.0, 1.0, 1e-3]),
+                  top_k=np.choose(kind, [0, 0, 40, min(V, 4096), 0, 1, 1000, 0, 3, 0]),
+                  top_p=np.choose(kind, [1.0, 1.0, 0.95, 0.9, 0.999, 1.0, 0.8, 1.0, 1.0, 0.5]),
+                  min_p=np.choose(kind, [0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.05, 0.0, 0.02, 0.0]),
+                  repetition_penalty=rng.choice([1.0, 1.3, 0.8], B),
+                  frequency_penalty=rng.choice([0.0, 0.4], B),
+                  presence_penalty=rng.choice([0.0, 0.3, -0.2], B))
+    hist = [rng.integers(-1, V + 1, int(rng.choice([0, 3, 700]))).tolist() for _ in range(B)]
+    return params, hist
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("V", [1, 7, 511, 4096, 4097, 8192, 8193, 16384, 16385, 20011, 32767, 32768])
+def test_vocabularies_at_the_edges_of_the_variants(V, bf16):
+    rng = np.random.default_rng(V + bf16)
+    B = 21
+    z = (rng.standard_normal((B, V)) * 2.5).astype(np.float32)
+    z[4, : V // 2] = -np.inf
+    z[11] = np.round(z[11], 1)                                # many equal values
+    z[15] = 0.25                                              # all of them equal
+    if V > 100:
+        z[13, 3:] = -np.inf                                   # fewer finite entries than logprobs asked for
+        z[16, 17] = 60.0
+    params, hist = _rows(rng, B, V)
+    w = H.custom(f"resident_{V}", workloads.f32_to_bf16_bits(z) if bf16 else z, params, hist, k_logprobs=5)
+    d = H.to_device(w)
+    for step in (0, 1):
+        H.compare(w, H.run_gpu(d, 3, step), 3, step)
+    if V >= 4096 and not bf16:
+        assert (H.last_row_why == 1).mean() > 0.8, H.last_row_why
+
+
+@pytest.mark.parametrize("t,V_shard,bf16", [(2, 4, False), (3, 5000, True), (8, 4096, False), (1, 9000, True)])
+def test_pieces(t, V_shard, bf16):
+    rng = np.random.default_rng(t)
+    B, V = 11, t * V_shard
+    z = (rng.standard_normal((B, V)) * 2.0).astype(np.float32)
+    params, hist = _rows(rng, B, V)
+    zz = workloads.f32_to_bf16_bits(z) if bf16 else z
+    w = H.custom("pieces", zz, params, hist, k_logprobs=2)
+    d = H.to_device(w)
+    shards = [H.logits_to_device(np.ascontiguousarray(zz[:, i * V_shard:(i + 1) * V_shard])) for i in range(t)]
+    out = sip.sip_sample_sharded(sip.ShardTable(shards, V_shard), d.params, d.indptr, d.tokens, 5, 1, 2)
+    torch.cuda.synchronize()
+    H.compare(w, tuple(x.cpu().numpy() for x in out), 5, 1)
+    whole = H.run_gpu(d, 5, 1)
+    for x, y in zip(out, whole):
+        assert np.array_equal(x.cpu().numpy(), y)
+
+
+def test_counts_beyond_the_counters_and_a_separate_prompt():
+    """A history that repeats a token more often than a 15-bit counter holds (general path), one
+    just within, and prompt tokens, which only the repetition penalty looks at."""
+    rng = np.random.default_rng(9)
+    B, V = 4, 6000
+    z = (rng.standard_normal((B, V)) * 2.0).astype(np.float32)
+    params = dict(temperature=1.0, top_k=50, frequency_penalty=[1e-4, 1e-4, 0.0, 0.3],
+                  presence_penalty=[0.0, 0.1, 0.2, 0.3], repetition_penalty=1.2)
+    hist = [[7] * 40000, [7] * 32767, [7] * 40000, [1, 2, 2]]
+    w = H.custom("long", z, params, hist, k_logprobs=3)
+    d = H.to_device(w)
+    H.compare(w, H.run_gpu(d, 1, 0), 1, 0)
+    assert (H.last_row_why == [4, 1, 1, 1]).all(), H.last_row_why
+    prompts = [rng.integers(0, V, 3000).tolist() for _ in range(B)]
+    p_ind = torch.from_numpy(np.concatenate(([0], np.cumsum([len(p) for p in prompts]))).astype(np.int64)).to(H.DEV)
+    p_tok = torch.from_numpy(np.concatenate(prompts).astype(np.int32)).to(H.DEV)
+    out = sip.sip_sample_call(logits=d.logits, V=V, params=d.params, hist_indptr=d.indptr, hist_tokens=d.tokens,
+                              prompt_indptr=p_ind, prompt_tokens=p_tok, seed=1, step=0, k_logprobs=3)
+    torch.cuda.synchronize()
+    ref = O.sample_batch(w.logits, w.params, w.hist_indptr, w.hist_tokens, 1, 0, 3,
+                         prompt_indptr=p_ind.cpu().numpy(), prompt_tokens=p_tok.cpu().numpy())
+    H.check_rows("prompt", range(B), ref, tuple(x.cpu().numpy() for x in out), 3)
