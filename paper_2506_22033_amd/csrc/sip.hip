@@ -89,7 +89,7 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t = 0) {
   // the streaming kernel marks a chunk's history tokens in an LDS bitmap of kChunkBitsMax bits:
   // cut finer (first at the piece boundaries, then inside the pieces) until a chunk fits
   {
-    const int unit = sip::kWave * (dtype == SIP_F32 ? 4 : 8);
+    const int unit = sip::kChunkUnit;
     const int n_units = (Vp + unit - 1) / unit;
     auto max_chunk = [&](int S) {
       return S >= pieces ? (n_units + S / pieces - 1) / (S / pieces) * unit : pieces / S * Vp;
@@ -281,6 +281,7 @@ sip_status sample_impl(const void* logits, int32_t B, int32_t V, int64_t row_str
   a.fin_inv = (65536 + a.fin_tps - 1) / a.fin_tps;
   a.chunks = reinterpret_cast<sip::ChunkOut*>(ws + lay.chunks);
   a.cand = reinterpret_cast<uint2*>(ws + lay.cand);
+  a.bf16 = dtype == SIP_BF16;
   a.S = plan.S; a.cap_c = plan.cap_c; a.nc_cap = plan.nc_cap;
   a.row_why = a.row_path + B;
   a.rescue_n = reinterpret_cast<int*>(ws + lay.rescue);

@@ -25,8 +25,16 @@ struct ChunkOut {
   float Tc;                 // every element of the chunk with z >= Tc is in the segment
   int R;                    // integer reference exponent of `bulk`
   unsigned int cnt;         // entries in the chunk's segment, or kCntOverflow
-  unsigned int pad[3];
+  unsigned int n_blk;       // block masses at the end of the segment (rows without any filter), 0 = none
+  unsigned int pad[2];
 };
+// A row without any filter is drawn over all its elements.  For such a row the streaming kernel
+// also leaves the bulk mass of every block of kBlkElems consecutive elements: fp32, in units of 2^R,
+// the chunk's blocks in order, the last of them ending with the chunk's segment.  Chunks (and the
+// chunks of a shard) begin at multiples of kChunkUnit, so that blocks and chunks agree.
+constexpr int kBlkShift = 9, kBlkElems = 1 << kBlkShift;
+constexpr int kChunkUnit = 512;
+static_assert(kChunkUnit % kBlkElems == 0, "a block lies in one chunk");
 
 // What the streaming kernel (the workgroup of a row's first chunk) leaves for the finishing
 // kernel about row b: its sampling parameters, the extent of its history in Args::tokens and
@@ -67,6 +75,7 @@ struct Args {
   int fin_tps, fin_inv;     // finishing kernel: threads per list segment (512 / S), and ceil(2^16 / that)
   ChunkOut* chunks;         // [B * S]
   uint2* cand;              // [B * S * cap_c]  (value bits, index | tag): one segment per chunk
+  int bf16;                 // the logits' type, for kernels that are not instantiated for each
   int S;                    // chunks per row
   int cap_c;                // list entries per chunk segment
   int nc_cap;               // longest list any finishing path can hold
@@ -443,6 +452,14 @@ __device__ __forceinline__ uint32_t dpp_scan_add_u32(uint32_t v) { SIP_DPP_STEPS
 __device__ __forceinline__ uint32_t dpp_scan_max_u32(uint32_t v) { SIP_DPP_STEPS(op_max, 0u) return v; }
 __device__ __forceinline__ uint32_t dpp_scan_min_u32(uint32_t v) { SIP_DPP_STEPS(op_min, 0xFFFFFFFFu) return v; }
 #undef SIP_DPP_STEPS
+// Sum over the wave in a fixed order of additions; the total is in lane 63.
+__device__ __forceinline__ float dpp_scan_add_f32(float x) {
+#define SIP_DPPF(CTRL, RM) x = x + __uint_as_float(dpp_mov<CTRL, RM>(0u, __float_as_uint(x)));
+  SIP_DPPF(0x111, 0xf) SIP_DPPF(0x112, 0xf) SIP_DPPF(0x114, 0xf) SIP_DPPF(0x118, 0xf)
+  SIP_DPPF(0x142, 0xa) SIP_DPPF(0x143, 0xc)
+#undef SIP_DPPF
+  return x;
+}
 __device__ __forceinline__ unsigned long long dpp_scan_add_u64(unsigned long long v) {
 #define SIP_DPP64(CTRL, RM)                                                                   \
   v += ((unsigned long long)dpp_mov<CTRL, RM>(0u, (uint32_t)(v >> 32)) << 32) | dpp_mov<CTRL, RM>(0u, (uint32_t)v);

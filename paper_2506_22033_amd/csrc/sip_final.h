@@ -878,7 +878,7 @@ __device__ __attribute__((noinline)) void restream_row(const Args& a, const int 
     for (int w = 0; w < kFinalWaves; ++w) o.bulk += fs.r64[w];
     o.Tc = Tc; o.R = R;
     o.cnt = fs.rq_n;
-    o.pad[0] = o.pad[1] = o.pad[2] = 0;
+    o.n_blk = 0; o.pad[0] = o.pad[1] = 0;
     a.chunks[(size_t)b * a.S] = o;
   }
   // what this workgroup wrote to global memory is read back by other waves of it

@@ -2,7 +2,7 @@
 // kernel left behind -- a list of a few thousand (value, index) entries that holds every
 // element at or above a value threshold and every element that carries a penalty, plus the
 // integer mass of everything else -- into the row's token, its logprob and the best-n list.
-// It never reads the logits.
+// It never reads the logits (but for one block of a row without any filter).
 //
 // Steps (Sec. 2.1 step 3 (1)-(3); Sec. 5.1 ApplyPenalty / temperature / softmax / filters /
 // draw), every sum an integer sum (masses in units of 2^-40 of the maximum's mass) so that no
@@ -20,7 +20,9 @@
 //       or by descending over the distinct keys of a bin with many ties) while another wave
 //       ranks the best-n;
 //   (6) draw: kept sets of up to 64 entries by that same wave from its registers; larger
-//       ones through a histogram of kept mass over 1024 vocabulary-index bins.
+//       ones through a histogram of kept mass over 1024 vocabulary-index bins; rows without any
+//       filter through the masses of the row's blocks, of which the one that holds the crossing is
+//       read again.
 //
 // Whatever the list cannot prove (a cut that may lie below the completeness threshold, an
 // overflow, a bin with too many members, ...) makes the row's number go to the rescue queue
@@ -43,7 +45,10 @@ constexpr int kFinTopMax = 256;                        // entries at or above th
 constexpr int kFinKeySteps = 64;                       // distinct keys of one bin that are stepped through
 constexpr uint32_t kFinNone = 0xFFFFFFFFu;
 constexpr int kFinDrawBig = -1;                        // internal: the draw goes through the index histogram
+constexpr int kFinDrawRow = -2;                        // internal: no filter, the draw goes through the row's block masses
+constexpr int kFinWholeRow = 16;                       // settled, over the whole row (see row_path in sip.h)
 static_assert(kFinBPT == 2, "scan code below is written for two bins per thread");
+static_assert(kFinMembers >= kBlkElems && kFinBins >= kBlkElems, "tables of a block's elements");
 
 struct __align__(16) FinShared {
   uint32_t hcnt[kFinBins];                  // entries per value bin
@@ -91,7 +96,7 @@ struct FinHint {
   float T = 0.0f;            // every element of the row above T is in the list
 };
 
-// Row b, start to finish.  Returns 1 (finished: outputs written) or the reason why the list
+// Row b, start to finish.  Returns 1 or kFinWholeRow (finished: outputs written) or the reason why the list
 // does not settle the row.  Every return value is workgroup-uniform.
 __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared& fs, FinHint* hint = nullptr) {
   constexpr int NT = kFinThreads;
@@ -128,6 +133,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   // wait for the records.
   // (The same goes for the part of the chunk summary that the exits do not look at.)
   unsigned long long my_bulk = 0;
+  bool have_blocks;                        // uniform: every chunk left its block masses
   auto list_is_used = [&]() {
 #pragma unroll
     for (int r = 0; r < CR; ++r) asm volatile("" ::"v"(creg[r].x), "v"(creg[r].y));
@@ -141,6 +147,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   int R;
   {
     if (lane < S) { my_cnt = co.cnt; my_bulk = co.bulk; }
+    have_blocks = __all(lane >= S || co.n_blk > 0);
     Tc = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(co.Tc)));   // the chunks of a row share
     R = __builtin_amdgcn_readfirstlane(co.R);                                                      // threshold and exponent
   }
@@ -667,7 +674,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
         key_cut = max(key_k, key_p);
       }
     } else if (code == 0 && !k_act && !minp_bounds) {
-      code = minp_on ? 12 : 13;                                                // min-p reaches below the list / no filter at all
+      code = minp_on ? 12 : (have_blocks ? kFinDrawRow : 13);                  // min-p reaches below the list / no filter at all
     }
     if (code == 0) {
       // ---- (6) draw.  The kept set is a range [0, n_hi) of the sorted list minus the entries of
@@ -797,13 +804,136 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     lds_barrier();
     code = fs.token == kFinNone ? 14 : 1;
   }
+  int settled = 1;
+  if (code == kFinDrawRow) {
+    // ---- (6'') no filter: the mass of every block of the row (512 elements) is its
+    // bulk mass, left by the streaming kernel, plus that of the list entries in it; prefix; and only
+    // the block that holds the crossing is read again, 1 or 2 KB.  (Re-reading the row for this, as
+    // rescue_row does, took 55 us of the 73 us of bf16 V = 151643, 256 rows.)
+    constexpr int sh = kBlkShift;
+    const uint32_t n_blk = ((uint32_t)V + (1u << sh) - 1) >> sh;               // <= kFinBins: V <= 2^18
+    for (int i = tid; i < kBlkElems; i += NT) fs.fill[i] = 0;
+    // 2^R units -> 2^-40 of the maximum's mass
+    const double x = fmin(fmax((double)R + 40.0 - (double)m * 1.4426950408889634074, -1000.0), 61.0);
+    const double xi = floor(x), unit = ldexp((double)__builtin_amdgcn_exp2f((float)(x - xi)), (int)xi);
+    for (int bt = 0; bt < nb; ++bt) {
+      if (nb > 1) {
+        load_batch(bt);
+        drop_beyond(bt);
+      }
+#pragma unroll
+      for (int r = 0; r < CR; ++r)
+        if (live(bt, r) && creg[r].y != kFinNone) {
+          if (nb > 1) creg[r].x = key_of(scaled_s(__uint_as_float(creg[r].x)));
+          const unsigned long long E = mass(value_of(creg[r].x));
+          if (E) atomicAdd(&fs.hidx[creg[r].y >> sh], E);
+        }
+    }
+    unsigned long long w[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t g = min(2u * (uint32_t)tid + (uint32_t)j, n_blk - 1);     // its chunk starts at floor(ch * n_blk / S)
+      const uint32_t ch = ((g + 1) * (uint32_t)S - 1) / n_blk;
+      const uint32_t first = ch * n_blk / (uint32_t)S, next = (ch + 1) * n_blk / (uint32_t)S;
+      const float* end = reinterpret_cast<const float*>(a.cand + ((size_t)b * (size_t)S + ch + 1) * (size_t)a.cap_c);
+      const float f = end[(int)(g - first) - (int)(next - first)];
+      w[j] = 2u * (uint32_t)tid + (uint32_t)j < n_blk ? (unsigned long long)fmin((double)f * unit, 4.0e18) : 0ull;
+    }
+    lds_barrier();
+    w[0] += fs.hidx[2 * tid]; w[1] += fs.hidx[2 * tid + 1];
+    const unsigned long long minc = dpp_scan_add_u64(w[0] + w[1]);
+    if (lane == kWave - 1) fs.r64[wave] = minc;
+    lds_barrier();
+    unsigned long long ex = minc - w[0] - w[1], S3 = 0;
+#pragma unroll
+    for (int ww = 0; ww < kFinWaves; ++ww) {
+      const unsigned long long m64 = fs.r64[ww];
+      if (ww < wave) ex += m64;
+      S3 += m64;
+    }
+    const unsigned long long target = (__umul64hi(j24, S3) << 40) | ((j24 * S3) >> 24);    // floor(j * S3 / 2^24)
+    if (ex <= target && target < ex + w[0]) { fs.bin_d = 2 * tid; fs.before_d = ex; }
+    ex += w[0];
+    if (ex <= target && target < ex + w[1]) { fs.bin_d = 2 * tid + 1; fs.before_d = ex; }
+    lds_barrier();
+    const int blk = fs.bin_d;
+    if (blk < 0) return 14;                                                    // uniform (no mass)
+    for (int bt = 0; bt < nb; ++bt) {
+      if (nb > 1) {
+        load_batch(bt);
+        drop_beyond(bt);
+      }
+#pragma unroll
+      for (int r = 0; r < CR; ++r)
+        if (live(bt, r) && creg[r].y != kFinNone && (int)(creg[r].y >> sh) == blk) {
+          if (nb > 1) creg[r].x = key_of(scaled_s(__uint_as_float(creg[r].x)));
+          const uint32_t q = atomicAdd(&fs.n_memb, 1u);                        // (a block's elements fit)
+          fs.m_key[q] = creg[r].x; fs.m_E[q] = mass(value_of(creg[r].x));
+          fs.fill[creg[r].y & ((1u << sh) - 1)] = q + 1;
+        }
+    }
+    lds_barrier();
+    if (wave == 0) {
+      // lane l has the block's elements 8l .. 8l + 7
+      const int e0 = (blk << sh) + lane * 8;
+      const char* row = reinterpret_cast<const char*>(a.logits) + (size_t)b * (size_t)a.row_stride * (a.bf16 ? 2 : 4);
+      uint32_t raw[8];
+      if (a.bf16) {                                                            // uniform
+        const uint4 q = *reinterpret_cast<const uint4*>(row + (size_t)min(e0, (V - 1) / 8 * 8) * 2);
+        const uint32_t w4[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) raw[i] = (i & 1) ? w4[i / 2] & 0xFFFF0000u : w4[i / 2] << 16;
+      } else {
+        const int e_last = (V - 1) / 4 * 4;
+        const uint4 q0 = *reinterpret_cast<const uint4*>(row + (size_t)min(e0, e_last) * 4);
+        const uint4 q1 = *reinterpret_cast<const uint4*>(row + (size_t)min(e0 + 4, e_last) * 4);
+        raw[0] = q0.x; raw[1] = q0.y; raw[2] = q0.z; raw[3] = q0.w;
+        raw[4] = q1.x; raw[5] = q1.y; raw[6] = q1.z; raw[7] = q1.w;
+      }
+      const BulkRef ref = make_bulk_ref(Tc, rp);
+      auto element = [&](int i, float& z) -> unsigned long long {              // mass of element e0 + i; z: its s
+        z = __uint_as_float(raw[i]);
+        if (e0 + i >= V) return 0ull;
+        const uint32_t slot = fs.fill[(e0 + i) & (kBlkElems - 1)];
+        if (slot) { z = value_of(fs.m_key[slot - 1]); return fs.m_E[slot - 1]; }
+        const float t = bulk_term(z, ref);
+        z = scaled_s(z);
+        return (unsigned long long)fmin((double)t * unit, 4.0e18);
+      };
+      unsigned long long mine = 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) { float z; mine += element(i, z); }
+      unsigned long long C = fs.before_d + dpp_scan_add_u64(mine) - mine;
+      // the first element whose running mass exceeds the target; the blocks' sums are rounded, so it
+      // can also be that none does: then the last one that has any mass
+      uint32_t tok = kFinNone, tok_key = 0, last = kFinNone, last_key = 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        float z;
+        const unsigned long long E = element(i, z);
+        C += E;
+        if (E) {
+          last = (uint32_t)(e0 + i); last_key = key_of(z);
+          if (tok == kFinNone && C > target) { tok = last; tok_key = last_key; }
+        }
+      }
+      const unsigned long long hit = __ballot(tok != kFinNone), any = __ballot(last != kFinNone);
+      const int src = hit ? __ffsll((long long)hit) - 1 : (any ? 63 - __clzll((long long)any) : 0);
+      if (lane == src && (hit || any)) {
+        fs.token = hit ? tok : last; fs.token_key = hit ? tok_key : last_key;
+      }
+    }
+    lds_barrier();
+    code = fs.token == kFinNone ? 14 : 1;
+    settled = kFinWholeRow;
+  }
   if (code != 1) return code;                                                  // uniform
   if (tid == 0) {
     double lnZ;
     total_mass(lnZ);
     emit(fs.token, fs.token_key, lnZ);
   }
-  return 1;
+  return settled;
 }
 
 __global__ __launch_bounds__(kFinThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void finish_kernel(Args a_by_value) {
@@ -818,8 +948,8 @@ __global__ __launch_bounds__(kFinThreads) __attribute__((amdgpu_waves_per_eu(4, 
   const int code = finish_row(a, b, fs);
   if (threadIdx.x == 0) {
     a.row_path[b] = code;
-    a.row_why[b] = code;
-    if (code != 1) {
+    a.row_why[b] = code == kFinWholeRow ? 13 : code;
+    if (code != 1 && code != kFinWholeRow) {
       const int q = atomicAdd(a.rescue_n, 1);
       if (q >= 0 && q < a.B) a.rescue_rows[q] = b;
     }

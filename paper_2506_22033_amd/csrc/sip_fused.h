@@ -27,9 +27,9 @@ __global__ __launch_bounds__(kFinalThreads) void finish_rescue_kernel(Args a_by_
   const int code = finish_row(a, b, u.fs, &hint);
   if (threadIdx.x == 0) {
     a.row_path[b] = code;
-    a.row_why[b] = code;
+    a.row_why[b] = code == kFinWholeRow ? 13 : code;
   }
-  if (code == 1) return;                     // uniform
+  if (code == 1 || code == kFinWholeRow) return;                     // uniform
   __syncthreads();
   RescueSeen seen;
   if (hint.valid) { seen.why = code; seen.retry_ok = hint.retry_ok; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }

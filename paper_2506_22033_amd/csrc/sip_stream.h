@@ -35,6 +35,7 @@ constexpr int kSampleSize = 8192;           // elements of a row the threshold i
 constexpr int kQueueCap = 480;              // entries of one wave's LDS candidate queue
 constexpr int kChunkCap = kStreamWaves * kQueueCap;   // entries of one chunk's segment in the workspace
 constexpr int kChunkBitsMax = 73728;        // most elements a chunk may have (history bitmap: 9 KB of LDS)
+constexpr int kBlkMax = kChunkBitsMax / kBlkElems;   // blocks of the longest chunk
 constexpr int kStreamHistRegs = 8;          // history tokens a thread requests at once
 constexpr float kBulkScale = 1073741824.0f; // 2^30
 
@@ -73,6 +74,11 @@ __device__ __forceinline__ bool whole_sample(int target, int V) {
   return target >= kWholeFrom && (uint32_t)target * (uint32_t)kSampleSize <= (uint32_t)kTailRank * (uint32_t)V;
 }
 
+// No filter at all: every element of the row may be drawn (rp.greedy excluded by the caller).
+__device__ __forceinline__ bool unfiltered(const RowParams& r, int V) {
+  return !(r.top_k >= 2 && r.top_k < V) && !(r.top_p < 1.0f) && !(r.min_p > 0.0f);
+}
+
 // How many of the row's largest elements the candidate list should hold; 0 = this row
 // cannot be finished from a candidate list (k is too large) and takes the exact multi-pass
 // path instead.
@@ -81,8 +87,8 @@ __device__ __forceinline__ int candidate_target(const RowParams& r, const Args& 
   if (r.greedy) return 512;
   const int k = (r.top_k >= 2 && r.top_k < a.V) ? r.top_k : 0;
   const bool p_on = r.top_p < 1.0f, minp_on = r.min_p > 0.0f;
-  if (k == 0 && !p_on && !minp_on) return 1024;       // plain temperature sampling: the list serves the maximum
-                                                      // and best-n, the draw re-reads the row
+  if (k == 0 && !p_on && !minp_on) return 512;        // plain temperature sampling: the list serves the maximum
+                                                      // and best-n, as with greedy rows
   int t;
   if (k > 0) {
     // top-k needs its k largest in the list.  The threshold is the j-th largest of kSampleSize
@@ -157,9 +163,13 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   __shared__ unsigned long long red64[kStreamWaves];
   __shared__ uint32_t wave_cnt[kStreamWaves];
   __shared__ uint32_t key_thr, need_thr;            // 13-bit key of the threshold bin; entries still wanted from inside it
+  __shared__ float blk_mass[kBlkMax];
   __shared__ uint32_t sub_hist[32];                 // that bin, split by the next 5 key bits
 
-  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+  // (the wave's number, and further down R, in a scalar register: as vector registers they were
+  // spilled, and a store to scratch ahead of the loads makes every wait for one of them a wait for
+  // all -- 3 us of the 33 at fp32 V = 152064, 256 rows)
+  const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
   // Workgroups are handed to the 8 XCDs round-robin by their id.  The chunks of one row read
   // the same sample, so they are renumbered to land on the same XCD (and its L2): id i works
   // on logical chunk (i % 8) * (n / 8) + i / 8 when n, the grid size, is a multiple of 8.
@@ -179,8 +189,8 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   const int lc = !SH ? ch : (split ? ch - sh * S_sh : 0);
   const int Vl = SH ? a.V_shard : V;
   const uint32_t ibase = SH ? (uint32_t)(sh * Vl) : 0u;
-  const int c0 = chunk_begin(lc, Vl, S_sh, kWave * EPL);
-  const int c1 = chunk_begin(lc + 1, Vl, S_sh, kWave * EPL);
+  const int c0 = chunk_begin(lc, Vl, S_sh, kChunkUnit);
+  const int c1 = chunk_begin(lc + 1, Vl, S_sh, kChunkUnit);
   if (c0 >= c1) return;                              // host guarantees every chunk is non-empty
   const char* row = SH ? shard_base(a, sh) + (size_t)b * (size_t)a.shard_stride * ESZ      // (moves on with the pieces)
                        : reinterpret_cast<const char*>(a.logits) + (size_t)b * (size_t)a.row_stride * ESZ;
@@ -282,11 +292,12 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   uint4 smp[SLOADS];
 #pragma unroll
   for (int j = 0; j < SLOADS; ++j) {
-    const int sb = wave * SLOADS + j;                  // even j: every other block of the row
     if (!SH) {
-      const int e0 = (int)(((long long)sb * V / NSB) / (kWave * EPL)) * (kWave * EPL) + lane * EPL;
-      smp[j] = *reinterpret_cast<const uint4*>(row + (size_t)e0 * ESZ);    // e0 + EPL <= V since V >= 16384
+      const int sb = wave * SLOADS + j;                // even j: every other block of the row
+      const uint32_t base = (uint32_t)sb * (uint32_t)V / (uint32_t)NSB / (uint32_t)(kWave * EPL) * (uint32_t)(kWave * EPL);
+      smp[j] = reinterpret_cast<const uint4*>(row + (size_t)base * ESZ)[lane];     // base + 64 * EPL <= V since V >= 16384
     } else {
+      const int sb = wave * SLOADS + j;
       // the same NSB blocks for every chunk of the row, smp_bps to a shard (the last shard may get
       // fewer), evenly spread inside it; V_shard >= 8192, so a block fits
       // (wave-uniform, and said so: with a per-lane index the table of piece pointers would be read
@@ -442,8 +453,12 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
       }
     }
     __syncthreads();
+    if (tid < kBlkMax) blk_mass[tid] = 0.0f;
     if (wave == 0) {
-      const uint32_t c = lane < 32 ? sub_hist[31 - min(lane, 31)] : 0u;       // lane l: sub-bin 31 - l, descending
+      // lane l: sub-bin 31 - l, descending (the lane's number worked out anew: one register less
+      // from the start to here)
+      const int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+      const uint32_t c = l < 32 ? sub_hist[31 - min(l, 31)] : 0u;
       const uint32_t incl = dpp_scan_add_u32(c);
       const unsigned long long reach = __ballot(lane < 32 && incl >= need_thr);
       const uint32_t first = reach ? (uint32_t)__ffsll((long long)reach) - 1u : 31u;
@@ -482,7 +497,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   const uint32_t kb = key_thr << 14;
   const float Tc = value_of(kb);
   const BulkRef ref = make_bulk_ref(Tc, rp);
-  const int R = ref.R;
+  const int R = __builtin_amdgcn_readfirstlane(ref.R);
 
   // ---- stream
   uint2* queue = reinterpret_cast<uint2*>(smem) + wave * kQueueCap;          // this wave's LDS queue
@@ -491,6 +506,11 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   float acc = 0.0f;                         // this thread's bulk mass, fixed order of additions
 
   uint32_t ib = ibase;                      // SH: first vocabulary id of the piece being processed
+  // Block masses of a row without any filter.  One scalar branch per load for every other row; a
+  // copy of the loop for these rows alone cost all of them registers (bf16 V = 129280, 1024 rows:
+  // streaming kernel 90 -> 115 us).  bf16 V = 151643, 256 rows, no filter: finishing kernel 72.6 ->
+  // 17 us, streaming kernel unchanged at 28 us, call 99.3 -> 43.3 us.
+  const bool plain = !SH && !rp.greedy && unfiltered(rp, V);                   // workgroup-uniform
   // `hb`: the history bits of the EPL elements (bit i: element e0 + i carries a penalty)
   auto process = [&](const uint4& q, int e0, bool guard, uint32_t hb) {
     float z[EPL];
@@ -521,6 +541,12 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
       g += e;
     }
     acc += g;
+    if (!SH && plain) {
+      // one (bf16) or two (fp32) waves' loads make a block: at most two summands, so the order of
+      // the additions does not matter
+      g = dpp_scan_add_f32(g);
+      if (lane == kWave - 1) unsafeAtomicAdd(&blk_mass[(uint32_t)(e0 - c0) / (uint32_t)kBlkElems], g);
+    }
   };
   // Element e0 of the piece being processed is bit (ib - ibase) + e0 - c0 of the bitmap, a
   // multiple of EPL: the bits of one 16-byte load are half a byte (fp32) or one byte (bf16).
@@ -606,6 +632,9 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   }
   uint2* seg = a.cand + (size_t)wg * (size_t)kChunkCap + off;
   for (uint32_t i = lane; i < min(qn, (uint32_t)kQueueCap); i += kWave) seg[i] = queue[i];
+  const bool blocks = plain && tot <= (uint32_t)(kChunkCap - kBlkMax / 2);       // workgroup-uniform
+  const int n_blk = blocks ? (c1 - c0 + kBlkElems - 1) / kBlkElems : 0;
+  if (tid < n_blk) (reinterpret_cast<float*>(a.cand + (size_t)(wg + 1) * (size_t)kChunkCap) - n_blk)[tid] = blk_mass[tid];
   if (tid == 0) {
     ChunkOut o;
     o.bulk = 0;
@@ -614,7 +643,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
     o.Tc = Tc;
     o.R = R;
     o.cnt = overflow ? kCntOverflow : tot;
-    o.pad[0] = o.pad[1] = o.pad[2] = 0;
+    o.n_blk = (uint32_t)n_blk; o.pad[0] = o.pad[1] = 0;
     a.chunks[wg] = o;
   }
 }
