@@ -349,8 +349,18 @@ __device__ __forceinline__ float penalise(float z, unsigned int count, float the
 struct RowDivisor {
   double inv;
   __device__ __forceinline__ explicit RowDivisor(float d) : inv(1.0 / (double)d) {}
+  __device__ __forceinline__ explicit RowDivisor(double i) : inv(i) {}
   __device__ __forceinline__ float of(float z) const { return (float)((double)z * inv); }
 };
+
+// penalise() without a branch: a penalty that is off takes part with its neutral value (theta = 1,
+// phi = psi = 0 change no bit of a value), and the division is by the row's RowDivisor.
+__device__ __forceinline__ float penalise_shared(float z, unsigned int count, const RowDivisor& by_theta, float theta,
+                                                 float phi, float psi) {
+  const float y = (z > 0.0f) ? by_theta.of(z) : __fmul_rn(z, theta);
+  const float x = __fsub_rn(__fsub_rn(y, __fmul_rn(phi, (float)count)), psi);
+  return count ? x : y;
+}
 
 // ---------------------------------------------------------------- keys
 // Order-preserving map fp32 -> u32 (larger float <=> larger key); -0 and +0 share a key.
@@ -482,5 +492,23 @@ __device__ __forceinline__ unsigned long long readlane_u64(unsigned long long v,
 __device__ __forceinline__ unsigned long long fix_of(float e) {
   return (unsigned long long)(e * kFixScale);
 }
+
+// exp(x) for x <= 0: the product with log2(e) carried in two floats, v_exp_f32 on the larger and a
+// first-order step for the smaller.  Its error is that of v_exp_f32 plus one rounding, as with
+// expf(), without expf()'s range reduction and special cases (16 -> 9 issue slots per element).
+__device__ __forceinline__ float exp_nonpos(float x) {
+  x = fmaxf(x, -150.0f);                   // (-inf and NaN among them; exp2 of it is 0)
+  const float hi = __fmul_rn(x, 1.44269502f);
+  const float lo = __fmaf_rn(x, 1.92596303e-8f, __fmaf_rn(x, 1.44269502f, -hi));
+  const float p = __builtin_amdgcn_exp2f(hi);
+  return __fmaf_rn(p, __fmul_rn(lo, 0.693147182f), p);
+}
+// Mass in units of 2^-40, rounded to nearest: added to 2^12 a double's last bit is 2^-40, so the
+// low bits of the sum are the integer (3 instructions; the conversion to 64 bits takes 7).
+constexpr unsigned long long kMagicBits = 0x40B0000000000000ull;      // 2^12
+__device__ __forceinline__ unsigned long long mass_bits(float e) {     // + kMagicBits
+  return (unsigned long long)__double_as_longlong((double)e + 4096.0);
+}
+__device__ __forceinline__ unsigned long long mass_units(float e) { return mass_bits(e) - kMagicBits; }
 
 }  // namespace sip

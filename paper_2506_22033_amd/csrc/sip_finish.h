@@ -101,7 +101,7 @@ struct FinHint {
 __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared& fs, FinHint* hint = nullptr) {
   constexpr int NT = kFinThreads;
   constexpr int CR = kFinCR;
-  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+  const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
   const int V = a.V;
   const int S = a.S;
 
@@ -157,7 +157,12 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   rp.tau = ri.tau; rp.top_p = ri.top_p; rp.min_p = ri.min_p; rp.theta = ri.theta; rp.phi = ri.phi; rp.psi = ri.psi;
   rp.top_k = ri.top_k; rp.row_id = ri.row_id;
   rp.greedy = (rp.tau == 0.0f) || (rp.top_k == 1);
-  auto scaled_s = [&](float z) { return rp.greedy ? z : __fdiv_rn(z, rp.tau); };
+  // (both reciprocals from one division: lane 0's is the temperature's, the others' the penalty's)
+  const double recip = 1.0 / (double)(lane == 0 ? (rp.greedy ? 1.0f : rp.tau) : rp.theta);
+  const unsigned long long recip_bits = (unsigned long long)__double_as_longlong(recip);
+  const RowDivisor by_tau(__longlong_as_double((long long)readlane_u64(recip_bits, 0)));
+  const RowDivisor by_theta(__longlong_as_double((long long)readlane_u64(recip_bits, 1)));
+  auto scaled_s = [&](float z) { return by_tau.of(z); };
   const long long h_lo = ri.lo, h_hi = ri.hi;
   // multiplicities in the history are needed for the frequency penalty, and, next to a separate
   // prompt, to tell the tokens that frequency and presence apply to (see penalty_plan())
@@ -318,7 +323,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
         const uint32_t v = creg[r].y & ~kTagBit;
         float z = __uint_as_float(creg[r].x);
         if (creg[r].y & kTagBit) {
-          z = penalise(z, need_hash ? hv[r] : mult_dflt, rp.theta, rp.phi, rp.psi);
+          z = penalise_shared(z, need_hash ? hv[r] : mult_dflt, by_theta, rp.theta, rp.phi, rp.psi);
           // lists of several batches are read again from memory: leave the penalised value there
           if (nb > 1) seg[slot_of(bt, r)] = make_uint2(__float_as_uint(z), v);
         }
@@ -351,12 +356,13 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   const float span = __fsub_rn(m, s_c);
   if (!(span >= 0.0f) || !(span < 3.0e38f)) return 7;                         // uniform
   const float binscale = span > 0.0f ? (float)(kFinBins - 2) / span : 0.0f;
+  const float binshift = -__fmul_rn(s_c, binscale);
   auto bin_of = [&](float s, uint32_t k) -> int {
     if (k <= key_c) return 0;
-    const int q = (int)(__fsub_rn(s, s_c) * binscale);
-    return 1 + min(kFinBins - 2, max(q, 0));
+    // (one rounding of s * binscale + shift: monotone in s)
+    return 1 + (int)__builtin_amdgcn_fmed3f(__fmaf_rn(s, binscale, binshift), 0.0f, (float)(kFinBins - 2));
   };
-  auto mass = [&](float s) { return fix_of(expf(__fsub_rn(s, m))); };
+  auto mass = [&](float s) { return mass_units(exp_nonpos(__fsub_rn(s, m))); };
   auto emit = [&](uint32_t token, uint32_t token_key, double lnZ) {          // one thread
     a.out_ids[b] = (int)token;
     if (a.k_lp >= 0) {

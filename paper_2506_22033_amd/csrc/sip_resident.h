@@ -42,24 +42,6 @@ constexpr int kResList = 1024;             // members of a cut's bin / entries a
 constexpr int kResMaxCount = 32767;        // longest history that 15-bit counters hold whatever it repeats
 constexpr float kResSpan = 28.6f;          // exp(-28.6) * 2^40 < 1/2: nothing further below the maximum has mass
 
-// exp(x) for x <= 0: the product with log2(e) carried in two floats, v_exp_f32 on the larger and a
-// first-order step for the smaller.  Its error is that of v_exp_f32 plus one rounding, as with
-// expf(), without expf()'s range reduction and special cases (16 -> 9 issue slots per element).
-__device__ __forceinline__ float exp_nonpos(float x) {
-  x = fmaxf(x, -150.0f);                   // (-inf and NaN among them; exp2 of it is 0)
-  const float hi = __fmul_rn(x, 1.44269502f);
-  const float lo = __fmaf_rn(x, 1.92596303e-8f, __fmaf_rn(x, 1.44269502f, -hi));
-  const float p = __builtin_amdgcn_exp2f(hi);
-  return __fmaf_rn(p, __fmul_rn(lo, 0.693147182f), p);
-}
-// Mass in units of 2^-40, rounded to nearest: added to 2^12 a double's last bit is 2^-40, so the
-// low bits of the sum are the integer (3 instructions; the conversion to 64 bits takes 7).
-constexpr unsigned long long kMagicBits = 0x40B0000000000000ull;      // 2^12
-__device__ __forceinline__ unsigned long long mass_bits(float e) {     // + kMagicBits
-  return (unsigned long long)__double_as_longlong((double)e + 4096.0);
-}
-__device__ __forceinline__ unsigned long long mass_units(float e) { return mass_bits(e) - kMagicBits; }
-
 template <int NT, int NPT>
 struct __align__(16) ResShared {
   union {
@@ -98,7 +80,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
   constexpr int NBLK = NL * NW;
   static_assert(NPT % EPL == 0 && NW <= 16 && NBLK <= 2 * kWave, "");
   __shared__ ResShared<NT, NPT> fs;
-  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+  const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
   const int b = blockIdx.x;
   const int V = a.V;
   const bool sharded = a.shard[0] != nullptr;          // uniform
@@ -218,9 +200,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
           for (int i = 0; i < EPL; ++i) {
             const uint32_t ci = (i & 1) ? c[i / 2] >> 16 : c[i / 2] & 0xFFFFu;
             const uint32_t n = ci & 0x7FFFu;
-            const float y = (z[i] > 0.0f) ? by_theta.of(z[i]) : __fmul_rn(z[i], rp.theta);
-            const float x = __fsub_rn(__fsub_rn(y, __fmul_rn(rp.phi, (float)n)), rp.psi);
-            z[i] = n ? x : (ci ? y : z[i]);
+            z[i] = ci ? penalise_shared(z[i], n, by_theta, rp.theta, rp.phi, rp.psi) : z[i];
           }
         }
       }
