@@ -38,8 +38,10 @@ constexpr int kFinCR = 10;                             // list entries a thread 
 constexpr int kFinBins = 1024;
 constexpr int kFinBPT = kFinBins / kFinThreads;        // bins per thread in the scans
 constexpr int kFinList = 4352;                         // entries of the bin-sorted list in LDS
-constexpr int kFinHash = 4096;                         // slots of the multiplicity table
-constexpr int kFinHashMax = 3072;                      // distinct history tokens it takes
+constexpr int kFinHash = 8192;                         // slots of the multiplicity table
+constexpr int kFinHashMax = 6144;                      // distinct history tokens it takes
+constexpr int kFinCountBits = 14;                      // a slot: token << 14 | multiplicity (18 + 14 bits), 0 = free
+constexpr uint32_t kFinCountMax = (1u << kFinCountBits) - 1;
 constexpr int kFinMembers = 512;                       // members of one index bin the draw resolves
 constexpr int kFinTopMax = 256;                        // entries at or above the bin of the n-th best
 constexpr int kFinKeySteps = 64;                       // distinct keys of one bin that are stepped through
@@ -58,7 +60,7 @@ struct __align__(16) FinShared {
   unsigned long long hidx[kFinBins];        // kept mass per vocabulary-index bin
   union {
     struct { uint32_t skey[kFinList]; uint32_t sidx[kFinList]; } list;      // entries sorted by bin, descending
-    struct { uint32_t key[kFinHash]; uint32_t val[kFinHash]; } hash;        // token -> multiplicity (before the list exists)
+    uint32_t hash[kFinHash];                                                // token -> multiplicity (before the list exists)
   } u;
   uint32_t m_key[kFinMembers];
   uint32_t m_idx[kFinMembers];
@@ -172,8 +174,10 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   // (32 KB to copy against 4 bytes and two LDS atomics per history token: it pays from about two
   // thousand tokens on)
   const bool use_table = need_hash && ri.slot >= 0 && ri.ndist >= 0 && ri.hi - ri.lo > 2048;
-  static_assert(kFinHash == kTableSlots && kFinHashMax == kTableMaxDistinct, "one table geometry");
+  static_assert(kFinHash == 2 * kTableSlots, "as many bytes: a slot's table is copied with its own geometry, half of the slots in use");
+  const bool long_hist = h_hi - h_lo > (long long)kFinCountMax;              // only then can a multiplicity outgrow its bits
   constexpr int HR = 8;                    // history tokens a thread requests at once
+  bool big_count = false;
   int htok[HR];
 #pragma unroll
   for (int j = 0; j < HR; ++j) {
@@ -186,19 +190,26 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     for (int i = tid; i < kFinBins * 4 / 16; i += NT) z4[i] = make_uint4(0, 0, 0, 0);
     z4 = reinterpret_cast<uint4*>(fs.fill);
     for (int i = tid; i < kFinBins * 20 / 16; i += NT) z4[i] = make_uint4(0, 0, 0, 0);
-    if (use_table) {                       // keys and multiplicities lie one behind the other, here as there
+    if (use_table) {
+      // keys and multiplicities (one behind the other there) become packed slots
       const uint4* t4 = reinterpret_cast<const uint4*>(a.st_table + (size_t)ri.slot * (size_t)(2 * kTableSlots));
-      uint4* k4 = reinterpret_cast<uint4*>(fs.u.hash.key);
-      uint4 tq[2 * kFinHash * 4 / 16 / NT];
+      uint4* s4 = reinterpret_cast<uint4*>(fs.u.hash);
+      constexpr int NQ = kTableSlots * 4 / 16 / NT;
+      uint4 tk[NQ], tv[NQ];
 #pragma unroll
-      for (int j = 0; j < 2 * kFinHash * 4 / 16 / NT; ++j) tq[j] = t4[j * NT + tid];
+      for (int j = 0; j < NQ; ++j) { tk[j] = t4[j * NT + tid]; tv[j] = t4[kTableSlots / 4 + j * NT + tid]; }
+      // (a token beyond the vocabulary keeps its place, with the multiplicity 0 that never matches)
+      auto pack = [&](uint32_t k, uint32_t v) -> uint32_t {
+        if (k == kTableEmpty) return 0u;
+        big_count |= v > kFinCountMax;
+        return k < (uint32_t)V ? (k << kFinCountBits) | min(v, kFinCountMax) : ~kFinCountMax;
+      };
 #pragma unroll
-      for (int j = 0; j < 2 * kFinHash * 4 / 16 / NT; ++j) k4[j * NT + tid] = tq[j];
+      for (int j = 0; j < NQ; ++j)
+        s4[j * NT + tid] = make_uint4(pack(tk[j].x, tv[j].x), pack(tk[j].y, tv[j].y), pack(tk[j].z, tv[j].z), pack(tk[j].w, tv[j].w));
     } else if (need_hash) {
-      uint4* k4 = reinterpret_cast<uint4*>(fs.u.hash.key);
-      for (int i = tid; i < kFinHash * 4 / 16; i += NT) k4[i] = make_uint4(kFinNone, kFinNone, kFinNone, kFinNone);
-      uint4* v4 = reinterpret_cast<uint4*>(fs.u.hash.val);
-      for (int i = tid; i < kFinHash * 4 / 16; i += NT) v4[i] = make_uint4(0, 0, 0, 0);
+      uint4* s4 = reinterpret_cast<uint4*>(fs.u.hash);
+      for (int i = tid; i < kFinHash * 4 / 16; i += NT) s4[i] = make_uint4(0, 0, 0, 0);
     }
     if (tid == 0) {
       fs.bin_k = -1; fs.bin_n = -1; fs.bin_d = -1; fs.code = 0; fs.code_top = 0; fs.hash_fail = 0; fs.n_memb = 0;
@@ -230,33 +241,53 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   };
   lds_barrier();                                                             // LDS is clear
 
-  // ---- (1) multiplicities: a hash table of kFinHash / 4 buckets of four slots, keyed by token.
-  // A bucket's four keys are one 16-byte LDS read; a token lives in the first bucket, from its
-  // home bucket on, that had a free slot when it came.  Slots of a bucket fill in order (a thread
-  // claims the first slot it finds free, by compare-and-swap), so a key, once there, stays.
-  uint4* const hkey4 = reinterpret_cast<uint4*>(fs.u.hash.key);
-  auto home = [](uint32_t t) { return (t * 0x9E3779B1u) >> 22; };
-  static_assert(kFinHash == 4096, "home() yields 10 bits: 1024 buckets of 4 slots");
+  // ---- (1) multiplicities: a hash table of kFinHash / 4 buckets of four slots, keyed by token (a
+  // state's table: half as many).  A bucket's four slots are one 16-byte LDS read; a token lives in
+  // the first bucket, from its home bucket on, that had a free slot when it came.  Slots of a bucket
+  // fill in order (a thread claims the first slot it finds free, by compare-and-swap), so a token,
+  // once there, stays.  Token and multiplicity share a word: twice the slots in the same LDS, so
+  // that buckets seldom overflow, and one read answers a look-up.  (Two arrays of 4096: fp32
+  // V = 256000, 2048 rows of 4096 tokens, counting 8.5 us and penalties 9.7 us of a row's 42; a row
+  // of 3000 distinct tokens 26 and 30 us.)
+  const uint4* const hslot4 = reinterpret_cast<const uint4*>(fs.u.hash);
+  const uint32_t n_bucket = use_table ? kTableSlots / 4 : kFinHash / 4;
+  const int home_shift = use_table ? 22 : 21;
+  auto home = [&](uint32_t t) { return (t * 0x9E3779B1u) >> home_shift; };
+  static_assert(kFinHash == 8192 && kTableSlots == 4096, "home() yields 11 bits, or the 10 of table_home()");
+  // Slot w against token t: below kFinCountMax it is the multiplicity of t less one (a multiplicity
+  // is never 0 in a slot that can match), else the slot is another's; a free slot gives (t << 14) - 1.
+  auto slot_for = [](uint32_t w, uint32_t t) -> uint32_t { return (w ^ (t << kFinCountBits)) - 1u; };
+  auto count_in = [&](const uint4& q, uint32_t t) -> uint32_t {                // multiplicity of t, 0 if the bucket has it not
+    const uint32_t u = min(min(min(slot_for(q.x, t), slot_for(q.y, t)), slot_for(q.z, t)), slot_for(q.w, t));
+    return u < kFinCountMax ? u + 1u : 0u;
+  };
   if (need_hash && !use_table) {
     uint32_t mine = 0;                     // slots this thread claimed = distinct tokens it saw first
     auto insert = [&](int ti) {
       if (ti < 0 || ti >= V) return;
       const uint32_t t = (uint32_t)ti;
       uint32_t bk = home(t);
-      for (int probe = 0; probe < kFinHash / 4; ++probe) {
-        const uint4 k4 = hkey4[bk];
-        const uint32_t ks[4] = {k4.x, k4.y, k4.z, k4.w};
-        int j = -1;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (j < 0 && ks[e] == t) j = e;
-          if (j < 0 && ks[e] == kFinNone) {                 // free when read: try to take it
-            const uint32_t old = atomicCAS(&fs.u.hash.key[4 * bk + e], kFinNone, t);
-            if (old == kFinNone) { ++mine; j = e; } else if (old == t) j = e;
-          }
+      for (int probe = 0; probe < kFinHash / 4 + 64; ++probe) {                // (a bucket may be looked at again)
+        if ((probe & 31) == 31 && fs.hash_fail) return;                        // given up already
+        const uint4 q = hslot4[bk];
+        const uint32_t x0 = slot_for(q.x, t), x1 = slot_for(q.y, t), x2 = slot_for(q.z, t), x3 = slot_for(q.w, t);
+        const uint32_t u = min(min(min(x0, x1), x2), x3);
+        const bool match = u < kFinCountMax;
+        const uint32_t want = match ? u : (t << kFinCountBits) - 1u;           // else the first free slot
+        const int at = x0 == want ? 0 : x1 == want ? 1 : x2 == want ? 2 : x3 == want ? 3 : 4;
+        if (at == 4) { bk = (bk + 1) & (kFinHash / 4 - 1); continue; }
+        uint32_t* const slot = &fs.u.hash[4 * bk + at];
+        if (!match) {
+          const uint32_t old = atomicCAS(slot, 0u, (t << kFinCountBits) | 1u);
+          if (old == 0u) { ++mine; return; }
+          if (!(slot_for(old, t) < kFinCountMax)) continue;                                // someone else's token came first: look again
         }
-        if (j >= 0) { atomicAdd(&fs.u.hash.val[4 * bk + j], 1u); return; }
-        bk = (bk + 1) & (kFinHash / 4 - 1);
+        if (long_hist) {                                                       // uniform
+          if ((atomicAdd(slot, 1u) & kFinCountMax) == kFinCountMax) fs.hash_fail = 1;
+        } else {
+          atomicAdd(slot, 1u);
+        }
+        return;
       }
       fs.hash_fail = 1;                    // table full
     };
@@ -279,18 +310,20 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
 #pragma unroll
     for (int w = 0; w < kFinWaves; ++w) ndist += fs.r32[w];
     if (fs.hash_fail || ndist > (uint32_t)kFinHashMax) return 4;            // uniform
+  } else if (use_table && long_hist) {
+    if (big_count) fs.hash_fail = 1;
+    lds_barrier();
+    if (fs.hash_fail) return 4;                                              // uniform
   }
   // multiplicity of token t, searched from bucket bk on (the rare continuation of the lookup
   // below: t's home bucket is full of other tokens); 0 = not in the history (a prompt token)
   auto count_slow = [&](uint32_t t, uint32_t bk) -> uint32_t {
-    for (int probe = 0; probe < kFinHash / 4; ++probe) {
-      const uint4 k4 = hkey4[bk];
-      if (k4.x == t) return fs.u.hash.val[4 * bk];
-      if (k4.y == t) return fs.u.hash.val[4 * bk + 1];
-      if (k4.z == t) return fs.u.hash.val[4 * bk + 2];
-      if (k4.w == t) return fs.u.hash.val[4 * bk + 3];
-      if (k4.w == kFinNone) return 0u;     // slots fill in order: a free last slot ends the search
-      bk = (bk + 1) & (kFinHash / 4 - 1);
+    for (uint32_t probe = 0; probe < n_bucket; ++probe) {
+      const uint4 q = hslot4[bk];
+      const uint32_t n = count_in(q, t);
+      if (n) return n;
+      if (q.w == 0u) return 0u;            // slots fill in order: a free last slot ends the search
+      bk = (bk + 1) & (n_bucket - 1);
     }
     return 0u;
   };
@@ -306,15 +339,15 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
       uint4 hk[CR];
 #pragma unroll
       for (int r = 0; r < CR; ++r)
-        if (live(bt, r)) hk[r] = hkey4[home(creg[r].y & ~kTagBit)];
+        if (live(bt, r)) hk[r] = hslot4[home(creg[r].y & ~kTagBit)];
 #pragma unroll
       for (int r = 0; r < CR; ++r) {
         hv[r] = 0u;
         if (!live(bt, r)) continue;
-        const uint32_t v = creg[r].y & ~kTagBit, bk = home(v);
-        const uint32_t hs = hk[r].x == v ? 4 * bk : hk[r].y == v ? 4 * bk + 1 : hk[r].z == v ? 4 * bk + 2 : hk[r].w == v ? 4 * bk + 3 : kFinNone;
-        if (hs != kFinNone) hv[r] = fs.u.hash.val[hs];
-        else if (hk[r].w != kFinNone && (creg[r].y & kTagBit) && creg[r].y != kFinNone) hv[r] = count_slow(v, (bk + 1) & (kFinHash / 4 - 1));
+        const uint32_t v = creg[r].y & ~kTagBit;
+        hv[r] = count_in(hk[r], v);
+        if (hv[r] == 0u && hk[r].w != 0u && (creg[r].y & kTagBit) && creg[r].y != kFinNone)
+          hv[r] = count_slow(v, (home(v) + 1) & (n_bucket - 1));
       }
     }
 #pragma unroll
