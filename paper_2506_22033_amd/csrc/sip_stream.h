@@ -21,6 +21,8 @@
 // value, tagged, and stays out of the bulk mass, so that the finishing kernel finds the raw
 // logit of every token it has to penalise in the list and never reads the logits itself.
 #pragma once
+#include <type_traits>
+
 #include "sip_device.h"
 
 namespace sip {
@@ -156,7 +158,11 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   // 30 KB of LDS: first the sample histogram (two 16-bit counters per word, 16 KB), then the
   // per-wave candidate queues; 9 KB for the history bitmap of the chunk (39.6 KB in all: four
   // workgroups per compute unit)
-  __shared__ __align__(16) unsigned char smem[(kSampleBins * 2 > kStreamWaves * kQueueCap * 8) ? kSampleBins * 2 : kStreamWaves * kQueueCap * 8];
+  typedef typename std::conditional<DT == SIP_F32, uint2, uint32_t>::type entry_t;      // see `process`
+  __shared__ __align__(16) unsigned char smem[(kSampleBins * 2 > kStreamWaves * kQueueCap * (int)sizeof(entry_t)) ? kSampleBins * 2 : kStreamWaves * kQueueCap * (int)sizeof(entry_t)];
+  // bf16: history bits of one 16-byte load -> what is or-ed into the load's four words (one LDS read
+  // and four instructions in the loop instead of sixteen; for the four of fp32 a table saves nothing)
+  __shared__ uint4 tag_words[DT == SIP_F32 ? 1 : 256];
   __shared__ uint32_t bmw[kChunkBitsMax / 32];
   uint32_t* hist = reinterpret_cast<uint32_t*>(smem);
   __shared__ uint32_t red32[kStreamWaves];
@@ -340,6 +346,10 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   for (int i = tid; i < kSampleBins / 2; i += kStreamThreads) hist[i] = 0;
   for (int i = tid; i < kChunkBitsMax / 32; i += kStreamThreads) bmw[i] = 0;
   if (tid < 32) sub_hist[tid] = 0;
+  if (DT == SIP_BF16 && tid < 256) {
+    auto word = [&](int i) -> uint32_t { return ((tid >> (2 * i)) & 1 ? 0xFFFFu : 0u) | ((tid >> (2 * i + 1)) & 1 ? 0xFFFF0000u : 0u); };
+    tag_words[tid] = make_uint4(word(0), word(1), word(2), word(3));
+  }
   __syncthreads();
   if (has_pen) {
     auto mark = [&](int t) {
@@ -500,7 +510,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   const int R = __builtin_amdgcn_readfirstlane(ref.R);
 
   // ---- stream
-  uint2* queue = reinterpret_cast<uint2*>(smem) + wave * kQueueCap;          // this wave's LDS queue
+  entry_t* queue = reinterpret_cast<entry_t*>(smem) + wave * kQueueCap;        // this wave's LDS queue
   const unsigned char* bm8 = reinterpret_cast<const unsigned char*>(bmw);
   uint32_t qn = 0;                          // wave-uniform: list entries seen (entries beyond the queue are dropped)
   float acc = 0.0f;                         // this thread's bulk mass, fixed order of additions
@@ -511,29 +521,40 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   // streaming kernel 90 -> 115 us).  bf16 V = 151643, 256 rows, no filter: finishing kernel 72.6 ->
   // 17 us, streaming kernel unchanged at 28 us, call 99.3 -> 43.3 us.
   const bool plain = !SH && !rp.greedy && unfiltered(rp, V);                   // workgroup-uniform
-  // `hb`: the history bits of the EPL elements (bit i: element e0 + i carries a penalty)
-  auto process = [&](const uint4& q, int e0, bool guard, uint32_t hb) {
+  // `hb`: the history bits of the EPL elements (bit i: element e0 + i carries a penalty); `tg`: bf16,
+  // the same as words to or into the load's (tag_words); `it`: the wave's load
+  // number in its chunk.  A queue entry is the element's value and its place: fp32 (bits, vocabulary
+  // id); bf16 one word, the value's 16 bits above load number, lane and element (5 + 6 + 3 bits).
+  // Whether it is a history token is looked up again when the queue goes out.
+  auto process = [&](const uint4& q, int e0, int it, bool guard, uint32_t hb, const uint4& tg) {
+    const uint32_t raw[4] = {q.x, q.y, q.z, q.w};
     float z[EPL];
-    unpack(q, z);
+    if constexpr (DT == SIP_F32) {
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) z[i] = __uint_as_float(raw[i] | (uint32_t)((int)(hb << (31 - i)) >> 31));
+    } else {
+      unpack(make_uint4(q.x | tg.x, q.y | tg.y, q.z | tg.z, q.w | tg.w), z);
+    }
     if (guard) {
 #pragma unroll
       for (int i = 0; i < EPL; ++i)
-        if (e0 + i >= c1) { z[i] = -INFINITY; hb &= ~(1u << i); }
+        if (e0 + i >= c1) z[i] = -INFINITY;
     }
+    const uint32_t place = DT == SIP_F32 ? (uint32_t)e0 + (SH ? ib : 0u) : ((uint32_t)it << 9) | ((uint32_t)lane << 3);
     float g = 0.0f;
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
-      // One comparison decides "at or above the threshold, or a history token": the history bit,
-      // spread over the word, is or-ed into the value's bits, which turns a tagged value into a
-      // NaN, and "not below" holds for every NaN.
-      const uint32_t tagm = (uint32_t)((int)(hb << (31 - i)) >> 31);          // 0 or all ones
-      const bool hit = !(__uint_as_float(__float_as_uint(z[i]) | tagm) < Tc);
+      // One comparison decides "at or above the threshold, or a history token": a history token's
+      // bits are all set, a NaN, and "not below" holds for every NaN.
+      const bool hit = !(z[i] < Tc);
       const unsigned long long mask = __ballot(hit);
       if (mask) {
         const uint32_t pos = qn + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                       __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-        if (hit && pos < (uint32_t)kQueueCap)
-          queue[pos] = make_uint2(__float_as_uint(z[i]), ((uint32_t)(e0 + i) + (SH ? ib : 0u)) | (tagm & kTagBit));
+        if (hit && pos < (uint32_t)kQueueCap) {
+          if constexpr (DT == SIP_F32) queue[pos] = make_uint2(raw[i], place + (uint32_t)i);
+          else queue[pos] = ((i & 1) ? raw[i / 2] & 0xFFFF0000u : raw[i / 2] << 16) | (place | (uint32_t)i);
+        }
         qn += (uint32_t)__popcll(mask);
       }
       float e = bulk_term(z[i], ref);
@@ -550,23 +571,30 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   };
   // Element e0 of the piece being processed is bit (ib - ibase) + e0 - c0 of the bitmap, a
   // multiple of EPL: the bits of one 16-byte load are half a byte (fp32) or one byte (bf16).
-  // Lanes past the end of the chunk read the last byte; `process` masks what they get.
+  // Lanes past the end of the chunk read the last byte; `process` discards what they get.
   auto hist_bits = [&](int e0) -> uint32_t {
     const uint32_t bit0 = (uint32_t)(e0 - c0) + (SH ? ib - ibase : 0u);
     const uint32_t byte = bm8[min(bit0 >> 3, (uint32_t)(kChunkBitsMax / 8 - 1))];
     return DT == SIP_F32 ? (byte >> (bit0 & 4u)) & 0xFu : byte;
   };
+  int it0 = 0;                              // number of the tile's first load
   auto process_tile = [&](const uint4 (&buf)[kStreamLoads], int t0) {
     const bool partial = t0 + TILE > c1;
     uint32_t hb[kStreamLoads];
+    uint4 tg[kStreamLoads] = {};
 #pragma unroll
     for (int j = 0; j < kStreamLoads; ++j) hb[j] = hist_bits(t0 + j * SUB + tid * EPL);
+    if constexpr (DT == SIP_BF16) {
+#pragma unroll
+      for (int j = 0; j < kStreamLoads; ++j) tg[j] = tag_words[hb[j]];
+    }
 #pragma unroll
     for (int j = 0; j < kStreamLoads; ++j) {
       const int e0 = t0 + j * SUB + tid * EPL;
-      if (!partial) process(buf[j], e0, false, hb[j]);
-      else if (t0 + j * SUB < c1) process(buf[j], e0, true, hb[j]);     // workgroup-uniform condition
+      if (!partial) process(buf[j], e0, it0 + j, false, hb[j], tg[j]);
+      else if (t0 + j * SUB < c1) process(buf[j], e0, it0 + j, true, hb[j], tg[j]);     // workgroup-uniform condition
     }
+    it0 += kStreamLoads;
   };
 
   // kStreamBufs register buffers in rotation: while one tile is processed the loads of the
@@ -631,7 +659,21 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
     tot += cc;
   }
   uint2* seg = a.cand + (size_t)wg * (size_t)kChunkCap + off;
-  for (uint32_t i = lane; i < min(qn, (uint32_t)kQueueCap); i += kWave) seg[i] = queue[i];
+  const int lpp = kStreamLoads * ((c1 - c0 + TILE - 1) / TILE);                // load numbers of one piece
+  for (uint32_t i = lane; i < min(qn, (uint32_t)kQueueCap); i += kWave) {
+    uint2 en;
+    if constexpr (DT == SIP_F32) {
+      en = queue[i];
+    } else {
+      const uint32_t w = queue[i];
+      uint32_t it = (w >> 9) & 31u, base = ibase + (uint32_t)c0;
+      if (SH) { const uint32_t pc = it / (uint32_t)lpp; it -= pc * (uint32_t)lpp; base += pc * (uint32_t)Vl; }
+      en = make_uint2(w & 0xFFFF0000u, base + it * (uint32_t)SUB + (uint32_t)wave * (uint32_t)(kWave * EPL) + (w & 511u));
+    }
+    const uint32_t bit = en.y - (uint32_t)g0;
+    if ((bmw[min(bit >> 5, (uint32_t)(kChunkBitsMax / 32 - 1))] >> (bit & 31u)) & 1u) en.y |= kTagBit;
+    seg[i] = en;
+  }
   const bool blocks = plain && tot <= (uint32_t)(kChunkCap - kBlkMax / 2);       // workgroup-uniform
   const int n_blk = blocks ? (c1 - c0 + kBlkElems - 1) / kBlkElems : 0;
   if (tid < n_blk) (reinterpret_cast<float*>(a.cand + (size_t)(wg + 1) * (size_t)kChunkCap) - n_blk)[tid] = blk_mass[tid];
