@@ -349,7 +349,7 @@ __device__ __forceinline__ float penalise(float z, unsigned int count, float the
 struct RowDivisor {
   double inv;
   __device__ __forceinline__ explicit RowDivisor(float d) : inv(1.0 / (double)d) {}
-  __device__ __forceinline__ explicit RowDivisor(double i) : inv(i) {}
+  __device__ __forceinline__ explicit RowDivisor(double reciprocal) : inv(reciprocal) {}     // worked out elsewhere
   __device__ __forceinline__ float of(float z) const { return (float)((double)z * inv); }
 };
 
