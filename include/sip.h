@@ -101,7 +101,7 @@ typedef struct {
  * Results mean the same whichever path ran.
  *
  * Kernels of a call (names as a profiler shows them): resident_kernel alone up to
- * SIP_MAX_RESIDENT_V entries; else stream_kernel (the one pass over the
+ * SIP_MAX_RESIDENT_V entries (on a state: below 16384, behind state_take_tick_kernel); else stream_kernel (the one pass over the
  * logits), then finish_rescue_kernel for batches of no more rows than the device has compute
  * units, else finish_kernel followed by rescue_kernel (which returns at once when no row was
  * passed on); exact_kernel alone for vocabulary sizes outside the single-pass kernels.

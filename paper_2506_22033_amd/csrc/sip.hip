@@ -302,7 +302,11 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
   hipEvent_t ev[6];
   for (int i = 0; i < 6; ++i) { ev[i] = g_prof[i]; g_prof[i] = nullptr; }
   const bool timed = ev[0] || ev[1] || ev[2] || ev[3] || ev[4] || ev[5];
-  if (a.V <= kResidentMaxV) {
+  // A state's call has to take its number before every row's kernel (a launch of its own here; the
+  // streaming kernel does it in passing), and a decode loop on a state waits for each launch: where
+  // the single-pass kernels serve the shape too, they keep it (bf16 V = 28532, 4 rows, hand-off:
+  // 53.4 us an iteration against 56.8; V = 28092, 13 rows: 53.7 against 59.3).
+  if (a.V <= kResidentMaxV && !(state && plan.fast)) {
     // a workgroup holds its whole row in registers: one kernel
     if (state) {
       a.call_tick = a.rescue_tick;
