@@ -53,7 +53,7 @@ constexpr int kCandLong = 24;        // candidate entries per thread of the larg
 
 struct FastShared {
   float Tc[kMaxChunks];
-  int R[kMaxChunks];
+  float r0[kMaxChunks];
   unsigned long long bulk[kMaxChunks];
   uint32_t segoff[kMaxChunks + 1];
   unsigned long long r64[kFinalWaves];
@@ -147,7 +147,7 @@ __device__ __forceinline__ int fast_row(const Args& a, const int b, const RowPar
   }
   if (tid < S) {
     const ChunkOut co = a.chunks[(size_t)b * a.S + tid];
-    fs.Tc[tid] = co.Tc; fs.R[tid] = co.R; fs.bulk[tid] = co.bulk;
+    fs.Tc[tid] = co.Tc; fs.r0[tid] = co.r0; fs.bulk[tid] = co.bulk;
     fs.segoff[tid] = co.cnt;
   }
   // history tokens of this thread (the first kTokRegs rounds stay in registers)
@@ -199,16 +199,8 @@ __device__ __forceinline__ int fast_row(const Args& a, const int b, const RowPar
     }
   }
   __syncthreads();
-  // largest chunk threshold and reference exponent: lane c reads chunk c (S <= 32), then a wave maximum
-  float T_row;
-  int R_max;
-  {
-    const int c = min(lane, S - 1);
-    const uint32_t kt = key_of(fs.Tc[c]);
-    const uint32_t kr = (uint32_t)fs.R[c] ^ 0x80000000u;
-    T_row = value_of(last_lane_u32(dpp_scan_max_u32(kt)));
-    R_max = (int)(last_lane_u32(dpp_scan_max_u32(kr)) ^ 0x80000000u);
-  }
+  // (the chunks of a row share threshold and unit)
+  const float T_row = value_of(key_of(fs.Tc[0]));
   if (fs.fail_seg || !(T_row == T_row)) return 3;                             // uniform
   const uint32_t total_seg = fs.segoff[nseg];
   if (total_seg > (uint32_t)a.nc_cap) return 5;                               // uniform
@@ -495,15 +487,13 @@ __device__ __forceinline__ int fast_row(const Args& a, const int b, const RowPar
   // bulk mass -> units of 2^-40 relative to the maximum
   unsigned long long bulk;
   {
-    const int c = min(lane, S - 1);
-    const int sh = R_max - fs.R[c];
-    const unsigned long long bc = fs.bulk[c];
-    bulk = last_lane_u64(dpp_scan_add_u64((lane < S && sh < 64) ? (bc >> sh) : 0ull));
+    const unsigned long long bc = fs.bulk[min(lane, S - 1)];
+    bulk = last_lane_u64(dpp_scan_add_u64(lane < S ? bc : 0ull));
   }
   // 2^x with x split into integer and fraction: the fraction goes through the hardware exp2 (1 ulp,
   // far inside the accuracy of the fp32 bulk sums), the integer part is an exponent shift
   const double ln2 = 0.6931471805599453094, log2e = 1.4426950408889634074;
-  const double x = fmin(fmax((double)R_max + 10.0 - (double)m * log2e, -2000.0), 2000.0);
+  const double x = fmin(fmax(bulk_exponent(T_row, fs.r0[0], log2e / (rp.greedy ? 1.0 : (double)rp.tau), m) + 10.0, -2000.0), 2000.0);
   const double xi = floor(x);
   const double bulk_rel = ldexp((double)bulk * (double)__builtin_amdgcn_exp2f((float)(x - xi)), (int)xi);
   const unsigned long long S0 = S_cand + (bulk_rel < 9.0e18 ? (unsigned long long)bulk_rel : 0ull);
@@ -831,7 +821,6 @@ __device__ __attribute__((noinline)) void restream_row(const Args& a, const int 
   uint2* region = a.cand + (size_t)b * (size_t)a.S * (size_t)a.cap_c;
   const uint32_t cap = (uint32_t)(a.S * a.cap_c);
   const BulkRef ref = make_bulk_ref(Tc, rp);
-  const int R = ref.R;
   __syncthreads();
   if (tid == 0) fs.rq_n = 0;
   __syncthreads();
@@ -884,7 +873,7 @@ __device__ __attribute__((noinline)) void restream_row(const Args& a, const int 
     ChunkOut o;
     o.bulk = 0;
     for (int w = 0; w < kFinalWaves; ++w) o.bulk += fs.r64[w];
-    o.Tc = Tc; o.R = R;
+    o.Tc = Tc; o.r0 = ref.r0;
     o.cnt = fs.rq_n;
     o.n_blk = 0; o.pad[0] = o.pad[1] = 0;
     a.chunks[(size_t)b * a.S] = o;

@@ -145,13 +145,12 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   const ChunkOut co = a.chunks[(size_t)b * S + min(lane, S - 1)];
   load_batch(0);
   uint32_t my_cnt = 0;
-  float Tc;
-  int R;
+  float Tc, r0;
   {
     if (lane < S) { my_cnt = co.cnt; my_bulk = co.bulk; }
     have_blocks = __all(lane >= S || co.n_blk > 0);
     Tc = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(co.Tc)));   // the chunks of a row share
-    R = __builtin_amdgcn_readfirstlane(co.R);                                                      // threshold and exponent
+    r0 = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(co.r0)));   // threshold and exponent
   }
   if ((ri.target & ~kPromptFlag) == 0) { list_is_used(); return 2; }          // uniform: k beyond any list
   const bool prompt_on = (ri.target & kPromptFlag) != 0;                     // tokens of a separate prompt are tagged too
@@ -163,6 +162,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   const double recip = 1.0 / (double)(lane == 0 ? (rp.greedy ? 1.0f : rp.tau) : rp.theta);
   const unsigned long long recip_bits = (unsigned long long)__double_as_longlong(recip);
   const RowDivisor by_tau(__longlong_as_double((long long)readlane_u64(recip_bits, 0)));
+  const double c_tau = 1.4426950408889634074 * by_tau.inv;                    // log2(e) / tau
   const RowDivisor by_theta(__longlong_as_double((long long)readlane_u64(recip_bits, 1)));
   auto scaled_s = [&](float z) { return by_tau.of(z); };
   const long long h_lo = ri.lo, h_hi = ri.hi;
@@ -473,8 +473,8 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   // 2^x with x split into integer and fraction: the fraction goes through the hardware exp2,
   // the integer part is an exponent shift.  (Only the waves that use it work it out.)
   auto total_mass = [&](double& lnZ) -> unsigned long long {
-    const double ln2 = 0.6931471805599453094, log2e = 1.4426950408889634074;
-    const double x = fmin(fmax((double)R + 10.0 - (double)m * log2e, -2000.0), 2000.0);
+    const double ln2 = 0.6931471805599453094;
+    const double x = fmin(fmax(bulk_exponent(Tc, r0, c_tau, m) + 10.0, -2000.0), 2000.0);
     const double xi = floor(x);
     const double bulk_rel = ldexp((double)bulk * (double)__builtin_amdgcn_exp2f((float)(x - xi)), (int)xi);
     const unsigned long long S0 = S_cand + (bulk_rel < 9.0e18 ? (unsigned long long)bulk_rel : 0ull);
@@ -852,8 +852,8 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     constexpr int sh = kBlkShift;
     const uint32_t n_blk = ((uint32_t)V + (1u << sh) - 1) >> sh;               // <= kFinBins: V <= 2^18
     for (int i = tid; i < kBlkElems; i += NT) fs.fill[i] = 0;
-    // 2^R units -> 2^-40 of the maximum's mass
-    const double x = fmin(fmax((double)R + 40.0 - (double)m * 1.4426950408889634074, -1000.0), 61.0);
+    // units of the bulk terms -> 2^-40 of the maximum's mass
+    const double x = fmin(fmax(bulk_exponent(Tc, r0, c_tau, m) + 40.0, -1000.0), 61.0);
     const double xi = floor(x), unit = ldexp((double)__builtin_amdgcn_exp2f((float)(x - xi)), (int)xi);
     for (int bt = 0; bt < nb; ++bt) {
       if (nb > 1) {

@@ -121,22 +121,27 @@ __device__ __forceinline__ void scale_pair(const RowParams& r, float& hi, float&
 }
 
 // Softmax mass of a non-candidate element relative to the threshold: 2^((z - Tc) * c + r0)
-// with c = log2(e)/tau and r0 = Tc*c - ceil(Tc*c) in (-1, 0], i.e. 2^(z*c - R).  Taking the
-// difference to Tc first keeps the product small where the term is not negligible, so one
-// fp32 multiplier is accurate enough; z = -inf gives exactly 0.
+// with c = log2(e)/tau and r0 = Tc*c - ceil(Tc*c) in (-1, 0].  Taking the difference to Tc first
+// keeps the product small where the term is not negligible, so one fp32 multiplier is accurate
+// enough; z = -inf gives exactly 0.  The terms are in units of 2^(Tc*c - r0), a whole power of two
+// that whoever reads the sums works out from Tc and r0 (bulk_exponent()), so that nothing has to
+// hold an exponent that a temperature near 0 makes as large as it likes.
 struct BulkRef {
   float Tc, c, r0;
-  int R;
 };
 __device__ __forceinline__ BulkRef make_bulk_ref(float Tc, const RowParams& rp) {
   float chi, clo;
   scale_pair(rp, chi, clo);
   const double tc = (double)Tc * ((double)chi + (double)clo);
   BulkRef r;
-  r.Tc = Tc; r.c = chi; r.R = 0; r.r0 = 0.0f;
-  const double tr = ceil(tc);
-  if (tr > -1048576.0 && tr < 1048576.0) { r.R = (int)tr; r.r0 = (float)(tc - tr); }
+  r.Tc = Tc; r.c = chi;
+  r.r0 = fabs(tc) < 4.0e15 ? (float)(tc - ceil(tc)) : 0.0f;                   // (else, and for c beyond fp32: no fraction left)
   return r;
+}
+// log2 of (unit of the bulk terms / mass of the maximum m), c = log2(e)/tau.  m >= Tc / tau as
+// rounded, so what comes out above 1 is the rounding of m, and no term is left of that size.
+__device__ __forceinline__ double bulk_exponent(float Tc, float r0, double c, float m) {
+  return (double)Tc * c - (double)r0 - (double)m * 1.4426950408889634074;
 }
 __device__ __forceinline__ float bulk_term(float z, const BulkRef& r) {
   return __builtin_amdgcn_exp2f(__fmaf_rn(__fsub_rn(z, r.Tc), r.c, r.r0));
@@ -172,7 +177,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   __shared__ float blk_mass[kBlkMax];
   __shared__ uint32_t sub_hist[32];                 // that bin, split by the next 5 key bits
 
-  // (the wave's number, and further down R, in a scalar register: as vector registers they were
+  // (the wave's number, and further down r0, in a scalar register: as vector registers they were
   // spilled, and a store to scratch ahead of the loads makes every wait for one of them a wait for
   // all -- 3 us of the 33 at fp32 V = 152064, 256 rows)
   const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
@@ -507,7 +512,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   const uint32_t kb = key_thr << 14;
   const float Tc = value_of(kb);
   const BulkRef ref = make_bulk_ref(Tc, rp);
-  const int R = __builtin_amdgcn_readfirstlane(ref.R);
+  const float r0 = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(ref.r0)));
 
   // ---- stream
   entry_t* queue = reinterpret_cast<entry_t*>(smem) + wave * kQueueCap;        // this wave's LDS queue
@@ -683,7 +688,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
     for (int w = 0; w < kStreamWaves; ++w) o.bulk += red64[w];
     o.Tc = Tc;
-    o.R = R;
+    o.r0 = r0;
     o.cnt = overflow ? kCntOverflow : tot;
     o.n_blk = (uint32_t)n_blk; o.pad[0] = o.pad[1] = 0;
     a.chunks[wg] = o;

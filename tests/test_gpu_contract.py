@@ -104,9 +104,10 @@ def test_rows_that_are_almost_entirely_masked(dtype):
         assert (H.last_row_path[[0, 1, 2, 4, 5]] == 1).all(), H.last_row_path
 
 
-def test_tiny_temperatures_are_ordinary_stochastic_rows():
+@pytest.mark.parametrize("V", [30000, 40000])
+def test_tiny_temperatures_are_ordinary_stochastic_rows(V):
     rng = np.random.default_rng(13)
-    V, B = 30000, 6
+    B = 6
     z = (rng.standard_normal((B, V)) * 2.0).astype(np.float32)
     z[1, 5] = z[1, 9] = z[1].max() + 0.5                # tied maxima: tau -> 0 keeps both
     params = dict(temperature=[1e-6, 1e-6, 1e-4, 3e-2, 1e-6, 1e-3], top_k=[0, 0, 5, 0, 0, 0],
@@ -116,3 +117,23 @@ def test_tiny_temperatures_are_ordinary_stochastic_rows():
     for step in range(4):
         st = H.compare(w, H.run_gpu(d, 4, step), 4, step)
         assert st.rows == B
+
+
+@pytest.mark.parametrize("B,V", [(12, 24000), (12, 40000), (300, 40000), (12, 151643)])
+def test_log_probabilities_at_tiny_temperatures(B, V):
+    """Rows that are all negative, as logits that are log-probabilities already, at temperatures that
+    take threshold / temperature beyond 2^20: the mass below the candidate list is next to nothing,
+    whatever the sign and size of the maximum (close to 0, tens below, and a flat row)."""
+    rng = np.random.default_rng(V + B)
+    z = (rng.standard_normal((B, V)) * 2.5).astype(np.float32)
+    kind = np.arange(B) % 12
+    z[np.arange(B), rng.integers(0, V, B)] += np.where(kind % 3 == 0, 30.0, 0.0).astype(np.float32)
+    z -= z.max(axis=1, keepdims=True)
+    z -= np.choose(kind % 3, [1e-4, 11.0, 25.0]).astype(np.float32)[:, None]
+    z[2, :] = np.float32(-12.0) - (rng.integers(0, 3, V) * 0.25).astype(np.float32)
+    params = dict(temperature=np.choose(kind, [1e-5, 1e-5, 4e-5, 5e-6, 2e-5, 1e-5, 1e-6, 1e-7, 1e-12, 1e-5, 3e-5, 1e-5]),
+                  top_p=np.where(kind >= 9, 0.9, 1.0), min_p=np.where(kind == 10, 0.1, 0.0))
+    w = H.custom("log_probabilities", z, params, k_logprobs=2)
+    d = H.to_device(w)
+    for step in range(8) if B < 20 else (0,):
+        H.compare(w, H.run_gpu(d, 21, step), 21, step)
