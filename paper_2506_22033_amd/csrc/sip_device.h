@@ -29,11 +29,11 @@ struct ChunkOut {
   unsigned int pad[2];
 };
 // A row without any filter is drawn over all its elements.  For such a row the streaming kernel
-// also leaves the bulk mass of every block of kBlkElems consecutive elements: fp32, in units of 2^R,
-// the chunk's blocks in order, the last of them ending with the chunk's segment.  Chunks (and the
-// chunks of a shard) begin at multiples of kChunkUnit, so that blocks and chunks agree.
-constexpr int kBlkShift = 9, kBlkElems = 1 << kBlkShift;
-constexpr int kChunkUnit = 512;
+// also leaves the bulk mass of every block of kBlkElems consecutive elements: 64-bit integers (see
+// blk_units()), the chunk's blocks in order, the last of them ending with the chunk's segment.
+// Chunks (and the chunks of a shard) begin at multiples of kChunkUnit, so that blocks and chunks agree.
+constexpr int kBlkShift = 10, kBlkElems = 1 << kBlkShift;
+constexpr int kChunkUnit = 1024;
 static_assert(kChunkUnit % kBlkElems == 0, "a block lies in one chunk");
 
 // What the streaming kernel (the workgroup of a row's first chunk) leaves for the finishing
@@ -462,13 +462,13 @@ __device__ __forceinline__ uint32_t dpp_scan_add_u32(uint32_t v) { SIP_DPP_STEPS
 __device__ __forceinline__ uint32_t dpp_scan_max_u32(uint32_t v) { SIP_DPP_STEPS(op_max, 0u) return v; }
 __device__ __forceinline__ uint32_t dpp_scan_min_u32(uint32_t v) { SIP_DPP_STEPS(op_min, 0xFFFFFFFFu) return v; }
 #undef SIP_DPP_STEPS
-// Sum over the wave in a fixed order of additions; the total is in lane 63.
-__device__ __forceinline__ float dpp_scan_add_f32(float x) {
-#define SIP_DPPF(CTRL, RM) x = x + __uint_as_float(dpp_mov<CTRL, RM>(0u, __float_as_uint(x)));
-  SIP_DPPF(0x111, 0xf) SIP_DPPF(0x112, 0xf) SIP_DPPF(0x114, 0xf) SIP_DPPF(0x118, 0xf)
-  SIP_DPPF(0x142, 0xa) SIP_DPPF(0x143, 0xc)
-#undef SIP_DPPF
-  return x;
+// Sums of 16 consecutive lanes, in the last of them.
+__device__ __forceinline__ uint32_t row16_sum_u32(uint32_t v) {
+  v += dpp_mov<0x111, 0xf>(0u, v);
+  v += dpp_mov<0x112, 0xf>(0u, v);
+  v += dpp_mov<0x114, 0xf>(0u, v);
+  v += dpp_mov<0x118, 0xf>(0u, v);
+  return v;
 }
 __device__ __forceinline__ unsigned long long dpp_scan_add_u64(unsigned long long v) {
 #define SIP_DPP64(CTRL, RM)                                                                   \

@@ -50,7 +50,7 @@ constexpr int kFinDrawBig = -1;                        // internal: the draw goe
 constexpr int kFinDrawRow = -2;                        // internal: no filter, the draw goes through the row's block masses
 constexpr int kFinWholeRow = 16;                       // settled, over the whole row (see row_path in sip.h)
 static_assert(kFinBPT == 2, "scan code below is written for two bins per thread");
-static_assert(kFinMembers >= kBlkElems && kFinBins >= kBlkElems, "tables of a block's elements");
+static_assert(kFinBins >= kBlkElems && kFinThreads << kBlkShift >= 1 << 18, "a table of a block's elements; a block per thread");
 
 struct __align__(16) FinShared {
   uint32_t hcnt[kFinBins];                  // entries per value bin
@@ -845,16 +845,18 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   }
   int settled = 1;
   if (code == kFinDrawRow) {
-    // ---- (6'') no filter: the mass of every block of the row (512 elements) is its
+    // ---- (6'') no filter: the mass of every block of the row (1024 elements) is its
     // bulk mass, left by the streaming kernel, plus that of the list entries in it; prefix; and only
-    // the block that holds the crossing is read again, 1 or 2 KB.  (Re-reading the row for this, as
-    // rescue_row does, took 55 us of the 73 us of bf16 V = 151643, 256 rows.)
-    constexpr int sh = kBlkShift;
-    const uint32_t n_blk = ((uint32_t)V + (1u << sh) - 1) >> sh;               // <= kFinBins: V <= 2^18
+    // the block that holds the crossing is read again, 2 or 4 KB.  (Re-reading the row for this, as
+    // rescue_row does, took 55 us of the 73 us of bf16 V = 151643, 256 rows.)  Bulk masses stay whole
+    // numbers in the streaming kernel's unit up to the one place where a running sum is compared:
+    // the block's elements, added anew, come to the block's sum bit for bit.
+    const uint32_t n_blk = ((uint32_t)V + kBlkElems - 1) >> kBlkShift;         // <= NT
     for (int i = tid; i < kBlkElems; i += NT) fs.fill[i] = 0;
-    // units of the bulk terms -> 2^-40 of the maximum's mass
-    const double x = fmin(fmax(bulk_exponent(Tc, r0, c_tau, m) + 40.0, -1000.0), 61.0);
+    // bulk units -> 2^-40 of the maximum's mass
+    const double x = fmin(fmax(bulk_exponent(Tc, r0, c_tau, m) + (double)(kFixShift - kBlkUnitShift), -1000.0), 61.0);
     const double xi = floor(x), unit = ldexp((double)__builtin_amdgcn_exp2f((float)(x - xi)), (int)xi);
+    auto rescaled = [&](unsigned long long u) { return (unsigned long long)fmin((double)u * unit, 4.0e18); };
     for (int bt = 0; bt < nb; ++bt) {
       if (nb > 1) {
         load_batch(bt);
@@ -865,25 +867,24 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
         if (live(bt, r) && creg[r].y != kFinNone) {
           if (nb > 1) creg[r].x = key_of(scaled_s(__uint_as_float(creg[r].x)));
           const unsigned long long E = mass(value_of(creg[r].x));
-          if (E) atomicAdd(&fs.hidx[creg[r].y >> sh], E);
+          if (E) atomicAdd(&fs.hidx[creg[r].y >> kBlkShift], E);
         }
     }
-    unsigned long long w[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint32_t g = min(2u * (uint32_t)tid + (uint32_t)j, n_blk - 1);     // its chunk starts at floor(ch * n_blk / S)
+    unsigned long long w;
+    {
+      const uint32_t g = min((uint32_t)tid, n_blk - 1);                        // its chunk starts at floor(ch * n_blk / S)
       const uint32_t ch = ((g + 1) * (uint32_t)S - 1) / n_blk;
       const uint32_t first = ch * n_blk / (uint32_t)S, next = (ch + 1) * n_blk / (uint32_t)S;
-      const float* end = reinterpret_cast<const float*>(a.cand + ((size_t)b * (size_t)S + ch + 1) * (size_t)a.cap_c);
-      const float f = end[(int)(g - first) - (int)(next - first)];
-      w[j] = 2u * (uint32_t)tid + (uint32_t)j < n_blk ? (unsigned long long)fmin((double)f * unit, 4.0e18) : 0ull;
+      const unsigned long long* end = reinterpret_cast<const unsigned long long*>(a.cand + ((size_t)b * (size_t)S + ch + 1) * (size_t)a.cap_c);
+      const unsigned long long u = end[(int)(g - first) - (int)(next - first)];
+      w = (uint32_t)tid < n_blk ? rescaled(u) : 0ull;
     }
     lds_barrier();
-    w[0] += fs.hidx[2 * tid]; w[1] += fs.hidx[2 * tid + 1];
-    const unsigned long long minc = dpp_scan_add_u64(w[0] + w[1]);
+    w += fs.hidx[tid];
+    const unsigned long long minc = dpp_scan_add_u64(w);
     if (lane == kWave - 1) fs.r64[wave] = minc;
     lds_barrier();
-    unsigned long long ex = minc - w[0] - w[1], S3 = 0;
+    unsigned long long ex = minc - w, S3 = 0;
 #pragma unroll
     for (int ww = 0; ww < kFinWaves; ++ww) {
       const unsigned long long m64 = fs.r64[ww];
@@ -891,9 +892,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
       S3 += m64;
     }
     const unsigned long long target = (__umul64hi(j24, S3) << 40) | ((j24 * S3) >> 24);    // floor(j * S3 / 2^24)
-    if (ex <= target && target < ex + w[0]) { fs.bin_d = 2 * tid; fs.before_d = ex; }
-    ex += w[0];
-    if (ex <= target && target < ex + w[1]) { fs.bin_d = 2 * tid + 1; fs.before_d = ex; }
+    if (ex <= target && target < ex + w) { fs.bin_d = tid; fs.before_d = ex; }
     lds_barrier();
     const int blk = fs.bin_d;
     if (blk < 0) return 14;                                                    // uniform (no mass)
@@ -904,62 +903,71 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
       }
 #pragma unroll
       for (int r = 0; r < CR; ++r)
-        if (live(bt, r) && creg[r].y != kFinNone && (int)(creg[r].y >> sh) == blk) {
+        if (live(bt, r) && creg[r].y != kFinNone && (int)(creg[r].y >> kBlkShift) == blk) {
           if (nb > 1) creg[r].x = key_of(scaled_s(__uint_as_float(creg[r].x)));
-          const uint32_t q = atomicAdd(&fs.n_memb, 1u);                        // (a block's elements fit)
-          fs.m_key[q] = creg[r].x; fs.m_E[q] = mass(value_of(creg[r].x));
-          fs.fill[creg[r].y & ((1u << sh) - 1)] = q + 1;
+          fs.fill[creg[r].y & (kBlkElems - 1)] = max(creg[r].x, 1u);           // key of s; 0: not in the list
         }
     }
     lds_barrier();
     if (wave == 0) {
-      // lane l has the block's elements 8l .. 8l + 7
-      const int e0 = (blk << sh) + lane * 8;
       const char* row = reinterpret_cast<const char*>(a.logits) + (size_t)b * (size_t)a.row_stride * (a.bf16 ? 2 : 4);
-      uint32_t raw[8];
-      if (a.bf16) {                                                            // uniform
-        const uint4 q = *reinterpret_cast<const uint4*>(row + (size_t)min(e0, (V - 1) / 8 * 8) * 2);
-        const uint32_t w4[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) raw[i] = (i & 1) ? w4[i / 2] & 0xFFFF0000u : w4[i / 2] << 16;
-      } else {
-        const int e_last = (V - 1) / 4 * 4;
-        const uint4 q0 = *reinterpret_cast<const uint4*>(row + (size_t)min(e0, e_last) * 4);
-        const uint4 q1 = *reinterpret_cast<const uint4*>(row + (size_t)min(e0 + 4, e_last) * 4);
-        raw[0] = q0.x; raw[1] = q0.y; raw[2] = q0.z; raw[3] = q0.w;
-        raw[4] = q1.x; raw[5] = q1.y; raw[6] = q1.z; raw[7] = q1.w;
-      }
       const BulkRef ref = make_bulk_ref(Tc, rp);
-      auto element = [&](int i, float& z) -> unsigned long long {              // mass of element e0 + i; z: its s
-        z = __uint_as_float(raw[i]);
-        if (e0 + i >= V) return 0ull;
-        const uint32_t slot = fs.fill[(e0 + i) & (kBlkElems - 1)];
-        if (slot) { z = value_of(fs.m_key[slot - 1]); return fs.m_E[slot - 1]; }
-        const float t = bulk_term(z, ref);
-        z = scaled_s(z);
-        return (unsigned long long)fmin((double)t * unit, 4.0e18);
-      };
-      unsigned long long mine = 0;
+      const int last_of_load = a.bf16 ? 7 : 3;
+      unsigned long long run_u = 0, run_E = fs.before_d;                       // ahead of the round: bulk units; list and earlier blocks
+#pragma nounroll
+      for (int half = 0; half < 2; ++half) {
+        // lane l has the elements 8l .. 8l + 7 of this half of the block
+        const int e0 = (blk << kBlkShift) + half * (kBlkElems / 2) + lane * 8;
+        uint32_t raw[8];
+        if (a.bf16) {                                                          // uniform
+          const uint4 q = *reinterpret_cast<const uint4*>(row + (size_t)min(e0, (V - 1) / 8 * 8) * 2);
+          const uint32_t w4[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-      for (int i = 0; i < 8; ++i) { float z; mine += element(i, z); }
-      unsigned long long C = fs.before_d + dpp_scan_add_u64(mine) - mine;
-      // the first element whose running mass exceeds the target; the blocks' sums are rounded, so it
-      // can also be that none does: then the last one that has any mass
-      uint32_t tok = kFinNone, tok_key = 0, last = kFinNone, last_key = 0;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        float z;
-        const unsigned long long E = element(i, z);
-        C += E;
-        if (E) {
-          last = (uint32_t)(e0 + i); last_key = key_of(z);
-          if (tok == kFinNone && C > target) { tok = last; tok_key = last_key; }
+          for (int i = 0; i < 8; ++i) raw[i] = (i & 1) ? w4[i / 2] & 0xFFFF0000u : w4[i / 2] << 16;
+        } else {
+          const int e_last = (V - 1) / 4 * 4;
+          const uint4 q0 = *reinterpret_cast<const uint4*>(row + (size_t)min(e0, e_last) * 4);
+          const uint4 q1 = *reinterpret_cast<const uint4*>(row + (size_t)min(e0 + 4, e_last) * 4);
+          raw[0] = q0.x; raw[1] = q0.y; raw[2] = q0.z; raw[3] = q0.w;
+          raw[4] = q1.x; raw[5] = q1.y; raw[6] = q1.z; raw[7] = q1.w;
         }
-      }
-      const unsigned long long hit = __ballot(tok != kFinNone), any = __ballot(last != kFinNone);
-      const int src = hit ? __ffsll((long long)hit) - 1 : (any ? 63 - __clzll((long long)any) : 0);
-      if (lane == src && (hit || any)) {
-        fs.token = hit ? tok : last; fs.token_key = hit ? tok_key : last_key;
+        // element e0 + i: key of its s if it is in the list (0: not), its bulk term, its mass as a list entry
+        auto element = [&](int i, uint32_t& key, float& t, unsigned long long& E) {
+          key = fs.fill[(e0 + i) & (kBlkElems - 1)];
+          const bool in = e0 + i < V;
+          t = in && !key ? bulk_term(__uint_as_float(raw[i]), ref) : 0.0f;
+          E = in && key ? mass(value_of(key)) : 0ull;
+        };
+        unsigned long long u = 0, E = 0;
+        float part = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          uint32_t key; float t; unsigned long long Ei;
+          element(i, key, t, Ei);
+          part += t; E += Ei;
+          if ((i & last_of_load) == last_of_load) { u += blk_units(part); part = 0.0f; }
+        }
+        const unsigned long long u_inc = dpp_scan_add_u64(u), E_inc = dpp_scan_add_u64(E);
+        unsigned long long C_u = run_u + u_inc - u, C_E = run_E + E_inc - E;
+        uint32_t tok = kFinNone, tok_key = 0;
+        part = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          uint32_t key; float t; unsigned long long Ei;
+          element(i, key, t, Ei);
+          part += t; C_E += Ei;
+          const unsigned long long to_here = C_u + blk_units(part);
+          if (tok == kFinNone && C_E + rescaled(to_here) > target) {
+            tok = (uint32_t)(e0 + i); tok_key = key ? key : key_of(scaled_s(__uint_as_float(raw[i])));
+          }
+          if ((i & last_of_load) == last_of_load) { C_u = to_here; part = 0.0f; }
+        }
+        const unsigned long long hit = __ballot(tok != kFinNone);
+        if (hit) {
+          if (lane == __ffsll((long long)hit) - 1) { fs.token = tok; fs.token_key = tok_key; }
+          break;
+        }
+        run_u += last_lane_u64(u_inc); run_E += last_lane_u64(E_inc);
       }
     }
     lds_barrier();

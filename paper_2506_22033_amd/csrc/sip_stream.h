@@ -146,6 +146,15 @@ __device__ __forceinline__ double bulk_exponent(float Tc, float r0, double c, fl
 __device__ __forceinline__ float bulk_term(float z, const BulkRef& r) {
   return __builtin_amdgcn_exp2f(__fmaf_rn(__fsub_rn(z, r.Tc), r.c, r.r0));
 }
+// Bulk terms of one 16-byte load, added in the order of its elements, as an integer in units of
+// 2^-41 of a term of 1, that is at most 2^-40 of the maximum's mass: added to 2^11 a double's last bit
+// is 2^-41, so the low bits of the sum are the integer (a load's terms add up to at most 8).
+constexpr unsigned long long kBlkMagic = 0x40A0000000000000ull;       // 2^11
+constexpr int kBlkUnitShift = 41;
+__device__ __forceinline__ unsigned long long blk_bits(float g) {      // + kBlkMagic
+  return (unsigned long long)__double_as_longlong((double)g + 2048.0);
+}
+__device__ __forceinline__ unsigned long long blk_units(float g) { return blk_bits(g) - kBlkMagic; }
 // per-thread fp32 partial sum -> integer units of 2^-30
 __device__ __forceinline__ unsigned long long bulk_units(float acc) {
   return acc > 0.0f ? (unsigned long long)(acc * kBulkScale) : 0ull;
@@ -174,7 +183,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   __shared__ unsigned long long red64[kStreamWaves];
   __shared__ uint32_t wave_cnt[kStreamWaves];
   __shared__ uint32_t key_thr, need_thr;            // 13-bit key of the threshold bin; entries still wanted from inside it
-  __shared__ float blk_mass[kBlkMax];
+  __shared__ unsigned long long blk_mass[kBlkMax];
   __shared__ uint32_t sub_hist[32];                 // that bin, split by the next 5 key bits
 
   // (the wave's number, and further down r0, in a scalar register: as vector registers they were
@@ -468,7 +477,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
       }
     }
     __syncthreads();
-    if (tid < kBlkMax) blk_mass[tid] = 0.0f;
+    if (tid < kBlkMax) blk_mass[tid] = 0ull;
     if (wave == 0) {
       // lane l: sub-bin 31 - l, descending (the lane's number worked out anew: one register less
       // from the start to here)
@@ -524,7 +533,8 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   // Block masses of a row without any filter.  One scalar branch per load for every other row; a
   // copy of the loop for these rows alone cost all of them registers (bf16 V = 129280, 1024 rows:
   // streaming kernel 90 -> 115 us).  bf16 V = 151643, 256 rows, no filter: finishing kernel 72.6 ->
-  // 17 us, streaming kernel unchanged at 28 us, call 99.3 -> 43.3 us.
+  // 16 us, streaming kernel 28 us as before, call 99.4 -> 43 us; with the sums in fp32 26.5 + 14.8 us,
+  // but fewer bits than the draw by re-reading the row has.
   const bool plain = !SH && !rp.greedy && unfiltered(rp, V);                   // workgroup-uniform
   // `hb`: the history bits of the EPL elements (bit i: element e0 + i carries a penalty); `tg`: bf16,
   // the same as words to or into the load's (tag_words); `it`: the wave's load
@@ -568,10 +578,11 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
     }
     acc += g;
     if (!SH && plain) {
-      // one (bf16) or two (fp32) waves' loads make a block: at most two summands, so the order of
-      // the additions does not matter
-      g = dpp_scan_add_f32(g);
-      if (lane == kWave - 1) unsafeAtomicAdd(&blk_mass[(uint32_t)(e0 - c0) / (uint32_t)kBlkElems], g);
+      // (in two halves of 24 and 20 bits: 32-bit sums over 16 lanes, and four atomics of the wave for the rest)
+      const unsigned long long t = blk_bits(g);
+      const uint32_t t0 = row16_sum_u32((uint32_t)t & 0xFFFFFFu), t1 = row16_sum_u32((uint32_t)(t >> 24) & 0xFFFFFFu);
+      static_assert(((kBlkMagic >> 24) & 0xFFFFFFu) == 0, "neither half holds any of the magic bits");
+      if ((lane & 15) == 15) atomicAdd(&blk_mass[(uint32_t)(e0 - c0) / (uint32_t)kBlkElems], ((unsigned long long)t1 << 24) + t0);
     }
   };
   // Element e0 of the piece being processed is bit (ib - ibase) + e0 - c0 of the bitmap, a
@@ -679,9 +690,9 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
     if ((bmw[min(bit >> 5, (uint32_t)(kChunkBitsMax / 32 - 1))] >> (bit & 31u)) & 1u) en.y |= kTagBit;
     seg[i] = en;
   }
-  const bool blocks = plain && tot <= (uint32_t)(kChunkCap - kBlkMax / 2);       // workgroup-uniform
+  const bool blocks = plain && tot <= (uint32_t)(kChunkCap - kBlkMax);           // workgroup-uniform
   const int n_blk = blocks ? (c1 - c0 + kBlkElems - 1) / kBlkElems : 0;
-  if (tid < n_blk) (reinterpret_cast<float*>(a.cand + (size_t)(wg + 1) * (size_t)kChunkCap) - n_blk)[tid] = blk_mass[tid];
+  if (tid < n_blk) (reinterpret_cast<unsigned long long*>(a.cand + (size_t)(wg + 1) * (size_t)kChunkCap) - n_blk)[tid] = blk_mass[tid];
   if (tid == 0) {
     ChunkOut o;
     o.bulk = 0;

@@ -3,8 +3,11 @@ block edges, the smallest and largest vocabulary, both kinds of finishing kernel
 batches and chunks whose list leaves no room for the masses (those rows are drawn the longer way)."""
 import numpy as np
 import pytest
+import torch
 
+import paper_2506_22033_amd as sip
 import workloads
+from oracle import sip_oracle as O
 from tests import sip_harness as H
 
 pytestmark = pytest.mark.gpu
@@ -28,3 +31,24 @@ def test_chunk_and_block_edges(B, V, bf16):
     for step in (0, 1, 2) if B < 10 else (0,):
         H.compare(w, H.run_gpu(d, 11, step), 11, step)
     assert (H.last_row_path == 16).mean() > 0.9 or B < 10, np.unique(H.last_row_path)
+
+
+def test_draws_of_flat_rows_against_float64():
+    """51200 draws from 512 flat rows of 40000 entries, with an edge of the cumulative distribution every 2.5e-5.
+    A cumulative mass that is off by eps moves a draw with probability 2 eps / 2.5e-5.  With integer sums what
+    is off are the fp32 sums of the 16-byte loads, 2^-25 of themselves each: 10000 independent ones come to
+    3e-10 of the total, to half of that at an edge on the way, so that less than one draw in 51200 is expected to
+    move (none does); with block sums in fp32 four of these did."""
+    V, B = 40000, 512
+    rng = np.random.default_rng(V)
+    z = torch.from_numpy((rng.standard_normal((B, V)) * 0.3).astype(np.float32)).to(H.DEV)
+    tau = torch.from_numpy(rng.uniform(0.6, 1.4, B).astype(np.float32)).to(H.DEV)
+    s = z / tau[:, None]
+    cdf = (s.double() - s.max(dim=1, keepdim=True).values.double()).exp_().cumsum_(1)
+    cdf /= cdf[:, -1:].clone()
+    moved = 0
+    for step in range(100):
+        u = torch.tensor([O.row_uniform(5, b, step) for b in range(B)], dtype=torch.float64, device=H.DEV)
+        want = torch.searchsorted(cdf, u[:, None], right=True)[:, 0]
+        moved += int((sip.sip_sample(z, dict(temperature=tau), None, None, 5, step, -1, V=V)[0] != want).sum())
+    assert moved <= 1, moved
