@@ -493,15 +493,17 @@ __device__ __forceinline__ unsigned long long fix_of(float e) {
   return (unsigned long long)(e * kFixScale);
 }
 
-// exp(x) for x <= 0: the product with log2(e) carried in two floats, v_exp_f32 on the larger and a
-// first-order step for the smaller.  Its error is that of v_exp_f32 plus one rounding, as with
-// expf(), without expf()'s range reduction and special cases (16 -> 9 issue slots per element).
+// exp(x) for x <= 0: 2^e 2^a with e + a = x log2(e), e whole, |a| <= 1/2 (the product in two floats,
+// rounded once in a), v_exp_f32 of a, an exponent shift.  As accurate as expf() -- over [-28.6, 0],
+// where there is any mass, 8.3e-8 at most and 2.6e-8 rms -- without its special cases (16 -> 12
+// issue slots per element).  The argument has to be reduced: v_exp_f32 of all of it, the low part as
+// a first-order step, is three instructions less and off by 1.4e-7 and 3.6e-8.
 __device__ __forceinline__ float exp_nonpos(float x) {
-  x = fmaxf(x, -150.0f);                   // (-inf and NaN among them; exp2 of it is 0)
+  x = fmaxf(x, -150.0f);                   // (-inf and NaN among them; their result is 0 in units of 2^-40)
   const float hi = __fmul_rn(x, 1.44269502f);
   const float lo = __fmaf_rn(x, 1.92596303e-8f, __fmaf_rn(x, 1.44269502f, -hi));
-  const float p = __builtin_amdgcn_exp2f(hi);
-  return __fmaf_rn(p, __fmul_rn(lo, 0.693147182f), p);
+  const float e = rintf(hi);
+  return __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f((hi - e) + lo), (int)e);
 }
 // Mass in units of 2^-40, rounded to nearest: added to 2^12 a double's last bit is 2^-40, so the
 // low bits of the sum are the integer (3 instructions; the conversion to 64 bits takes 7).

@@ -86,3 +86,18 @@ def test_counts_beyond_the_counters_and_a_separate_prompt():
     ref = O.sample_batch(w.logits, w.params, w.hist_indptr, w.hist_tokens, 1, 0, 3,
                          prompt_indptr=p_ind.cpu().numpy(), prompt_tokens=p_tok.cpu().numpy())
     H.check_rows("prompt", range(B), ref, tuple(x.cpu().numpy() for x in out), 3)
+
+
+def test_masses_are_as_accurate_as_a_float_exponential():
+    """Two tokens x apart: the better one's log-probability is -log(1 + e^-x), which gives the mass of the
+    other back.  What it is off by, rms: expf's error against float64, 2.62e-8, and the rounding of the
+    log-probability to fp32, 2.69e-8 as worked out here."""
+    x = np.linspace(0.0, 8.0, 1 << 17, dtype=np.float32)
+    z = torch.zeros(len(x), 8, dtype=torch.float32, device=H.DEV)
+    z[:, 1] = -torch.from_numpy(x).to(H.DEV)
+    _, ids, lp = sip.sip_sample(z, dict(temperature=torch.ones(len(x), device=H.DEV)), None, None, 0, 0, 1, V=2)
+    assert int(ids[:, 1].max()) == 0
+    got, want = np.expm1(-lp[:, 1].double().cpu().numpy()), np.exp(-x.astype(np.float64))
+    rms = float(np.sqrt(np.mean((got / want - 1.0) ** 2)))
+    rounded = np.expm1(np.log1p(want).astype(np.float32).astype(np.float64)) / want - 1.0
+    assert rms < 1.03 * np.hypot(2.62e-8, np.sqrt(np.mean(rounded ** 2))), rms
