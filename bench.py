@@ -487,8 +487,8 @@ def main() -> int:
         # a batch of at most one row per compute unit is finished by one kernel (finish_rescue_kernel);
         # a larger one by finish_kernel and, behind it, rescue_kernel (include/sip.h, "Kernels of a call")
         one_kernel = w.B <= torch.cuda.get_device_properties(dev).multi_processor_count
-        # (rows of up to SIP_MAX_RESIDENT_V entries: resident_kernel alone)
-        names = (("resident_kernel", (0, 1)),) if w.V <= 32768 else \
+        # (rows of up to SIP_MAX_RESIDENT_V entries, in such a batch: resident_kernel alone)
+        names = (("resident_kernel", (0, 1)),) if w.V <= 32768 and one_kernel else \
                 (("stream_kernel", (0, 1)), ("finish_rescue_kernel", (2, 3))) if one_kernel else \
                 (("stream_kernel", (0, 1)), ("finish_kernel", (2, 3)), ("rescue_kernel", (4, 5)))
         for name, (i0, i1) in names:

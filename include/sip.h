@@ -83,8 +83,8 @@ typedef struct {
  *
  * Diagnostic: after a call has completed, the first 2 * B int32 of the workspace say, per row,
  * which code path finished it (path[B]) and what the finishing kernel made of it (why[B]).
- *   path: 1 = settled from the candidate list the one pass over the logits left behind, or, up to
- *   SIP_MAX_RESIDENT_V entries, from the row held in registers; any
+ *   path: 1 = settled from the candidate list the one pass over the logits left behind, or from
+ *   the row held in registers (see "Kernels of a call"); any
  *   other value = finished after reading the row again (normally from cache): 15 = from a second,
  *   longer candidate list (one more read of that row); 16 = by the row's workgroup over the whole
  *   row (plain temperature sampling without any filter: two more reads; a nucleus that reaches
@@ -100,11 +100,14 @@ typedef struct {
  *   14 no mass / exact-only shape.
  * Results mean the same whichever path ran.
  *
- * Kernels of a call (names as a profiler shows them): resident_kernel alone up to
- * SIP_MAX_RESIDENT_V entries (on a state: below 16384, behind state_take_tick_kernel); else stream_kernel (the one pass over the
- * logits), then finish_rescue_kernel for batches of no more rows than the device has compute
- * units, else finish_kernel followed by rescue_kernel (which returns at once when no row was
- * passed on); exact_kernel alone for vocabulary sizes outside the single-pass kernels.
+ * Kernels of a call (names as a profiler shows them): resident_kernel alone for vocabularies below
+ * 16384 (on a state behind state_take_tick_kernel), and, without a state, up to SIP_MAX_RESIDENT_V
+ * for batches of no more rows than the device has compute units, unless nothing but best-n is asked
+ * for; for larger batches only if params names no top_k, top_p or min_p and k_logprobs <= 0 (min_p
+ * alone: up to three times as many rows).  Else stream_kernel (the one pass over the logits), then
+ * finish_rescue_kernel for batches of no more rows than the device has compute units, else
+ * finish_kernel followed by rescue_kernel (which returns at once when no row was passed on);
+ * exact_kernel alone for vocabulary sizes outside the single-pass kernels.
  */
 size_t sip_workspace_bytes(int32_t B, int32_t V, sip_dtype dtype, int64_t hist_nnz, int32_t k_logprobs);
 
@@ -159,8 +162,8 @@ sip_status sip_sample(const void* logits, int32_t B, int32_t V, int64_t row_stri
  *  workspace     at least sip_workspace_bytes_sharded(...) bytes: it includes room for B whole
  *                rows, used only by rows that leave the single-pass path (their workgroup puts
  *                the row together there first) and by shapes the single-pass kernels do not
- *                serve (V above 262144, V_shard below 8192; rows of up to SIP_MAX_RESIDENT_V
- *                entries only if they leave the registers for the exact path).
+ *                serve (V above 262144, V_shard below 8192; rows held in registers only if they
+ *                leave them for the exact path).
  * Everything else as for sip_sample().
  */
 size_t sip_workspace_bytes_sharded(int32_t B, int32_t V_shard, int32_t t, sip_dtype dtype, int64_t hist_nnz,

@@ -33,12 +33,7 @@ struct Plan {
   size_t final_lds;
 };
 
-// Rows up to here are held in registers by one workgroup (sip_resident.h).  At the line both ways
-// cost the same on an easy row (bf16 V = 31931, 67 rows: 20.4 us against 13.0 + 13.0 us for the
-// streaming and the finishing kernel; fp32 V = 28520, 43 rows: 27.6 against 11.5 + 17.8 us), below
-// it the one kernel wins (fp32 V = 23702 greedy: 6.8 against 14.5 us), and on rows whose nucleus
-// outgrows a candidate list it wins everywhere (V = 32000, 4 rows: 25.7 against 77.6 us).  Beyond,
-// the row no longer fits 16 waves x 128 registers.
+// Rows up to here fit the registers of one workgroup (16 waves x 128; sip_resident.h).
 constexpr int kResidentMaxV = SIP_MAX_RESIDENT_V;
 static_assert(kResidentMaxV == 1024 * 32, "the largest variant launched below");
 constexpr int kFastMinV = 16384;
@@ -212,6 +207,30 @@ template <bool SH>
 sip_status launch(const sip::Args& a, int32_t B, int dtype, const Plan& plan, bool state, sip::StateHeader* head,
                   hipStream_t stream);
 
+// Where both ways serve a row (16384 to 32768 entries): whether it is held in registers.  That takes
+// a compute unit for a row and 9 to 34 us, whatever the row's filters keep; a batch of more rows than
+// compute units takes as many rounds of it.  The streaming and finishing kernels overlap their rows,
+// but pay for a row that its list does not settle: a nucleus that outgrows it, or queues that overflow
+// (bf16 rows of one chunk under a wide min-p).  Which rows are like that, or greedy, is not known here;
+// which parameters the call has is.  us, both ways / in registers (fp32 unless said, 256 compute units):
+//   up to one row per compute unit, V = 32768, 64 rows: greedy 16 / 10; no filter 24 / 14; min-p 20 / 15;
+//   top-k 20 / 18; top-k and top-p 20 / 22.5; top-p, peaked rows 23 / 22.5, flat rows 83 / 25 (bf16 171 /
+//   27); all parameters, 512 tokens of history, best 20: 27 / 32, and V = 24000 bf16, 256 rows 215 / 31.
+//   So: in registers, up to a fifth slower on the rows that a list settles and several times faster
+//   where one of them is not; but greedy rows and best 5, without any filter: 17 / 23, by streaming.
+//   V = 24000, 2048 rows: greedy 78 / 53; no filter 119 / 100; min-p 107 / 105, V = 32000 and 512 tokens
+//   of history 125 / 152, 600 rows of it 56 / 57; top-k and top-p 106 / 158; top-p, peaked 118 / 141.
+//   So: in registers without a filter, min-p alone up to three rounds.
+bool resident_is_chosen(const sip::Args& a, int32_t B, bool state, int compute_units) {
+  // A state's call would have to take its number in a launch of its own before this kernel (the
+  // streaming kernel does it in passing): bf16 V = 28532, 4 rows, hand-off: 56.8 us an iteration
+  // against 53.4; V = 28092, 13 rows: 59.3 against 53.7.
+  if (state) return false;
+  const bool top = a.p.top_k || a.p.top_p, best = a.k_lp > 0;
+  if (B <= compute_units) return top || a.p.min_p || !best;
+  return !top && !best && (!a.p.min_p || B <= 3 * compute_units);
+}
+
 // Argument checks common to the entry points, workspace carving and the kernel launches.
 sip_status sample_impl(const void* logits, int32_t B, int32_t V, int64_t row_stride, sip_dtype dtype,
                        const sip_params* params, const HistSource& h, uint64_t seed, uint64_t step,
@@ -302,11 +321,7 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
   hipEvent_t ev[6];
   for (int i = 0; i < 6; ++i) { ev[i] = g_prof[i]; g_prof[i] = nullptr; }
   const bool timed = ev[0] || ev[1] || ev[2] || ev[3] || ev[4] || ev[5];
-  // A state's call has to take its number before every row's kernel (a launch of its own here; the
-  // streaming kernel does it in passing), and a decode loop on a state waits for each launch: where
-  // the single-pass kernels serve the shape too, they keep it (bf16 V = 28532, 4 rows, hand-off:
-  // 53.4 us an iteration against 56.8; V = 28092, 13 rows: 53.7 against 59.3).
-  if (a.V <= kResidentMaxV && !(state && plan.fast)) {
+  if (a.V <= kResidentMaxV && (!plan.fast || resident_is_chosen(a, B, state, dev->compute_units))) {
     // a workgroup holds its whole row in registers: one kernel
     if (state) {
       a.call_tick = a.rescue_tick;

@@ -101,3 +101,24 @@ def test_masses_are_as_accurate_as_a_float_exponential():
     rms = float(np.sqrt(np.mean((got / want - 1.0) ** 2)))
     rounded = np.expm1(np.log1p(want).astype(np.float32).astype(np.float64)) / want - 1.0
     assert rms < 1.03 * np.hypot(2.62e-8, np.sqrt(np.mean(rounded ** 2))), rms
+
+
+@pytest.mark.parametrize("params,k,rounds,in_registers", [
+    (dict(top_k=12000, top_p=0.9), 0, 1, True), (dict(top_k=12000, top_p=0.9), 0, 2, False),
+    (dict(top_k=12000), 5, 1, True), (dict(top_k=12000), 0, 2, False),
+    ({}, 0, 1, True), ({}, 0, 5, True), ({}, 1, 1, False), (dict(min_p=0.0), 0, 3, True), (dict(min_p=0.0), 0, 4, False)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_which_way_a_batch_goes(params, k, rounds, in_registers, bf16):
+    """Vocabularies that both ways serve: one row more than fills a round of workgroups changes over, where a
+    call's parameters say so.  A k that no candidate list holds (code 2), or no filter (path 16), tells which."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(rounds)
+    B, V = (rounds - 1) * cus + (1 if rounds > 1 else cus), 20000
+    z = np.tile((rng.standard_normal((8, V)) * 2.0).astype(np.float32), ((B + 7) // 8, 1))[:B]
+    w = H.custom("ways", workloads.f32_to_bf16_bits(z) if bf16 else z, dict(temperature=0.9, **params), None, k_logprobs=k)
+    out = H.run_gpu(H.to_device(w), 2, 0)
+    if params.get("top_k"):
+        assert (H.last_row_why == (1 if in_registers else 2)).all(), np.unique(H.last_row_why)
+    else:
+        assert (H.last_row_path == (1 if in_registers else 16)).all(), np.unique(H.last_row_path)
+    H.compare(w, out, 2, 0, rows=range(0, B, max(1, B // 16)))
