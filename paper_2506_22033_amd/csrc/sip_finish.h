@@ -42,6 +42,7 @@ constexpr int kFinHash = 8192;                         // slots of the multiplic
 constexpr int kFinHashMax = 6144;                      // distinct history tokens it takes
 constexpr int kFinCountBits = 14;                      // a slot: token << 14 | multiplicity (18 + 14 bits), 0 = free
 constexpr uint32_t kFinCountMax = (1u << kFinCountBits) - 1;
+constexpr uint32_t kFinFold = 8192;                    // histories that could outgrow these bits: taken out of a count beyond it
 constexpr int kFinMembers = 512;                       // members of one index bin the draw resolves
 constexpr int kFinTopMax = 256;                        // entries at or above the bin of the n-th best
 constexpr int kFinKeySteps = 64;                       // distinct keys of one bin that are stepped through
@@ -177,7 +178,6 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   static_assert(kFinHash == 2 * kTableSlots, "as many bytes: a slot's table is copied with its own geometry, half of the slots in use");
   const bool long_hist = h_hi - h_lo > (long long)kFinCountMax;              // only then can a multiplicity outgrow its bits
   constexpr int HR = 8;                    // history tokens a thread requests at once
-  bool big_count = false;
   int htok[HR];
 #pragma unroll
   for (int j = 0; j < HR; ++j) {
@@ -201,8 +201,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
       // (a token beyond the vocabulary keeps its place, with the multiplicity 0 that never matches)
       auto pack = [&](uint32_t k, uint32_t v) -> uint32_t {
         if (k == kTableEmpty) return 0u;
-        big_count |= v > kFinCountMax;
-        return k < (uint32_t)V ? (k << kFinCountBits) | min(v, kFinCountMax) : ~kFinCountMax;
+        return k < (uint32_t)V ? (k << kFinCountBits) | (v <= kFinCountMax ? v : ((v - 1) & (kFinFold - 1)) + 1) : ~kFinCountMax;
       };
 #pragma unroll
       for (int j = 0; j < NQ; ++j)
@@ -261,6 +260,22 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     const uint32_t u = min(min(min(slot_for(q.x, t), slot_for(q.y, t)), slot_for(q.z, t)), slot_for(q.w, t));
     return u < kFinCountMax ? u + 1u : 0u;
   };
+  // A multiplicity that a long history could carry beyond its bits: every kFinFold of it are taken out
+  // of the slot again, after the batch of 4096 tokens that got it there (so that a slot never reaches
+  // kFinCountMax), and noted as one entry (m_key: token) that the look-up adds back.
+  static_assert(kFinFold + HR * kFinThreads < kFinCountMax, "a batch on top of what folding leaves");
+  uint32_t n_fold = 0;                     // uniform: such entries
+  auto note_fold = [&](uint32_t t, uint32_t slot) {
+    const uint32_t q = atomicAdd(&fs.n_memb, 1u);
+    if (q < (uint32_t)kFinMembers) { fs.m_key[q] = t; fs.m_idx[q] = slot; } else fs.hash_fail = 1;
+  };
+  auto fold = [&]() {
+    lds_barrier();
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(fs.n_memb, (uint32_t)kFinMembers));
+    for (uint32_t q = n_fold + tid; q < n; q += NT) atomicSub(&fs.u.hash[fs.m_idx[q]], kFinFold);
+    n_fold = n;
+    lds_barrier();
+  };
   if (need_hash && !use_table) {
     uint32_t mine = 0;                     // slots this thread claimed = distinct tokens it saw first
     auto insert = [&](int ti) {
@@ -283,7 +298,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
           if (!(slot_for(old, t) < kFinCountMax)) continue;                                // someone else's token came first: look again
         }
         if (long_hist) {                                                       // uniform
-          if ((atomicAdd(slot, 1u) & kFinCountMax) == kFinCountMax) fs.hash_fail = 1;
+          if ((atomicAdd(slot, 1u) & kFinCountMax) == kFinFold) note_fold(t, 4 * bk + (uint32_t)at);
         } else {
           atomicAdd(slot, 1u);
         }
@@ -294,6 +309,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
 #pragma unroll
     for (int j = 0; j < HR; ++j)
       if ((long long)j * NT < h_hi - h_lo) insert(htok[j]);                  // uniform condition
+    if (long_hist) fold();
     for (long long i0 = h_lo + (long long)HR * NT; i0 < h_hi; i0 += (long long)HR * NT) {
 #pragma unroll
       for (int j = 0; j < HR; ++j) {
@@ -302,6 +318,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
       }
 #pragma unroll
       for (int j = 0; j < HR; ++j) insert(htok[j]);
+      if (long_hist) fold();
     }
     const uint32_t wtot = wave_add_u32(mine);
     if (lane == 0) fs.r32[wave] = wtot;
@@ -311,9 +328,15 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     for (int w = 0; w < kFinWaves; ++w) ndist += fs.r32[w];
     if (fs.hash_fail || ndist > (uint32_t)kFinHashMax) return 4;            // uniform
   } else if (use_table && long_hist) {
-    if (big_count) fs.hash_fail = 1;
+    const uint32_t* tab = a.st_table + (size_t)ri.slot * (size_t)(2 * kTableSlots);
+    for (int i = tid; i < kTableSlots; i += NT) {
+      const uint32_t k = tab[i], v = tab[kTableSlots + i];
+      if (k < (uint32_t)V && v > kFinCountMax)
+        for (uint32_t e = (v - 1) / kFinFold; e; --e) note_fold(k, 0u);
+    }
     lds_barrier();
     if (fs.hash_fail) return 4;                                              // uniform
+    n_fold = (uint32_t)__builtin_amdgcn_readfirstlane((int)fs.n_memb);
   }
   // multiplicity of token t, searched from bucket bk on (the rare continuation of the lookup
   // below: t's home bucket is full of other tokens); 0 = not in the history (a prompt token)
@@ -349,6 +372,12 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
         if (hv[r] == 0u && hk[r].w != 0u && (creg[r].y & kTagBit) && creg[r].y != kFinNone)
           hv[r] = count_slow(v, (home(v) + 1) & (n_bucket - 1));
       }
+#pragma nounroll
+      for (uint32_t q = 0; q < n_fold; ++q) {                                // uniform, hardly ever any
+        const uint32_t t = fs.m_key[q];
+#pragma unroll
+        for (int r = 0; r < CR; ++r) hv[r] += (creg[r].y & ~kTagBit) == t ? kFinFold : 0u;
+      }
     }
 #pragma unroll
     for (int r = 0; r < CR; ++r) {
@@ -372,6 +401,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     if (lane == 0) { fs.rkey[wave] = wk; fs.ridx[wave] = wi; }
   }
   lds_barrier();
+  if (long_hist && tid == 0) fs.n_memb = 0;                                  // (from here on the draw's)
   bkey = 0; bidx = kFinNone;
 #pragma unroll
   for (int w = 0; w < kFinWaves; ++w) {

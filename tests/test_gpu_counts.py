@@ -1,6 +1,6 @@
 """Multiplicities under a frequency penalty at the edges of the finishing kernel's table: as many
-distinct tokens as it takes and more, a token repeated as often as a slot's bits hold and more, the
-last token of the largest vocabulary, and the same on a state's table."""
+distinct tokens as it takes and more, tokens repeated as often as a slot's bits hold and several times
+as often, the last token of the largest vocabulary, and the same on a state's table."""
 import numpy as np
 import pytest
 import torch
@@ -19,10 +19,10 @@ def test_multiplicities_at_the_edges_of_the_table(V, B):
     z[:, [0, 7, V - 1]] += 9.0                                 # penalised tokens at the top
     some = rng.permutation(V)
     hist = [some[:3072].tolist(), some[:6144].tolist(), some[:6145].tolist(), [7] * 16383, [7] * 16384 + [0],
-            [7] * 20000 + some[:1000].tolist(), [0, V - 1, V - 1, -1, V], [V - 1] * 4096 + [0] * 100, [0, 7, 7, V - 1] * 500]
+            rng.permutation([7] * 42000 + [V - 1] * 24577 + [0] * 8193 + some[:1000].tolist()).tolist(), [0, V - 1, V - 1, -1, V], [V - 1] * 4096 + [0] * 100, [0, 7, 7, V - 1] * 500]
     params = dict(temperature=[1.0, 0.8, 1.0, 1.0, 0.7, 1.0, 1.0, 0.9, 0.0], top_k=[50, 40, 0, 50, 20, 50, 1000, 50, 0],
                   top_p=[1.0, 0.9, 1.0, 0.95, 1.0, 1.0, 0.9, 1.0, 1.0], min_p=[0, 0, 0.05, 0, 0, 0, 0, 0.02, 0],
-                  frequency_penalty=[0.5, 0.3, 0.5, 2e-4, 2e-4, 3e-4, 0.7, 1e-3, 1e-3], presence_penalty=0.2,
+                  frequency_penalty=[0.5, 0.3, 0.5, 2e-4, 2e-4, 1e-4, 0.7, 1e-3, 1e-3], presence_penalty=0.2,
                   repetition_penalty=[1.0, 1.2, 1.0, 1.1, 1.0, 1.0, 1.3, 1.0, 1.0])
     rep = B // 9
     params = {k: np.tile(np.broadcast_to(np.asarray(v, dtype=np.float64), (9,)), rep) for k, v in params.items()}
@@ -31,8 +31,8 @@ def test_multiplicities_at_the_edges_of_the_table(V, B):
     for step in (0, 1) if B == 9 else (0,):
         H.compare(w, H.run_gpu(d, 5, step), 5, step)
     why = H.last_row_why.reshape(rep, 9)
-    assert (why[:, [3, 6, 7, 8]] == 1).all(), why              # settled by the finishing kernel
-    assert (why[:, [4, 5]] == 4).all(), why                    # a multiplicity beyond its bits
+    assert (why[:, [0, 1, 3, 4, 5, 6, 7, 8]] == 1).all(), why  # settled by the finishing kernel
+    assert (why[:, 2] == 4).all(), why                         # one distinct token more than its table takes
 
 
 def test_a_states_table_with_a_multiplicity_beyond_its_bits():
@@ -40,7 +40,7 @@ def test_a_states_table_with_a_multiplicity_beyond_its_bits():
     V, B, L_max, k = 50000, 3, 20000, 3
     z = (rng.standard_normal((B, V)) * 2.0).astype(np.float32)
     z[:, 7] += 9.0
-    prompts = [[7] * 17000 + [3], [7] * 16000 + [3, 9], rng.integers(0, V, 2600).tolist()]
+    prompts = [[7] * 18500 + [3], [7] * 16383 + [3, 9], rng.integers(0, V, 2600).tolist()]
     ost = O.DecodeState(B, L_max, V)
     for s, p in enumerate(prompts):
         ost.assign(s, p)
@@ -51,10 +51,13 @@ def test_a_states_table_with_a_multiplicity_beyond_its_bits():
     sip.sip_state_assign(state, B, L_max, i32(list(range(B))), indptr, i32([t for p in prompts for t in p]))
     params = dict(temperature=np.full(B, 0.8, np.float32), top_k=np.full(B, 30, np.int32),
                   frequency_penalty=np.array([2e-4, 2e-4, 0.5], np.float32))
+    ws = torch.empty(sip.sip_workspace_bytes(B, V, sip.SIP_F32, B * L_max, k), dtype=torch.uint8, device=H.DEV)
     out = sip.sip_sample_call(logits=torch.from_numpy(z).to(H.DEV), V=V, state=state, slots=B, L_max=L_max,
                               params={n: torch.from_numpy(v).to(H.DEV) for n, v in params.items()},
-                              slot_of_row=i32(list(range(B))), seed=1, step=0, k_logprobs=k)
+                              slot_of_row=i32(list(range(B))), seed=1, step=0, k_logprobs=k,
+                              workspace=ws)
     torch.cuda.synchronize()
+    assert (ws[4 * B:8 * B].view(torch.int32) == 1).all()
     full = {n: params.get(n) for n in ("temperature", "top_k", "top_p", "min_p", "repetition_penalty",
                                        "frequency_penalty", "presence_penalty")}
     ref = O.sample_state(z, full, ost, list(range(B)), 1, 0, k)
