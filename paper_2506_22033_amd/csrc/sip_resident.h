@@ -26,9 +26,8 @@
 // of filter).  Against exact_kernel, which these vocabularies used to go through: V = 4096, 64
 // rows, top-k and top-p: 53 -> 11 us; V = 12556, 468 rows, no filter: 99 -> 19 us.
 //
-// What this cannot settle -- more than kResList members in a bin of a cut (all-equal rows), a
-// count beyond 15 bits, top_p <= 0, no finite maximum -- goes through exact_row() in the same
-// workgroup.
+// What this cannot settle -- more than kResList members in a bin of a cut (all-equal rows), top_p <= 0,
+// no finite maximum -- goes through exact_row() in the same workgroup.
 #pragma once
 #include "sip_device.h"
 #include "sip_exact.h"
@@ -40,6 +39,7 @@ namespace sip {
 constexpr int kResBins = 2048;
 constexpr int kResList = 1024;             // members of a cut's bin / entries at or above the bin of the n-th best
 constexpr int kResMaxCount = 32767;        // longest history that 15-bit counters hold whatever it repeats
+constexpr uint32_t kResFold = 16384;       // longer ones: taken out of a count beyond it, and noted
 constexpr float kResSpan = 28.6f;          // exp(-28.6) * 2^40 < 1/2: nothing further below the maximum has mass
 
 template <int NT, int NPT>
@@ -137,7 +137,9 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
     if (lane == 0) { fs.t_minp = t; fs.j24 = u; }
   }
   const bool counts = rp.phi != 0.0f;                  // otherwise "occurs" is all that matters
-  int code = (pen.any && counts && pen.h.hi - pen.h.lo > kResMaxCount) ? 4 : 0;     // uniform, like every `code` below
+  const bool long_hist = counts && pen.h.hi - pen.h.lo > kResMaxCount;               // uniform
+  int code = (pen.any && counts && pen.h.hi - pen.h.lo > (long long)kResFold * kResList) ? 4 : 0;   // uniform, like every `code` below
+  uint32_t n_fold = 0;                                 // uniform: notes (m_key: token) of kResFold each
   __syncthreads();
 
   // ---- (1) multiplicities
@@ -154,8 +156,28 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
       for (int j = 0; j < 4; ++j)
         if (t[j] >= 0 && t[j] < V) {
           const uint32_t one = (t[j] & 1) ? 0x10000u : 1u;
-          if (counts) atomicAdd(&fs.u.cnt[t[j] >> 1], one); else atomicOr(&fs.u.cnt[t[j] >> 1], one);
+          if (long_hist) {
+            const uint32_t old = atomicAdd(&fs.u.cnt[t[j] >> 1], one);
+            if (((t[j] & 1) ? old >> 16 : old & 0xFFFFu) == kResFold) {
+              const uint32_t q = atomicAdd(&fs.n_m, 1u);                       // (at most one for every kResFold tokens)
+              if (q < (uint32_t)kResList) fs.m_key[q] = (uint32_t)t[j];
+            }
+          } else if (counts) {
+            atomicAdd(&fs.u.cnt[t[j] >> 1], one);
+          } else {
+            atomicOr(&fs.u.cnt[t[j] >> 1], one);
+          }
         }
+      if (long_hist) {
+        // what has grown beyond kResFold gives it up again before the next batch could take it beyond 15 bits
+        static_assert(kResFold + 4 * 1024 < 32768, "a batch on top of what folding leaves");
+        __syncthreads();
+        const uint32_t n = min(fs.n_m, (uint32_t)kResList);
+        for (uint32_t q = n_fold + tid; q < n; q += NT)
+          atomicSub(&fs.u.cnt[fs.m_key[q] >> 1], (fs.m_key[q] & 1) ? kResFold << 16 : kResFold);
+        n_fold = n;
+        __syncthreads();
+      }
     }
     for (long long i0 = pen.p_lo; i0 < pen.p_hi; i0 += 4 * NT) {
       int t[4];
@@ -199,7 +221,8 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
 #pragma unroll
           for (int i = 0; i < EPL; ++i) {
             const uint32_t ci = (i & 1) ? c[i / 2] >> 16 : c[i / 2] & 0xFFFFu;
-            const uint32_t n = ci & 0x7FFFu;
+            uint32_t n = ci & 0x7FFFu;
+            for (uint32_t o = 0; o < n_fold; ++o) n += fs.m_key[o] == (uint32_t)(e0 + i) ? kResFold : 0u;   // hardly ever any
             z[i] = ci ? penalise_shared(z[i], n, by_theta, rp.theta, rp.phi, rp.psi) : z[i];
           }
         }
@@ -227,6 +250,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
   __syncthreads();
   const float m = value_of(wave_max_u32(fs.rkey[lane & (NW - 1)]));
   const float low = value_of(wave_min_u32(fs.rlow[lane & (NW - 1)]));
+  if (long_hist && tid == 0) fs.n_m = 0;               // (from here on the members')
   if (!(m > -3.0e38f && m < 3.0e38f)) code = 6;
   const float lo_s = fmaxf(low, __fsub_rn(m, kResSpan));
   const float span = __fsub_rn(m, lo_s);

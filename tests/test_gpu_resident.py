@@ -65,18 +65,18 @@ def test_pieces(t, V_shard, bf16):
 
 
 def test_counts_beyond_the_counters_and_a_separate_prompt():
-    """A history that repeats a token more often than a 15-bit counter holds (general path), one
-    just within, and prompt tokens, which only the repetition penalty looks at."""
+    """Histories that repeat tokens more often than a 15-bit counter holds, one just within, and
+    prompt tokens, which only the repetition penalty looks at."""
     rng = np.random.default_rng(9)
     B, V = 4, 6000
     z = (rng.standard_normal((B, V)) * 2.0).astype(np.float32)
     params = dict(temperature=1.0, top_k=50, frequency_penalty=[1e-4, 1e-4, 0.0, 0.3],
                   presence_penalty=[0.0, 0.1, 0.2, 0.3], repetition_penalty=1.2)
-    hist = [[7] * 40000, [7] * 32767, [7] * 40000, [1, 2, 2]]
+    hist = [rng.permutation([7] * 50000 + [V - 1] * 16385 + [0] * 16384).tolist(), [7] * 32767, [7] * 40000, [1, 2, 2]]
     w = H.custom("long", z, params, hist, k_logprobs=3)
     d = H.to_device(w)
     H.compare(w, H.run_gpu(d, 1, 0), 1, 0)
-    assert (H.last_row_why == [4, 1, 1, 1]).all(), H.last_row_why
+    assert (H.last_row_why == 1).all(), H.last_row_why
     prompts = [rng.integers(0, V, 3000).tolist() for _ in range(B)]
     p_ind = torch.from_numpy(np.concatenate(([0], np.cumsum([len(p) for p in prompts]))).astype(np.int64)).to(H.DEV)
     p_tok = torch.from_numpy(np.concatenate(prompts).astype(np.int32)).to(H.DEV)
