@@ -57,7 +57,7 @@ struct __align__(16) ResShared {
   unsigned long long blk[NT * NPT / (kWave * 4)];      // kept mass per (load, wave)
   unsigned long long r64[16], r64b[16];
   uint32_t r32[16], rkey[16], rlow[16];
-  uint32_t n_a, n_m, n_best, key_k, key_p;
+  uint32_t n_a, n_m, m_lo, m_hi, n_best, key_k, key_p;
   unsigned long long s1_part;
   int bin_k, bin_n, bin_p;
   uint32_t arg_max;
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
     if (pen.any)
       for (int i = tid; i < NT * NPT * 2 / 16; i += NT) z4[i] = make_uint4(0, 0, 0, 0);
     if (tid == 0) {
-      fs.n_a = 0; fs.n_m = 0; fs.key_k = 0; fs.key_p = kFinNone; fs.s1_part = 0;
+      fs.n_a = 0; fs.n_m = 0; fs.m_lo = kFinNone; fs.m_hi = 0; fs.key_k = 0; fs.key_p = kFinNone; fs.s1_part = 0;
       fs.bin_k = -1; fs.bin_n = -1; fs.bin_p = 1 << 30; fs.arg_max = kFinNone;
     }
   }
@@ -422,9 +422,9 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
       bin_n2 = fs.bin_n; n_best = fs.n_best;
     }
     if (code == 0 && n_best > (uint32_t)kResList) code = 9;
-    if (code == 0 && bin_m >= 0 && fs.hcnt[bin_m] > (uint32_t)kResList) code = 9;
-    // ---- members of the cut's bin, and the entries the best-n are chosen from
+    // ---- members of the cut's bin, their least and largest key, and the entries the best-n are chosen from
     auto gather = [&](int bin_a, int bin_b) {
+      uint32_t lo = kFinNone, hi = 0;
       const int first = min(bin_a >= 0 ? bin_a : 1 << 30, bin_b >= 0 ? bin_b : 1 << 30);
 #pragma unroll
       for (int j = 0; j < NL; ++j) {
@@ -440,13 +440,21 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
               if (at < (uint32_t)kResList) { fs.a_key[at] = key_of(x); fs.a_idx[at] = (uint32_t)v; }
             }
             if (bin == bin_b) {
-              const uint32_t at = atomicAdd(&fs.n_m, 1u);
-              if (at < (uint32_t)kResList) { fs.m_key[at] = key_of(x); fs.m_E[at] = mass_units(e[j * EPL + i]); }
+              const uint32_t at = atomicAdd(&fs.n_m, 1u), key = key_of(x);
+              if (at < (uint32_t)kResList) { fs.m_key[at] = key; fs.m_E[at] = mass_units(e[j * EPL + i]); }
+              lo = min(lo, key); hi = max(hi, key);
             }
           }
         }
       }
+      if (__any(hi != 0u)) {
+        lo = wave_min_u32(lo); hi = wave_max_u32(hi);
+        if (lane == 0) { atomicMin(&fs.m_lo, lo); atomicMax(&fs.m_hi, hi); }
+      }
     };
+    // Logits that take few different values (quantised ones, rows of equal values) put thousands of
+    // equal entries into the bin of a cut: then there is nothing to compare, however many they are.
+    auto members_equal = [&]() { return fs.m_lo == fs.m_hi; };
     // the smallest member (of K1) whose strictly larger mass stays below the limit
     auto nucleus_in_bin = [&](unsigned long long above, uint32_t nm, uint32_t key_k) {
       for (uint32_t t = tid; t < nm; t += NT) {
@@ -461,8 +469,13 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
       gather(n_top > 0 ? bin_n : -1, bin_m);
       __syncthreads();
       if (bin_m >= 0) {
-        const uint32_t nm = min(fs.n_m, (uint32_t)kResList);
-        if (k_cut) {
+        const uint32_t nm = fs.n_m;
+        if (members_equal()) {
+          if (tid == 0 && k_cut) { fs.key_k = fs.m_lo; fs.s1_part = nm * fs.m_E[0]; }
+          if (tid == 0 && !k_cut) fs.key_p = fs.m_lo;
+        } else if (nm > (uint32_t)kResList) {
+          code = 9;
+        } else if (k_cut) {
           const uint32_t k_rem = k - fs.hoff[bin_k];                           // 1 <= k_rem <= members
           for (uint32_t t = tid; t < nm; t += NT) {
             const uint32_t kt = fs.m_key[t];
@@ -503,20 +516,27 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
         }
       }
       if (bin_m >= 0) __syncthreads();
-      if (k_act && p_act) {
+      if (k_act && p_act && code == 0) {
         // ---- top-p on the mass that survived top-k
         const uint32_t key_k = fs.key_k;
         limit = limit_of(fs.hmass[bin_k] + fs.s1_part);
         find_nucleus_bin(bin_k);
-        if (tid == 0) fs.n_m = 0;
+        if (tid == 0) { fs.n_m = 0; fs.m_lo = kFinNone; fs.m_hi = 0; }
         __syncthreads();
         bin_m = fs.bin_p;
-        if (bin_m >= kResBins) code = 10;
-        else if (fs.hcnt[bin_m] > (uint32_t)kResList) code = 9;
-        if (code == 0) {
+        if (bin_m >= kResBins) {
+          code = 10;
+        } else {
           gather(-1, bin_m);
           __syncthreads();
-          nucleus_in_bin(fs.hmass[bin_m], min(fs.n_m, (uint32_t)kResList), key_k);
+          const uint32_t nm = fs.n_m;
+          if (members_equal()) {
+            if (tid == 0) fs.key_p = fs.m_lo;
+          } else if (nm > (uint32_t)kResList) {
+            code = 9;
+          } else {
+            nucleus_in_bin(fs.hmass[bin_m], nm, key_k);
+          }
           __syncthreads();
         }
       }

@@ -122,3 +122,29 @@ def test_which_way_a_batch_goes(params, k, rounds, in_registers, bf16):
     else:
         assert (H.last_row_path == (1 if in_registers else 16)).all(), np.unique(H.last_row_path)
     H.compare(w, out, 2, 0, rows=range(0, B, max(1, B // 16)))
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("V", [16500, 32768])
+def test_more_equal_values_than_can_be_compared(V, bf16):
+    """Cuts through more than 1024 entries of one bin: all of one value (a row of equal values, 3000 equal
+    largest, logits in steps of one half), which is settled from the registers, or two values (general path)."""
+    rng = np.random.default_rng(V)
+    B = 12
+    z = (rng.standard_normal((B, V)) * 2.0).astype(np.float32)
+    z[:3] = 0.25
+    for b in range(3, 6):
+        z[b, rng.permutation(V)[:3000]] = 11.0
+    z[6:9] = np.round(z[6:9] * 2) / 2
+    for b in range(9, 12):                                     # two values in one of 2047 bins over 30 and more
+        z[b, 0], z[b, 1] = -25.0, 12.0
+        z[b, rng.permutation(V)[:3000]] = rng.choice(np.float32([11.0, 10.9999]), 3000)
+    params = dict(temperature=1.0, top_k=[50, 0, 50] * 4, top_p=[1.0, 0.8, 0.8] * 4)
+    hist = [rng.integers(0, V, 50).tolist() for _ in range(B)]
+    w = H.custom("ties", workloads.f32_to_bf16_bits(z) if bf16 else z, dict(params, presence_penalty=0.3), hist, k_logprobs=0)
+    d = H.to_device(w)
+    for step in (0, 1):
+        H.compare(w, H.run_gpu(d, 8, step), 8, step)
+    assert (H.last_row_why[:9] == 1).all(), H.last_row_why
+    if not bf16:
+        assert (H.last_row_why[9:] == 9).all(), H.last_row_why
