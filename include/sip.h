@@ -87,16 +87,18 @@ typedef struct {
  *   the row held in registers (see "Kernels of a call"); any
  *   other value = finished after reading the row again (normally from cache): 15 = from a second,
  *   longer candidate list (one more read of that row); 16 = by the row's workgroup over the whole
- *   row (plain temperature sampling without any filter: two more reads; a nucleus that reaches
- *   below the candidate list: four to six); anything else = the exact multi-pass path, the value
+ *   row (plain temperature sampling without any filter: one block of 1024 entries is read again if
+ *   why = 1, the row twice if why = 13; a nucleus that reaches below the candidate list: four to six
+ *   times); anything else = the exact multi-pass path, the value
  *   naming the reason (2 top_k too large for any candidate list, 3-13 the candidate list could
  *   not prove the answer, 17-29 nor could the longer one), or 14: vocabulary size outside the
  *   single-pass kernels (why = 1: settled from registers all the same).
- *   why: 1 = the finishing kernel (or the one that holds the row) settled it; else why it passed the row on: 2 no list was
- *   made, 3 a chunk's list overflowed, 4 more distinct history tokens than the table of
- *   multiplicities holds, 5 list too long, 6 maximum not proven, 7 value span not representable,
+ *   why: 1 = the finishing kernel (or the one that holds the row) settled it; else why it passed the
+ *   row on: 2 no list was made, 3 a chunk's list overflowed, 4 more distinct history tokens than the
+ *   table of multiplicities holds, 5 list too long, 6 maximum not proven, 7 value span not representable,
  *   8 k-th / n-th largest not in the list, 9 too many equal values in one bin, 10 top_p <= 0,
- *   11 nucleus reaches below the list, 12 min-p cut below the list, 13 no filter at all,
+ *   11 nucleus reaches below the list, 12 min-p cut below the list, 13 no filter at all and no masses
+ *   of the row's blocks (a list that left no room for them, or logits in pieces),
  *   14 no mass / exact-only shape.
  * Results mean the same whichever path ran.
  *

@@ -1025,7 +1025,7 @@ __global__ __launch_bounds__(kFinThreads) __attribute__((amdgpu_waves_per_eu(4, 
   const int code = finish_row(a, b, fs);
   if (threadIdx.x == 0) {
     a.row_path[b] = code;
-    a.row_why[b] = code == kFinWholeRow ? 13 : code;
+    a.row_why[b] = code == kFinWholeRow ? 1 : code;
     if (code != 1 && code != kFinWholeRow) {
       const int q = atomicAdd(a.rescue_n, 1);
       if (q >= 0 && q < a.B) a.rescue_rows[q] = b;

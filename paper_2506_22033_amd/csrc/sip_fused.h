@@ -27,7 +27,7 @@ __global__ __launch_bounds__(kFinalThreads) void finish_rescue_kernel(Args a_by_
   const int code = finish_row(a, b, u.fs, &hint);
   if (threadIdx.x == 0) {
     a.row_path[b] = code;
-    a.row_why[b] = code == kFinWholeRow ? 13 : code;
+    a.row_why[b] = code == kFinWholeRow ? 1 : code;
   }
   if (code == 1 || code == kFinWholeRow) return;                     // uniform
   __syncthreads();
