@@ -38,6 +38,13 @@ constexpr int kQueueCap = 480;              // entries of one wave's LDS candida
 constexpr int kChunkCap = kStreamWaves * kQueueCap;   // entries of one chunk's segment in the workspace
 constexpr int kChunkBitsMax = 73728;        // most elements a chunk may have (history bitmap: 9 KB of LDS)
 constexpr int kBlkMax = kChunkBitsMax / kBlkElems;   // blocks of the longest chunk
+// Load numbers of a chunk of p whole pieces, each rounded up to tiles; they have 5 bits in a bf16 queue entry.
+constexpr int kLoadBits = 5;
+constexpr int load_numbers(int p, int tile) { return p * kStreamLoads * ((kChunkBitsMax / p + tile - 1) / tile); }
+constexpr int most_load_numbers(int p, int tile) {
+  return p == 0 ? 0 : load_numbers(p, tile) > most_load_numbers(p - 1, tile) ? load_numbers(p, tile) : most_load_numbers(p - 1, tile);
+}
+static_assert(most_load_numbers(SIP_MAX_SHARDS, kStreamThreads * kStreamLoads * 8) <= 1 << kLoadBits, "see `process`");
 constexpr int kStreamHistRegs = 8;          // history tokens a thread requests at once
 constexpr float kBulkScale = 1073741824.0f; // 2^30
 
@@ -169,9 +176,9 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   constexpr int TILE = SUB * kStreamLoads;
   constexpr int SLOADS = kSampleSize / SUB;         // sample loads per thread (4 fp32, 2 bf16)
   constexpr int NSB = SLOADS * kStreamWaves;        // 1 KB sample blocks spread over the row
-  // 30 KB of LDS: first the sample histogram (two 16-bit counters per word, 16 KB), then the
-  // per-wave candidate queues; 9 KB for the history bitmap of the chunk (39.6 KB in all: four
-  // workgroups per compute unit)
+  // LDS: first the sample histogram (two 16-bit counters per word, 16 KB), then, in its place, the
+  // per-wave candidate queues (fp32 30 KB, bf16 15 KB); 9 KB for the history bitmap of the chunk; bf16
+  // also 4 KB of tag words.  39.8 KB in all (bf16 29.8): four workgroups per compute unit.
   typedef typename std::conditional<DT == SIP_F32, uint2, uint32_t>::type entry_t;      // see `process`
   __shared__ __align__(16) unsigned char smem[(kSampleBins * 2 > kStreamWaves * kQueueCap * (int)sizeof(entry_t)) ? kSampleBins * 2 : kStreamWaves * kQueueCap * (int)sizeof(entry_t)];
   // bf16: history bits of one 16-byte load -> what is or-ed into the load's four words (one LDS read
@@ -682,7 +689,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
       en = queue[i];
     } else {
       const uint32_t w = queue[i];
-      uint32_t it = (w >> 9) & 31u, base = ibase + (uint32_t)c0;
+      uint32_t it = (w >> 9) & ((1u << kLoadBits) - 1), base = ibase + (uint32_t)c0;
       if (SH) { const uint32_t pc = it / (uint32_t)lpp; it -= pc * (uint32_t)lpp; base += pc * (uint32_t)Vl; }
       en = make_uint2(w & 0xFFFF0000u, base + it * (uint32_t)SUB + (uint32_t)wave * (uint32_t)(kWave * EPL) + (w & 511u));
     }
