@@ -30,7 +30,7 @@ def _run_and_compare(w, steps=(0, 1), rows=None, seed=0):
 
 
 # ---------------------------------------------------------------- reduced shapes: all rows, several tiles + ragged tail
-@pytest.mark.parametrize("idx,B,V,Hh", [(0, 8, 5003, None), (1, 6, 9001, 96), (2, 12, 20011, 300),
+@pytest.mark.parametrize("idx,B,V,Hh", [(0, 8, 5003, None), (1, 6, 9001, 96), (2, 12, 20011, 300), (2, 12, 36011, 300),
                                         (3, 6, 12345, 128), (4, 10, 33333, 512)])
 def test_reduced_workloads_every_row(idx, B, V, Hh):
     w = workloads.make(idx, B=B, V=V, H=Hh)
@@ -64,8 +64,9 @@ def test_c5_full(steps):
 
 
 # ---------------------------------------------------------------- properties that hold at any size
-def test_determinism_and_row_id_keying():
-    w = workloads.make(2, B=16, V=30000, H=256)
+@pytest.mark.parametrize("V", [30000, 40000])
+def test_determinism_and_row_id_keying(V):
+    w = workloads.make(2, B=16, V=V, H=256)
     d = H.to_device(w)
     a = H.run_gpu(d, 5, 9)
     b = H.run_gpu(d, 5, 9)
@@ -73,7 +74,7 @@ def test_determinism_and_row_id_keying():
         assert np.array_equal(x.view(np.int32), y.view(np.int32))
     # reversed batch with explicit row ids reproduces the same per-sequence results
     perm = np.arange(w.B)[::-1].copy()
-    w2 = workloads.make(2, B=16, V=30000, H=256)
+    w2 = workloads.make(2, B=16, V=V, H=256)
     w2.logits = w.logits[perm].copy()
     w2.params = {k: (None if v is None else v[perm].copy()) for k, v in w.params.items()}
     hist = [w.history(b) for b in perm]

@@ -42,8 +42,42 @@ def test_vocabularies_at_the_edges_of_the_variants(V, bf16):
     d = H.to_device(w)
     for step in (0, 1):
         H.compare(w, H.run_gpu(d, 3, step), 3, step)
-    if V >= 4096 and not bf16:
+    if V >= 4096:
         assert (H.last_row_why == 1).mean() > 0.8, H.last_row_why
+
+
+@pytest.mark.parametrize("V,bf16", [(1000, False), (4097, True), (16383, False)])
+def test_a_state(V, bf16):
+    """Below 16384 entries a state's rows are held in registers too: tick taken ahead, ids appended."""
+    rng = np.random.default_rng(V)
+    B, L_max, k = 6, 40, 2
+    prompts = [rng.integers(0, V, n).tolist() for n in (0, 1, 5, 30, 38, 12)]
+    ost = O.DecodeState(B, L_max, V)
+    state = torch.zeros(sip.sip_state_bytes(B, L_max), dtype=torch.uint8, device=H.DEV)
+    sip.sip_state_init(state, B, L_max)
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=H.DEV)                       # noqa: E731
+    for s, p in enumerate(prompts):
+        ost.assign(s, p)
+    indptr = torch.tensor(np.concatenate(([0], np.cumsum([len(p) for p in prompts]))), dtype=torch.int64, device=H.DEV)
+    sip.sip_state_assign(state, B, L_max, i32(list(range(B))), indptr, i32([t for p in prompts for t in p]))
+    params = dict(temperature=np.float32([0.0, 0.8, 1.0, 1.2, 0.7, 1.0]), top_k=np.int32([0, 20, 0, 0, 5, 300]),
+                  top_p=np.float32([1, 1, 0.9, 1, 0.8, 1]), frequency_penalty=np.full(B, 0.4, np.float32),
+                  repetition_penalty=np.full(B, 1.2, np.float32))
+    full = {n: params.get(n) for n in ("temperature", "top_k", "top_p", "min_p", "repetition_penalty",
+                                       "frequency_penalty", "presence_penalty")}
+    dev = {n: torch.from_numpy(v).to(H.DEV) for n, v in params.items()}
+    ws = torch.empty(sip.sip_workspace_bytes(B, V, sip.SIP_BF16 if bf16 else sip.SIP_F32, B * L_max, k),
+                     dtype=torch.uint8, device=H.DEV)
+    order = [3, 0, 5, 1, 4, 2]
+    for t in range(4):                                        # (slot 4 is full after two of them)
+        z = (rng.standard_normal((B, V)) * 2.0).astype(np.float32)
+        zz = workloads.f32_to_bf16_bits(z) if bf16 else z
+        out = sip.sip_sample_call(logits=H.logits_to_device(zz), V=V, state=state, slots=B, L_max=L_max, params=dev,
+                                  slot_of_row=i32(order), seed=4, step=0, k_logprobs=k, workspace=ws)
+        torch.cuda.synchronize()
+        assert (ws[4 * B:8 * B].view(torch.int32) == 1).all()
+        ref = O.sample_state(zz, full, ost, order, 4, 0, k)
+        H.check_rows(f"state step {t}", range(B), ref, tuple(x.cpu().numpy() for x in out), k)
 
 
 @pytest.mark.parametrize("t,V_shard,bf16", [(2, 4, False), (3, 5000, True), (8, 4096, False), (1, 9000, True)])
