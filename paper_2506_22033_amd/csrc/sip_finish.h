@@ -42,7 +42,7 @@ constexpr int kFinHash = 8192;                         // slots of the multiplic
 constexpr int kFinHashMax = 6144;                      // distinct history tokens it takes
 constexpr int kFinCountBits = 14;                      // a slot: token << 14 | multiplicity (18 + 14 bits), 0 = free
 constexpr uint32_t kFinCountMax = (1u << kFinCountBits) - 1;
-constexpr uint32_t kFinFold = 8192;                    // histories that could outgrow these bits: taken out of a count beyond it
+constexpr uint32_t kFinFold = 4096, kFinFolded = 8192; // histories that could outgrow these bits, see note_fold
 constexpr int kFinMembers = 512;                       // members of one index bin the draw resolves
 constexpr int kFinTopMax = 256;                        // entries at or above the bin of the n-th best
 constexpr int kFinKeySteps = 64;                       // distinct keys of one bin that are stepped through
@@ -71,7 +71,7 @@ struct __align__(16) FinShared {
   int bin_k, bin_n, bin_d;
   int code, code_top;
   int retry_ok;                             // code 11 only: a second, longer list can be expected to hold the nucleus
-  uint32_t hash_fail, n_memb, key_cut, n_hi;
+  uint32_t hash_fail, n_memb, n_fold, key_cut, n_hi;
   uint32_t token, token_key;
   unsigned long long before_d;
 };
@@ -201,7 +201,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
       // (a token beyond the vocabulary keeps its place, with the multiplicity 0 that never matches)
       auto pack = [&](uint32_t k, uint32_t v) -> uint32_t {
         if (k == kTableEmpty) return 0u;
-        return k < (uint32_t)V ? (k << kFinCountBits) | (v <= kFinCountMax ? v : ((v - 1) & (kFinFold - 1)) + 1) : ~kFinCountMax;
+        return k < (uint32_t)V ? (k << kFinCountBits) | (v <= kFinCountMax ? v : kFinFolded | (v & (kFinFold - 1))) : ~kFinCountMax;
       };
 #pragma unroll
       for (int j = 0; j < NQ; ++j)
@@ -211,7 +211,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
       for (int i = tid; i < kFinHash * 4 / 16; i += NT) s4[i] = make_uint4(0, 0, 0, 0);
     }
     if (tid == 0) {
-      fs.bin_k = -1; fs.bin_n = -1; fs.bin_d = -1; fs.code = 0; fs.code_top = 0; fs.hash_fail = 0; fs.n_memb = 0;
+      fs.bin_k = -1; fs.bin_n = -1; fs.bin_d = -1; fs.code = 0; fs.code_top = 0; fs.hash_fail = 0; fs.n_memb = 0; fs.n_fold = 0;
       fs.token = kFinNone; fs.token_key = 0;
     }
   }
@@ -260,21 +260,21 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     const uint32_t u = min(min(min(slot_for(q.x, t), slot_for(q.y, t)), slot_for(q.z, t)), slot_for(q.w, t));
     return u < kFinCountMax ? u + 1u : 0u;
   };
-  // A multiplicity that a long history could carry beyond its bits: every kFinFold of it are taken out
-  // of the slot again, after the batch of 4096 tokens that got it there (so that a slot never reaches
-  // kFinCountMax), and noted as one entry (m_key: token) that the look-up adds back.
-  static_assert(kFinFold + HR * kFinThreads < kFinCountMax, "a batch on top of what folding leaves");
-  uint32_t n_fold = 0;                     // uniform: such entries
+  // A multiplicity that a long history could carry beyond its bits: once it has reached kFinFolded +
+  // kFinFold, kFinFold are taken out of the slot again, after the batch of 4096 tokens that got it there
+  // (so that a slot never exceeds kFinCountMax), and noted as one entry (m_key: token).  A slot below
+  // kFinFolded has no notes; the look-up adds the others'.
+  static_assert(kFinFolded + kFinFold + HR * kFinThreads - 1 == kFinCountMax, "a batch on top of what folding leaves");
   auto note_fold = [&](uint32_t t, uint32_t slot) {
     const uint32_t q = atomicAdd(&fs.n_memb, 1u);
     if (q < (uint32_t)kFinMembers) { fs.m_key[q] = t; fs.m_idx[q] = slot; } else fs.hash_fail = 1;
   };
   auto fold = [&]() {
     lds_barrier();
-    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(fs.n_memb, (uint32_t)kFinMembers));
-    for (uint32_t q = n_fold + tid; q < n; q += NT) atomicSub(&fs.u.hash[fs.m_idx[q]], kFinFold);
-    n_fold = n;
+    const uint32_t n = min(fs.n_memb, (uint32_t)kFinMembers);
+    for (uint32_t q = fs.n_fold + tid; q < n; q += NT) atomicSub(&fs.u.hash[fs.m_idx[q]], kFinFold);
     lds_barrier();
+    if (tid == 0) fs.n_fold = n;
   };
   if (need_hash && !use_table) {
     uint32_t mine = 0;                     // slots this thread claimed = distinct tokens it saw first
@@ -298,7 +298,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
           if (!(slot_for(old, t) < kFinCountMax)) continue;                                // someone else's token came first: look again
         }
         if (long_hist) {                                                       // uniform
-          if ((atomicAdd(slot, 1u) & kFinCountMax) == kFinFold) note_fold(t, 4 * bk + (uint32_t)at);
+          if ((atomicAdd(slot, 1u) & kFinCountMax) == kFinFolded + kFinFold - 1) note_fold(t, 4 * bk + (uint32_t)at);
         } else {
           atomicAdd(slot, 1u);
         }
@@ -332,11 +332,10 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     for (int i = tid; i < kTableSlots; i += NT) {
       const uint32_t k = tab[i], v = tab[kTableSlots + i];
       if (k < (uint32_t)V && v > kFinCountMax)
-        for (uint32_t e = (v - 1) / kFinFold; e; --e) note_fold(k, 0u);
+        for (uint32_t e = (v - kFinFolded) / kFinFold; e; --e) note_fold(k, 0u);
     }
     lds_barrier();
     if (fs.hash_fail) return 4;                                              // uniform
-    n_fold = (uint32_t)__builtin_amdgcn_readfirstlane((int)fs.n_memb);
   }
   // multiplicity of token t, searched from bucket bk on (the rare continuation of the lookup
   // below: t's home bucket is full of other tokens); 0 = not in the history (a prompt token)
@@ -351,32 +350,40 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     return 0u;
   };
 
+  auto folded = [&](uint32_t t) -> uint32_t {                                  // what was taken out of token t's slot
+    uint32_t n = 0;
+#pragma nounroll
+    for (uint32_t q = fs.n_memb; q > 0; --q) n += fs.m_key[q - 1] == t ? kFinFold : 0u;
+    return n;
+  };
+
   // ---- (2) penalised values (Sec. 5.1 ApplyPenalty); maximum of the list, lowest index on ties
   uint32_t bkey = 0, bidx = kFinNone;
   for (int bt = 0; bt < nb; ++bt) {
     if (bt > 0) load_batch(bt);
     drop_beyond(bt);
-    // the home buckets of all entries are read from the table together, then the counts
+    // the home buckets of the entries are read from the table together, then the counts
     uint32_t hv[CR];
     if (need_hash) {
-      uint4 hk[CR];
+      // (in two halves: all ten at once and the rare loops below them do not fit the registers)
+      static_assert(CR % 2 == 0, "");
 #pragma unroll
-      for (int r = 0; r < CR; ++r)
-        if (live(bt, r)) hk[r] = hslot4[home(creg[r].y & ~kTagBit)];
+      for (int r0 = 0; r0 < CR; r0 += CR / 2) {
+        uint4 hk[CR / 2];
 #pragma unroll
-      for (int r = 0; r < CR; ++r) {
-        hv[r] = 0u;
-        if (!live(bt, r)) continue;
-        const uint32_t v = creg[r].y & ~kTagBit;
-        hv[r] = count_in(hk[r], v);
-        if (hv[r] == 0u && hk[r].w != 0u && (creg[r].y & kTagBit) && creg[r].y != kFinNone)
-          hv[r] = count_slow(v, (home(v) + 1) & (n_bucket - 1));
-      }
-#pragma nounroll
-      for (uint32_t q = 0; q < n_fold; ++q) {                                // uniform, hardly ever any
-        const uint32_t t = fs.m_key[q];
+        for (int r = r0; r < r0 + CR / 2; ++r)
+          if (live(bt, r)) hk[r - r0] = hslot4[home(creg[r].y & ~kTagBit)];
 #pragma unroll
-        for (int r = 0; r < CR; ++r) hv[r] += (creg[r].y & ~kTagBit) == t ? kFinFold : 0u;
+        for (int r = r0; r < r0 + CR / 2; ++r) {
+          const uint4& h4 = hk[r - r0];
+          hv[r] = 0u;
+          if (!live(bt, r)) continue;
+          const uint32_t v = creg[r].y & ~kTagBit;
+          hv[r] = count_in(h4, v);
+          if (hv[r] == 0u && h4.w != 0u && (creg[r].y & kTagBit) && creg[r].y != kFinNone)
+            hv[r] = count_slow(v, (home(v) + 1) & (n_bucket - 1));
+          if (hv[r] >= kFinFolded) hv[r] += folded(v);
+        }
       }
     }
 #pragma unroll
