@@ -306,19 +306,19 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
       }
       fs.hash_fail = 1;                    // table full
     };
+    // (one copy of the eight inserts: every other row pays for the kernel's length)
+    for (long long i0 = h_lo;;) {
 #pragma unroll
-    for (int j = 0; j < HR; ++j)
-      if ((long long)j * NT < h_hi - h_lo) insert(htok[j]);                  // uniform condition
-    if (long_hist) fold();
-    for (long long i0 = h_lo + (long long)HR * NT; i0 < h_hi; i0 += (long long)HR * NT) {
+      for (int j = 0; j < HR; ++j)
+        if (i0 + (long long)j * NT < h_hi) insert(htok[j]);                   // uniform condition
+      if (long_hist) fold();
+      i0 += (long long)HR * NT;
+      if (i0 >= h_hi) break;
 #pragma unroll
       for (int j = 0; j < HR; ++j) {
         const long long i = i0 + tid + (long long)j * NT;
         htok[j] = i < h_hi ? a.tokens[i] : -1;
       }
-#pragma unroll
-      for (int j = 0; j < HR; ++j) insert(htok[j]);
-      if (long_hist) fold();
     }
     const uint32_t wtot = wave_add_u32(mine);
     if (lane == 0) fs.r32[wave] = wtot;
