@@ -986,6 +986,8 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
         }
         const unsigned long long u_inc = dpp_scan_add_u64(u), E_inc = dpp_scan_add_u64(E);
         unsigned long long C_u = run_u + u_inc - u, C_E = run_E + E_inc - E;
+        run_u += last_lane_u64(u_inc); run_E += last_lane_u64(E_inc);
+        if (run_E + rescaled(run_u) <= target) continue;                       // uniform: not in this half
         uint32_t tok = kFinNone, tok_key = 0;
         part = 0.0f;
 #pragma unroll
@@ -1000,11 +1002,8 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
           if ((i & last_of_load) == last_of_load) { C_u = to_here; part = 0.0f; }
         }
         const unsigned long long hit = __ballot(tok != kFinNone);
-        if (hit) {
-          if (lane == __ffsll((long long)hit) - 1) { fs.token = tok; fs.token_key = tok_key; }
-          break;
-        }
-        run_u += last_lane_u64(u_inc); run_E += last_lane_u64(E_inc);
+        if (lane == __ffsll((long long)hit) - 1) { fs.token = tok; fs.token_key = tok_key; }
+        break;
       }
     }
     lds_barrier();

@@ -218,13 +218,21 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
 #pragma unroll
         for (int i = 0; i < EPL / 2; ++i) { c[i] = fs.u.cnt[e0 / 2 + i]; some |= c[i] != 0u; }
         if (__any(some)) {
+          uint32_t ci[EPL], n[EPL];
 #pragma unroll
           for (int i = 0; i < EPL; ++i) {
-            const uint32_t ci = (i & 1) ? c[i / 2] >> 16 : c[i / 2] & 0xFFFFu;
-            uint32_t n = ci & 0x7FFFu;
-            for (uint32_t o = 0; o < n_fold; ++o) n += fs.m_key[o] == (uint32_t)(e0 + i) ? kResFold : 0u;   // hardly ever any
-            z[i] = ci ? penalise_shared(z[i], n, by_theta, rp.theta, rp.phi, rp.psi) : z[i];
+            ci[i] = (i & 1) ? c[i / 2] >> 16 : c[i / 2] & 0xFFFFu;
+            n[i] = ci[i] & 0x7FFFu;
           }
+#pragma nounroll
+          for (uint32_t o = 0; o < n_fold; ++o) {                              // hardly ever any
+            const uint32_t at = fs.m_key[o] - (uint32_t)e0;
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) n[i] += at == (uint32_t)i ? kResFold : 0u;
+          }
+#pragma unroll
+          for (int i = 0; i < EPL; ++i)
+            z[i] = ci[i] ? penalise_shared(z[i], n[i], by_theta, rp.theta, rp.phi, rp.psi) : z[i];
         }
       }
 #pragma unroll
