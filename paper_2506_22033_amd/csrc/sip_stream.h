@@ -303,10 +303,18 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   // they travel meanwhile
   uint4 buf[kStreamBufs][kStreamLoads];
   int tnext = c0;                                    // first element of the next tile to request
+  int n_pj = 0;                                      // SH: the piece it is in
+  auto roll = [&]() {                                // SH: on to the next piece (a piece can be a single tile)
+    if (tnext >= c1) {
+      ++n_pj; tnext = c0;
+      if (n_pj < np) row = shard_base(a, sh + n_pj) + (size_t)b * (size_t)a.shard_stride * ESZ;
+    }
+  };
 #pragma unroll
   for (int k = 0; k < kStreamBufs; ++k) {
     load_tile(tnext, buf[k]);                        // (past the chunk's end: its last 16 bytes again, never looked at)
     tnext += TILE;
+    if (SH) roll();
   }
 
   // ---- threshold: the same 8192-element sample (1 KB blocks spread evenly over the row) is
@@ -642,14 +650,6 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
     // the same rotation over np pieces: every piece is [c0, c1) of its shard; the requests run
     // ahead of the processing across the piece boundaries (`row` is what load_tile reads from)
     int c_pj = 0, tcur = c0;                         // tile being processed
-    int n_pj = 0;                                    // piece of the next tile to request, `tnext` its first element
-    auto roll = [&]() {
-      if (tnext >= c1) {
-        ++n_pj; tnext = c0;
-        if (n_pj < np) row = shard_base(a, sh + n_pj) + (size_t)b * (size_t)a.shard_stride * ESZ;
-      }
-    };
-    roll();
     bool more = true;
     while (more) {
 #pragma unroll

@@ -104,7 +104,10 @@ def test_shapes_outside_the_single_pass_kernels(t, V_shard, bf16):
     assert (path == 14).all()
 
 
-@pytest.mark.parametrize("t,V_shard,B,bf16", [(8, 16384, 160, True), (6, 20000, 300, False), (3, 17000, 600, False)])
+@pytest.mark.parametrize("t,V_shard,B,bf16", [(8, 16384, 160, True), (6, 20000, 300, False), (3, 17000, 600, False),
+                                                # pieces of exactly one tile
+                                                (8, 8192, 7, True), (8, 8192, 160, True), (4, 8192, 300, True),
+                                                (2, 8192, 600, True)])
 def test_large_batches_stream_several_whole_pieces_per_workgroup(t, V_shard, B, bf16):
     """With fewer chunks per row than pieces (large B) a workgroup streams several pieces one after
     the other; every 8th row is compared with the oracle."""
