@@ -43,10 +43,11 @@ sip_status sip_probe_read(const void* src, size_t bytes, int32_t workgroups, voi
 
 /*
  * Diagnostic, HOST only: into how many chunks (workgroups of the streaming kernel) a row of this
- * shape is cut; t_shards = 0 for logits in one matrix, else V = t_shards * V_shard.  0 = the shape
- * is served by the exact multi-pass kernel alone, -1 = invalid arguments.  A row's chunks are
- * whole units of 64 16-byte loads, dealt out evenly (to each vocabulary piece, if there are
- * pieces); none is empty.
+ * shape is cut; t_shards = 0 for logits in one matrix, else V = t_shards * V_shard.  0 = no chunks: rows
+ * are held in registers or take the exact multi-pass path, -1 = invalid arguments.  A row's chunks are
+ * whole units of 1024 elements, dealt out evenly (to each vocabulary piece, if there are
+ * pieces); none is empty.  (Up to SIP_MAX_RESIDENT_V entries a call may not launch them at all, see
+ * "Kernels of a call" in sip.h; the workspace holds them either way.)
  */
 int32_t sip_plan_chunks(int32_t B, int32_t V, sip_dtype dtype, int32_t t_shards);
 

@@ -18,13 +18,15 @@
 //       over the blocks, and the wave that holds the crossing finds it in its registers.
 //
 // What bounds it: vector issue of the one compute unit that has the row (16 waves, 4 to a SIMD, so
-// an instruction per element costs V / 1024 x 16 cycles).  Hence what is done once per row is done
+// an instruction per element costs V / 1024 x 16 cycles; 59 % of the slots at V = 32000) and the chain of
+// its barriers.  Hence what is done once per row is done
 // by one wave, parameters that are off take part with their neutral value instead of a branch,
 // temperature and repetition penalty are products with a double reciprocal (RowDivisor), masses
 // become integers through a double's low bits, and bins cost three instructions; with the
-// straightforward forms of these V = 32000 took 34.5 us, now 25.7 (fp32, 4 rows, one of each kind
-// of filter).  Against exact_kernel, which these vocabularies used to go through: V = 4096, 64
-// rows, top-k and top-p: 53 -> 11 us; V = 12556, 468 rows, no filter: 99 -> 19 us.
+// straightforward forms of these V = 32000 took 34.5 us, now 26 (fp32, 4 rows, one of each kind
+// of filter).  Against exact_kernel, which vocabularies below 16384 used to go through: V = 4096, 64
+// rows, top-k and top-p: 53 -> 11 us; V = 12556, 468 rows, no filter: 99 -> 19 us.  Which of the larger
+// ones come here: resident_is_chosen().
 //
 // What this cannot settle -- more than kResList members in a bin of a cut (all-equal rows), top_p <= 0,
 // no finite maximum -- goes through exact_row() in the same workgroup.
