@@ -21,12 +21,12 @@ constexpr uint32_t kCntOverflow = 0xFFFFFFFFu;   // ChunkOut::cnt of a chunk who
 // Args::cand) holds every element with z >= Tc and every element whose token is in the row's
 // history (tagged, see kTagBit); `bulk` is the softmax mass of all other elements.
 struct ChunkOut {
-  unsigned long long bulk;  // sum over the elements not in the list of 2^((z - Tc)*c + r0), in units of 2^-30
+  unsigned long long bulk;  // sum over the elements not in the list of 2^(z*c + off), in units of 2^-30
   float Tc;                 // every element of the chunk with z >= Tc is in the segment
-  float r0;                 // the part of Tc*c that is in the terms of `bulk`, see BulkRef
+  float off;                // see BulkRef and published_off()
   unsigned int cnt;         // entries in the chunk's segment, or kCntOverflow
   unsigned int n_blk;       // block masses at the end of the segment (rows without any filter), 0 = none
-  unsigned int pad[2];
+  double unit;              // log2 of the terms' unit
 };
 // A row without any filter is drawn over all its elements.  For such a row the streaming kernel
 // also leaves the bulk mass of every block of kBlkElems consecutive elements: 64-bit integers (see

@@ -53,7 +53,7 @@ constexpr int kCandLong = 24;        // candidate entries per thread of the larg
 
 struct FastShared {
   float Tc[kMaxChunks];
-  float r0[kMaxChunks];
+  double unit;
   unsigned long long bulk[kMaxChunks];
   uint32_t segoff[kMaxChunks + 1];
   unsigned long long r64[kFinalWaves];
@@ -147,7 +147,7 @@ __device__ __forceinline__ int fast_row(const Args& a, const int b, const RowPar
   }
   if (tid < S) {
     const ChunkOut co = a.chunks[(size_t)b * a.S + tid];
-    fs.Tc[tid] = co.Tc; fs.r0[tid] = co.r0; fs.bulk[tid] = co.bulk;
+    fs.Tc[tid] = co.Tc; if (tid == 0) fs.unit = co.unit; fs.bulk[tid] = co.bulk;
     fs.segoff[tid] = co.cnt;
   }
   // history tokens of this thread (the first kTokRegs rounds stay in registers)
@@ -492,8 +492,8 @@ __device__ __forceinline__ int fast_row(const Args& a, const int b, const RowPar
   }
   // 2^x with x split into integer and fraction: the fraction goes through the hardware exp2 (1 ulp,
   // far inside the accuracy of the fp32 bulk sums), the integer part is an exponent shift
-  const double ln2 = 0.6931471805599453094, log2e = 1.4426950408889634074;
-  const double x = fmin(fmax(bulk_exponent(T_row, fs.r0[0], log2e / (rp.greedy ? 1.0 : (double)rp.tau), m) + 10.0, -2000.0), 2000.0);
+  const double ln2 = 0.6931471805599453094;
+  const double x = fmin(fmax(bulk_exponent(fs.unit, m) + 10.0, -2000.0), 2000.0);
   const double xi = floor(x);
   const double bulk_rel = ldexp((double)bulk * (double)__builtin_amdgcn_exp2f((float)(x - xi)), (int)xi);
   const unsigned long long S0 = S_cand + (bulk_rel < 9.0e18 ? (unsigned long long)bulk_rel : 0ull);
@@ -854,13 +854,13 @@ __device__ __attribute__((noinline)) void restream_row(const Args& a, const int 
 #pragma unroll
       for (int i = 0; i < EPL; ++i) {
         if (e0 + i >= V) z[i] = -INFINITY;
-        const bool hit = z[i] >= Tc;
+        const bool hit = z[i] >= ref.Tc;
         if (hit) {
           const uint32_t pos = atomicAdd(&fs.rq_n, 1u);
           if (pos < cap) region[pos] = make_uint2(__float_as_uint(z[i]), (uint32_t)(e0 + i));
         }
-        float e = bulk_term(z[i], ref);
-        e = (hit || ((hw >> i) & 1u)) ? 0.0f : e;
+        float e = bulk_term(bulk_arg(z[i], ref));
+        e = (hit || ref.none || ((hw >> i) & 1u)) ? 0.0f : e;
         g += e;
       }
       acc += g;
@@ -873,9 +873,9 @@ __device__ __attribute__((noinline)) void restream_row(const Args& a, const int 
     ChunkOut o;
     o.bulk = 0;
     for (int w = 0; w < kFinalWaves; ++w) o.bulk += fs.r64[w];
-    o.Tc = Tc; o.r0 = ref.r0;
+    o.Tc = ref.Tc; o.off = published_off(ref);
     o.cnt = fs.rq_n;
-    o.n_blk = 0; o.pad[0] = o.pad[1] = 0;
+    o.n_blk = 0; o.unit = ref.unit;
     a.chunks[(size_t)b * a.S] = o;
   }
   // what this workgroup wrote to global memory is read back by other waves of it
@@ -1398,8 +1398,7 @@ __device__ __attribute__((noinline)) int whole_row_finish(const Args& a, const i
   const bool minp_on = cut && rp.min_p > 0.0f;
   const float t_minp = minp_on ? (float)log((double)rp.min_p) : 0.0f;
   const unsigned long long j24 = (unsigned long long)(philox_word0(a.seed, rp.row_id, step_of(a)) >> 8);
-  float c_row, c_lo;
-  scale_pair(rp, c_row, c_lo);
+  const float c_row = (float)log2_scale(rp);
   uint32_t key_cut = 0;
   if (cut) {
     if (whole_row_cut<DT>(row, V, has_pen, bm, pre, cnt, hm, hc, fs, rp.tau, m, limit) != 1) return 10;   // uniform

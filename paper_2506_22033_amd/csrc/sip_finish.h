@@ -146,12 +146,14 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   const ChunkOut co = a.chunks[(size_t)b * S + min(lane, S - 1)];
   load_batch(0);
   uint32_t my_cnt = 0;
-  float Tc, r0;
+  float Tc, off_c;                         // threshold, offset and unit of the bulk terms
+  double bulk_unit;
   {
     if (lane < S) { my_cnt = co.cnt; my_bulk = co.bulk; }
     have_blocks = __all(lane >= S || co.n_blk > 0);
     Tc = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(co.Tc)));   // the chunks of a row share
-    r0 = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(co.r0)));   // threshold and exponent
+    off_c = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(co.off)));   // both
+    bulk_unit = __longlong_as_double((long long)readlane_u64((unsigned long long)__double_as_longlong(co.unit), 0));
   }
   if ((ri.target & ~kPromptFlag) == 0) { list_is_used(); return 2; }          // uniform: k beyond any list
   const bool prompt_on = (ri.target & kPromptFlag) != 0;                     // tokens of a separate prompt are tagged too
@@ -163,7 +165,6 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   const double recip = 1.0 / (double)(lane == 0 ? (rp.greedy ? 1.0f : rp.tau) : rp.theta);
   const unsigned long long recip_bits = (unsigned long long)__double_as_longlong(recip);
   const RowDivisor by_tau(__longlong_as_double((long long)readlane_u64(recip_bits, 0)));
-  const double c_tau = 1.4426950408889634074 * by_tau.inv;                    // log2(e) / tau
   const RowDivisor by_theta(__longlong_as_double((long long)readlane_u64(recip_bits, 1)));
   auto scaled_s = [&](float z) { return by_tau.of(z); };
   const long long h_lo = ri.lo, h_hi = ri.hi;
@@ -511,7 +512,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   // the integer part is an exponent shift.  (Only the waves that use it work it out.)
   auto total_mass = [&](double& lnZ) -> unsigned long long {
     const double ln2 = 0.6931471805599453094;
-    const double x = fmin(fmax(bulk_exponent(Tc, r0, c_tau, m) + 10.0, -2000.0), 2000.0);
+    const double x = fmin(fmax(bulk_exponent(bulk_unit, m) + 10.0, -2000.0), 2000.0);
     const double xi = floor(x);
     const double bulk_rel = ldexp((double)bulk * (double)__builtin_amdgcn_exp2f((float)(x - xi)), (int)xi);
     const unsigned long long S0 = S_cand + (bulk_rel < 9.0e18 ? (unsigned long long)bulk_rel : 0ull);
@@ -891,9 +892,10 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     const uint32_t n_blk = ((uint32_t)V + kBlkElems - 1) >> kBlkShift;         // <= NT
     for (int i = tid; i < kBlkElems; i += NT) fs.fill[i] = 0;
     // bulk units -> 2^-40 of the maximum's mass
-    const double x = fmin(fmax(bulk_exponent(Tc, r0, c_tau, m) + (double)(kFixShift - kBlkUnitShift), -1000.0), 61.0);
-    const double xi = floor(x), unit = ldexp((double)__builtin_amdgcn_exp2f((float)(x - xi)), (int)xi);
-    auto rescaled = [&](unsigned long long u) { return (unsigned long long)fmin((double)u * unit, 4.0e18); };
+    // (in double: of the 2^-24 that a unit in fp32 is off by, the list's share moves draws)
+    const double unit = exp2(fmin(fmax(bulk_exponent(bulk_unit, m) + (double)(kFixShift - kBlkUnitShift), -1000.0), 61.0));
+    // (an ulp of fp32 sums below zero where all there is of a load is in the list)
+    auto rescaled = [&](unsigned long long u) { return (unsigned long long)fmin(fmax((double)(long long)u * unit, 0.0), 4.0e18); };
     for (int bt = 0; bt < nb; ++bt) {
       if (nb > 1) {
         load_batch(bt);
@@ -948,7 +950,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     lds_barrier();
     if (wave == 0) {
       const char* row = reinterpret_cast<const char*>(a.logits) + (size_t)b * (size_t)a.row_stride * (a.bf16 ? 2 : 4);
-      const BulkRef ref = make_bulk_ref(Tc, rp);
+      const BulkRef ref = published_ref(Tc, off_c, rp);
       const int last_of_load = a.bf16 ? 7 : 3;
       unsigned long long run_u = 0, run_E = fs.before_d;                       // ahead of the round: bulk units; list and earlier blocks
 #pragma nounroll
@@ -968,20 +970,22 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
           raw[0] = q0.x; raw[1] = q0.y; raw[2] = q0.z; raw[3] = q0.w;
           raw[4] = q1.x; raw[5] = q1.y; raw[6] = q1.z; raw[7] = q1.w;
         }
-        // element e0 + i: key of its s if it is in the list (0: not), its bulk term, its mass as a list entry
-        auto element = [&](int i, uint32_t& key, float& t, unsigned long long& E) {
+        // element e0 + i: key of its s if it is in the list (0: not), what it added to its load's sum, its
+        // mass as a list entry and what the streaming kernel took out of the sum again for that
+        auto element = [&](int i, uint32_t& key, float& t, unsigned long long& E, unsigned long long& out) {
           key = fs.fill[(e0 + i) & (kBlkElems - 1)];
           const bool in = e0 + i < V;
-          t = in && !key ? bulk_term(__uint_as_float(raw[i]), ref) : 0.0f;
+          t = in && !ref.none ? bulk_term(bulk_arg(__uint_as_float(raw[i]), ref)) : 0.0f;
           E = in && key ? mass(value_of(key)) : 0ull;
+          out = key ? blk_units(t) : 0ull;
         };
         unsigned long long u = 0, E = 0;
         float part = 0.0f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          uint32_t key; float t; unsigned long long Ei;
-          element(i, key, t, Ei);
-          part += t; E += Ei;
+          uint32_t key; float t; unsigned long long Ei, out;
+          element(i, key, t, Ei, out);
+          part += t; E += Ei; u -= out;
           if ((i & last_of_load) == last_of_load) { u += blk_units(part); part = 0.0f; }
         }
         const unsigned long long u_inc = dpp_scan_add_u64(u), E_inc = dpp_scan_add_u64(E);
@@ -992,9 +996,9 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
         part = 0.0f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          uint32_t key; float t; unsigned long long Ei;
-          element(i, key, t, Ei);
-          part += t; C_E += Ei;
+          uint32_t key; float t; unsigned long long Ei, out;
+          element(i, key, t, Ei, out);
+          part += t; C_E += Ei; C_u -= out;
           const unsigned long long to_here = C_u + blk_units(part);
           if (tok == kFinNone && C_E + rescaled(to_here) > target) {
             tok = (uint32_t)(e0 + i); tok_key = key ? key : key_of(scaled_s(__uint_as_float(raw[i])));

@@ -10,11 +10,14 @@
 //     every question that needs exact
 //     values (top-k, top-p, min-p, draw, best-n, maximum) is answered later from these few
 //     thousand entries per row;
-//   * all other elements only contribute their softmax mass 2^(z*c - R), c = log2(e)/tau,
-//     R = ceil(Tc*c).  Because z < Tc, every term is <= 1: no running maximum, no rescaling
+//   * all other elements only contribute their softmax mass, 2^(z*c + off) with c = log2(e)/tau and
+//     off = -Tc*c.  Because z < Tc, every term is < 1: no running maximum, no rescaling
 //     (Sec. 5.1 row-wise softmax, here fused with temperature scaling).  Each thread adds its
 //     terms in fp32 in a fixed order; the per-thread sums are combined as integers in units
 //     of 2^-30.
+// What bounds it: fp32 rows HBM (V = 152064, 256 rows 33.1 -> 29.6 us, 5.3 TB/s), bf16 rows vector issue (V =
+// 129280, 1024 rows 86.4 -> 74.7 us), both against a loop that compared, selected and pushed element by
+// element (16.9 vector instructions per bf16 element, now 11.8) and waited for loads it had just issued.
 // History penalties (Sec. 5.1 ApplyPenalty) touch at most |history| elements of a row.  The
 // workgroup marks the row's history tokens that fall into its chunk in an LDS bitmap (one bit
 // per element of the chunk); an element whose bit is set goes into the list whatever its
@@ -120,39 +123,59 @@ __device__ __forceinline__ int candidate_target(const RowParams& r, const Args& 
   return t;
 }
 
-// log2(e)/tau as an unevaluated fp32 sum hi + lo (greedy rows: tau = 1)
-__device__ __forceinline__ void scale_pair(const RowParams& r, float& hi, float& lo) {
-  const double c = 1.4426950408889634074 / (r.greedy ? 1.0 : (double)r.tau);
-  hi = (float)c;
-  lo = (float)(c - (double)hi);
-}
+// log2(e)/tau (greedy rows: tau = 1)
+__device__ __forceinline__ double log2_scale(const RowParams& r) { return 1.4426950408889634074 / (r.greedy ? 1.0 : (double)r.tau); }
 
-// Softmax mass of a non-candidate element relative to the threshold: 2^((z - Tc) * c + r0)
-// with c = log2(e)/tau and r0 = Tc*c - ceil(Tc*c) in (-1, 0].  Taking the difference to Tc first
-// keeps the product small where the term is not negligible, so one fp32 multiplier is accurate
-// enough; z = -inf gives exactly 0.  The terms are in units of 2^(Tc*c - r0), a whole power of two
-// that whoever reads the sums works out from Tc and r0 (bulk_exponent()), so that nothing has to
-// hold an exponent that a temperature near 0 makes as large as it likes.
+// One fused multiply-add answers both questions the stream asks of an element: x = z * c + off with
+// c = log2(e)/tau and off = -Tc*c (rounded) is negative exactly if z < Tc -- rounding keeps a sign, and
+// Tc is put, by an ulp at most, where z * c + off changes it -- and 2^x is then the element's softmax
+// mass in units of 2^-off, a number that whoever reads the sums works out from Tc and off
+// (bulk_exponent()).  Negligible terms apart x is small, so its one rounding leaves the term as
+// accurate as the fp32 result; what c's own rounding does to Tc*c is in the unit, exactly.  z = -inf
+// gives 0.
 struct BulkRef {
-  float Tc, c, r0;
+  float Tc, c, off;
+  bool none;               // no element below the threshold has any mass
+  double unit;             // log2 of the terms' unit (masses being 2^(z * log2(e)/tau))
 };
+// `Tc`: where the threshold should lie; the result's is where it lies (every reader takes that one).
+// At temperatures so small that whatever lies below the threshold has less than 2^-64 of its mass the
+// multiply-add only tells which side an element is on.
 __device__ __forceinline__ BulkRef make_bulk_ref(float Tc, const RowParams& rp) {
-  float chi, clo;
-  scale_pair(rp, chi, clo);
-  const double tc = (double)Tc * ((double)chi + (double)clo);
+  const double c = log2_scale(rp);
   BulkRef r;
-  r.Tc = Tc; r.c = chi;
-  r.r0 = fabs(tc) < 4.0e15 ? (float)(tc - ceil(tc)) : 0.0f;                   // (else, and for c beyond fp32: no fraction left)
+  r.c = (float)c; r.Tc = Tc;
+  double tc = (double)Tc * (double)r.c;
+  r.none = !(fabs(tc) < 1073741824.0) || !(r.c < INFINITY);
+  r.unit = 0.0;
+  if (r.none) { r.c = 1.0f; r.off = 0.0f - Tc; return r; }
+  if (fabs(tc) < 0x1p-100) { r.Tc = 0.0f; tc = 0.0; }                          // (so that off has its 24 bits)
+  r.off = 0.0f - (float)tc;
+  // the smallest z with z * c + off >= 0: off is within half an ulp of -Tc*c, z within one of Tc
+  // (products of two fp32 numbers are exact in double)
+  const uint32_t k = key_of(r.Tc);
+  const double at = -(double)r.off;
+  const float lower = value_of(k - 1u), upper = value_of(k + 1u);
+  if ((double)lower * (double)r.c >= at) r.Tc = lower;
+  else if (!((double)r.Tc * (double)r.c >= at)) r.Tc = upper;
+  r.unit = at + (double)r.Tc * (c - (double)r.c);
   return r;
 }
-// log2 of (unit of the bulk terms / mass of the maximum m), c = log2(e)/tau.  m >= Tc / tau as
-// rounded, so what comes out above 1 is the rounding of m, and no term is left of that size.
-__device__ __forceinline__ double bulk_exponent(float Tc, float r0, double c, float m) {
-  return (double)Tc * c - (double)r0 - (double)m * 1.4426950408889634074;
+// `off` as the chunk summaries carry it
+__device__ __forceinline__ float published_off(const BulkRef& r) { return r.none ? INFINITY : r.off; }
+// The same from a chunk summary (but for the unit).
+__device__ __forceinline__ BulkRef published_ref(float Tc, float off, const RowParams& rp) {
+  BulkRef r;
+  r.Tc = Tc; r.c = (float)log2_scale(rp); r.off = off; r.none = !(off < INFINITY); r.unit = 0.0;
+  return r;
 }
-__device__ __forceinline__ float bulk_term(float z, const BulkRef& r) {
-  return __builtin_amdgcn_exp2f(__fmaf_rn(__fsub_rn(z, r.Tc), r.c, r.r0));
-}
+// log2 of (unit of the bulk terms / mass of the maximum m).  m >= Tc / tau as rounded, so what comes
+// out above 0 is the rounding of m, and no term is left of that size.
+__device__ __forceinline__ double bulk_exponent(double unit, float m) { return unit - (double)m * 1.4426950408889634074; }
+__device__ __forceinline__ float bulk_arg(float z, const BulkRef& r) { return __fmaf_rn(z, r.c, r.off); }
+// What an element adds to the running sum: its mass if x < 0; something below 1 that is taken out
+// again if it belongs to the list (no select in the loop).
+__device__ __forceinline__ float bulk_term(float x) { return __builtin_amdgcn_exp2f(-fabsf(x)); }
 // Bulk terms of one 16-byte load, added in the order of its elements, as an integer in units of
 // 2^-41 of a term of 1, that is at most 2^-40 of the maximum's mass: added to 2^11 a double's last bit
 // is 2^-41, so the low bits of the sum are the integer (a load's terms add up to at most 8).
@@ -177,18 +200,18 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   constexpr int SLOADS = kSampleSize / SUB;         // sample loads per thread (4 fp32, 2 bf16)
   constexpr int NSB = SLOADS * kStreamWaves;        // 1 KB sample blocks spread over the row
   // LDS: first the sample histogram (two 16-bit counters per word, 16 KB), then, in its place, the
-  // per-wave candidate queues (fp32 30 KB, bf16 15 KB); 9 KB for the history bitmap of the chunk; bf16
-  // also 4 KB of tag words.  39.8 KB in all (bf16 29.8): four workgroups per compute unit.
+  // per-wave candidate queues (fp32 30 KB, bf16 15 KB); 9 KB for the history bitmap of the chunk.
+  // 39.8 KB in all (bf16 25.8): four workgroups per compute unit.
   typedef typename std::conditional<DT == SIP_F32, uint2, uint32_t>::type entry_t;      // see `process`
-  __shared__ __align__(16) unsigned char smem[(kSampleBins * 2 > kStreamWaves * kQueueCap * (int)sizeof(entry_t)) ? kSampleBins * 2 : kStreamWaves * kQueueCap * (int)sizeof(entry_t)];
-  // bf16: history bits of one 16-byte load -> what is or-ed into the load's four words (one LDS read
-  // and four instructions in the loop instead of sixteen; for the four of fp32 a table saves nothing)
-  __shared__ uint4 tag_words[DT == SIP_F32 ? 1 : 256];
-  __shared__ uint32_t bmw[kChunkBitsMax / 32];
+  constexpr int kQueueBytes = kStreamWaves * kQueueCap * (int)sizeof(entry_t);
+  constexpr int kFrontBytes = kSampleBins * 2 > kQueueBytes ? kSampleBins * 2 : kQueueBytes;
+  __shared__ __align__(16) unsigned char smem[kFrontBytes + kChunkBitsMax / 8];
+  uint32_t* const bmw = reinterpret_cast<uint32_t*>(smem + kFrontBytes);
   uint32_t* hist = reinterpret_cast<uint32_t*>(smem);
   __shared__ uint32_t red32[kStreamWaves];
   __shared__ unsigned long long red64[kStreamWaves];
-  __shared__ uint32_t wave_cnt[kStreamWaves];
+  __shared__ uint32_t seg_cnt;                      // entries of the chunk's segment so far
+  __shared__ BulkRef ref_lds;
   __shared__ uint32_t key_thr, need_thr;            // 13-bit key of the threshold bin; entries still wanted from inside it
   __shared__ unsigned long long blk_mass[kBlkMax];
   __shared__ uint32_t sub_hist[32];                 // that bin, split by the next 5 key bits
@@ -305,8 +328,8 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   int tnext = c0;                                    // first element of the next tile to request
   int n_pj = 0;                                      // SH: the piece it is in
   auto roll = [&]() {                                // SH: on to the next piece (a piece can be a single tile)
-    if (tnext >= c1) {
-      ++n_pj; tnext = c0;
+    if (tnext >= c1 && n_pj < np) {                  // (behind the last piece: on with its last 16 bytes)
+      if (++n_pj < np) tnext = c0;
       if (n_pj < np) row = shard_base(a, sh + n_pj) + (size_t)b * (size_t)a.shard_stride * ESZ;
     }
   };
@@ -375,14 +398,10 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   for (int i = tid; i < kSampleBins / 2; i += kStreamThreads) hist[i] = 0;
   for (int i = tid; i < kChunkBitsMax / 32; i += kStreamThreads) bmw[i] = 0;
   if (tid < 32) sub_hist[tid] = 0;
-  if (DT == SIP_BF16 && tid < 256) {
-    auto word = [&](int i) -> uint32_t { return ((tid >> (2 * i)) & 1 ? 0xFFFFu : 0u) | ((tid >> (2 * i + 1)) & 1 ? 0xFFFF0000u : 0u); };
-    tag_words[tid] = make_uint4(word(0), word(1), word(2), word(3));
-  }
   __syncthreads();
   if (has_pen) {
     auto mark = [&](int t) {
-      const uint32_t r = (uint32_t)(t - g0);
+      const uint32_t r = (uint32_t)(t - g0) ^ (uint32_t)(EPL - 1);             // (last element of a load first, see `process`)
       if (t >= g0 && t < g1) atomicOr(&bmw[r >> 5], 1u << (r & 31));
     };
 #pragma unroll
@@ -493,6 +512,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
     }
     __syncthreads();
     if (tid < kBlkMax) blk_mass[tid] = 0ull;
+    if (tid == 0) seg_cnt = 0;
     if (wave == 0) {
       // lane l: sub-bin 31 - l, descending (the lane's number worked out anew: one register less
       // from the start to here)
@@ -501,7 +521,10 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
       const uint32_t incl = dpp_scan_add_u32(c);
       const unsigned long long reach = __ballot(lane < 32 && incl >= need_thr);
       const uint32_t first = reach ? (uint32_t)__ffsll((long long)reach) - 1u : 31u;
-      if (lane == 0) key_thr = (K << 5) | (31u - first);                       // 18-bit key from here on
+      // 18-bit key from here on.  (One wave does the long arithmetic behind it, with the other seven waiting.)
+      const uint32_t k18 = (K << 5) | (31u - first);
+      const BulkRef r = make_bulk_ref(value_of(k18 << 14), rp);
+      if (lane == 0) { key_thr = k18; ref_lds = r; }
     }
     __syncthreads();
   }
@@ -530,19 +553,18 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
     for (int w = 1; w < kStreamWaves; ++w) klo = min(klo, red32[w]);
     const uint32_t k18 = klo == 0xFFFFFFFFu ? 512u : max(klo >> 14, 512u);
     __syncthreads();
-    if (tid == 0) key_thr = k18;
+    if (tid == 0) ref_lds = make_bulk_ref(value_of(k18 << 14), rp);
     __syncthreads();
   }
-  const uint32_t kb = key_thr << 14;
-  const float Tc = value_of(kb);
-  const BulkRef ref = make_bulk_ref(Tc, rp);
-  const float r0 = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(ref.r0)));
+  BulkRef ref = ref_lds;
+  auto uniform = [](float x) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x))); };
+  ref.Tc = uniform(ref.Tc); ref.c = uniform(ref.c); ref.off = uniform(ref.off);
 
   // ---- stream
   entry_t* queue = reinterpret_cast<entry_t*>(smem) + wave * kQueueCap;        // this wave's LDS queue
   const unsigned char* bm8 = reinterpret_cast<const unsigned char*>(bmw);
   uint32_t qn = 0;                          // wave-uniform: list entries seen (entries beyond the queue are dropped)
-  float acc = 0.0f;                         // this thread's bulk mass, fixed order of additions
+  float acc = 0.0f;                         // this thread's sum of bulk_term(), fixed order of additions
 
   uint32_t ib = ibase;                      // SH: first vocabulary id of the piece being processed
   // Block masses of a row without any filter.  One scalar branch per load for every other row; a
@@ -551,46 +573,55 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   // 16 us, streaming kernel 28 us as before, call 99.4 -> 43 us; with the sums in fp32 26.5 + 14.8 us,
   // but fewer bits than the draw by re-reading the row has.
   const bool plain = !SH && !rp.greedy && unfiltered(rp, V);                   // workgroup-uniform
-  // `hb`: the history bits of the EPL elements (bit i: element e0 + i carries a penalty); `tg`: bf16,
-  // the same as words to or into the load's (tag_words); `it`: the wave's load
+  // Per element a multiply-add, its sign shifted into a mask, an exponential and an addition; the
+  // elements at or above the threshold and the history tokens (`hb`) are then pushed lane by lane, one
+  // of each lane at a time, which takes one or two rounds of a load at the usual list lengths.
+  // Bit p of mask and `hb` is element EPL - 1 - p.  `it`: the wave's load
   // number in its chunk.  A queue entry is the element's value and its place: fp32 (bits, vocabulary
   // id); bf16 one word, the value's 16 bits above load number, lane and element (5 + 6 + 3 bits).
   // Whether it is a history token is looked up again when the queue goes out.
-  auto process = [&](const uint4& q, int e0, int it, bool guard, uint32_t hb, const uint4& tg) {
-    const uint32_t raw[4] = {q.x, q.y, q.z, q.w};
+  auto process = [&](const uint4& q, int e0, int it, bool guard, uint32_t hb) {
     float z[EPL];
-    if constexpr (DT == SIP_F32) {
-#pragma unroll
-      for (int i = 0; i < EPL; ++i) z[i] = __uint_as_float(raw[i] | (uint32_t)((int)(hb << (31 - i)) >> 31));
-    } else {
-      unpack(make_uint4(q.x | tg.x, q.y | tg.y, q.z | tg.z, q.w | tg.w), z);
-    }
+    unpack(q, z);
     if (guard) {
 #pragma unroll
       for (int i = 0; i < EPL; ++i)
         if (e0 + i >= c1) z[i] = -INFINITY;
     }
-    const uint32_t place = DT == SIP_F32 ? (uint32_t)e0 + (SH ? ib : 0u) : ((uint32_t)it << 9) | ((uint32_t)lane << 3);
-    float g = 0.0f;
+    uint32_t below = ~0u;
+    float x[EPL];
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
-      // One comparison decides "at or above the threshold, or a history token": a history token's
-      // bits are all set, a NaN, and "not below" holds for every NaN.
-      const bool hit = !(z[i] < Tc);
-      const unsigned long long mask = __ballot(hit);
-      if (mask) {
-        const uint32_t pos = qn + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-        if (hit && pos < (uint32_t)kQueueCap) {
-          if constexpr (DT == SIP_F32) queue[pos] = make_uint2(raw[i], place + (uint32_t)i);
-          else queue[pos] = ((i & 1) ? raw[i / 2] & 0xFFFF0000u : raw[i / 2] << 16) | (place | (uint32_t)i);
+      x[i] = bulk_arg(z[i], ref);
+      below = __builtin_amdgcn_alignbit(below, __float_as_uint(x[i]), 31);
+    }
+    uint32_t hits = ~below | hb;
+    if (guard) hits = e0 < c1 ? hits & (~0u << max(e0 + EPL - c1, 0)) : 0u;
+    const uint32_t place = DT == SIP_F32 ? (uint32_t)(e0 + EPL - 1) + (SH ? ib : 0u) : ((uint32_t)it << 9) | ((uint32_t)lane << 3) | 7u;
+    // (a queue that is full is looked at once per load: what it gets beyond its room lies in the next
+    // waves' or in the bitmap, and the chunk is given up)
+    if (__builtin_amdgcn_readfirstlane((int)qn) <= kQueueCap) {
+      for (;;) {
+        const unsigned long long mask = __ballot(hits != 0);
+        if (!mask) break;
+        const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, qn));
+        if (hits) {
+          const uint32_t p = (uint32_t)__ffs((int)hits) - 1u, y = place - p;
+          if constexpr (DT == SIP_F32) {
+            const float hi = (p & 1u) ? z[0] : z[1], lo = (p & 1u) ? z[2] : z[3];
+            queue[pos] = make_uint2(__float_as_uint(p < 2u ? lo : hi), y);
+          } else {
+            const unsigned long long w = p < 4u ? ((unsigned long long)q.w << 32) | q.z : ((unsigned long long)q.y << 32) | q.x;
+            queue[pos] = ((uint32_t)(w >> ((y << 4) & 63u)) << 16) | y;
+          }
         }
+        hits &= hits - 1u;
         qn += (uint32_t)__popcll(mask);
       }
-      float e = bulk_term(z[i], ref);
-      e = hit ? 0.0f : e;
-      g += e;
     }
+    float g = bulk_term(x[0]);
+#pragma unroll
+    for (int i = 1; i < EPL; ++i) g += bulk_term(x[i]);
     acc += g;
     if (!SH && plain) {
       // (in two halves of 24 and 20 bits: 32-bit sums over 16 lanes, and four atomics of the wave for the rest)
@@ -602,88 +633,78 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   };
   // Element e0 of the piece being processed is bit (ib - ibase) + e0 - c0 of the bitmap, a
   // multiple of EPL: the bits of one 16-byte load are half a byte (fp32) or one byte (bf16).
-  // Lanes past the end of the chunk read the last byte; `process` discards what they get.
-  auto hist_bits = [&](int e0) -> uint32_t {
-    const uint32_t bit0 = (uint32_t)(e0 - c0) + (SH ? ib - ibase : 0u);
-    const uint32_t byte = bm8[min(bit0 >> 3, (uint32_t)(kChunkBitsMax / 8 - 1))];
+  // Lanes past the end of the chunk read the last byte; `process` discards what they get.  (e0 =
+  // t0 + tid * EPL + a multiple of 64, so that one address serves the loads of a tile.)
+  auto hist_bits = [&](int t0, int j, bool guard) -> uint32_t {
+    uint32_t bit0 = (uint32_t)(t0 - c0 + tid * EPL) + (SH ? ib - ibase : 0u);
+    uint32_t at = (bit0 >> 3) + (uint32_t)(j * (SUB / 8));
+    if (guard) at = min(at, (uint32_t)(kChunkBitsMax / 8 - 1));
+    const uint32_t byte = bm8[at];
     return DT == SIP_F32 ? (byte >> (bit0 & 4u)) & 0xFu : byte;
   };
   int it0 = 0;                              // number of the tile's first load
   auto process_tile = [&](const uint4 (&buf)[kStreamLoads], int t0) {
     const bool partial = t0 + TILE > c1;
     uint32_t hb[kStreamLoads];
-    uint4 tg[kStreamLoads] = {};
+    if (!partial) {
 #pragma unroll
-    for (int j = 0; j < kStreamLoads; ++j) hb[j] = hist_bits(t0 + j * SUB + tid * EPL);
-    if constexpr (DT == SIP_BF16) {
+      for (int j = 0; j < kStreamLoads; ++j) hb[j] = hist_bits(t0, j, false);
 #pragma unroll
-      for (int j = 0; j < kStreamLoads; ++j) tg[j] = tag_words[hb[j]];
-    }
+      for (int j = 0; j < kStreamLoads; ++j) process(buf[j], t0 + j * SUB + tid * EPL, it0 + j, false, hb[j]);
+    } else {
 #pragma unroll
-    for (int j = 0; j < kStreamLoads; ++j) {
-      const int e0 = t0 + j * SUB + tid * EPL;
-      if (!partial) process(buf[j], e0, it0 + j, false, hb[j], tg[j]);
-      else if (t0 + j * SUB < c1) process(buf[j], e0, it0 + j, true, hb[j], tg[j]);     // workgroup-uniform condition
+      for (int j = 0; j < kStreamLoads; ++j)
+        if (t0 + j * SUB < c1) process(buf[j], t0 + j * SUB + tid * EPL, it0 + j, true, hist_bits(t0, j, true));     // workgroup-uniform condition
     }
     it0 += kStreamLoads;
   };
 
-  // kStreamBufs register buffers in rotation: while one tile is processed the loads of the
-  // others are in flight
+  // Two register buffers in turn: while one tile is processed the other's loads are in flight.  Every
+  // tile processed is followed by a request, also where nothing is left to request (it repeats the last
+  // 16 bytes), and the loop is left from its middle: with a request that may not have been made the
+  // compiler counts the outstanding loads as if it had not, and waits for the loads just issued.
+  static_assert(kStreamBufs == 2, "");
   if (!SH) {
-    int tcur = c0;
-    bool more = true;
-    while (more) {
-#pragma unroll
-      for (int k = 0; k < kStreamBufs; ++k) {
-        if (tcur < c1) {
-          process_tile(buf[k], tcur);
-          if (tnext < c1) load_tile(tnext, buf[k]);
-          tnext += TILE;
-          tcur += TILE;
-        } else {
-          more = false;
-        }
-      }
+    for (int tcur = c0;;) {
+      process_tile(buf[0], tcur);
+      load_tile(tnext, buf[0]);
+      tnext += TILE; tcur += TILE;
+      if (tcur >= c1) break;
+      process_tile(buf[1], tcur);
+      load_tile(tnext, buf[1]);
+      tnext += TILE; tcur += TILE;
+      if (tcur >= c1) break;
     }
   } else {
-    // the same rotation over np pieces: every piece is [c0, c1) of its shard; the requests run
-    // ahead of the processing across the piece boundaries (`row` is what load_tile reads from)
+    // the same over np pieces: every piece is [c0, c1) of its shard; the requests run ahead of the
+    // processing across the piece boundaries (`row` is what load_tile reads from)
     int c_pj = 0, tcur = c0;                         // tile being processed
-    bool more = true;
-    while (more) {
-#pragma unroll
-      for (int k = 0; k < kStreamBufs; ++k) {
-        if (c_pj < np) {
-          process_tile(buf[k], tcur);
-          if (n_pj < np) { load_tile(tnext, buf[k]); tnext += TILE; roll(); }
-          tcur += TILE;
-          if (tcur >= c1) { ++c_pj; tcur = c0; ib += (uint32_t)Vl; }
-        } else {
-          more = false;
-        }
-      }
+    auto on = [&]() {
+      tcur += TILE;
+      if (tcur >= c1) { ++c_pj; tcur = c0; ib += (uint32_t)Vl; }
+      return c_pj < np;
+    };
+    for (;;) {
+      process_tile(buf[0], tcur);
+      load_tile(tnext, buf[0]); tnext += TILE; roll();
+      if (!on()) break;
+      process_tile(buf[1], tcur);
+      load_tile(tnext, buf[1]); tnext += TILE; roll();
+      if (!on()) break;
     }
   }
-  // ---- chunk summary; the eight queues go out, one behind the other, to the chunk's segment
-  // (no global stores inside the loop: they would force every wait on a tile load to drain the
-  // whole memory queue)
-  const unsigned long long wsum = dpp_scan_add_u64(bulk_units(acc));      // integer from here on
-  if (lane == kWave - 1) { red64[wave] = wsum; wave_cnt[wave] = qn; }
-  __syncthreads();
-  uint32_t off = 0, tot = 0;
-  bool overflow = false;
-#pragma unroll
-  for (int w = 0; w < kStreamWaves; ++w) {
-    const uint32_t c = wave_cnt[w];
-    overflow |= c > (uint32_t)kQueueCap;
-    const uint32_t cc = min(c, (uint32_t)kQueueCap);
-    if (w < wave) off += cc;
-    tot += cc;
-  }
+  // ---- the queues go out, one behind the other in the order in which the waves get here, to the
+  // chunk's segment (no global stores inside the loop: they would force every wait on a tile load to
+  // drain the whole memory queue); what their entries added to the sums is taken out of them again,
+  // in integers
+  const uint32_t n_out = min(qn, (uint32_t)kQueueCap);
+  uint32_t off = 0;
+  if (lane == 0) off = atomicAdd(&seg_cnt, n_out);
+  off = (uint32_t)__builtin_amdgcn_readfirstlane((int)off);
+  unsigned long long units = bulk_units(acc);
   uint2* seg = a.cand + (size_t)wg * (size_t)kChunkCap + off;
   const int lpp = kStreamLoads * ((c1 - c0 + TILE - 1) / TILE);                // load numbers of one piece
-  for (uint32_t i = lane; i < min(qn, (uint32_t)kQueueCap); i += kWave) {
+  for (uint32_t i = lane; i < n_out; i += kWave) {
     uint2 en;
     if constexpr (DT == SIP_F32) {
       en = queue[i];
@@ -693,22 +714,34 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
       if (SH) { const uint32_t pc = it / (uint32_t)lpp; it -= pc * (uint32_t)lpp; base += pc * (uint32_t)Vl; }
       en = make_uint2(w & 0xFFFF0000u, base + it * (uint32_t)SUB + (uint32_t)wave * (uint32_t)(kWave * EPL) + (w & 511u));
     }
-    const uint32_t bit = en.y - (uint32_t)g0;
+    const float t = bulk_term(bulk_arg(__uint_as_float(en.x), ref));
+    units -= bulk_units(t);
+    const uint32_t place = en.y - (uint32_t)g0, bit = place ^ (uint32_t)(EPL - 1);
+    if (!SH && plain) atomicAdd(&blk_mass[min(place / (uint32_t)kBlkElems, (uint32_t)kBlkMax - 1u)], 0ull - blk_units(t));
     if ((bmw[min(bit >> 5, (uint32_t)(kChunkBitsMax / 32 - 1))] >> (bit & 31u)) & 1u) en.y |= kTagBit;
     seg[i] = en;
   }
+  const unsigned long long wsum = dpp_scan_add_u64(units);
+  if (lane == kWave - 1) { red64[wave] = wsum; red32[wave] = qn; }
+  __syncthreads();
+  bool overflow = false;
+#pragma unroll
+  for (int w = 0; w < kStreamWaves; ++w) overflow |= red32[w] > (uint32_t)kQueueCap;
+  const uint32_t tot = seg_cnt;
   const bool blocks = plain && tot <= (uint32_t)(kChunkCap - kBlkMax);           // workgroup-uniform
   const int n_blk = blocks ? (c1 - c0 + kBlkElems - 1) / kBlkElems : 0;
-  if (tid < n_blk) (reinterpret_cast<unsigned long long*>(a.cand + (size_t)(wg + 1) * (size_t)kChunkCap) - n_blk)[tid] = blk_mass[tid];
+  if (tid < n_blk) (reinterpret_cast<unsigned long long*>(a.cand + (size_t)(wg + 1) * (size_t)kChunkCap) - n_blk)[tid] = ref.none ? 0ull : blk_mass[tid];
   if (tid == 0) {
     ChunkOut o;
-    o.bulk = 0;
+    long long sum = 0;
 #pragma unroll
-    for (int w = 0; w < kStreamWaves; ++w) o.bulk += red64[w];
-    o.Tc = Tc;
-    o.r0 = r0;
+    for (int w = 0; w < kStreamWaves; ++w) sum += (long long)red64[w];
+    o.bulk = ref.none || sum < 0 ? 0ull : (unsigned long long)sum;               // (an ulp of the threads' sums below 0)
+    o.Tc = ref.Tc;
+    o.off = published_off(ref);
     o.cnt = overflow ? kCntOverflow : tot;
-    o.n_blk = (uint32_t)n_blk; o.pad[0] = o.pad[1] = 0;
+    o.n_blk = (uint32_t)n_blk;
+    o.unit = ref_lds.unit;
     a.chunks[wg] = o;
   }
 }
