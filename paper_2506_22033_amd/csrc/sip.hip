@@ -18,6 +18,7 @@
 #include "sip_fused.h"
 #include "sip_handoff.h"
 #include "sip_resident.h"
+#include "sip_row.h"
 #include "sip_state.h"
 #include "sip_stream.h"
 
@@ -47,7 +48,7 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t = 0) {
   const int Vp = V / pieces;                           // elements per piece
   p.fast = V >= kFastMinV && V <= kFastMaxV && Vp >= kFastMinPiece && pieces <= sip::kMaxChunks;
   if (!p.fast) return p;
-  const int tile = sip::kStreamThreads * sip::kStreamLoads * (dtype == SIP_F32 ? 4 : 8);
+  const int tile = dtype == SIP_F32 ? sip::StreamShape<SIP_F32, false>::kTile : sip::StreamShape<SIP_BF16, false>::kTile;
   const int n_tiles = (Vp + tile - 1) / tile * pieces;
   // Chunks per row.  Up to 256 rows: as many workgroups as fit on the chip at once (4 per compute
   // unit), so that there is a single, full round.  Larger batches run in rounds of that many
@@ -105,7 +106,7 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t = 0) {
 }
 
 struct Layout {
-  size_t row_path, rescue, side_z, side_c, rowinfo, chunks, cand, gather, total;
+  size_t row_path, tick, side_z, side_c, rowinfo, chunks, cand, gather, total;
 };
 
 thread_local hipEvent_t g_prof[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};   // one-shot, see sip_profile_kernel_events()
@@ -168,7 +169,7 @@ Layout make_layout(int32_t B, const Plan& p, int64_t nnz, size_t gather_row_byte
   size_t off = 0;
   l.row_path = off; off += align_up((size_t)2 * B * sizeof(int));            // first, so that callers can find it: path
                                                                              // codes, then the finishing kernel's own codes
-  l.rescue = off; off += align_up(((size_t)B + 1) * sizeof(int) + 16);       // count, row numbers, the state's call counter
+  l.tick = off; off += align_up(sizeof(unsigned long long));                 // the state's call counter as taken by this call
   l.side_z = off; off += align_up((size_t)nnz * sizeof(float));
   l.side_c = off; off += align_up((size_t)nnz * sizeof(unsigned int));
   l.rowinfo = off;
@@ -229,6 +230,30 @@ bool resident_is_chosen(const sip::Args& a, int32_t B, bool state, int compute_u
   const bool top = a.p.top_k || a.p.top_p, best = a.k_lp > 0;
   if (B <= compute_units) return top || a.p.min_p || !best;
   return !top && !best && (!a.p.min_p || B <= 3 * compute_units);
+}
+
+// Whether a row's workgroup streams and finishes it (sip_row.h) or the row is streamed in chunks for the
+// finishing kernel.  A row to a workgroup pays the set-up once and overlaps one row's finishing with
+// another's streaming, or at least needs no second kernel; but up to one row per compute unit it leaves
+// chip idle that chunks would use, and beyond that the rows come in rounds of two per compute unit.
+// us a call in chunks / a row to a workgroup (256 compute units; nucleus 0.95 or no filter):
+//   V = 40000 bf16 (80 KB): 96 rows 23 / 23, 160 27 / 23, 300 36 / 33, 640 51 / 50, 2048 115 / 108
+//   V = 128256 bf16 (256 KB): 96 28 / 30, 128 31 / 30, 160 32 / 31, 256 34 / 31, 300 44 / 46, 512 49 / 48, 1024 87 / 84, 2048 178 / 159
+//   V = 128256 fp32 (513 KB): 192 35 / 35, 224 39 / 37, 384 56 / 58, 768 114 / 101, 2048 277 / 240
+//   V = 262144 fp32 (1 MB): 128 39 / 47, 224 57 / 54, 300 78 / 90, 512 127 / 120, 2048 486 / 425
+//   V = 100000 and 200000, both types: 420 to 500 rows 0 to 11 % less, 520 8 % more to 4 % less, 600 2 % more
+//   to 8 % less, 700 and 1030 2 to 17 % less.
+// So up to one row per compute unit from a number of rows on that grows with the row's bytes, to 7/8 of
+// the compute units; above, not in the first half of a round -- unless the row is short -- but in the
+// third and later rounds always.  A state's call would have to take its number in a launch of its own
+// ahead of it (V = 152064, 256 rows: 74 / 73 bf16, 81 / 82 fp32; 520 rows 108 / 113, 136 / 139; 1030
+// 161 / 155, 220 / 205).
+bool row_is_chosen(int32_t B, int32_t V, int dtype, bool state, int compute_units) {
+  const int64_t row_bytes = (int64_t)V * (dtype == SIP_F32 ? 4 : 2), cu = compute_units;
+  if (state) return B >= 4 * cu;
+  if (B <= cu) return B >= std::min(cu * 7 / 8, cu * 3 / 8 + row_bytes / 4096);
+  if (row_bytes <= 200 * 1024) return true;
+  return B <= 2 * cu ? B >= cu * 25 / 16 : B >= cu * 75 / 32;
 }
 
 // Argument checks common to the entry points, workspace carving and the kernel launches.
@@ -303,9 +328,8 @@ sip_status sample_impl(const void* logits, int32_t B, int32_t V, int64_t row_str
   a.bf16 = dtype == SIP_BF16;
   a.S = plan.S; a.cap_c = plan.cap_c; a.nc_cap = plan.nc_cap;
   a.row_why = a.row_path + B;
-  a.rescue_n = reinterpret_cast<int*>(ws + lay.rescue);
-  a.rescue_rows = a.rescue_n + 1;
-  a.rescue_tick = reinterpret_cast<unsigned long long*>(ws + lay.rescue + (((size_t)B + 1) * sizeof(int) + 7) / 8 * 8);
+  a.tick_room = reinterpret_cast<unsigned long long*>(ws + lay.tick);
+  a.one_seg = 0;
 
   sip::StateHeader* head = h.slot ? h.state.head : nullptr;
   return sh.t ? launch<true>(a, B, (int)dtype, plan, h.slot != nullptr, head, stream)
@@ -324,7 +348,7 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
   if (a.V <= kResidentMaxV && (!plan.fast || resident_is_chosen(a, B, state, dev->compute_units))) {
     // a workgroup holds its whole row in registers: one kernel
     if (state) {
-      a.call_tick = a.rescue_tick;
+      a.call_tick = a.tick_room;
       hipLaunchKernelGGL(sip::state_take_tick_kernel, dim3(1), dim3(64), 0, stream, head, a.call_tick);
     }
     const bool f32 = dtype == SIP_F32;
@@ -355,17 +379,45 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
     }
     return SIP_OK;
   }
-  a.call_tick = state ? a.rescue_tick : nullptr;   // the streaming kernel takes the state's counter and leaves it here
+  a.call_tick = state ? a.tick_room : nullptr;   // the streaming kernel takes the state's counter and leaves it here
   auto k_stream = dtype == SIP_F32 ? sip::stream_kernel<SIP_F32, SH> : sip::stream_kernel<SIP_BF16, SH>;
   auto k_rescue = dtype == SIP_F32 ? sip::rescue_kernel<SIP_F32, SH> : sip::rescue_kernel<SIP_BF16, SH>;
   const size_t dyn = std::max(plan.final_lds, 2 * words * sizeof(uint32_t));
-  // The pass over the logits, then one workgroup per row on what it left.  A batch of no more rows
-  // than the device has compute units: the workgroup also takes its row through the heavier logic
-  // if the list does not settle it (sip_fused.h).  Larger batches: the lean finishing kernel, two
-  // workgroups per compute unit, and a small fixed grid behind it for the rows (normally none) that
-  // need more.
+  // A row streamed and finished by one workgroup, or the pass over the logits in chunks, then one
+  // workgroup per row on what it left.  A batch of no more rows than the device has compute units: the
+  // workgroup also takes its row through the heavier logic if the list does not settle it
+  // (sip_fused.h).  Larger batches: the lean kernel, two workgroups per compute unit, and a small fixed
+  // grid behind it for the rows (normally none) that need more.
   const bool fused = B <= dev->compute_units && (size_t)plan.final_lds <= sip::kFusedRawBytes &&
                      2 * words * sizeof(uint32_t) <= sip::kFusedRawBytes;
+  a.one_seg = row_is_chosen(B, a.V, dtype, state, dev->compute_units);
+  if (a.one_seg) {
+    // the row's workgroup streams and finishes it, and the rescue kernel is behind it
+    if (state) hipLaunchKernelGGL(sip::state_take_tick_kernel, dim3(1), dim3(64), 0, stream, head, a.call_tick);
+    if (fused) {
+      auto k_both = dtype == SIP_F32 ? sip::row_rescue_kernel<SIP_F32, SH> : sip::row_rescue_kernel<SIP_BF16, SH>;
+      if (timed) {
+        hipExtLaunchKernelGGL(k_both, dim3(B), dim3(sip::kStreamThreads), 0, stream, ev[0], ev[1], 0, a);
+        for (int i = 2; i < 6; ++i)
+          if (ev[i]) (void)hipEventRecord(ev[i], stream);     // one kernel: empty intervals
+      } else {
+        hipLaunchKernelGGL(k_both, dim3(B), dim3(sip::kStreamThreads), 0, stream, a);
+      }
+      return hipGetLastError() == hipSuccess ? SIP_OK : SIP_ERR_HIP;
+    }
+    auto k_row = dtype == SIP_F32 ? sip::row_kernel<SIP_F32, SH> : sip::row_kernel<SIP_BF16, SH>;
+    const int n_rescue_wg = std::min<int>(B, kRescueGrid);
+    if (timed) {
+      hipExtLaunchKernelGGL(k_row, dim3(B), dim3(sip::kStreamThreads), 0, stream, ev[0], ev[1], 0, a);
+      for (int i = 2; i < 4; ++i)
+        if (ev[i]) (void)hipEventRecord(ev[i], stream);       // no finishing kernel: an empty interval
+      hipExtLaunchKernelGGL(k_rescue, dim3(n_rescue_wg), dim3(sip::kFinalThreads), dyn, stream, ev[4], ev[5], 0, a);
+    } else {
+      hipLaunchKernelGGL(k_row, dim3(B), dim3(sip::kStreamThreads), 0, stream, a);
+      hipLaunchKernelGGL(k_rescue, dim3(n_rescue_wg), dim3(sip::kFinalThreads), dyn, stream, a);
+    }
+    return hipGetLastError() == hipSuccess ? SIP_OK : SIP_ERR_HIP;
+  }
   if (timed) hipExtLaunchKernelGGL(k_stream, dim3(B * plan.S), dim3(sip::kStreamThreads), 0, stream, ev[0], ev[1], 0, a);
   else hipLaunchKernelGGL(k_stream, dim3(B * plan.S), dim3(sip::kStreamThreads), 0, stream, a);
   if (fused) {

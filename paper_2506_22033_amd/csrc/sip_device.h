@@ -80,10 +80,9 @@ struct Args {
   int cap_c;                // list entries per chunk segment
   int nc_cap;               // longest list any finishing path can hold
   int* row_path;            // [B] diagnostic: 1 = finished by the single-pass path, >1 = exact path (reason)
-  int* row_why;             // [B] diagnostic: 1, or why the finishing kernel handed the row to the rescue kernel
-  int* rescue_n;            // rows the finishing kernel could not settle from the list ...
-  int* rescue_rows;         // [B] ... and which; the rescue kernel takes them from here
-  unsigned long long* rescue_tick;   // room in the workspace for `call_tick`
+  int* row_why;             // [B] diagnostic: 1, or why the finishing kernel left the row to the rescue kernel
+  int one_seg;              // the row's S segments are one: its workgroup made the whole list (sip_row.h)
+  unsigned long long* tick_room;     // room in the workspace for `call_tick`
   // Device-resident history (sip_sample_state): `slot` != nullptr replaces the CSR above.  Row b's
   // history is tokens[slot[b] * L_max .. + st_len[slot[b]]); `tokens` then points at the state's
   // token table and nnz = slots * L_max.
@@ -207,20 +206,19 @@ __device__ __attribute__((noinline)) void gather_row(const Args& a, int b) {
 // kernel those are as many round trips one after the other.  This touches every line at once,
 // at the start (scalar loads only, results thrown away).
 __device__ __forceinline__ void warm_kernel_arguments() {
-  static_assert(sizeof(Args) >= 0x1c4 && sizeof(Args) <= 0x200, "eight lines of 64 bytes");
+  static_assert(sizeof(Args) >= 0x184 && sizeof(Args) <= 0x1c0, "seven lines of 64 bytes");
   const void* p = (const void*)__builtin_amdgcn_kernarg_segment_ptr();
-  uint32_t t0, t1, t2, t3, t4, t5, t6, t7;
+  uint32_t t0, t1, t2, t3, t4, t5, t6;
   asm volatile(
-      "s_load_dword %0, %8, 0x0\n\t"
-      "s_load_dword %1, %8, 0x40\n\t"
-      "s_load_dword %2, %8, 0x80\n\t"
-      "s_load_dword %3, %8, 0xc0\n\t"
-      "s_load_dword %4, %8, 0x100\n\t"
-      "s_load_dword %5, %8, 0x140\n\t"
-      "s_load_dword %6, %8, 0x180\n\t"
-      "s_load_dword %7, %8, 0x1c0\n\t"
+      "s_load_dword %0, %7, 0x0\n\t"
+      "s_load_dword %1, %7, 0x40\n\t"
+      "s_load_dword %2, %7, 0x80\n\t"
+      "s_load_dword %3, %7, 0xc0\n\t"
+      "s_load_dword %4, %7, 0x100\n\t"
+      "s_load_dword %5, %7, 0x140\n\t"
+      "s_load_dword %6, %7, 0x180\n\t"
       "s_waitcnt lgkmcnt(0)"
-      : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(t4), "=&s"(t5), "=&s"(t6), "=&s"(t7)
+      : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(t4), "=&s"(t5), "=&s"(t6)
       : "s"(p));
 }
 

@@ -952,7 +952,7 @@ __device__ __forceinline__ void rescue_row(const Args& a, const int b, unsigned 
     }
     if (threadIdx.x == 0) fs.ndist_out = -1;
     // At most two attempts, written as a loop so that the kernel holds one copy of the code.
-    int S = a.S, cap_c = a.cap_c;
+    int S = a.one_seg ? 1 : a.S, cap_c = a.one_seg ? a.S * a.cap_c : a.cap_c;
 #pragma nounroll
     for (int attempt = 0; attempt < 2; ++attempt) {
       int r;
@@ -1031,9 +1031,10 @@ __device__ __forceinline__ void rescue_row(const Args& a, const int b, unsigned 
   }
 }
 
-// The rows that finish_kernel could not settle (it leaves their numbers in Args::rescue_rows),
-// one workgroup per row at a time.  Launched with a fixed, small grid after every finish_kernel;
-// with nothing to rescue a workgroup reads the count and returns.
+// The rows that the kernel before it could not settle (row_why is not 1), one workgroup per row at a
+// time: the i-th of them is workgroup i % grid's.  Launched with a fixed, small grid; every workgroup
+// looks at all the codes, four of a thread at a time, so that nothing has to be counted (and nothing
+// set to zero) ahead of it.  Nothing to rescue, 1024 rows: 4.7 us, as with a queue in memory.
 template <int DT, bool SH>
 __global__ __launch_bounds__(kFinalThreads) void rescue_kernel(Args a_by_value) {
   // The arguments are read where they are used, straight from the kernel-argument segment
@@ -1044,11 +1045,38 @@ __global__ __launch_bounds__(kFinalThreads) void rescue_kernel(Args a_by_value) 
   extern __shared__ __align__(16) unsigned char dynraw[];
   __shared__ ExactShared ex;
   __shared__ FastShared fs;
-  const int n_rescue = min(max(*a.rescue_n, 0), a.B);
+  constexpr int PER = 4, SPAN = PER * kFinalThreads;
+  __shared__ unsigned short mine[SPAN];                // this workgroup's, from the rows looked at
+  __shared__ int n_mine;
+  __shared__ uint32_t wave_n[kFinalWaves];
+  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+  uint32_t seen = 0;                                   // unsettled rows so far
 #pragma nounroll
-  for (int qi = blockIdx.x; qi < n_rescue; qi += gridDim.x) {
-    if (qi != (int)blockIdx.x) __syncthreads();    // the row before this one is done with the tables in LDS
-    rescue_row<DT, SH>(a, min(max(a.rescue_rows[qi], 0), a.B - 1), dynraw, ex, fs);
+  for (int base = 0; base < a.B; base += SPAN) {
+    uint32_t bad = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int r = base + j * kFinalThreads + tid;
+      bad |= (r < a.B && a.row_why[min(r, a.B - 1)] != 1) ? 1u << j : 0u;
+    }
+    if (!__syncthreads_or((int)bad)) continue;         // uniform
+    const uint32_t n = (uint32_t)__popc(bad), incl = wave_incl_scan_u32(n);
+    if (lane == kWave - 1) wave_n[wave] = incl;
+    if (tid == 0) n_mine = 0;
+    __syncthreads();
+    uint32_t i = seen + incl - n;
+    for (int w = 0; w < kFinalWaves; ++w) {
+      if (w < wave) i += wave_n[w];
+      seen += wave_n[w];
+    }
+    for (; bad; bad &= bad - 1, ++i)
+      if (i % gridDim.x == blockIdx.x) mine[atomicAdd(&n_mine, 1)] = (unsigned short)((__ffs((int)bad) - 1) * kFinalThreads + tid);
+    __syncthreads();
+#pragma nounroll
+    for (int q = 0; q < n_mine; ++q) {
+      rescue_row<DT, SH>(a, base + (int)mine[q], dynraw, ex, fs);
+      __syncthreads();                                 // done with the tables in LDS
+    }
   }
 }
 

@@ -25,8 +25,8 @@
 //       read again.
 //
 // Whatever the list cannot prove (a cut that may lie below the completeness threshold, an
-// overflow, a bin with too many members, ...) makes the row's number go to the rescue queue
-// with a reason code; rescue_kernel (sip_final.h) then takes the row over.
+// overflow, a bin with too many members, ...) leaves a reason code in row_why; rescue_kernel
+// (sip_final.h) then takes the row over.
 #pragma once
 #include "sip_device.h"
 #include "sip_stream.h"
@@ -34,7 +34,7 @@
 namespace sip {
 constexpr int kFinThreads = 512;
 constexpr int kFinWaves = kFinThreads / kWave;
-constexpr int kFinCR = 10;                             // list entries a thread holds in registers
+constexpr int kFinCR = kRowRegs;                       // list entries a thread holds in registers
 constexpr int kFinBins = 1024;
 constexpr int kFinBPT = kFinBins / kFinThreads;        // bins per thread in the scans
 constexpr int kFinList = 4352;                         // entries of the bin-sorted list in LDS
@@ -101,12 +101,17 @@ struct FinHint {
 
 // Row b, start to finish.  Returns 1 or kFinWholeRow (finished: outputs written) or the reason why the list
 // does not settle the row.  Every return value is workgroup-uniform.
-__device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared& fs, FinHint* hint = nullptr) {
+// ROW: the calling workgroup has made the list itself, as one segment; `hand` holds the row's record and
+// the summary.
+template <bool ROW>
+__device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared& fs, FinHint* hint = nullptr,
+                                          const RowHand* hand = nullptr) {
   constexpr int NT = kFinThreads;
   constexpr int CR = kFinCR;
   const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
   const int V = a.V;
-  const int S = a.S;
+  const int S = ROW ? 1 : a.S;
+  const int cap_c = ROW ? a.S * a.cap_c : a.cap_c;
 
   // ---- (0) Everything this kernel reads from memory has an address that does not depend on
   // anything else it reads, except the history tokens: the row's parameters and history extent
@@ -114,20 +119,22 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   // the list itself are requested at once.  The list is read before the segment sizes are
   // known: thread t belongs to segment t / tps and takes, in round r, slot r * tps + t % tps of
   // it; slots beyond the segment's size are dropped afterwards.
-  const int tps = a.fin_tps;                                   // kFinThreads / S
-  int c_seg = (tid * a.fin_inv) >> 16;                         // tid / tps, put right below
+  const int tps = ROW ? kFinThreads : a.fin_tps;               // kFinThreads / S
+  int c_seg = ROW ? 0 : (tid * a.fin_inv) >> 16;               // tid / tps, put right below
   c_seg -= c_seg * tps > tid;
   const int j_seg = tid - c_seg * tps;
   const bool seg_thread = c_seg < S;
-  uint2* seg = a.cand + ((size_t)b * (size_t)S + (size_t)min(c_seg, S - 1)) * (size_t)a.cap_c;
+  uint2* seg = a.cand + ((size_t)b * (size_t)S + (size_t)min(c_seg, S - 1)) * (size_t)cap_c;
   uint2 creg[CR];                          // (bits of z, later of z' and then the key of s; index | tag, later index)
   auto slot_of = [&](int bt, int r) { return (bt * CR + r) * tps + j_seg; };
   // Unchecked against the sizes, and unconditional (a branch around a load makes the compiler wait
   // for every load in flight where the branches meet): slots past the segment's capacity read its
   // last slot, threads without a segment the last segment's; drop_beyond() discards what they get.
+  // (ROW: the list's length is known, and no slot past it is read)
+  const int last_slot = ROW ? max(min((int)hand->co.cnt, cap_c), 1) - 1 : cap_c - 1;
   auto load_batch = [&](int bt) {
 #pragma unroll
-    for (int r = 0; r < CR; ++r) creg[r] = seg[min(slot_of(bt, r), a.cap_c - 1)];
+    for (int r = 0; r < CR; ++r) creg[r] = seg[min(slot_of(bt, r), last_slot)];
   };
   // (the two small records first: loads come back in the order of their requests, and what
   // depends on the records -- the history loads, the plan of the phases -- need not wait for the list)
@@ -142,9 +149,18 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     for (int r = 0; r < CR; ++r) asm volatile("" ::"v"(creg[r].x), "v"(creg[r].y));
     asm volatile("" ::"v"((uint32_t)my_bulk), "v"((uint32_t)(my_bulk >> 32)));
   };
-  const RowInfo ri = a.rowinfo[b];
-  const ChunkOut co = a.chunks[(size_t)b * S + min(lane, S - 1)];
-  load_batch(0);
+  const RowInfo ri = ROW ? hand->ri : a.rowinfo[b];
+  const ChunkOut co = ROW ? hand->co : a.chunks[(size_t)b * S + min(lane, S - 1)];
+  if constexpr (ROW) {
+    if (hand->direct) {                    // uniform
+#pragma unroll
+      for (int r = 0; r < CR; ++r) creg[r] = hand->list[r];
+    } else {
+      load_batch(0);
+    }
+  } else {
+    load_batch(0);
+  }
   uint32_t my_cnt = 0;
   float Tc, off_c;                         // threshold, offset and unit of the bulk terms
   double bulk_unit;
@@ -223,18 +239,20 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   const bool k_act = !rp.greedy && rp.top_k >= 2 && rp.top_k < V;
   const uint32_t n_top = (uint32_t)max(0, min(a.k_lp, V));
 
-  const bool any_over = __any(my_cnt > (uint32_t)a.cap_c);                   // includes the overflow mark
-  const uint32_t total = wave_add_u32(my_cnt);
-  const uint32_t longest = wave_max_u32(my_cnt);
-  const unsigned long long bulk = wave_add_u64(my_bulk);
+  const bool direct = ROW && hand->direct;                                   // a round is 64 entries of every queue
+  const bool any_over = ROW ? hand->co.cnt > (uint32_t)cap_c : __any(my_cnt > (uint32_t)cap_c);   // includes the overflow mark
+  const uint32_t total = ROW ? hand->co.cnt : wave_add_u32(my_cnt);
+  const uint32_t longest = ROW ? (direct ? hand->longest * (uint32_t)kFinWaves : hand->co.cnt) : wave_max_u32(my_cnt);
+  const unsigned long long bulk = ROW ? hand->co.bulk : wave_add_u64(my_bulk);
   if (any_over || !(Tc == Tc)) { list_is_used(); return 3; }                 // uniform
   if (total > (uint32_t)a.nc_cap) { list_is_used(); return 5; }              // uniform
   const int nb = (int)((longest + (uint32_t)(CR * tps) - 1) / (uint32_t)(CR * tps));   // uniform: batches of CR rounds
-  const int cnt_seg = seg_thread ? __shfl((int)my_cnt, c_seg, kWave) : 0;    // size of this thread's segment
+  const int cnt_seg = ROW ? (int)hand->co.cnt : seg_thread ? __shfl((int)my_cnt, c_seg, kWave) : 0;    // size of this thread's segment
   // whether round r of batch bt holds anything at all (uniform): every round is unrolled code that
   // costs time even when no lane has an entry, unless the whole wave branches around it
   auto live = [&](int bt, int r) { return (uint32_t)((bt * CR + r) * tps) < longest; };
   auto drop_beyond = [&](int bt) {
+    if (direct) return;                    // (a register without an entry says so already)
 #pragma unroll
     for (int r = 0; r < CR; ++r)
       if (!(slot_of(bt, r) < cnt_seg)) creg[r] = make_uint2(0u, kFinNone);
@@ -914,7 +932,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
       const uint32_t g = min((uint32_t)tid, n_blk - 1);                        // its chunk starts at floor(ch * n_blk / S)
       const uint32_t ch = ((g + 1) * (uint32_t)S - 1) / n_blk;
       const uint32_t first = ch * n_blk / (uint32_t)S, next = (ch + 1) * n_blk / (uint32_t)S;
-      const unsigned long long* end = reinterpret_cast<const unsigned long long*>(a.cand + ((size_t)b * (size_t)S + ch + 1) * (size_t)a.cap_c);
+      const unsigned long long* end = reinterpret_cast<const unsigned long long*>(a.cand + ((size_t)b * (size_t)S + ch + 1) * (size_t)cap_c);
       const unsigned long long u = end[(int)(g - first) - (int)(next - first)];
       w = (uint32_t)tid < n_blk ? rescaled(u) : 0ull;
     }
@@ -1032,14 +1050,10 @@ __global__ __launch_bounds__(kFinThreads) __attribute__((amdgpu_waves_per_eu(4, 
   warm_kernel_arguments();
   __shared__ FinShared fs;
   const int b = blockIdx.x;
-  const int code = finish_row(a, b, fs);
+  const int code = finish_row<false>(a, b, fs);
   if (threadIdx.x == 0) {
     a.row_path[b] = code;
-    a.row_why[b] = code == kFinWholeRow ? 1 : code;
-    if (code != 1 && code != kFinWholeRow) {
-      const int q = atomicAdd(a.rescue_n, 1);
-      if (q >= 0 && q < a.B) a.rescue_rows[q] = b;
-    }
+    a.row_why[b] = code == kFinWholeRow ? 1 : code;                            // anything but 1: the rescue kernel's
   }
 }
 

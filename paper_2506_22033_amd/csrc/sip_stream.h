@@ -33,22 +33,35 @@ namespace sip {
 constexpr int kStreamThreads = 512;
 constexpr int kStreamWaves = kStreamThreads / kWave;
 static_assert(kStreamWaves == 8, "a chunk's segment is made of eight wave queues");
-constexpr int kStreamLoads = 2;             // 16-byte loads per thread per tile
-constexpr int kStreamBufs = 2;              // tiles held in registers: one being processed, the others in flight
 constexpr int kSampleBins = 8192;           // 13-bit keys: sign, exponent, 4 mantissa bits
 constexpr int kSampleSize = 8192;           // elements of a row the threshold is estimated from
+constexpr int kTailKeys = 3 * kStreamThreads;         // the three largest sample keys of every thread
 constexpr int kQueueCap = 480;              // entries of one wave's LDS candidate queue
 constexpr int kChunkCap = kStreamWaves * kQueueCap;   // entries of one chunk's segment in the workspace
 constexpr int kChunkBitsMax = 73728;        // most elements a chunk may have (history bitmap: 9 KB of LDS)
-constexpr int kBlkMax = kChunkBitsMax / kBlkElems;   // blocks of the longest chunk
-// Load numbers of a chunk of p whole pieces, each rounded up to tiles; they have 5 bits in a bf16 queue entry.
-constexpr int kLoadBits = 5;
-constexpr int load_numbers(int p, int tile) { return p * kStreamLoads * ((kChunkBitsMax / p + tile - 1) / tile); }
-constexpr int most_load_numbers(int p, int tile) {
-  return p == 0 ? 0 : load_numbers(p, tile) > most_load_numbers(p - 1, tile) ? load_numbers(p, tile) : most_load_numbers(p - 1, tile);
-}
-static_assert(most_load_numbers(SIP_MAX_SHARDS, kStreamThreads * kStreamLoads * 8) <= 1 << kLoadBits, "see `process`");
-constexpr int kStreamHistRegs = 8;          // history tokens a thread requests at once
+constexpr int kRowBitsMax = 262144;         // and a row that one workgroup streams (32 KB)
+// What differs between a workgroup that streams one chunk of a row for the finishing kernel (ROW =
+// false: four workgroups per compute unit, 40 KB of LDS and 64 registers each) and one that streams the
+// whole row and finishes it itself (sip_row.h: two, with 80 KB and 128 registers).
+template <int DT, bool ROW>
+struct StreamShape {
+  static constexpr int EPL = DT == SIP_F32 ? 4 : 8;                    // elements per 16-byte load
+  static constexpr int kLoads = ROW ? 4 : 2;                           // 16-byte loads per thread per tile, of which two are held
+  static constexpr int kTile = kStreamThreads * kLoads * EPL;
+  typedef typename std::conditional<DT == SIP_F32, uint2, uint32_t>::type entry_t;      // of a queue, see `process`
+  static constexpr int kQueue = ROW ? (DT == SIP_F32 ? 704 : 1408) : kQueueCap;         // entries of one wave's queue
+  static constexpr int kBits = ROW ? kRowBitsMax : kChunkBitsMax;      // most elements a workgroup streams
+  static constexpr int kBlocks = kBits / kBlkElems;
+  static constexpr int kHistRegs = ROW ? 8 : DT == SIP_F32 ? 3 : 4;                        // history tokens a thread requests with the sample
+  // Load numbers of p whole pieces, each rounded up to tiles: they have kLoadBits in a bf16 queue entry.
+  static constexpr int kLoadBits = ROW ? 7 : 5;
+  static constexpr int load_numbers(int p) { return p * kLoads * ((kBits / p + kTile - 1) / kTile); }
+  static constexpr int most_load_numbers(int p) {
+    return p == 0 ? 0 : load_numbers(p) > most_load_numbers(p - 1) ? load_numbers(p) : most_load_numbers(p - 1);
+  }
+};
+static_assert(StreamShape<SIP_BF16, false>::most_load_numbers(SIP_MAX_SHARDS) <= 1 << StreamShape<SIP_BF16, false>::kLoadBits, "see `process`");
+static_assert(StreamShape<SIP_BF16, true>::most_load_numbers(SIP_MAX_SHARDS) <= 1 << StreamShape<SIP_BF16, true>::kLoadBits, "see `process`");
 constexpr float kBulkScale = 1073741824.0f; // 2^30
 
 // Per-row decisions shared by the streaming and the finishing kernel.
@@ -191,57 +204,72 @@ __device__ __forceinline__ unsigned long long bulk_units(float acc) {
 }
 
 
-template <int DT, bool SH>
-__global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void stream_kernel(Args a) {
-  constexpr int EPL = (DT == SIP_F32) ? 4 : 8;      // elements per 16-byte load
+// LDS: first the sample histogram (two 16-bit counters per word, 16 KB) and the threads' largest
+// sample keys (6 KB), then, in their place, the per-wave candidate queues (a chunk's: fp32 30 KB, bf16 15 KB; a row's: 44 KB); then the history
+// bitmap (9 or 32 KB).
+template <int DT, bool ROW>
+struct __align__(16) StreamShared {
+  typedef StreamShape<DT, ROW> Sh;
+  static constexpr int kQueueBytes = kStreamWaves * Sh::kQueue * (int)sizeof(typename Sh::entry_t);
+  static constexpr int kFrontBytes = kSampleBins * 2 + kTailKeys * 4 > kQueueBytes ? kSampleBins * 2 + kTailKeys * 4 : kQueueBytes;
+  unsigned char front[kFrontBytes];
+  uint32_t bmw[Sh::kBits / 32];
+  unsigned long long blk_mass[Sh::kBlocks];
+  unsigned long long red64[kStreamWaves];
+  uint32_t red32[kStreamWaves];
+  uint32_t sub_hist[32];                   // the threshold bin, split by the next 5 key bits
+  BulkRef ref;
+  uint32_t seg_cnt;                        // entries of the segment so far
+  uint32_t key_thr;                        // the threshold's key: 13 bits, later 18
+};
+
+// What a workgroup that finishes its row itself takes from here to there (ROW; all of it uniform).
+constexpr int kRowRegs = 10;               // list entries a thread holds in registers
+struct RowHand {
+  RowInfo ri;
+  ChunkOut co;
+  uint32_t longest;                        // entries of the longest queue
+  bool direct;                             // the queues went to registers, lane l's entry r being entry 64 * r + l of its wave's
+  uint2 list[kRowRegs];                    // (per thread)
+};
+
+// Streams chunk wg % S of row wg / S (ROW: row wg).  False: the row cannot be finished from a list.
+template <int DT, bool SH, bool ROW>
+__device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamShared<DT, ROW>& sm, RowHand* hand) {
+  typedef StreamShape<DT, ROW> Sh;
+  typedef typename Sh::entry_t entry_t;
+  constexpr int EPL = Sh::EPL;
   constexpr int ESZ = (DT == SIP_F32) ? 4 : 2;
+  constexpr int NL = Sh::kLoads;
   constexpr int SUB = kStreamThreads * EPL;         // elements per workgroup-wide load
-  constexpr int TILE = SUB * kStreamLoads;
+  constexpr int TILE = Sh::kTile;
   constexpr int SLOADS = kSampleSize / SUB;         // sample loads per thread (4 fp32, 2 bf16)
   constexpr int NSB = SLOADS * kStreamWaves;        // 1 KB sample blocks spread over the row
-  // LDS: first the sample histogram (two 16-bit counters per word, 16 KB), then, in its place, the
-  // per-wave candidate queues (fp32 30 KB, bf16 15 KB); 9 KB for the history bitmap of the chunk.
-  // 39.8 KB in all (bf16 25.8): four workgroups per compute unit.
-  typedef typename std::conditional<DT == SIP_F32, uint2, uint32_t>::type entry_t;      // see `process`
-  constexpr int kQueueBytes = kStreamWaves * kQueueCap * (int)sizeof(entry_t);
-  constexpr int kFrontBytes = kSampleBins * 2 > kQueueBytes ? kSampleBins * 2 : kQueueBytes;
-  __shared__ __align__(16) unsigned char smem[kFrontBytes + kChunkBitsMax / 8];
-  uint32_t* const bmw = reinterpret_cast<uint32_t*>(smem + kFrontBytes);
-  uint32_t* hist = reinterpret_cast<uint32_t*>(smem);
-  __shared__ uint32_t red32[kStreamWaves];
-  __shared__ unsigned long long red64[kStreamWaves];
-  __shared__ uint32_t seg_cnt;                      // entries of the chunk's segment so far
-  __shared__ BulkRef ref_lds;
-  __shared__ uint32_t key_thr, need_thr;            // 13-bit key of the threshold bin; entries still wanted from inside it
-  __shared__ unsigned long long blk_mass[kBlkMax];
-  __shared__ uint32_t sub_hist[32];                 // that bin, split by the next 5 key bits
+  uint32_t* const bmw = sm.bmw;
+  uint32_t* const hist = reinterpret_cast<uint32_t*>(sm.front);
 
   // (the wave's number, and further down r0, in a scalar register: as vector registers they were
   // spilled, and a store to scratch ahead of the loads makes every wait for one of them a wait for
   // all -- 3 us of the 33 at fp32 V = 152064, 256 rows)
   const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
-  // Workgroups are handed to the 8 XCDs round-robin by their id.  The chunks of one row read
-  // the same sample, so they are renumbered to land on the same XCD (and its L2): id i works
-  // on logical chunk (i % 8) * (n / 8) + i / 8 when n, the grid size, is a multiple of 8.
-  int wg = blockIdx.x;
-  if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-  const int b = wg / a.S, ch = wg - b * a.S;
+  const int S = ROW ? 1 : a.S;
+  const int b = ROW ? wg : wg / S, ch = ROW ? 0 : wg - b * S;
   const int V = a.V;
   // SH (vocabulary-sharded logits): the row's chunks are dealt out to the shards, S / t_shards
   // each, and a chunk lies inside its shard; c0, c1 and every element index below are then
   // relative to the shard, `ibase` being the shard's first vocabulary id.
   // With more chunks than shards a chunk is a part of one shard (np = 1 piece); with fewer, it is
   // np whole shards in a row, streamed one after the other.
-  const bool split = !SH || a.S >= a.t_shards;       // uniform
-  const int S_sh = !SH ? a.S : (split ? a.S / a.t_shards : 1);
-  const int np = (SH && !split) ? a.t_shards / a.S : 1;
+  const bool split = !SH || S >= a.t_shards;         // uniform
+  const int S_sh = !SH ? S : (split ? S / a.t_shards : 1);
+  const int np = (SH && !split) ? a.t_shards / S : 1;
   const int sh = !SH ? 0 : (split ? ch / S_sh : ch * np);
   const int lc = !SH ? ch : (split ? ch - sh * S_sh : 0);
   const int Vl = SH ? a.V_shard : V;
   const uint32_t ibase = SH ? (uint32_t)(sh * Vl) : 0u;
   const int c0 = chunk_begin(lc, Vl, S_sh, kChunkUnit);
   const int c1 = chunk_begin(lc + 1, Vl, S_sh, kChunkUnit);
-  if (c0 >= c1) return;                              // host guarantees every chunk is non-empty
+  if (c0 >= c1) return false;                        // host guarantees every chunk is non-empty
   const char* row = SH ? shard_base(a, sh) + (size_t)b * (size_t)a.shard_stride * ESZ      // (moves on with the pieces)
                        : reinterpret_cast<const char*>(a.logits) + (size_t)b * (size_t)a.row_stride * ESZ;
 
@@ -249,11 +277,11 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   // once): lanes past the end of the chunk re-read its last 16 bytes and `process` discards
   // what they hold by index.
   const int e_last = ((c1 - 1) / EPL) * EPL;
-  auto load_tile = [&](int t0, uint4 (&buf)[kStreamLoads]) {
+  auto load_tile = [&](int t0, uint4 (&buf)[NL]) {
 #pragma unroll
-    for (int j = 0; j < kStreamLoads; ++j) {
-      const int e0 = min(t0 + j * SUB + tid * EPL, e_last);
-      buf[j] = *reinterpret_cast<const uint4*>(row + (size_t)e0 * ESZ);
+    for (int j = 0; j < NL; ++j) {
+      const uint32_t e0 = (uint32_t)min(t0 + j * SUB + tid * EPL, e_last);     // (a scalar base and 32 bits beside it)
+      buf[j] = *reinterpret_cast<const uint4*>(row + e0 * (uint32_t)ESZ);
     }
   };
   auto unpack = [&](const uint4& q, float (&z)[EPL]) {
@@ -293,10 +321,11 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   const long long r_h1 = *reinterpret_cast<const long long*>(rec(csr_on ? a.indptr : nullptr, 8 * (size_t)b + 8));
   const long long r_p0 = *reinterpret_cast<const long long*>(rec(prompt_csr ? a.p_indptr : nullptr, 8 * (size_t)b));
   const long long r_p1 = *reinterpret_cast<const long long*>(rec(prompt_csr ? a.p_indptr : nullptr, 8 * (size_t)b + 8));
+  const int r_slot = *reinterpret_cast<const int*>(rec(a.slot, 4 * (size_t)b));
   // (all of them are named here, once: otherwise the compiler moves each read to the branch that
   // first looks at its value, and the round trips follow one another)
   asm volatile("" ::"s"(r_tau), "s"(r_k), "s"(r_p), "s"(r_minp), "s"(r_theta), "s"(r_phi), "s"(r_psi), "s"(r_id),
-               "s"(r_h0), "s"(r_h1), "s"(r_p0), "s"(r_p1));
+               "s"(r_h0), "s"(r_h1), "s"(r_p0), "s"(r_p1), "s"(r_slot));
   // ---- the records: defaults for what the call does not have
   RowParams rp;
   rp.tau = a.p.temperature ? r_tau : 1.0f;
@@ -312,19 +341,71 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   // ---- What one thread of the grid does for the whole call.  Device-resident history: the call
   // takes its number from the state's call counter (one atomic add, so that calls in flight at once
   // on one state each get their own) and leaves it in the workspace, where the kernels behind this
-  // one read it (step_of()).  The finishing kernel counts the rows it passes on from zero.
+  // one read it (step_of()).  (A workgroup that goes on to finish its row finds it there.)
   // (Here, on the one path that every workgroup takes, and not before the records above have been
   // read: with no store ahead of them in the kernel the compiler reads them through the scalar
   // cache.)
-  if (a.call_tick && blockIdx.x == 0 && tid == 0) *a.call_tick = atomicAdd(a.st_tick, 1ull);
-  if (blockIdx.x == 0 && tid == 0) *a.rescue_n = 0;
+  if (!ROW && a.call_tick && blockIdx.x == 0 && tid == 0) *a.call_tick = atomicAdd(a.st_tick, 1ull);
   if (target == 0) {
-    if (ch == 0 && tid == 0) a.rowinfo[b].target = 0;                        // the finishing kernel looks at nothing else
-    return;
+    if (!ROW && ch == 0 && tid == 0) a.rowinfo[b].target = 0;                // the finishing kernel looks at nothing else
+    return false;
   }
-  // ---- the first tiles of the chunk are requested before anything else is worked out, so that
-  // they travel meanwhile
-  uint4 buf[kStreamBufs][kStreamLoads];
+  // ---- threshold: the same 8192-element sample (1 KB blocks spread evenly over the row) is
+  // read by every chunk of the row, so all chunks agree on Tc = the j-th largest sample value
+  // rounded down to an 18-bit key (found in two levels: 13 bits, then 5 more), j / 8192 = target / V
+  // (for long lists: half of the blocks, j / 4096 = target / V; see whole_sample())
+  // All blocks are requested, whether or not the row's rank calls for the whole sample: a branch
+  // around a load makes the compiler wait for that load where the branches meet, one exposed
+  // memory latency per block.
+  auto load_sample = [&](int j) -> uint4 {
+    const int sb = wave * SLOADS + j;                  // even j: every other block of the row
+    if (!SH) {
+      const uint32_t base = (uint32_t)sb * (uint32_t)V / (uint32_t)NSB / (uint32_t)(kWave * EPL) * (uint32_t)(kWave * EPL);
+      return reinterpret_cast<const uint4*>(row + (size_t)base * ESZ)[lane];     // base + 64 * EPL <= V since V >= 16384
+    }
+    // the same NSB blocks for every chunk of the row, smp_bps to a shard (the last shard may get
+    // fewer), evenly spread inside it; V_shard >= 8192, so a block fits
+    // (wave-uniform, and said so: with a per-lane index the table of piece pointers would be read
+    // through a vector load from the kernel-argument segment, and a wait for that one)
+    const int ssh = __builtin_amdgcn_readfirstlane((sb * a.smp_inv) >> 16);   // sb / smp_bps
+    const int e0 = (sb - ssh * a.smp_bps) * a.smp_step + lane * EPL;
+    const char* srow = shard_base(a, ssh) + (size_t)b * (size_t)a.shard_stride * ESZ;
+    return *reinterpret_cast<const uint4*>(srow + (size_t)e0 * ESZ);
+  };
+  uint4 smp[SLOADS];
+#pragma unroll
+  for (int j = 0; j < SLOADS; ++j) smp[j] = load_sample(j);
+  // ---- history bitmap of the chunk: bit (v - g0) for every history token v in [g0, g1), the
+  // vocabulary ids this workgroup streams.  Requested here, entered while wave 0 looks for the
+  // threshold, by the seven others.  (A device-resident state's extent takes a read of its own.)
+  HistRange hr{0, 0, 0};
+  int slot = -1, ndist = -1;
+  if (a.slot) {                                      // uniform
+    hr.side = (long long)b * a.L_max;
+    if (r_slot >= 0 && r_slot < a.slots) {
+      const int n = a.st_len[r_slot];
+      slot = r_slot; ndist = a.st_ndist[r_slot];
+      hr.lo = (long long)r_slot * a.L_max;
+      hr.hi = hr.lo + (n < 0 ? 0 : (n > a.L_max ? a.L_max : n));
+    }
+  } else {
+    hr = hist_range_csr(a, r_h0, r_h1);
+  }
+  const PenaltyPlan pen = penalty_plan_of(a, hr, r_p0, r_p1, rp.theta, rp.phi, rp.psi);
+  const bool has_pen = pen.any;                                                                       // uniform
+  const int g0 = (int)ibase + c0;
+  const int g1 = (!SH || split) ? (int)ibase + c1 : (int)ibase + np * Vl;
+  constexpr int MT = kStreamThreads - kWave;         // threads that enter tokens
+  // (Without a branch, like the sample: what is not there is read from memory that is.)
+  const long long n_hist = has_pen ? hr.hi - hr.lo : 0;
+  const int* const first_tok = n_hist > 0 ? a.tokens + hr.lo : reinterpret_cast<const int*>(dummy);
+  const uint32_t last_tok = (uint32_t)min(max(n_hist, 1ll), 1ll << 20) - 1u;
+  int htok[Sh::kHistRegs];
+#pragma unroll
+  for (int j = 0; j < Sh::kHistRegs; ++j) htok[j] = first_tok[min((uint32_t)(tid - kWave + j * MT), last_tok)];
+  // ---- the first tiles of the chunk, which travel while the threshold is worked out.  (Behind sample
+  // and tokens: loads come back in the order of their requests.)
+  uint4 buf[2][NL];
   int tnext = c0;                                    // first element of the next tile to request
   int n_pj = 0;                                      // SH: the piece it is in
   auto roll = [&]() {                                // SH: on to the next piece (a piece can be a single tile)
@@ -334,174 +415,110 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
     }
   };
 #pragma unroll
-  for (int k = 0; k < kStreamBufs; ++k) {
+  for (int k = 0; k < 2; ++k) {
     load_tile(tnext, buf[k]);                        // (past the chunk's end: its last 16 bytes again, never looked at)
     tnext += TILE;
     if (SH) roll();
   }
 
-  // ---- threshold: the same 8192-element sample (1 KB blocks spread evenly over the row) is
-  // read by every chunk of the row, so all chunks agree on Tc = the j-th largest sample value
-  // rounded down to an 18-bit key (found in two levels: 13 bits, then 5 more), j / 8192 = target / V
-  // (for long lists: half of the blocks, j / 4096 = target / V; see whole_sample())
-  // All blocks are requested, whether or not the row's rank calls for the whole sample: a branch
-  // around a load makes the compiler wait for that load where the branches meet, one exposed
-  // memory latency per block.
-  uint4 smp[SLOADS];
-#pragma unroll
-  for (int j = 0; j < SLOADS; ++j) {
-    if (!SH) {
-      const int sb = wave * SLOADS + j;                // even j: every other block of the row
-      const uint32_t base = (uint32_t)sb * (uint32_t)V / (uint32_t)NSB / (uint32_t)(kWave * EPL) * (uint32_t)(kWave * EPL);
-      smp[j] = reinterpret_cast<const uint4*>(row + (size_t)base * ESZ)[lane];     // base + 64 * EPL <= V since V >= 16384
-    } else {
-      const int sb = wave * SLOADS + j;
-      // the same NSB blocks for every chunk of the row, smp_bps to a shard (the last shard may get
-      // fewer), evenly spread inside it; V_shard >= 8192, so a block fits
-      // (wave-uniform, and said so: with a per-lane index the table of piece pointers would be read
-      // through a vector load from the kernel-argument segment, and waiting for that one also waits
-      // for the tiles requested above)
-      const int ssh = __builtin_amdgcn_readfirstlane((sb * a.smp_inv) >> 16);   // sb / smp_bps
-      const int e0 = (sb - ssh * a.smp_bps) * a.smp_step + lane * EPL;
-      const char* srow = shard_base(a, ssh) + (size_t)b * (size_t)a.shard_stride * ESZ;
-      smp[j] = *reinterpret_cast<const uint4*>(srow + (size_t)e0 * ESZ);
-    }
-  }
-  const bool whole = whole_sample(target, V);        // workgroup-uniform, like everything about the threshold
-  // ---- history bitmap of the chunk: bit (v - g0) for every history token v in [g0, g1), the
-  // vocabulary ids this workgroup streams.  Requested here, entered after the first barrier.
-  // (A device-resident state's extent takes two dependent reads of its own.)
-  const HistRange hr = a.slot ? hist_range(a, b) : hist_range_csr(a, r_h0, r_h1);
-  const PenaltyPlan pen = penalty_plan_of(a, hr, r_p0, r_p1, rp.theta, rp.phi, rp.psi);
-  const bool has_pen = pen.any;                                                                       // uniform
-  const bool hist_pen = has_pen && hr.hi > hr.lo;
-  const int g0 = (int)ibase + c0;
-  const int g1 = (!SH || split) ? (int)ibase + c1 : (int)ibase + np * Vl;
-  if (ch == 0 && tid == 0) {               // the row's record for the finishing kernel
+  if (ROW || (ch == 0 && tid == 0)) {      // the row's record for the finishing kernel
     RowInfo ri;
     ri.tau = rp.tau; ri.top_p = rp.top_p; ri.min_p = rp.min_p; ri.theta = rp.theta; ri.phi = rp.phi; ri.psi = rp.psi;
     ri.top_k = rp.top_k; ri.target = target | (pen.prompt_on ? kPromptFlag : 0);
     ri.row_id = rp.row_id; ri.lo = hr.lo; ri.hi = hr.hi;
-    ri.slot = -1; ri.ndist = -1;
-    if (a.slot) {
-      const int sl = a.slot[b];
-      if (sl >= 0 && sl < a.slots) { ri.slot = sl; ri.ndist = a.st_ndist[sl]; }
-    }
-    a.rowinfo[b] = ri;
+    ri.slot = slot; ri.ndist = ndist;
+    if (ROW) hand->ri = ri; else a.rowinfo[b] = ri;
   }
-  int htok[kStreamHistRegs];
-#pragma unroll
-  for (int j = 0; j < kStreamHistRegs; ++j) {
-    const long long i = hr.lo + tid + (long long)j * kStreamThreads;
-    htok[j] = (hist_pen && i < hr.hi) ? a.tokens[i] : -1;
+  {
+    uint4* z4 = reinterpret_cast<uint4*>(hist);
+    for (int i = tid; i < kSampleBins * 2 / 16; i += kStreamThreads) z4[i] = make_uint4(0, 0, 0, 0);
+    z4 = reinterpret_cast<uint4*>(bmw);
+    const int n_bits = ROW ? min((V + 127) / 128, Sh::kBits / 128) : Sh::kBits / 128;
+    for (int i = tid; i < n_bits; i += kStreamThreads) z4[i] = make_uint4(0, 0, 0, 0);
   }
-  for (int i = tid; i < kSampleBins / 2; i += kStreamThreads) hist[i] = 0;
-  for (int i = tid; i < kChunkBitsMax / 32; i += kStreamThreads) bmw[i] = 0;
-  if (tid < 32) sub_hist[tid] = 0;
+  if (tid < 32) sm.sub_hist[tid] = 0;
+  if (tid < Sh::kBlocks) sm.blk_mass[tid] = 0ull;
+  if (tid == 0) sm.seg_cnt = 0;
   __syncthreads();
-  if (has_pen) {
-    auto mark = [&](int t) {
-      const uint32_t r = (uint32_t)(t - g0) ^ (uint32_t)(EPL - 1);             // (last element of a load first, see `process`)
-      if (t >= g0 && t < g1) atomicOr(&bmw[r >> 5], 1u << (r & 31));
-    };
-#pragma unroll
-    for (int j = 0; j < kStreamHistRegs; ++j) mark(htok[j]);
-    for (long long i0 = hr.lo + (long long)kStreamHistRegs * kStreamThreads; i0 < hr.hi;
-         i0 += (long long)kStreamHistRegs * kStreamThreads) {
-#pragma unroll
-      for (int j = 0; j < kStreamHistRegs; ++j) {
-        const long long i = i0 + tid + (long long)j * kStreamThreads;
-        htok[j] = i < hr.hi ? a.tokens[i] : -1;
-      }
-#pragma unroll
-      for (int j = 0; j < kStreamHistRegs; ++j) mark(htok[j]);
-    }
-    for (long long i = pen.p_lo + tid; i < pen.p_hi; i += kStreamThreads) mark(a.p_tokens[i]);   // separate prompt
-  }
   // Only the upper tail of the sample matters.  When j is small, a thread enters just the
   // three largest of its values: far fewer LDS atomics, and hardly any on the same word.
   // (Should one thread hold more than three of the j largest, the threshold comes out a
   // little low, which only lengthens the candidate list.)
+  const bool whole = whole_sample(target, V);        // workgroup-uniform, like everything about the threshold
   const int n_smp = whole ? kSampleSize : kSampleSize / 2;
   uint32_t want = ((uint32_t)target * (uint32_t)n_smp + (uint32_t)V - 1u) / (uint32_t)V;     // < 2^32: target <= 2^14
   if (want < 2u) want = 2u;
   if (want > (uint32_t)n_smp) want = (uint32_t)n_smp;
   const uint32_t j = want;
   const bool tail_only = whole || j <= (uint32_t)(kTailRank / 2);
-  uint32_t t0 = 0, t1 = 0, t2 = 0;                   // full keys of this thread's three largest sample values
-  {
-    if (tail_only) {
-      // the three largest as floats, one maximum and two medians per value
-      float f0 = -INFINITY, f1 = -INFINITY, f2 = -INFINITY;
+  uint32_t* const tail_keys = hist + kSampleBins / 2;          // full keys of the threads' three largest sample values
+  if (tail_only) {
+    // the three largest as floats, one maximum and two medians per value
+    float f0 = -INFINITY, f1 = -INFINITY, f2 = -INFINITY;
 #pragma unroll
-      for (int l = 0; l < SLOADS; ++l) {
-        if (!whole && (l & 1)) continue;
-        float z[EPL];
-        unpack(smp[l], z);
+    for (int l = 0; l < SLOADS; ++l) {
+      if (!whole && (l & 1)) continue;
+      float z[EPL];
+      unpack(smp[l], z);
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) {
-          const float x = z[i];
-          f2 = __builtin_amdgcn_fmed3f(f1, f2, x);
-          f1 = __builtin_amdgcn_fmed3f(f0, f1, x);
-          f0 = fmaxf(f0, x);
-        }
-      }
-      t0 = key_of(f0); t1 = key_of(f1); t2 = key_of(f2);
-    } else {
-#pragma unroll
-      for (int l = 0; l < SLOADS; l += 2) {
-        float z[EPL];
-        unpack(smp[l], z);
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) {
-          const uint32_t k13 = key_of(z[i]) >> 19;
-          atomicAdd(&hist[k13 >> 1], (k13 & 1u) ? 0x10000u : 1u);
-        }
+      for (int i = 0; i < EPL; ++i) {
+        const float x = z[i];
+        f2 = __builtin_amdgcn_fmed3f(f1, f2, x);
+        f1 = __builtin_amdgcn_fmed3f(f0, f1, x);
+        f0 = fmaxf(f0, x);
       }
     }
-    if (tail_only) {
-      atomicAdd(&hist[t0 >> 20], ((t0 >> 19) & 1u) ? 0x10000u : 1u);
-      atomicAdd(&hist[t1 >> 20], ((t1 >> 19) & 1u) ? 0x10000u : 1u);
-      atomicAdd(&hist[t2 >> 20], ((t2 >> 19) & 1u) ? 0x10000u : 1u);
+    const uint32_t t0 = key_of(f0), t1 = key_of(f1), t2 = key_of(f2);
+    atomicAdd(&hist[t0 >> 20], ((t0 >> 19) & 1u) ? 0x10000u : 1u);
+    atomicAdd(&hist[t1 >> 20], ((t1 >> 19) & 1u) ? 0x10000u : 1u);
+    atomicAdd(&hist[t2 >> 20], ((t2 >> 19) & 1u) ? 0x10000u : 1u);
+    tail_keys[tid] = t0; tail_keys[kStreamThreads + tid] = t1; tail_keys[2 * kStreamThreads + tid] = t2;
+  } else {
+#pragma unroll
+    for (int l = 0; l < SLOADS; l += 2) {
+      float z[EPL];
+      unpack(smp[l], z);
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) {
+        const uint32_t k13 = key_of(z[i]) >> 19;
+        atomicAdd(&hist[k13 >> 1], (k13 & 1u) ? 0x10000u : 1u);
+      }
     }
   }
   __syncthreads();
-  {
-    constexpr int WPT = kSampleBins / 2 / kStreamThreads;      // words per thread (16)
-    const int wtop = kSampleBins / 2 - tid * WPT;              // thread 0 owns the highest bins
-    uint32_t local = 0;
-#pragma unroll
-    for (int i = 1; i <= WPT; ++i) { const uint32_t w = hist[wtop - i]; local += (w & 0xFFFFu) + (w >> 16); }
-    const uint32_t incl_w = dpp_scan_add_u32(local);
-    if (lane == kWave - 1) red32[wave] = incl_w;
-    __syncthreads();
-    uint32_t off = 0;
-    for (int w = 0; w < wave; ++w) off += red32[w];
-    const uint32_t incl = off + incl_w, excl = incl - local;
-    if (excl < j && j <= incl) {
-      uint32_t run = excl, found = 0, need = 1;      // run: sample values above the bin looked at
-      for (int i = 1; i <= WPT; ++i) {
-        const uint32_t w = hist[wtop - i];
-        if (run + (w >> 16) >= j) { found = 2u * (uint32_t)(wtop - i) + 1u; need = j - run; break; }
-        run += (w >> 16);
-        if (run + (w & 0xFFFFu) >= j) { found = 2u * (uint32_t)(wtop - i); need = j - run; break; }
-        run += (w & 0xFFFFu);
-      }
-      key_thr = found; need_thr = need;
-    }
-    __syncthreads();                                 // also: the histogram is dead from here on
+  // ---- wave 0 alone finds the bin of the j-th largest (between barriers of all eight the same took
+  // twice as long); the threshold bin is as wide as 1/16 of its values (and bf16 logits or a
+  // spike-and-bulk row put hundreds of sample values into it), so it is split by the next 5 key bits
+  // and only as many of its sub-bins are taken as the target asks for.
+  uint32_t K = 0, need = 1;                          // wave 0: the bin, and what is still wanted from inside it
+  if (wave == 0) {
+    constexpr int WPL = kSampleBins / 2 / kWave;     // words per lane (64), lane 0 owning the highest bins
+    const uint4* mine = reinterpret_cast<const uint4*>(hist + kSampleBins / 2 - (lane + 1) * WPL);
+    uint32_t s = 0;                                  // (both counters of a word at once: 8192 values at most)
+#pragma unroll 4
+    for (int i = 0; i < WPL / 4; ++i) { const uint4 w = mine[(i + lane) % (WPL / 4)]; s += w.x + w.y + w.z + w.w; }
+    const uint32_t local = (s & 0xFFFFu) + (s >> 16), incl = dpp_scan_add_u32(local);
+    const unsigned long long at = __ballot(incl >= j);
+    const int src = at ? __ffsll((long long)at) - 1 : kWave - 1;
+    uint32_t run = (uint32_t)__builtin_amdgcn_readlane((int)(incl - local), src);          // sample values above its words
+    const int word = kSampleBins / 2 - 1 - src * WPL - lane;
+    const uint32_t w = hist[word], incl2 = run + dpp_scan_add_u32((w & 0xFFFFu) + (w >> 16));
+    const unsigned long long at2 = __ballot(incl2 >= j);
+    const int src2 = at2 ? __ffsll((long long)at2) - 1 : kWave - 1;
+    const uint32_t cw = (uint32_t)__builtin_amdgcn_readlane((int)w, src2);
+    run = (uint32_t)__builtin_amdgcn_readlane((int)incl2, src2) - (cw & 0xFFFFu) - (cw >> 16);
+    const bool upper = run + (cw >> 16) >= j;
+    K = 2u * (uint32_t)(kSampleBins / 2 - 1 - src * WPL - src2) + (upper ? 1u : 0u);
+    need = j - run - (upper ? 0u : cw >> 16);
   }
-  // ---- second level: the threshold bin is as wide as 1/16 of its values (and bf16 logits
-  // or a spike-and-bulk row put hundreds of sample values into it), so it is split by the
-  // next 5 key bits and only as many of its sub-bins are taken as the target asks for
   {
-    const uint32_t K = key_thr;
     auto enter = [&](uint32_t kf) {
-      if ((kf >> 19) == K) atomicAdd(&sub_hist[(kf >> 14) & 31u], 1u);
+      if ((kf >> 19) == K) atomicAdd(&sm.sub_hist[(kf >> 14) & 31u], 1u);
     };
-    if (tail_only) {
-      enter(t0); enter(t1); enter(t2);
-    } else {
+    if (!tail_only) {
+      if (tid == 0) sm.key_thr = K;
+      __syncthreads();
+      K = sm.key_thr;
 #pragma unroll
       for (int l = 0; l < SLOADS; l += 2) {
         float z[EPL];
@@ -509,61 +526,82 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
         for (int i = 0; i < EPL; ++i) enter(key_of(z[i]));
       }
+      __syncthreads();
+    } else if (wave == 0) {
+      const uint4* k4 = reinterpret_cast<const uint4*>(tail_keys);
+#pragma unroll 2
+      for (int i = 0; i < kTailKeys / 4 / kWave; ++i) { const uint4 k = k4[i * kWave + lane]; enter(k.x); enter(k.y); enter(k.z); enter(k.w); }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     }
-    __syncthreads();
-    if (tid < kBlkMax) blk_mass[tid] = 0ull;
-    if (tid == 0) seg_cnt = 0;
     if (wave == 0) {
-      // lane l: sub-bin 31 - l, descending (the lane's number worked out anew: one register less
-      // from the start to here)
-      const int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-      const uint32_t c = l < 32 ? sub_hist[31 - min(l, 31)] : 0u;
+      // lane l: sub-bin 31 - l, descending
+      const uint32_t c = lane < 32 ? sm.sub_hist[31 - min(lane, 31)] : 0u;
       const uint32_t incl = dpp_scan_add_u32(c);
-      const unsigned long long reach = __ballot(lane < 32 && incl >= need_thr);
+      const unsigned long long reach = __ballot(lane < 32 && incl >= need);
       const uint32_t first = reach ? (uint32_t)__ffsll((long long)reach) - 1u : 31u;
-      // 18-bit key from here on.  (One wave does the long arithmetic behind it, with the other seven waiting.)
-      const uint32_t k18 = (K << 5) | (31u - first);
+      const uint32_t k18 = (K << 5) | (31u - first);                           // 18-bit key from here on
       const BulkRef r = make_bulk_ref(value_of(k18 << 14), rp);
-      if (lane == 0) { key_thr = k18; ref_lds = r; }
+      if (lane == 0) { sm.key_thr = k18; sm.ref = r; }
     }
-    __syncthreads();
   }
+  if (has_pen && wave > 0) {
+    auto mark = [&](int t) {
+      const uint32_t r = (uint32_t)(t - g0) ^ (uint32_t)(EPL - 1);             // (last element of a load first, see `process`)
+      if (t >= g0 && t < g1) atomicOr(&bmw[r >> 5], 1u << (r & 31));
+    };
+#pragma unroll
+    for (int j = 0; j < Sh::kHistRegs; ++j)
+      if (tid - kWave + j * MT < n_hist) mark(htok[j]);
+    auto mark_all = [&](const int* tok, long long lo, long long hi) {
+      constexpr int N = 8;                           // requests at once
+      for (long long i0 = lo; i0 < hi; i0 += (long long)N * MT) {
+        int t[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) t[j] = tok[min(i0 + (tid - kWave) + j * MT, hi - 1)];      // (the last one again marks nothing new)
+#pragma unroll
+        for (int j = 0; j < N; ++j) mark(t[j]);
+      }
+    };
+    mark_all(a.tokens, hr.lo + (long long)Sh::kHistRegs * MT, hr.hi);
+    mark_all(a.p_tokens, pen.p_lo, pen.p_hi);                                  // separate prompt
+  }
+  __syncthreads();                                   // also: the histogram is dead from here on
   // A row that is masked almost everywhere (-inf for all but a few hundred tokens, as a grammar
   // constraint leaves it) has fewer finite values in its sample than the list asks for, and the
   // threshold has landed among the -inf (keys up to 511 in 18 bits: -inf and the negative NaNs).
   // Then the lowest finite sample value is the threshold: the list takes every finite element
   // from there up, and what lies below it is bulk as usual.  (No finite sample value at all: the
   // lowest finite float, which makes the finishing kernel pass the row on.)
-  if (key_thr <= 511u) {                                                       // workgroup-uniform
+  if (sm.key_thr <= 511u) {                                                       // workgroup-uniform
     float lo = INFINITY;
-#pragma unroll
-    for (int l = 0; l < SLOADS; ++l) {
+#pragma nounroll
+    for (int l = 0; l < SLOADS; ++l) {                 // (read again: held until here, the sample costs registers)
       float z[EPL];
-      unpack(smp[l], z);
+      unpack(load_sample(l), z);
 #pragma unroll
       for (int i = 0; i < EPL; ++i)
         if (z[i] > -INFINITY && z[i] < lo) lo = z[i];
     }
     uint32_t klo = last_lane_u32(dpp_scan_min_u32(lo == INFINITY ? 0xFFFFFFFFu : key_of(lo)));
-    __syncthreads();                                                           // red32 is free again
-    if (lane == 0) red32[wave] = klo;
+    if (lane == 0) sm.red32[wave] = klo;
     __syncthreads();
-    klo = red32[0];
+    klo = sm.red32[0];
 #pragma unroll
-    for (int w = 1; w < kStreamWaves; ++w) klo = min(klo, red32[w]);
+    for (int w = 1; w < kStreamWaves; ++w) klo = min(klo, sm.red32[w]);
     const uint32_t k18 = klo == 0xFFFFFFFFu ? 512u : max(klo >> 14, 512u);
     __syncthreads();
-    if (tid == 0) ref_lds = make_bulk_ref(value_of(k18 << 14), rp);
+    if (tid == 0) sm.ref = make_bulk_ref(value_of(k18 << 14), rp);
     __syncthreads();
   }
-  BulkRef ref = ref_lds;
+  BulkRef ref = sm.ref;
   auto uniform = [](float x) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x))); };
   ref.Tc = uniform(ref.Tc); ref.c = uniform(ref.c); ref.off = uniform(ref.off);
 
   // ---- stream
-  entry_t* queue = reinterpret_cast<entry_t*>(smem) + wave * kQueueCap;        // this wave's LDS queue
+  entry_t* const queue = reinterpret_cast<entry_t*>(sm.front) + wave * Sh::kQueue;   // this wave's LDS queue
   const unsigned char* bm8 = reinterpret_cast<const unsigned char*>(bmw);
-  uint32_t qn = 0;                          // wave-uniform: list entries seen (entries beyond the queue are dropped)
+  uint32_t qn = 0;                          // wave-uniform: list entries in the queue
   float acc = 0.0f;                         // this thread's sum of bulk_term(), fixed order of additions
 
   uint32_t ib = ibase;                      // SH: first vocabulary id of the piece being processed
@@ -578,7 +616,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   // of each lane at a time, which takes one or two rounds of a load at the usual list lengths.
   // Bit p of mask and `hb` is element EPL - 1 - p.  `it`: the wave's load
   // number in its chunk.  A queue entry is the element's value and its place: fp32 (bits, vocabulary
-  // id); bf16 one word, the value's 16 bits above load number, lane and element (5 + 6 + 3 bits).
+  // id); bf16 one word, the value's 16 bits above load number, lane and element (5 or 7 + 6 + 3 bits).
   // Whether it is a history token is looked up again when the queue goes out.
   auto process = [&](const uint4& q, int e0, int it, bool guard, uint32_t hb) {
     float z[EPL];
@@ -600,7 +638,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
     const uint32_t place = DT == SIP_F32 ? (uint32_t)(e0 + EPL - 1) + (SH ? ib : 0u) : ((uint32_t)it << 9) | ((uint32_t)lane << 3) | 7u;
     // (a queue that is full is looked at once per load: what it gets beyond its room lies in the next
     // waves' or in the bitmap, and the chunk is given up)
-    if (__builtin_amdgcn_readfirstlane((int)qn) <= kQueueCap) {
+    if (__builtin_amdgcn_readfirstlane((int)qn) <= Sh::kQueue) {
       for (;;) {
         const unsigned long long mask = __ballot(hits != 0);
         if (!mask) break;
@@ -628,7 +666,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
       const unsigned long long t = blk_bits(g);
       const uint32_t t0 = row16_sum_u32((uint32_t)t & 0xFFFFFFu), t1 = row16_sum_u32((uint32_t)(t >> 24) & 0xFFFFFFu);
       static_assert(((kBlkMagic >> 24) & 0xFFFFFFu) == 0, "neither half holds any of the magic bits");
-      if ((lane & 15) == 15) atomicAdd(&blk_mass[(uint32_t)(e0 - c0) / (uint32_t)kBlkElems], ((unsigned long long)t1 << 24) + t0);
+      if ((lane & 15) == 15) atomicAdd(&sm.blk_mass[(uint32_t)(e0 - c0) / (uint32_t)kBlkElems], ((unsigned long long)t1 << 24) + t0);
     }
   };
   // Element e0 of the piece being processed is bit (ib - ibase) + e0 - c0 of the bitmap, a
@@ -638,43 +676,96 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   auto hist_bits = [&](int t0, int j, bool guard) -> uint32_t {
     uint32_t bit0 = (uint32_t)(t0 - c0 + tid * EPL) + (SH ? ib - ibase : 0u);
     uint32_t at = (bit0 >> 3) + (uint32_t)(j * (SUB / 8));
-    if (guard) at = min(at, (uint32_t)(kChunkBitsMax / 8 - 1));
+    if (guard) at = min(at, (uint32_t)(Sh::kBits / 8 - 1));
     const uint32_t byte = bm8[at];
     return DT == SIP_F32 ? (byte >> (bit0 & 4u)) & 0xFu : byte;
   };
   int it0 = 0;                              // number of the tile's first load
-  auto process_tile = [&](const uint4 (&buf)[kStreamLoads], int t0) {
-    const bool partial = t0 + TILE > c1;
-    uint32_t hb[kStreamLoads];
-    if (!partial) {
+  auto process_tile = [&](const uint4 (&buf)[NL], int t0) {
+    uint32_t hb[NL];
 #pragma unroll
-      for (int j = 0; j < kStreamLoads; ++j) hb[j] = hist_bits(t0, j, false);
+    for (int j = 0; j < NL; ++j) hb[j] = hist_bits(t0, j, false);
 #pragma unroll
-      for (int j = 0; j < kStreamLoads; ++j) process(buf[j], t0 + j * SUB + tid * EPL, it0 + j, false, hb[j]);
+    for (int j = 0; j < NL; ++j) process(buf[j], t0 + j * SUB + tid * EPL, it0 + j, false, hb[j]);
+    it0 += NL;
+  };
+  auto process_end = [&](const uint4 (&buf)[NL], int t0) {                     // a tile that the chunk ends in
+#pragma unroll
+    for (int j = 0; j < NL; ++j)
+      if (t0 + j * SUB < c1) process(buf[j], t0 + j * SUB + tid * EPL, it0 + j, true, hist_bits(t0, j, true));     // workgroup-uniform condition
+    it0 += NL;
+  };
+  // A queue goes out to the segment, behind what other queues have put there so far (in the order in
+  // which the waves get here); what its entries added to the sums is taken out of them again, in
+  // integers.
+  const uint32_t seg_cap = ROW ? (uint32_t)(a.S * kChunkCap) : (uint32_t)kChunkCap;
+  uint2* const seg = a.cand + (size_t)wg * (size_t)seg_cap;
+  const int lpp = NL * ((c1 - c0 + TILE - 1) / TILE);                          // load numbers of one piece
+  unsigned long long taken = 0;
+  bool lost = false;                        // wave-uniform: the queue overflowed
+  // entry i of the queue, as the list has it
+  auto taken_out = [&](uint32_t i) -> uint2 {
+    uint2 en;
+    if constexpr (DT == SIP_F32) {
+      en = queue[i];
     } else {
-#pragma unroll
-      for (int j = 0; j < kStreamLoads; ++j)
-        if (t0 + j * SUB < c1) process(buf[j], t0 + j * SUB + tid * EPL, it0 + j, true, hist_bits(t0, j, true));     // workgroup-uniform condition
+      const uint32_t w = queue[i];
+      uint32_t it = (w >> 9) & ((1u << Sh::kLoadBits) - 1), base = ibase + (uint32_t)c0;
+      if (SH) { const uint32_t pc = it / (uint32_t)lpp; it -= pc * (uint32_t)lpp; base += pc * (uint32_t)Vl; }
+      en = make_uint2(w & 0xFFFF0000u, base + it * (uint32_t)SUB + (uint32_t)wave * (uint32_t)(kWave * EPL) + (w & 511u));
     }
-    it0 += kStreamLoads;
+    const uint32_t bit = (en.y - (uint32_t)g0) ^ (uint32_t)(EPL - 1);
+    if ((bmw[min(bit >> 5, (uint32_t)(Sh::kBits / 32 - 1))] >> (bit & 31u)) & 1u) en.y |= kTagBit;
+    return en;
+  };
+  auto take_out = [&](const uint2& en) {
+    const float t = bulk_term(bulk_arg(__uint_as_float(en.x), ref));
+    taken += bulk_units(t);
+    if (!SH && plain) atomicAdd(&sm.blk_mass[min(((en.y & ~kTagBit) - (uint32_t)g0) / (uint32_t)kBlkElems, (uint32_t)Sh::kBlocks - 1u)], 0ull - blk_units(t));
+  };
+  uint32_t n_flushed = 0;                   // entries that went out ahead of the end
+  auto queue_place = [&](uint32_t& n_out) -> uint32_t {
+    n_out = min((uint32_t)__builtin_amdgcn_readfirstlane((int)qn), (uint32_t)Sh::kQueue);
+    lost |= qn > (uint32_t)Sh::kQueue;
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(&sm.seg_cnt, n_out);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+  };
+  auto flush = [&]() {
+    uint32_t n_out;
+    const uint32_t at = queue_place(n_out);
+    for (uint32_t i = lane; i < n_out; i += kWave) {
+      const uint2 en = taken_out(i);
+      take_out(en);
+      if (!ROW || at + i < seg_cap) seg[at + i] = en;
+    }
+    n_flushed += n_out;
+    qn = 0;
   };
 
   // Two register buffers in turn: while one tile is processed the other's loads are in flight.  Every
   // tile processed is followed by a request, also where nothing is left to request (it repeats the last
   // 16 bytes), and the loop is left from its middle: with a request that may not have been made the
   // compiler counts the outstanding loads as if it had not, and waits for the loads just issued.
-  static_assert(kStreamBufs == 2, "");
+  // (ROW: a whole row may fill a queue several times; between two of its pairs of tiles a queue that is
+  // half full goes out.  Stores in the loop cost the waits that come next, so no earlier.)
   if (!SH) {
-    for (int tcur = c0;;) {
+    int tcur = c0;
+    while (tcur + TILE < c1) {
       process_tile(buf[0], tcur);
       load_tile(tnext, buf[0]);
       tnext += TILE; tcur += TILE;
-      if (tcur >= c1) break;
+      if (tcur + TILE >= c1) {
+#pragma unroll
+        for (int j = 0; j < NL; ++j) buf[0][j] = buf[1][j];
+        break;
+      }
       process_tile(buf[1], tcur);
       load_tile(tnext, buf[1]);
       tnext += TILE; tcur += TILE;
-      if (tcur >= c1) break;
+      if (ROW && __builtin_amdgcn_readfirstlane((int)qn) > Sh::kQueue / 2) flush();
     }
+    process_end(buf[0], tcur);
   } else {
     // the same over np pieces: every piece is [c0, c1) of its shard; the requests run ahead of the
     // processing across the piece boundaries (`row` is what load_tile reads from)
@@ -685,65 +776,91 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
       return c_pj < np;
     };
     for (;;) {
-      process_tile(buf[0], tcur);
+      if (tcur + TILE <= c1) process_tile(buf[0], tcur); else process_end(buf[0], tcur);
       load_tile(tnext, buf[0]); tnext += TILE; roll();
       if (!on()) break;
-      process_tile(buf[1], tcur);
+      if (tcur + TILE <= c1) process_tile(buf[1], tcur); else process_end(buf[1], tcur);
       load_tile(tnext, buf[1]); tnext += TILE; roll();
       if (!on()) break;
+      if (ROW && __builtin_amdgcn_readfirstlane((int)qn) > Sh::kQueue / 2) flush();
     }
   }
-  // ---- the queues go out, one behind the other in the order in which the waves get here, to the
-  // chunk's segment (no global stores inside the loop: they would force every wait on a tile load to
-  // drain the whole memory queue); what their entries added to the sums is taken out of them again,
-  // in integers
-  const uint32_t n_out = min(qn, (uint32_t)kQueueCap);
-  uint32_t off = 0;
-  if (lane == 0) off = atomicAdd(&seg_cnt, n_out);
-  off = (uint32_t)__builtin_amdgcn_readfirstlane((int)off);
-  unsigned long long units = bulk_units(acc);
-  uint2* seg = a.cand + (size_t)wg * (size_t)kChunkCap + off;
-  const int lpp = kStreamLoads * ((c1 - c0 + TILE - 1) / TILE);                // load numbers of one piece
-  for (uint32_t i = lane; i < n_out; i += kWave) {
-    uint2 en;
-    if constexpr (DT == SIP_F32) {
-      en = queue[i];
-    } else {
-      const uint32_t w = queue[i];
-      uint32_t it = (w >> 9) & ((1u << kLoadBits) - 1), base = ibase + (uint32_t)c0;
-      if (SH) { const uint32_t pc = it / (uint32_t)lpp; it -= pc * (uint32_t)lpp; base += pc * (uint32_t)Vl; }
-      en = make_uint2(w & 0xFFFF0000u, base + it * (uint32_t)SUB + (uint32_t)wave * (uint32_t)(kWave * EPL) + (w & 511u));
-    }
-    const float t = bulk_term(bulk_arg(__uint_as_float(en.x), ref));
-    units -= bulk_units(t);
-    const uint32_t place = en.y - (uint32_t)g0, bit = place ^ (uint32_t)(EPL - 1);
-    if (!SH && plain) atomicAdd(&blk_mass[min(place / (uint32_t)kBlkElems, (uint32_t)kBlkMax - 1u)], 0ull - blk_units(t));
-    if ((bmw[min(bit >> 5, (uint32_t)(kChunkBitsMax / 32 - 1))] >> (bit & 31u)) & 1u) en.y |= kTagBit;
-    seg[i] = en;
-  }
-  const unsigned long long wsum = dpp_scan_add_u64(units);
-  if (lane == kWave - 1) { red64[wave] = wsum; red32[wave] = qn; }
-  __syncthreads();
-  bool overflow = false;
+  // ---- the queues go out (ROW = false: only now, all of them), and the chunk's summary
+  uint32_t n_last = 0;
+  if constexpr (ROW) {
+    // What is left in the queue also stays in registers, so that finishing need not read it back (it does
+    // where a queue has gone out before, or is longer); all rounds are under way at once.
+    const uint32_t at = queue_place(n_last);
 #pragma unroll
-  for (int w = 0; w < kStreamWaves; ++w) overflow |= red32[w] > (uint32_t)kQueueCap;
-  const uint32_t tot = seg_cnt;
-  const bool blocks = plain && tot <= (uint32_t)(kChunkCap - kBlkMax);           // workgroup-uniform
+    for (int r = 0; r < kRowRegs; ++r) {
+      hand->list[r] = make_uint2(0u, kTagBit);
+      if ((uint32_t)(r * kWave) < n_last) hand->list[r] = taken_out(min((uint32_t)(r * kWave + lane), n_last - 1u));       // uniform condition
+    }
+#pragma unroll
+    for (int r = 0; r < kRowRegs; ++r) {
+      const uint32_t i = (uint32_t)(r * kWave + lane);
+      if (i < n_last) {
+        take_out(hand->list[r]);
+        if (at + i < seg_cap) seg[at + i] = hand->list[r];
+      } else {
+        hand->list[r] = make_uint2(0u, 0xFFFFFFFFu);
+      }
+    }
+    for (uint32_t i = (uint32_t)(kRowRegs * kWave + lane); i < n_last; i += kWave) {
+      const uint2 en = taken_out(i);
+      take_out(en);
+      if (at + i < seg_cap) seg[at + i] = en;
+    }
+  } else {
+    flush();
+  }
+  const unsigned long long wsum = dpp_scan_add_u64(bulk_units(acc) - taken);
+  // (31: the queue overflowed; 30: part of it went out early; below: its entries at the end)
+  if (lane == kWave - 1) { sm.red64[wave] = wsum; sm.red32[wave] = n_last | (n_flushed ? 1u << 30 : 0u) | (lost ? 1u << 31 : 0u); }
+  __syncthreads();
+  uint32_t marks = 0, longest = 0;
+#pragma unroll
+  for (int w = 0; w < kStreamWaves; ++w) { marks |= sm.red32[w]; longest = max(longest, sm.red32[w] & ~(3u << 30)); }
+  bool overflow = (marks >> 31) != 0u;
+  const uint32_t tot = sm.seg_cnt;
+  overflow |= tot > seg_cap;
+  const bool blocks = plain && tot <= seg_cap - (uint32_t)Sh::kBlocks;           // workgroup-uniform
   const int n_blk = blocks ? (c1 - c0 + kBlkElems - 1) / kBlkElems : 0;
-  if (tid < n_blk) (reinterpret_cast<unsigned long long*>(a.cand + (size_t)(wg + 1) * (size_t)kChunkCap) - n_blk)[tid] = ref.none ? 0ull : blk_mass[tid];
-  if (tid == 0) {
+  if (tid < n_blk) (reinterpret_cast<unsigned long long*>(seg + seg_cap) - n_blk)[tid] = ref.none ? 0ull : sm.blk_mass[tid];
+  if (ROW || tid == 0) {
     ChunkOut o;
     long long sum = 0;
 #pragma unroll
-    for (int w = 0; w < kStreamWaves; ++w) sum += (long long)red64[w];
+    for (int w = 0; w < kStreamWaves; ++w) sum += (long long)sm.red64[w];
     o.bulk = ref.none || sum < 0 ? 0ull : (unsigned long long)sum;               // (an ulp of the threads' sums below 0)
     o.Tc = ref.Tc;
     o.off = published_off(ref);
     o.cnt = overflow ? kCntOverflow : tot;
     o.n_blk = (uint32_t)n_blk;
-    o.unit = ref_lds.unit;
-    a.chunks[wg] = o;
+    o.unit = sm.ref.unit;
+    if (ROW) {                             // (scalar registers: vector registers are short there)
+      hand->co = o;
+      hand->co.bulk = readlane_u64(o.bulk, 0);
+      hand->co.unit = __longlong_as_double((long long)readlane_u64((unsigned long long)__double_as_longlong(o.unit), 0));
+      hand->co.cnt = (uint32_t)__builtin_amdgcn_readfirstlane((int)o.cnt);
+      hand->co.n_blk = (uint32_t)__builtin_amdgcn_readfirstlane((int)o.n_blk);
+      hand->longest = (uint32_t)__builtin_amdgcn_readfirstlane((int)longest);
+      hand->direct = __builtin_amdgcn_readfirstlane(!(marks >> 30) && longest <= (uint32_t)(kRowRegs * kWave)) != 0;
+    }
+    if (tid == 0) a.chunks[ROW ? (size_t)b * (size_t)a.S : (size_t)wg] = o;
   }
+  return true;
+}
+
+template <int DT, bool SH>
+__global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void stream_kernel(Args a) {
+  __shared__ StreamShared<DT, false> sm;
+  // Workgroups are handed to the 8 XCDs round-robin by their id.  The chunks of one row read
+  // the same sample, so they are renumbered to land on the same XCD (and its L2): id i works
+  // on logical chunk (i % 8) * (n / 8) + i / 8 when n, the grid size, is a multiple of 8.
+  int wg = blockIdx.x;
+  if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  stream_part<DT, SH, false>(a, wg, sm, nullptr);
 }
 
 }  // namespace sip
