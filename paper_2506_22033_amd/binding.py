@@ -166,13 +166,14 @@ def dtype_code(logits: torch.Tensor) -> int:
 
 
 def make_params(params: Optional[Dict[str, Optional[torch.Tensor]]], B: int) -> SipParams:
-    sp = SipParams()
-    for name in PARAM_FIELDS:
-        t = None if params is None else params.get(name)
-        if t is not None:
-            if t.dtype != _PARAM_DTYPES[name] or t.numel() != B or not t.is_contiguous() or not t.is_cuda:
-                raise TypeError(f"params[{name!r}] must be a contiguous device tensor of {B} x {_PARAM_DTYPES[name]}")
-        setattr(sp, name, _ptr(t))
+    sp = SipParams()                     # (every pointer NULL)
+    if params is not None:
+        for name, dtype in _PARAM_DTYPES.items():
+            t = params.get(name)
+            if t is not None:
+                if t.dtype != dtype or t.numel() != B or not t.is_contiguous() or not t.is_cuda:
+                    raise TypeError(f"params[{name!r}] must be a contiguous device tensor of {B} x {dtype}")
+                setattr(sp, name, t.data_ptr())
     return sp
 
 
@@ -213,11 +214,10 @@ def sip_sample(logits: torch.Tensor, params: Optional[Dict[str, Optional[torch.T
         need = sip_workspace_bytes(B, V, dt, nnz, k_logprobs)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
     sp = make_params(params, B)
-    s = torch.cuda.current_stream(dev) if stream is None else stream
     status = lib.sip_sample(_ptr(logits), B, V, logits.stride(0), dt, ctypes.byref(sp),
                             _ptr(hist_indptr) if nnz else None, _ptr(hist_tokens) if nnz else None, nnz,
                             seed, step, _ptr(out_ids), _ptr(out_lp_ids), _ptr(out_lp), k_logprobs,
-                            _ptr(workspace), workspace.numel() * workspace.element_size(), s.cuda_stream)
+                            _ptr(workspace), _nbytes(workspace), _stream_handle(dev, stream))
     if status != SIP_OK:
         raise SipError(status)
     return out_ids, out_lp_ids, out_lp
@@ -271,7 +271,9 @@ def _nbytes(t: torch.Tensor) -> int:
 
 
 def _stream_handle(dev, stream):
-    return (torch.cuda.current_stream(dev) if stream is None else stream).cuda_stream
+    # (the handle itself: the Stream object that torch.cuda.current_stream() builds around it takes 1.9 us, twice
+    # in a decode iteration, ahead of the launches)
+    return torch._C._cuda_getCurrentRawStream(dev.index) if stream is None else stream.cuda_stream
 
 
 def sip_state_init(state: torch.Tensor, slots: int, L_max: int,
