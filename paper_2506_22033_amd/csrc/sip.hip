@@ -69,7 +69,11 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t = 0) {
       if (S == 2 || cost < best_cost) { best_cost = cost; want = S; }
     }
   }
-  want = std::max(1, std::min({want, sip::kMaxChunks, std::max(1, n_tiles / 2)}));
+  // A chunk holds at least two tiles; where the batch is small, one: a short bf16 row would else be one or
+  // two chunks, whose queues overflow under a long history.  (V = 24275 bf16, 61 rows of 3034 tokens on a
+  // state, one chunk: half of the rows took the exact path, 254 us; three: 78.)  The workspace grows with
+  // the chunks, so for at most 256 of them.
+  want = std::max(1, std::min({want, sip::kMaxChunks, std::max({1, n_tiles / 2, std::min(n_tiles, 256 / B)})}));
   if (want >= pieces) {
     want = want / pieces * pieces;                     // a chunk is part of one piece: a multiple of their number
   } else {
@@ -96,7 +100,7 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t = 0) {
       want = next;
     }
   }
-  p.S = want;                                          // <= n_tiles / 2: every chunk holds at least two tiles
+  p.S = want;                                          // <= n_tiles
   p.cap_c = sip::kChunkCap;
   // the longest list a row may have: what the heavier per-row logic holds in registers, and what
   // the row's chunks can hand over

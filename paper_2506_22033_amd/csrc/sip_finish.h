@@ -245,7 +245,6 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   const uint32_t longest = ROW ? (direct ? hand->longest * (uint32_t)kFinWaves : hand->co.cnt) : wave_max_u32(my_cnt);
   const unsigned long long bulk = ROW ? hand->co.bulk : wave_add_u64(my_bulk);
   if (any_over || !(Tc == Tc)) { list_is_used(); return 3; }                 // uniform
-  if (total > (uint32_t)a.nc_cap) { list_is_used(); return 5; }              // uniform
   const int nb = (int)((longest + (uint32_t)(CR * tps) - 1) / (uint32_t)(CR * tps));   // uniform: batches of CR rounds
   const int cnt_seg = ROW ? (int)hand->co.cnt : seg_thread ? __shfl((int)my_cnt, c_seg, kWave) : 0;    // size of this thread's segment
   // whether round r of batch bt holds anything at all (uniform): every round is unrolled code that
