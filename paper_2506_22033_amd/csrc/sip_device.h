@@ -197,7 +197,17 @@ __device__ __attribute__((noinline)) void gather_row(const Args& a, int b) {
   for (int sh = 0; sh < a.t_shards; ++sh) {
     const uint4* src = reinterpret_cast<const uint4*>(shard_base(a, sh) + (size_t)b * (size_t)a.shard_stride * ESZ);
     uint4* d = reinterpret_cast<uint4*>(dst) + (size_t)sh * piece;
-    for (size_t i = threadIdx.x; i < piece; i += blockDim.x) d[i] = src[i];
+    constexpr int N = 4;                   // loads in flight a thread
+    const uint32_t n = (uint32_t)piece;
+    uint32_t i = threadIdx.x;
+    for (; i + (N - 1) * blockDim.x < n; i += N * blockDim.x) {
+      uint4 q[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) q[j] = src[i + (uint32_t)j * blockDim.x];
+#pragma unroll
+      for (int j = 0; j < N; ++j) d[i + (uint32_t)j * blockDim.x] = q[j];
+    }
+    for (; i < n; i += blockDim.x) d[i] = src[i];
   }
   __syncthreads();
 }

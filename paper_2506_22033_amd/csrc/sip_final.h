@@ -650,7 +650,12 @@ __device__ __forceinline__ int fast_row(const Args& a, const int b, const RowPar
       }
       __syncthreads();
       const uint32_t nm = (uint32_t)__builtin_amdgcn_readfirstlane((int)fs.n_memb2);
-      if (nm > (uint32_t)kMembers) return 9;                                  // uniform
+      if (nm > (uint32_t)kMembers) {                                          // uniform
+        if (k_act) return 9;
+        // (without top-k what settles a cut below the list settles this one too)
+        if (tid == 0) { fs.limit_out = limit; fs.lnz_out = lnZ; fs.has_pen_out = has_pen; fs.retry_ok_out = 0; }
+        return kWholeRowCut;
+      }
       if (nm <= (uint32_t)kWave) {
         if (wave == 0) {
           const uint32_t kt = fs.m_key[lane];
@@ -999,7 +1004,7 @@ __device__ __forceinline__ void rescue_row(const Args& a, const int b, unsigned 
       if (skipped && pen1.any) history_bitmap(a, b, pen1, reinterpret_cast<uint32_t*>(dynraw));   // (else the first attempt left it there)
       restream_row<DT>(a, b, rp, t_new, fs, bm1);
       S = 1; cap_c = a.S * a.cap_c;
-      if (cut_below && fs.rq_n > (uint32_t)(kFinalThreads * kCandLong)) {
+      if (cut_below && fs.rq_n > (uint32_t)min(kFinalThreads * kCandLong, a.S * a.cap_c)) {
         // The second list does not fit either: the cut is settled over the whole row, from the
         // tables of an attempt on the first list -- which are there, untouched, unless that
         // attempt was skipped: then the first list is made again (the second one lies where it
@@ -1080,8 +1085,7 @@ __global__ __launch_bounds__(kFinalThreads) void rescue_kernel(Args a_by_value) 
   }
 }
 
-// Draw over the whole row: for a row without any filter (plain temperature sampling), or, with
-// `key_cut` / min-p, for a row whose kept set reaches below the candidate list.  Maximum,
+// Draw over the whole row, for a row without any filter (plain temperature sampling).  Maximum,
 // total mass and best-n came from the list; the draw itself needs every element's mass in
 // vocabulary order, so the row is read once more here (it is still in the last-level cache),
 // plus the one block in which the running mass crosses the target.  Out of line: rarely needed,
@@ -1093,10 +1097,8 @@ __device__ __attribute__((noinline)) int whole_row_draw(const char* row, const i
                                                         const uint32_t* cnt, unsigned long long* hd, FastShared& fs,
                                                         const float tau, const bool greedy, const float m,
                                                         const float zmax, const float c_row,
-                                                        const unsigned long long j24, const uint32_t key_cut,
-                                                        const bool minp_on, const float t_minp) {
+                                                        const unsigned long long j24) {
   const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-  const bool filtered = key_cut != 0 || minp_on;        // uniform: only part of the row is kept
   auto scaled_s = [&](float z) { return greedy ? z : __fdiv_rn(z, tau); };
   constexpr int EPL = (DT == SIP_F32) ? 4 : 8;
   constexpr int ESZ = (DT == SIP_F32) ? 4 : 2;
@@ -1131,14 +1133,6 @@ __device__ __attribute__((noinline)) int whole_row_draw(const char* row, const i
           const float sv = value_of(cnt[pre[v >> 5] + __popc(word & ((1u << (v & 31)) - 1u))]);
           keys[i] = key_of(sv);
           E[i] = expf(__fsub_rn(sv, m));
-          if (filtered && !(keys[i] >= key_cut && (!minp_on || __fsub_rn(sv, m) >= t_minp))) E[i] = 0.0f;
-        } else if (filtered) {
-          // a cut by value: the exact s decides who is kept; the mass is exp(s - max) with the
-          // hardware exp2, the same expression in both passes below
-          const float sv = scaled_s(z[i]);
-          keys[i] = key_of(sv);
-          const bool keep = keys[i] >= key_cut && (!minp_on || __fsub_rn(sv, m) >= t_minp);
-          E[i] = keep ? __builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(sv, m), 1.44269504f)) : 0.0f;
         } else {
           // exp(z/tau - max) as 2^((z - zmax) * c): no division, hardware exp2; the two passes
           // below use the same expression, which is all the draw needs
@@ -1238,7 +1232,7 @@ __device__ __attribute__((noinline)) int whole_row_draw(const char* row, const i
       running += last_lane_u64(incl);
     }
     if (lane == 0) {
-      if (!filtered && found >= 0 && !(has_pen && ((bm[found >> 5] >> (found & 31)) & 1u)))
+      if (found >= 0 && !(has_pen && ((bm[found >> 5] >> (found & 31)) & 1u)))
         found_key = key_of(scaled_s(__uint_as_float(found_key)));
       fs.token = found; fs.token_key = found_key;
     }
@@ -1248,31 +1242,43 @@ __device__ __attribute__((noinline)) int whole_row_draw(const char* row, const i
   return (token == 0x7FFFFFFF || token < 0) ? 13 : 1;
 }
 
-// Nucleus cut of a row whose cut lies below the candidate list (top-p alone on a flat
-// distribution keeps tens of thousands of tokens): a radix descent over the whole row on the
-// exact fp32 s.  Each level is one read of the row (it is in the last-level cache): count
-// and integer mass per bin, 2048 bins over the current interval of s, monotone in s so that
-// equal values never part; the bin in which the mass of everything larger first stays short
-// of the limit becomes the next interval.  Once that bin holds at most kMembers elements
-// they are gathered and resolved by all-pairs comparison as in the list path.  Leaves the key
-// of the smallest kept value in fs.key_p and returns 1, or returns 11 (more than kMembers equal
-// values at the cut, no mass): the caller then takes the row to the exact path.
+// Nucleus and draw of a row whose cut lies below the candidate list (top-p alone on a flat
+// distribution keeps tens of thousands of tokens), in two reads of the row (it is in the last-level
+// cache).  The first puts the mass of every element into one of 2048 bins over the exact fp32 s,
+// monotone in s so that equal values never part; the bin in which the mass of everything larger first
+// stays short of the limit holds the cut.  The second sums, per block of consecutive elements, what lies
+// above that bin and what lies in it, and lists the latter; once the cut among them is known (all equal:
+// they are all kept) the kept ones join their blocks' sums, and one block is read again for the token.
+// More members than the list takes, and not all equal: the bin becomes the interval of another pair of
+// reads, at most kLevels of them.  All sums are integers.  Returns 1 (fs.token, fs.token_key), or a code:
+// the caller then takes the row to the exact path.
+// What bounds it: vector issue of one compute unit (about 25 instructions an element and read) and the
+// first read's 64-bit LDS additions.  One row of V = 213087 bf16 whose cut falls among equal values: 1060 ->
+// 261 us for the call (count and mass bins on each of up to three levels, a read to gather at most 256
+// members, a read for the block masses; more equal members than that went to the exact path); eleven rows
+// of V = 44143 fp32, three wide nuclei among them, 144 -> 127.
 template <int DT>
-__device__ __attribute__((noinline)) int whole_row_cut(const char* row, const int V, const bool has_pen,
-                                                       const uint32_t* bm, const unsigned short* pre,
-                                                       const uint32_t* cnt, unsigned long long* hm, uint32_t* hc,
-                                                       FastShared& fs, const float tau, const float m,
-                                                       const unsigned long long limit) {
+__device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, const int V, const bool has_pen,
+                                                           const uint32_t* bm, const unsigned short* pre,
+                                                           const uint32_t* cnt, unsigned long long* hm,
+                                                           unsigned long long* hd, FastShared& fs, const double inv_tau,
+                                                           const float m, const unsigned long long limit,
+                                                           const unsigned long long j24, const bool minp_on, const float t_minp) {
   const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   constexpr int NT = kFinalThreads;
   constexpr int EPL = (DT == SIP_F32) ? 4 : 8;
   constexpr int ESZ = (DT == SIP_F32) ? 4 : 2;
+  constexpr int UNR = 4;                                  // loads in flight per thread
   constexpr int kLevels = 3;
   constexpr float kSpan = 28.0f;                          // exp(-28) * 2^40 < 1: nothing below has mass
-  // s of every element of one 16-byte load (penalised elements take theirs from the slot table)
-  auto svals = [&](int e0, float (&sv)[EPL]) {
-    const int e_last = ((V - 1) / EPL) * EPL;
-    const uint4 q = *reinterpret_cast<const uint4*>(row + (size_t)min(e0, e_last) * ESZ);
+  constexpr int BLK = UNR * kWave * EPL;                  // elements of a block: one wave's loads
+  constexpr uint32_t kList = kBins;                       // members listed (key, block) where the bins were
+  static_assert(262144 / (UNR * kWave * 4) <= kBins / 2, "two sums per block in hd[]");
+  const RowDivisor by_tau(inv_tau);
+  const int e_last = ((V - 1) / EPL) * EPL;
+  auto ldrow = [&](int e0) { return *reinterpret_cast<const uint4*>(row + (size_t)min(e0, e_last) * ESZ); };
+  // s of every element of one 16-byte load (penalised elements take theirs from the slot table); NaN past the end
+  auto svals = [&](const uint4& q, int e0, float (&sv)[EPL]) {
     float z[EPL];
     if (DT == SIP_F32) {
       z[0] = __uint_as_float(q.x); z[1] = __uint_as_float(q.y);
@@ -1285,55 +1291,63 @@ __device__ __attribute__((noinline)) int whole_row_cut(const char* row, const in
         z[2 * i + 1] = __uint_as_float(w4[i] & 0xFFFF0000u);
       }
     }
+    // the elements of one load share a bitmap word (e0 is a multiple of EPL <= 8)
+    const uint32_t word = has_pen ? bm[min(e0, V - 1) >> 5] : 0u;
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
-      const int v = min(e0 + i, V - 1);
-      const uint32_t word = has_pen ? bm[v >> 5] : 0u;
-      sv[i] = ((word >> (v & 31)) & 1u) ? value_of(cnt[pre[v >> 5] + __popc(word & ((1u << (v & 31)) - 1u))])
-                                        : __fdiv_rn(z[i], tau);
+      const int v = e0 + i;
+      sv[i] = v < V ? by_tau.of(z[i]) : __uint_as_float(0x7FC00000u);
+      if (v < V && ((word >> (v & 31)) & 1u)) sv[i] = value_of(cnt[pre[v >> 5] + __popc(word & ((1u << (v & 31)) - 1u))]);
     }
   };
-  auto mass = [&](float sv) { return fix_of(__builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(sv, m), 1.44269504f))); };
+  auto mass = [&](float sv) { return mass_units(__builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(sv, m), 1.44269504f))); };
+  auto kept_minp = [&](float sv) { return !minp_on || __fsub_rn(sv, m) >= t_minp; };
   float lo[kLevels], sc[kLevels];
   int pick[kLevels];
   auto bin_at = [&](int l, float sv) { return min(kBins - 1, max(0, (int)(__fsub_rn(sv, lo[l]) * sc[l]))); };
+  // where s lies against the interval of level n (the picked bins of the levels above it): -1 below, 0 in it, 1 above
+  auto side = [&](int n, float sv) {
+    int r = 0;
+#pragma unroll
+    for (int l = 0; l < kLevels; ++l)
+      if (l < n && r == 0) { const int d = bin_at(l, sv) - pick[l]; r = d > 0 ? 1 : (d < 0 ? -1 : 0); }
+    return r;
+  };
   float cur_lo = m - kSpan, cur_w = kSpan;
   unsigned long long above = 0;                           // mass of everything larger than the current interval
-  uint32_t n_in = 0;
-  int levels = 0;
+  const int nblk = (V + BLK - 1) / BLK;
+  uint32_t key_cut = 0;
 #pragma unroll
   for (int level = 0; level < kLevels; ++level) {
-    const float cur_sc = (float)kBins / cur_w;
-    lo[level] = cur_lo; sc[level] = cur_sc; pick[level] = 0;
+    lo[level] = cur_lo; sc[level] = (float)kBins / cur_w; pick[level] = 0;
+    // ---- first read: mass per bin of the current interval
     __syncthreads();
-    for (int i = tid; i < kBins; i += NT) { hm[i] = 0; hc[i] = 0; }
-    if (tid == 0) fs.bin_p = 1 << 30;
+    for (int i = tid; i < kBins; i += NT) { hm[i] = 0; hd[i] = 0; }
+    if (tid == 0) { fs.bin_p = 1 << 30; fs.n_memb2 = 0; fs.key_p = 0xFFFFFFFFu; fs.key_k = 0; fs.bin_d = -1; fs.token = 0x7FFFFFFF; }
     __syncthreads();
-    for (int e0 = tid * EPL; e0 < V; e0 += NT * EPL) {
-      float sv[EPL];
-      svals(e0, sv);
+    for (int t0 = tid * EPL; t0 < V; t0 += UNR * NT * EPL) {
+      uint4 q[UNR];
 #pragma unroll
-      for (int i = 0; i < EPL; ++i) {
-        bool in = e0 + i < V && sv[i] == sv[i];
+      for (int u = 0; u < UNR; ++u) q[u] = ldrow(t0 + u * NT * EPL);
 #pragma unroll
-        for (int l = 0; l < kLevels; ++l)
-          if (l < level) in = in && bin_at(l, sv[i]) == pick[l];
-        if (in) {
-          const int bin = min(kBins - 1, max(0, (int)(__fsub_rn(sv[i], cur_lo) * cur_sc)));
-          atomicAdd(&hc[bin], 1u);
-          const unsigned long long E = mass(sv[i]);
-          if (E) atomicAdd(&hm[bin], E);
-        }
+      for (int u = 0; u < UNR; ++u) {
+        float sv[EPL];
+        svals(q[u], t0 + u * NT * EPL, sv);
+#pragma unroll
+        for (int i = 0; i < EPL; ++i)
+          if (sv[i] >= cur_lo && (level == 0 || side(level, sv[i]) == 0)) {
+            const unsigned long long E = mass(sv[i]);
+            if (E) atomicAdd(&hm[bin_at(level, sv[i])], E);
+          }
       }
     }
     __syncthreads();
     {
       // thread t owns bins kBins-1-4t .. kBins-4-4t; exclusive suffix mass in descending bin order
       const int b0 = kBins - 1 - kBinsPerThread * tid;
-      uint32_t c[kBinsPerThread];
       unsigned long long w[kBinsPerThread], msum = 0;
 #pragma unroll
-      for (int j = 0; j < kBinsPerThread; ++j) { c[j] = hc[b0 - j]; w[j] = hm[b0 - j]; msum += w[j]; }
+      for (int j = 0; j < kBinsPerThread; ++j) { w[j] = hm[b0 - j]; msum += w[j]; }
       const unsigned long long minc = dpp_scan_add_u64(msum);
       if (lane == kWave - 1) fs.r64[wave] = minc;
       __syncthreads();
@@ -1346,7 +1360,7 @@ __device__ __attribute__((noinline)) int whole_row_cut(const char* row, const in
 #pragma unroll
       for (int j = 0; j < kBinsPerThread; ++j) {
         mex_j[j] = mex;
-        if (c[j] && mex < limit) mine = b0 - j;           // bins descend: the last one wins
+        if (w[j] && mex < limit) mine = b0 - j;           // bins descend: the last one wins
         mex += w[j];
       }
       const uint32_t wmin = last_lane_u32(dpp_scan_min_u32((uint32_t)mine));
@@ -1355,51 +1369,144 @@ __device__ __attribute__((noinline)) int whole_row_cut(const char* row, const in
       const int bp = fs.bin_p;
 #pragma unroll
       for (int j = 0; j < kBinsPerThread; ++j)
-        if (b0 - j == bp) { fs.before_d = mex_j[j]; fs.n_memb3 = c[j]; }
+        if (b0 - j == bp) fs.before_d = mex_j[j];
     }
     __syncthreads();
     const int bp = fs.bin_p;
     if (bp >= kBins) return 11;                           // uniform: nothing qualifies (limit of 0)
-    pick[level] = bp; above = fs.before_d; n_in = fs.n_memb3;
-    levels = level + 1;
-    if (n_in <= (uint32_t)kMembers) break;                // uniform
+    pick[level] = bp; above = fs.before_d;
+    // ---- second read: sums per block, members of the bin
+    uint2* const list = reinterpret_cast<uint2*>(hm);     // (the bins are done with)
+    const int per_wave = (nblk + kFinalWaves - 1) / kFinalWaves;
+    uint32_t kmin = 0xFFFFFFFFu, kmax = 0;
+    for (int blk = wave * per_wave; blk < min(nblk, (wave + 1) * per_wave); ++blk) {
+      const int base = blk * BLK;
+      uint4 q[UNR];
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) q[u] = ldrow(base + (u * kWave + lane) * EPL);
+      unsigned long long A = 0, M = 0;
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        float sv[EPL];
+        svals(q[u], base + (u * kWave + lane) * EPL, sv);
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+          const int r = sv[i] >= lo[0] && kept_minp(sv[i]) ? side(level + 1, sv[i]) : -1;
+          const unsigned long long E = r >= 0 ? mass(sv[i]) : 0ull;
+          A += r > 0 ? E : 0ull;
+          const bool member = r == 0 && E != 0;
+          const unsigned long long ball = __ballot(member);
+          if (ball) {
+            M += member ? E : 0ull;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&fs.n_memb2, (uint32_t)__popcll(ball));
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) +
+                 __builtin_amdgcn_mbcnt_hi((uint32_t)(ball >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ball, 0u));
+            if (member) {
+              const uint32_t k = key_of(sv[i]);
+              kmin = min(kmin, k); kmax = max(kmax, k);
+              if (at < kList) list[at] = make_uint2(k, (uint32_t)blk);
+            }
+          }
+        }
+      }
+      A = dpp_scan_add_u64(A); M = dpp_scan_add_u64(M);
+      if (lane == kWave - 1) { hd[blk] = A; hd[kBins / 2 + blk] = M; }
+    }
+    if (kmax) { atomicMin(&fs.key_p, kmin); atomicMax(&fs.key_k, kmax); }
+    __syncthreads();
+    const uint32_t n = fs.n_memb2;
+    kmin = fs.key_p; kmax = fs.key_k;
+    if (kmin == kmax) {                                   // uniform: all equal, and the first of them is kept
+      key_cut = kmin;
+      for (int i = tid; i < nblk; i += NT) hd[i] += hd[kBins / 2 + i];
+      __syncthreads();
+      break;
+    }
+    if (n <= kList) {
+      // the smallest key above which the mass stays short of the limit: bisection, kmax being one
+      uint32_t k_lo = kmin, k_hi = kmax;                  // the answer lies in [k_lo, k_hi]
+      while (k_lo < k_hi) {                               // uniform
+        const uint32_t mid = k_lo + ((k_hi - k_lo) >> 1);
+        unsigned long long g = 0;
+        for (uint32_t q = tid; q < n; q += NT) {
+          const uint32_t k = list[q].x;
+          if (k > mid) g += mass(value_of(k));
+        }
+        g = dpp_scan_add_u64(g);
+        __syncthreads();
+        if (lane == kWave - 1) fs.r64[wave] = g;
+        __syncthreads();
+        unsigned long long G = above;
+#pragma unroll
+        for (int ww = 0; ww < kFinalWaves; ++ww) G += fs.r64[ww];
+        if (G < limit) k_hi = mid; else k_lo = mid + 1;
+      }
+      key_cut = k_hi;
+      for (uint32_t q = tid; q < n; q += NT)
+        if (list[q].x >= key_cut) atomicAdd(&hd[list[q].y], mass(value_of(list[q].x)));
+      __syncthreads();
+      break;
+    }
+    if (level + 1 == kLevels) return 11;                  // uniform
     cur_w = cur_w * (1.0f / (float)kBins);
     cur_lo = lo[level] + (float)bp * cur_w;
   }
-  if (n_in > (uint32_t)kMembers) return 11;               // uniform
-  // gather the elements of the last bin and resolve them
-  __syncthreads();
-  if (tid == 0) { fs.n_memb2 = 0; fs.key_p = 0xFFFFFFFFu; }
-  __syncthreads();
-  for (int e0 = tid * EPL; e0 < V; e0 += NT * EPL) {
-    float sv[EPL];
-    svals(e0, sv);
+  // ---- prefix over the blocks, and the block that holds the crossing
+  unsigned long long target;
+  {
+    static_assert(kBins / 2 <= 2 * NT, "two blocks per thread");
+    const unsigned long long w0 = 2 * tid < nblk ? hd[2 * tid] : 0ull, w1 = 2 * tid + 1 < nblk ? hd[2 * tid + 1] : 0ull;
+    const unsigned long long minc = dpp_scan_add_u64(w0 + w1);
+    __syncthreads();
+    if (lane == kWave - 1) fs.r64[wave] = minc;
+    __syncthreads();
+    unsigned long long ex = minc - w0 - w1, S3 = 0;
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-      bool in = e0 + i < V && sv[i] == sv[i];
+    for (int ww = 0; ww < kFinalWaves; ++ww) {
+      if (ww < wave) ex += fs.r64[ww];
+      S3 += fs.r64[ww];
+    }
+    target = (__umul64hi(j24, S3) << 40) | ((j24 * S3) >> 24);               // floor(j * S3 / 2^24)
+    if (ex <= target && target < ex + w0) { fs.bin_d = 2 * tid; fs.before_d = ex; }
+    ex += w0;
+    if (ex <= target && target < ex + w1) { fs.bin_d = 2 * tid + 1; fs.before_d = ex; }
+  }
+  __syncthreads();
+  const int blk_d = fs.bin_d;
+  if (blk_d < 0) return 13;                                                   // uniform (no mass at all)
+  if (wave == 0) {                                                            // lane prefixes in vocabulary order
+    const int base = blk_d * BLK;
+    unsigned long long running = fs.before_d;
+    bool found = false;
+#pragma nounroll
+    for (int u = 0; u < UNR && !found; ++u) {
+      const int e0 = base + (u * kWave + lane) * EPL;
+      float sv[EPL];
+      svals(ldrow(e0), e0, sv);
+      unsigned long long E[EPL], tot = 0;
 #pragma unroll
-      for (int l = 0; l < kLevels; ++l)
-        if (l < levels) in = in && bin_at(l, sv[i]) == pick[l];
-      if (in) {
-        const uint32_t q = atomicAdd(&fs.n_memb2, 1u);
-        if (q < (uint32_t)kMembers) { fs.m_key[q] = key_of(sv[i]); fs.m_E[q] = mass(sv[i]); }
+      for (int i = 0; i < EPL; ++i) {
+        E[i] = sv[i] >= lo[0] && kept_minp(sv[i]) && key_of(sv[i]) >= key_cut ? mass(sv[i]) : 0ull;
+        tot += E[i];
       }
+      const unsigned long long incl = dpp_scan_add_u64(tot);
+      unsigned long long c = running + incl - tot;
+      int hit = -1;
+      uint32_t hit_key = 0;
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) {
+        c += E[i];
+        if (hit < 0 && E[i] && c > target) { hit = e0 + i; hit_key = key_of(sv[i]); }
+      }
+      const unsigned long long ball = __ballot(hit >= 0);
+      found = ball != 0;
+      if (found && lane == __ffsll((long long)ball) - 1) { fs.token = hit; fs.token_key = hit_key; }
+      running += last_lane_u64(incl);
     }
   }
   __syncthreads();
-  const uint32_t nm = min(fs.n_memb2, (uint32_t)kMembers);
-  if ((uint32_t)tid < nm) {
-    const uint32_t kt = fs.m_key[tid];
-    unsigned long long G = above;
-    for (uint32_t q = 0; q < nm; ++q) {
-      const uint32_t kq = fs.m_key[q];
-      const unsigned long long Eq = fs.m_E[q];
-      G += kq > kt ? Eq : 0ull;
-    }
-    if (G < limit) atomicMin(&fs.key_p, kt);
-  }
-  __syncthreads();
-  return fs.key_p == 0xFFFFFFFFu ? 11 : 1;
+  return fs.token == 0x7FFFFFFF ? 13 : 1;
 }
 
 // Continuation of fast_row for the two kinds of row that are finished over the whole row
@@ -1426,15 +1533,13 @@ __device__ __attribute__((noinline)) int whole_row_finish(const Args& a, const i
   const bool minp_on = cut && rp.min_p > 0.0f;
   const float t_minp = minp_on ? (float)log((double)rp.min_p) : 0.0f;
   const unsigned long long j24 = (unsigned long long)(philox_word0(a.seed, rp.row_id, step_of(a)) >> 8);
-  const float c_row = (float)log2_scale(rp);
-  uint32_t key_cut = 0;
   if (cut) {
-    if (whole_row_cut<DT>(row, V, has_pen, bm, pre, cnt, hm, hc, fs, rp.tau, m, limit) != 1) return 10;   // uniform
-    key_cut = fs.key_p;
-  }
-  if (whole_row_draw<DT>(row, V, has_pen, bm, pre, cnt, hd, fs, rp.tau, rp.greedy, m, zmax, c_row, j24, key_cut,
-                         minp_on, t_minp) != 1)
+    const int r = whole_row_nucleus<DT>(row, V, has_pen, bm, pre, cnt, hm, hd, fs, 1.0 / (double)rp.tau, m, limit, j24,
+                                        minp_on, t_minp);
+    if (r != 1) return r == 11 ? 10 : r;                                      // uniform
+  } else if (whole_row_draw<DT>(row, V, has_pen, bm, pre, cnt, hd, fs, rp.tau, rp.greedy, m, zmax, (float)log2_scale(rp), j24) != 1) {
     return 13;                                                                // uniform
+  }
   if (threadIdx.x == 0) {
     const int token = fs.token;
     a.out_ids[b] = token;
