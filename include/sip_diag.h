@@ -47,7 +47,8 @@ sip_status sip_probe_read(const void* src, size_t bytes, int32_t workgroups, voi
  * are held in registers or take the exact multi-pass path, -1 = invalid arguments.  A row's chunks are
  * whole units of 1024 elements, dealt out evenly (to each vocabulary piece, if there are
  * pieces); none is empty.  (Up to SIP_MAX_RESIDENT_V entries a call may not launch them at all, see
- * "Kernels of a call" in sip.h; the workspace holds them either way.)
+ * "Kernels of a call" in sip.h; the workspace holds them either way.  A call with millions of history
+ * tokens may cut its rows into fewer where the workspace would else exceed sip_noalloc_scratch_bytes().)
  */
 int32_t sip_plan_chunks(int32_t B, int32_t V, sip_dtype dtype, int32_t t_shards);
 

@@ -41,8 +41,9 @@ constexpr int kFastMinV = 16384;
 constexpr int kFastMaxV = 262144;
 constexpr int kFastMinPiece = 8192;      // smallest vocabulary shard: its sample blocks (at most 32 of 256 elements) must fit
 
-// `t` > 0: the logits come in t vocabulary shards of V / t elements (0: one piece).
-Plan make_plan(int32_t B, int32_t V, int dtype, int t = 0) {
+// `t` > 0: the logits come in t vocabulary shards of V / t elements (0: one piece).  `small_chunks`: see
+// plan_for().
+Plan make_plan(int32_t B, int32_t V, int dtype, int t, bool small_chunks = true) {
   Plan p{};
   const int pieces = t > 0 ? t : 1;
   const int Vp = V / pieces;                           // elements per piece
@@ -73,7 +74,7 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t = 0) {
   // two chunks, whose queues overflow under a long history.  (V = 24275 bf16, 61 rows of 3034 tokens on a
   // state, one chunk: half of the rows took the exact path, 254 us; three: 78.)  The workspace grows with
   // the chunks, so for at most 256 of them.
-  want = std::max(1, std::min({want, sip::kMaxChunks, std::max({1, n_tiles / 2, std::min(n_tiles, 256 / B)})}));
+  want = std::max(1, std::min({want, sip::kMaxChunks, std::max({1, n_tiles / 2, small_chunks ? std::min(n_tiles, 256 / B) : 0})}));
   if (want >= pieces) {
     want = want / pieces * pieces;                     // a chunk is part of one piece: a multiple of their number
   } else {
@@ -187,6 +188,16 @@ Layout make_layout(int32_t B, const Plan& p, int64_t nnz, size_t gather_row_byte
   return l;
 }
 
+// A call's plan.  Chunks of one tile take up to 7.9 MB of workspace more than chunks of two (256 segments
+// of 30 KB): where that alone would put a call with a history of millions of tokens beyond the built-in
+// scratch, its chunks hold two tiles -- through every entry point, so that all of them give the same bits.
+Plan plan_for(int32_t B, int32_t V, int dtype, int t, int64_t nnz, size_t gather_row_bytes = 0) {
+  const Plan p = make_plan(B, V, dtype, t);
+  if (make_layout(B, p, nnz, gather_row_bytes).total <= kNoallocBytes) return p;
+  const Plan coarse = make_plan(B, V, dtype, t, false);
+  return make_layout(B, coarse, nnz, gather_row_bytes).total <= kNoallocBytes ? coarse : p;
+}
+
 // Where a call's token histories come from: a CSR handed in by the caller, or the slots of a
 // device-resident state.
 struct HistSource {
@@ -281,7 +292,7 @@ sip_status sample_impl(const void* logits, int32_t B, int32_t V, int64_t row_str
       if (!sh.base[i] || (reinterpret_cast<uintptr_t>(sh.base[i]) & 15u) != 0) return SIP_ERR_INVALID_ARG;
   }
   if (B > SIP_MAX_B || V > SIP_MAX_V || k_logprobs > SIP_MAX_K_LOGPROBS) return SIP_ERR_UNSUPPORTED;
-  const Plan plan = make_plan(B, V, (int)dtype, sh.t);
+  const Plan plan = plan_for(B, V, (int)dtype, sh.t, h.nnz + h.p_nnz, sh.t ? (size_t)V * esz : 0);
   const Layout lay = make_layout(B, plan, h.nnz + h.p_nnz, sh.t ? (size_t)V * esz : 0);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) != 0 || workspace_bytes < lay.total)
     return SIP_ERR_WORKSPACE;
@@ -462,7 +473,7 @@ extern "C" {
 size_t sip_workspace_bytes(int32_t B, int32_t V, sip_dtype dtype, int64_t hist_nnz, int32_t k_logprobs) {
   if (!shape_ok(B, V, (int)dtype, hist_nnz, k_logprobs)) return 0;
   if (B > SIP_MAX_B || V > SIP_MAX_V || k_logprobs > SIP_MAX_K_LOGPROBS) return 0;
-  return make_layout(B, make_plan(B, V, (int)dtype), hist_nnz).total;
+  return make_layout(B, plan_for(B, V, (int)dtype, 0, hist_nnz), hist_nnz).total;
 }
 
 sip_status sip_sample(const void* logits, int32_t B, int32_t V, int64_t row_stride, sip_dtype dtype,
@@ -489,7 +500,7 @@ sip_status sip_sample_noalloc(const void* logits, int32_t B, int32_t V, int64_t 
   if (hist_nnz > 0 && (!hist_indptr || !hist_tokens)) return SIP_ERR_INVALID_ARG;
   if (!shape_ok(B, V, (int)dtype, hist_nnz, k_logprobs)) return SIP_ERR_INVALID_ARG;
   if (B > SIP_MAX_B || V > SIP_MAX_V || k_logprobs > SIP_MAX_K_LOGPROBS) return SIP_ERR_UNSUPPORTED;
-  const size_t need = make_layout(B, make_plan(B, V, (int)dtype), hist_nnz).total;
+  const size_t need = make_layout(B, plan_for(B, V, (int)dtype, 0, hist_nnz), hist_nnz).total;
   if (need > kNoallocBytes) return SIP_ERR_SCRATCH;
   DeviceSetup* d = device_setup();                 // the current device's copy of the array
   if (!d) return SIP_ERR_HIP;
@@ -505,7 +516,8 @@ size_t sip_workspace_bytes_sharded(int32_t B, int32_t V_shard, int32_t t, sip_dt
   if (t < 1 || t > SIP_MAX_SHARDS || V_shard <= 0 || (int64_t)V_shard * t > SIP_MAX_V || B > SIP_MAX_B) return 0;
   const int32_t V = V_shard * t;
   if (!shape_ok(B, V, (int)dtype, hist_nnz, k_logprobs) || k_logprobs > SIP_MAX_K_LOGPROBS) return 0;
-  return make_layout(B, make_plan(B, V, (int)dtype, t), hist_nnz, (size_t)V * (dtype == SIP_F32 ? 4 : 2)).total;
+  const size_t row_bytes = (size_t)V * (dtype == SIP_F32 ? 4 : 2);
+  return make_layout(B, plan_for(B, V, (int)dtype, t, hist_nnz, row_bytes), hist_nnz, row_bytes).total;
 }
 
 sip_status sip_sample_sharded(const void* const* shard_logits, int32_t t, int32_t B, int32_t V_shard,
@@ -610,7 +622,8 @@ size_t sip_call_workspace_bytes(const sip_call* c) {
   if (!shape_ok(c->B, V, (int)c->dtype, h.nnz, c->k_logprobs)) return 0;
   if (c->B > SIP_MAX_B || V > SIP_MAX_V || c->k_logprobs > SIP_MAX_K_LOGPROBS) return 0;
   const size_t esz = c->dtype == SIP_F32 ? 4 : 2;
-  return make_layout(c->B, make_plan(c->B, V, (int)c->dtype, sh.t), h.nnz + h.p_nnz, sh.t ? (size_t)V * esz : 0).total;
+  const size_t row_bytes = sh.t ? (size_t)V * esz : 0;
+  return make_layout(c->B, plan_for(c->B, V, (int)c->dtype, sh.t, h.nnz + h.p_nnz, row_bytes), h.nnz + h.p_nnz, row_bytes).total;
 }
 
 sip_status sip_sample_call(const sip_call* c) {

@@ -308,3 +308,17 @@ def test_binding_refuses_host_tensors():
     import torch
     with pytest.raises(TypeError):
         sip.sip_sample(torch.zeros(2, 8), None, None, None, 0, 0, 0)
+
+
+@pytest.mark.parametrize("B,V,dtype", [(61, 24275, sip.SIP_BF16), (1, 16384, sip.SIP_BF16), (128, 16384, sip.SIP_F32),
+                                       (85, 40000, sip.SIP_BF16)])
+def test_small_chunks_do_not_push_a_call_out_of_the_built_in_scratch(B, V, dtype):
+    """Cut into chunks of one tile a small batch takes more workspace than in chunks of two: histories that fit the
+    built-in scratch with the latter (whose segments take 30 KB a chunk) still do."""
+    scratch, tile = sip.sip_noalloc_scratch_bytes(), 4096 if dtype == sip.SIP_F32 else 8192
+    coarse = max(1, -(-V // tile) // 2)
+    fixed = B * (coarse * (3840 * 8 + 32) + 64 + 8) + 8192           # segments, summaries, rows' records, alignment
+    nnz = (scratch - fixed) // 8
+    assert sip.sip_workspace_bytes(B, V, dtype, 0, 0) > fixed - 8192
+    assert scratch - 16384 < sip.sip_workspace_bytes(B, V, dtype, nnz, 0) <= scratch
+    assert sip.sip_workspace_bytes(B, V, dtype, nnz + 2048, 0) > scratch
