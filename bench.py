@@ -486,9 +486,16 @@ def main() -> int:
     if not bool((path == 14).all()):                # the library launched its single-pass kernels
         # a batch of at most one row per compute unit is finished by one kernel (finish_rescue_kernel);
         # a larger one by finish_kernel and, behind it, rescue_kernel (include/sip.h, "Kernels of a call")
-        one_kernel = w.B <= torch.cuda.get_device_properties(dev).multi_processor_count
-        # (rows of up to SIP_MAX_RESIDENT_V entries, in such a batch: resident_kernel alone)
+        cu = torch.cuda.get_device_properties(dev).multi_processor_count
+        one_kernel = w.B <= cu
+        # a row to a workgroup that streams and finishes it: the rule of row_is_chosen() in csrc/sip.hip
+        row_bytes = w.V * esz
+        by_row = w.B >= min(cu * 7 // 8, cu * 3 // 8 + row_bytes // 4096) if one_kernel else \
+            row_bytes <= 200 * 1024 or (w.B >= cu * 25 // 16 if w.B <= 2 * cu else w.B >= cu * 75 // 32)
+        # (rows of up to SIP_MAX_RESIDENT_V entries, in a batch of one kernel: resident_kernel alone)
         names = (("resident_kernel", (0, 1)),) if w.V <= 32768 and one_kernel else \
+                (("row_rescue_kernel", (0, 1)),) if by_row and one_kernel else \
+                (("row_kernel", (0, 1)), ("rescue_kernel", (4, 5))) if by_row else \
                 (("stream_kernel", (0, 1)), ("finish_rescue_kernel", (2, 3))) if one_kernel else \
                 (("stream_kernel", (0, 1)), ("finish_kernel", (2, 3)), ("rescue_kernel", (4, 5)))
         for name, (i0, i1) in names:

@@ -88,8 +88,8 @@ typedef struct {
  *   other value = finished after reading the row again (normally from cache): 15 = from a second,
  *   longer candidate list (one more read of that row); 16 = by the row's workgroup over the whole
  *   row (plain temperature sampling without any filter: one block of 1024 entries is read again if
- *   why = 1, the row twice if why = 13; a nucleus that reaches below the candidate list: four to six
- *   times); anything else = the exact multi-pass path, the value
+ *   why = 1, the row twice if why = 13; a nucleus that reaches below the candidate list: twice,
+ *   and one block for the token); anything else = the exact multi-pass path, the value
  *   naming the reason (2 top_k too large for any candidate list, 3-13 the candidate list could
  *   not prove the answer, 17-29 nor could the longer one), or 14: vocabulary size outside the
  *   single-pass kernels (why = 1: settled from registers all the same).
@@ -106,9 +106,12 @@ typedef struct {
  * 16384 (on a state behind state_take_tick_kernel), and, without a state, up to SIP_MAX_RESIDENT_V
  * for batches of no more rows than the device has compute units, unless nothing but best-n is asked
  * for; for larger batches only if params names no top_k, top_p or min_p and k_logprobs <= 0 (min_p
- * alone: up to three times as many rows).  Else stream_kernel (the one pass over the logits), then
- * finish_rescue_kernel for batches of no more rows than the device has compute units, else
- * finish_kernel followed by rescue_kernel (which returns at once when no row was passed on);
+ * alone: up to three times as many rows).  Else either one workgroup streams and finishes a row --
+ * row_rescue_kernel for batches of no more rows than the device has compute units, else row_kernel
+ * followed by rescue_kernel (which returns at once when no row was passed on), on a state behind
+ * state_take_tick_kernel -- or stream_kernel (the one pass over the logits, in chunks of rows), then
+ * finish_rescue_kernel or, for more rows than compute units, finish_kernel followed by rescue_kernel;
+ * row_is_chosen() in sip.hip says which, from B, the bytes of a row and whether there is a state;
  * exact_kernel alone for vocabulary sizes outside the single-pass kernels.
  */
 size_t sip_workspace_bytes(int32_t B, int32_t V, sip_dtype dtype, int64_t hist_nnz, int32_t k_logprobs);

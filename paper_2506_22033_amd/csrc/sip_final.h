@@ -1,6 +1,6 @@
 // The heavier per-row logic of the single-pass path, for the rows that the finishing kernel
 // (sip_finish.h) cannot settle from the list the streaming kernel left behind: rescue_row(),
-// run by rescue_kernel on the rows queued for it or, in small batches, by the workgroup that
+// run by rescue_kernel on the rows passed on to it or, in small batches, by the workgroup that
 // just tried (sip_fused.h).  It tries, in this order,
 //   - the row's list again in register variants that hold up to 24 entries per thread
 //     (fast_row: lists of up to 12288 entries, as top_k in the thousands makes them), with the
@@ -9,7 +9,7 @@
 //   - a second, longer list, made by reading the row once more with a lower threshold
 //     (restream_row), and the same logic on that one;
 //   - the continuations over the whole row (whole_row_finish): a nucleus that reaches below any
-//     list is cut by a radix descent on the exact fp32 s, and a row without any filter is drawn
+//     list is cut and drawn from in two reads of the row, and a row without any filter is drawn
 //     over all its elements;
 //   - the exact multi-pass path (sip_exact.h).
 //

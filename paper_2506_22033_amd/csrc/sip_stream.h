@@ -6,7 +6,8 @@
 // its chunk once:
 //   * elements >= Tc ("candidates") are collected, value and index, in per-wave LDS queues
 //     (a wave that finds more than its queue holds reports an overflow and the row falls back
-//     to the exact path) and written out to per-wave segments in the workspace at the end --
+//     to the exact path) and written out at the end as the chunk's one segment of the workspace
+//     (a workgroup that finishes its row itself keeps them in registers, sip_row.h) --
 //     every question that needs exact
 //     values (top-k, top-p, min-p, draw, best-n, maximum) is answered later from these few
 //     thousand entries per row;
