@@ -1335,7 +1335,9 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
         svals(q[u], t0 + u * NT * EPL, sv);
 #pragma unroll
         for (int i = 0; i < EPL; ++i)
-          if (sv[i] >= cur_lo && (level == 0 || side(level, sv[i]) == 0)) {
+          // (who is in the interval, bin_at() alone says: the interval's rounded lower end can lie an ulp above
+          // a value of the bin that it was)
+          if (sv[i] >= lo[0] && side(level, sv[i]) == 0) {
             const unsigned long long E = mass(sv[i]);
             if (E) atomicAdd(&hm[bin_at(level, sv[i])], E);
           }
