@@ -78,7 +78,9 @@ typedef struct {
 
 /*
  * Bytes of device scratch sip_sample() needs for this shape.  Depends only on its
- * arguments; returns 0 for an invalid shape.  The workspace must be 256-byte aligned; its
+ * arguments; returns 0 for an invalid shape.  The size for a longer history also serves every
+ * shorter one, and for rows of up to 128 KB (one piece) and up to 256 of them the size for more
+ * rows also serves fewer.  The workspace must be 256-byte aligned; its
  * contents need not be preserved between calls and need not be initialised.
  *
  * Diagnostic: after a call has completed, the first 2 * B int32 of the workspace say, per row,

@@ -191,11 +191,29 @@ Layout make_layout(int32_t B, const Plan& p, int64_t nnz, size_t gather_row_byte
 // A call's plan.  Chunks of one tile take up to 7.9 MB of workspace more than chunks of two (256 segments
 // of 30 KB): where that alone would put a call with a history of millions of tokens beyond the built-in
 // scratch, its chunks hold two tiles -- through every entry point, so that all of them give the same bits.
-Plan plan_for(int32_t B, int32_t V, int dtype, int t, int64_t nnz, size_t gather_row_bytes = 0) {
+Plan plan_for(int32_t B, int32_t V, int dtype, int t, int64_t nnz, size_t gather_row_bytes = 0, bool* coarse = nullptr) {
   const Plan p = make_plan(B, V, dtype, t);
   if (make_layout(B, p, nnz, gather_row_bytes).total <= kNoallocBytes) return p;
-  const Plan coarse = make_plan(B, V, dtype, t, false);
-  return make_layout(B, coarse, nnz, gather_row_bytes).total <= kNoallocBytes ? coarse : p;
+  const Plan two = make_plan(B, V, dtype, t, false);
+  const bool give_way = make_layout(B, two, nnz, gather_row_bytes).total <= kNoallocBytes;
+  if (coarse) *coarse = give_way && two.S != p.S;
+  return give_way ? two : p;
+}
+
+// What the size functions report.  A call's own need falls where its chunks of one tile become chunks of
+// two, with a longer history as above or with more rows (256 / B in make_plan()).  A caller that sized its
+// workspace for its longest histories and largest batch is served on every smaller call all the same: the
+// largest need of the batches up to this one that are cut into chunks of one tile counts, and for a
+// history beyond which they give way the built-in scratch's size, which bounds the need up to there.
+size_t workspace_need(int32_t B, int32_t V, int dtype, int t, int64_t nnz, size_t gather_row_bytes = 0) {
+  size_t need = 0;
+  for (int32_t b = 1; ; ++b) {
+    if (b < B && make_plan(b, V, dtype, t).S == make_plan(b, V, dtype, t, false).S) b = B;   // (from here on they all agree)
+    bool coarse = false;
+    const size_t own = make_layout(b, plan_for(b, V, dtype, t, nnz, gather_row_bytes, &coarse), nnz, gather_row_bytes).total;
+    need = std::max(need, coarse ? kNoallocBytes : own);
+    if (b >= B) return need;
+  }
 }
 
 // Where a call's token histories come from: a CSR handed in by the caller, or the slots of a
@@ -473,7 +491,7 @@ extern "C" {
 size_t sip_workspace_bytes(int32_t B, int32_t V, sip_dtype dtype, int64_t hist_nnz, int32_t k_logprobs) {
   if (!shape_ok(B, V, (int)dtype, hist_nnz, k_logprobs)) return 0;
   if (B > SIP_MAX_B || V > SIP_MAX_V || k_logprobs > SIP_MAX_K_LOGPROBS) return 0;
-  return make_layout(B, plan_for(B, V, (int)dtype, 0, hist_nnz), hist_nnz).total;
+  return workspace_need(B, V, (int)dtype, 0, hist_nnz);
 }
 
 sip_status sip_sample(const void* logits, int32_t B, int32_t V, int64_t row_stride, sip_dtype dtype,
@@ -517,7 +535,7 @@ size_t sip_workspace_bytes_sharded(int32_t B, int32_t V_shard, int32_t t, sip_dt
   const int32_t V = V_shard * t;
   if (!shape_ok(B, V, (int)dtype, hist_nnz, k_logprobs) || k_logprobs > SIP_MAX_K_LOGPROBS) return 0;
   const size_t row_bytes = (size_t)V * (dtype == SIP_F32 ? 4 : 2);
-  return make_layout(B, plan_for(B, V, (int)dtype, t, hist_nnz, row_bytes), hist_nnz, row_bytes).total;
+  return workspace_need(B, V, (int)dtype, t, hist_nnz, row_bytes);
 }
 
 sip_status sip_sample_sharded(const void* const* shard_logits, int32_t t, int32_t B, int32_t V_shard,
@@ -623,7 +641,7 @@ size_t sip_call_workspace_bytes(const sip_call* c) {
   if (c->B > SIP_MAX_B || V > SIP_MAX_V || c->k_logprobs > SIP_MAX_K_LOGPROBS) return 0;
   const size_t esz = c->dtype == SIP_F32 ? 4 : 2;
   const size_t row_bytes = sh.t ? (size_t)V * esz : 0;
-  return make_layout(c->B, plan_for(c->B, V, (int)c->dtype, sh.t, h.nnz + h.p_nnz, row_bytes), h.nnz + h.p_nnz, row_bytes).total;
+  return workspace_need(c->B, V, (int)c->dtype, sh.t, h.nnz + h.p_nnz, row_bytes);
 }
 
 sip_status sip_sample_call(const sip_call* c) {

@@ -322,3 +322,21 @@ def test_small_chunks_do_not_push_a_call_out_of_the_built_in_scratch(B, V, dtype
     assert sip.sip_workspace_bytes(B, V, dtype, 0, 0) > fixed - 8192
     assert scratch - 16384 < sip.sip_workspace_bytes(B, V, dtype, nnz, 0) <= scratch
     assert sip.sip_workspace_bytes(B, V, dtype, nnz + 2048, 0) > scratch
+
+
+@pytest.mark.parametrize("dtype", [sip.SIP_F32, sip.SIP_BF16])
+@pytest.mark.parametrize("V", [16384, 24280, 40000, 65536])
+def test_a_workspace_sized_for_the_longest_histories_and_largest_batch_serves_smaller_calls(V, dtype):
+    """The size neither falls as the history grows, across the place where a call's chunks of one tile give way, nor
+    with the rows of a batch of short rows."""
+    scratch = sip.sip_noalloc_scratch_bytes()
+    pieces = lambda B, nnz: sip.sip_workspace_bytes_sharded(B, V // 2, 2, dtype, nnz, 0)              # noqa: E731
+    whole = lambda B, nnz: sip.sip_workspace_bytes(B, V, dtype, nnz, 0)                               # noqa: E731
+    for need in (whole, pieces):
+        for B in (1, 2, 7, 61, 85, 128, 200, 256):
+            sizes = [need(B, nnz) for nnz in range(0, scratch // 8 + (1 << 19), 5003)]
+            assert sizes == sorted(sizes), (B, [i for i in range(1, len(sizes)) if sizes[i] < sizes[i - 1]])
+        if V * (2 if dtype == sip.SIP_BF16 else 4) <= 128 * 1024:
+            for nnz in (0, 100_000, 4_000_000, 4_540_000, 5_000_000):
+                sizes = [need(B, nnz) for B in range(1, 257)]
+                assert sizes == sorted(sizes), (nnz, [i + 1 for i in range(1, 256) if sizes[i] < sizes[i - 1]])
