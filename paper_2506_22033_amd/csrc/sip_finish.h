@@ -911,8 +911,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     // bulk units -> 2^-40 of the maximum's mass
     // (in double: of the 2^-24 that a unit in fp32 is off by, the list's share moves draws)
     const double unit = exp2(fmin(fmax(bulk_exponent(bulk_unit, m) + (double)(kFixShift - kBlkUnitShift), -1000.0), 61.0));
-    // (an ulp of fp32 sums below zero where all there is of a load is in the list)
-    auto rescaled = [&](unsigned long long u) { return (unsigned long long)fmin(fmax((double)(long long)u * unit, 0.0), 4.0e18); };
+    auto rescaled = [&](unsigned long long u) { return (unsigned long long)fmin((double)u * unit, 4.0e18); };
     for (int bt = 0; bt < nb; ++bt) {
       if (nb > 1) {
         load_batch(bt);
@@ -987,22 +986,20 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
           raw[0] = q0.x; raw[1] = q0.y; raw[2] = q0.z; raw[3] = q0.w;
           raw[4] = q1.x; raw[5] = q1.y; raw[6] = q1.z; raw[7] = q1.w;
         }
-        // element e0 + i: key of its s if it is in the list (0: not), what it added to its load's sum, its
-        // mass as a list entry and what the streaming kernel took out of the sum again for that
-        auto element = [&](int i, uint32_t& key, float& t, unsigned long long& E, unsigned long long& out) {
+        // element e0 + i: key of its s if it is in the list (0: not), its bulk term, its mass as a list entry
+        auto element = [&](int i, uint32_t& key, float& t, unsigned long long& E) {
           key = fs.fill[(e0 + i) & (kBlkElems - 1)];
           const bool in = e0 + i < V;
-          t = in && !ref.none ? bulk_term(bulk_arg(__uint_as_float(raw[i]), ref)) : 0.0f;
+          t = in && !key && !ref.none ? bulk_term(bulk_arg(__uint_as_float(raw[i]), ref)) : 0.0f;
           E = in && key ? mass(value_of(key)) : 0ull;
-          out = key ? blk_units(t) : 0ull;
         };
         unsigned long long u = 0, E = 0;
         float part = 0.0f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          uint32_t key; float t; unsigned long long Ei, out;
-          element(i, key, t, Ei, out);
-          part += t; E += Ei; u -= out;
+          uint32_t key; float t; unsigned long long Ei;
+          element(i, key, t, Ei);
+          part += t; E += Ei;
           if ((i & last_of_load) == last_of_load) { u += blk_units(part); part = 0.0f; }
         }
         const unsigned long long u_inc = dpp_scan_add_u64(u), E_inc = dpp_scan_add_u64(E);
@@ -1013,9 +1010,9 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
         part = 0.0f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          uint32_t key; float t; unsigned long long Ei, out;
-          element(i, key, t, Ei, out);
-          part += t; C_E += Ei; C_u -= out;
+          uint32_t key; float t; unsigned long long Ei;
+          element(i, key, t, Ei);
+          part += t; C_E += Ei;
           const unsigned long long to_here = C_u + blk_units(part);
           if (tok == kFinNone && C_E + rescaled(to_here) > target) {
             tok = (uint32_t)(e0 + i); tok_key = key ? key : key_of(scaled_s(__uint_as_float(raw[i])));

@@ -17,8 +17,8 @@
 //     terms in fp32 in a fixed order; the per-thread sums are combined as integers in units
 //     of 2^-30.
 // What bounds it: fp32 rows HBM (V = 152064, 256 rows 33.1 -> 29.6 us, 5.3 TB/s), bf16 rows vector issue (V =
-// 129280, 1024 rows 86.4 -> 74.7 us), both against a loop that compared, selected and pushed element by
-// element (16.9 vector instructions per bf16 element, now 11.8) and waited for loads it had just issued.
+// 129280, 1024 rows 86.4 -> 74.7 us, and a minimum per element more since), both against a loop that compared,
+// selected and pushed element by element and waited for loads it had just issued.
 // History penalties (Sec. 5.1 ApplyPenalty) touch at most |history| elements of a row.  The
 // workgroup marks the row's history tokens that fall into its chunk in an LDS bitmap (one bit
 // per element of the chunk); an element whose bit is set goes into the list whatever its
@@ -50,7 +50,8 @@ struct StreamShape {
   static constexpr int kLoads = ROW ? 4 : 2;                           // 16-byte loads per thread per tile, of which two are held
   static constexpr int kTile = kStreamThreads * kLoads * EPL;
   typedef typename std::conditional<DT == SIP_F32, uint2, uint32_t>::type entry_t;      // of a queue, see `process`
-  static constexpr int kQueue = ROW ? (DT == SIP_F32 ? 704 : 1408) : kQueueCap;         // entries of one wave's queue
+  static constexpr int kQueue = ROW ? (DT == SIP_F32 ? 704 : 1280) : kQueueCap;         // entries of one wave's queue
+  static constexpr int kTags = 1 << EPL;                               // history bits of one load
   static constexpr int kBits = ROW ? kRowBitsMax : kChunkBitsMax;      // most elements a workgroup streams
   static constexpr int kBlocks = kBits / kBlkElems;
   static constexpr int kHistRegs = ROW ? 8 : 4;                         // history tokens a thread requests with the sample
@@ -187,9 +188,12 @@ __device__ __forceinline__ BulkRef published_ref(float Tc, float off, const RowP
 // out above 0 is the rounding of m, and no term is left of that size.
 __device__ __forceinline__ double bulk_exponent(double unit, float m) { return unit - (double)m * 1.4426950408889634074; }
 __device__ __forceinline__ float bulk_arg(float z, const BulkRef& r) { return __fmaf_rn(z, r.c, r.off); }
-// What an element adds to the running sum: its mass if x < 0; something below 1 that is taken out
-// again if it belongs to the list (no select in the loop).
-__device__ __forceinline__ float bulk_term(float x) { return __builtin_amdgcn_exp2f(-fabsf(x)); }
+// What an element adds to the running sum: its mass if x < 0, nothing if it belongs to the list, that is
+// for x >= 0 and for a NaN.  Read as integers the bits of a negative number lie below those of -inf, and
+// those of everything else at or above them: one minimum instead of a comparison and a selection.
+__device__ __forceinline__ float bulk_term(float x) {
+  return __builtin_amdgcn_exp2f(__int_as_float(min(__float_as_int(x), (int)0xFF800000u)));
+}
 // Bulk terms of one 16-byte load, added in the order of its elements, as an integer in units of
 // 2^-41 of a term of 1, that is at most 2^-40 of the maximum's mass: added to 2^11 a double's last bit
 // is 2^-41, so the low bits of the sum are the integer (a load's terms add up to at most 8).
@@ -206,8 +210,8 @@ __device__ __forceinline__ unsigned long long bulk_units(float acc) {
 
 
 // LDS: first the sample histogram (two 16-bit counters per word, 16 KB) and the threads' largest
-// sample keys (6 KB), then, in their place, the per-wave candidate queues (a chunk's: fp32 30 KB, bf16 15 KB; a row's: 44 KB); then the history
-// bitmap (9 or 32 KB).
+// sample keys (6 KB), then, in their place, the per-wave candidate queues (a chunk's: fp32 30 KB, bf16 15 KB; a row's: 44 or 40 KB); then the history
+// bitmap (9 or 32 KB) and the tag words (fp32 256 bytes, bf16 4 KB).
 template <int DT, bool ROW>
 struct __align__(16) StreamShared {
   typedef StreamShape<DT, ROW> Sh;
@@ -215,10 +219,15 @@ struct __align__(16) StreamShared {
   static constexpr int kFrontBytes = kSampleBins * 2 + kTailKeys * 4 > kQueueBytes ? kSampleBins * 2 + kTailKeys * 4 : kQueueBytes;
   unsigned char front[kFrontBytes];
   uint32_t bmw[Sh::kBits / 32];
+  uint4 tag_words[Sh::kTags];              // history bits of a load -> what is or-ed into its four words
   unsigned long long blk_mass[Sh::kBlocks];
-  unsigned long long red64[kStreamWaves];
-  uint32_t red32[kStreamWaves];
-  uint32_t sub_hist[32];                   // the threshold bin, split by the next 5 key bits
+  union {
+    uint32_t sub_hist[32];                 // the threshold bin, split by the next 5 key bits (dead once it is found)
+    struct {
+      unsigned long long red64[kStreamWaves];
+      uint32_t red32[kStreamWaves];
+    };
+  };
   BulkRef ref;
   uint32_t seg_cnt;                        // entries of the segment so far
   uint32_t key_thr;                        // the threshold's key: 13 bits, later 18
@@ -437,6 +446,13 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
     const int n_bits = ROW ? min((V + 127) / 128, Sh::kBits / 128) : Sh::kBits / 128;
     for (int i = tid; i < n_bits; i += kStreamThreads) z4[i] = make_uint4(0, 0, 0, 0);
   }
+  if (tid < Sh::kTags) {                   // (bit p is element EPL - 1 - p, see `process`)
+    auto word = [&](int i) -> uint32_t {
+      if constexpr (DT == SIP_F32) return (tid >> (3 - i)) & 1 ? ~0u : 0u;
+      else return ((tid >> (7 - 2 * i)) & 1 ? 0xFFFFu : 0u) | ((tid >> (6 - 2 * i)) & 1 ? 0xFFFF0000u : 0u);
+    };
+    sm.tag_words[tid] = make_uint4(word(0), word(1), word(2), word(3));
+  }
   if (tid < 32) sm.sub_hist[tid] = 0;
   if (tid < Sh::kBlocks) sm.blk_mass[tid] = 0ull;
   if (tid == 0) sm.seg_cnt = 0;
@@ -609,7 +625,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
   entry_t* const queue = reinterpret_cast<entry_t*>(sm.front) + wave * Sh::kQueue;   // this wave's LDS queue
   const unsigned char* bm8 = reinterpret_cast<const unsigned char*>(bmw);
   uint32_t qn = 0;                          // wave-uniform: list entries in the queue
-  float acc = 0.0f;                         // this thread's sum of bulk_term(), fixed order of additions
+  float acc = 0.0f;                         // this thread's bulk mass, fixed order of additions
 
   uint32_t ib = ibase;                      // SH: first vocabulary id of the piece being processed
   // Block masses of a row without any filter.  One scalar branch per load for every other row; a
@@ -618,16 +634,18 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
   // 16 us, streaming kernel 28 us as before, call 99.4 -> 43 us; with the sums in fp32 26.5 + 14.8 us,
   // but fewer bits than the draw by re-reading the row has.
   const bool plain = !SH && !rp.greedy && unfiltered(rp, V);                   // workgroup-uniform
-  // Per element a multiply-add, its sign shifted into a mask, an exponential and an addition; the
+  // Per element a multiply-add, its sign shifted into a mask, a minimum, an exponential and an addition; the
   // elements at or above the threshold and the history tokens (`hb`) are then pushed lane by lane, one
   // of each lane at a time, which takes one or two rounds of a load at the usual list lengths.
-  // Bit p of mask and `hb` is element EPL - 1 - p.  `it`: the wave's load
+  // Bit p of mask and `hb` is element EPL - 1 - p.  A history token's bits are all set for the sum, a NaN,
+  // which bulk_term() leaves out: what belongs to the list must not pass through the fp32 sums, not even to be
+  // taken out again (6000 tokens around the threshold, penalised away: 3e-5 of the total was left behind).  `it`: the wave's load
   // number in its chunk.  A queue entry is the element's value and its place: fp32 (bits, vocabulary
   // id); bf16 one word, the value's 16 bits above load number, lane and element (5 or 7 + 6 + 3 bits).
   // Whether it is a history token is looked up again when the queue goes out.
-  auto process = [&](const uint4& q, int e0, int it, bool guard, uint32_t hb) {
+  auto process = [&](const uint4& q, int e0, int it, bool guard, uint32_t hb, const uint4& tg) {
     float z[EPL];
-    unpack(q, z);
+    unpack(make_uint4(q.x | tg.x, q.y | tg.y, q.z | tg.z, q.w | tg.w), z);
     if (guard) {
 #pragma unroll
       for (int i = 0; i < EPL; ++i)
@@ -653,8 +671,8 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
         if (hits) {
           const uint32_t p = (uint32_t)__ffs((int)hits) - 1u, y = place - p;
           if constexpr (DT == SIP_F32) {
-            const float hi = (p & 1u) ? z[0] : z[1], lo = (p & 1u) ? z[2] : z[3];
-            queue[pos] = make_uint2(__float_as_uint(p < 2u ? lo : hi), y);
+            const uint32_t hi = (p & 1u) ? q.x : q.y, lo = (p & 1u) ? q.z : q.w;
+            queue[pos] = make_uint2(p < 2u ? lo : hi, y);
           } else {
             const unsigned long long w = p < 4u ? ((unsigned long long)q.w << 32) | q.z : ((unsigned long long)q.y << 32) | q.x;
             queue[pos] = ((uint32_t)(w >> ((y << 4) & 63u)) << 16) | y;
@@ -692,23 +710,27 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
     uint32_t hb[NL];
 #pragma unroll
     for (int j = 0; j < NL; ++j) hb[j] = hist_bits(t0, j, false);
+    uint4 tg[NL];                           // (looked up for rows without a penalty too: behind a branch a load they took 1 us more of 36)
 #pragma unroll
-    for (int j = 0; j < NL; ++j) process(buf[j], t0 + j * SUB + tid * EPL, it0 + j, false, hb[j]);
+    for (int j = 0; j < NL; ++j) tg[j] = sm.tag_words[hb[j]];
+#pragma unroll
+    for (int j = 0; j < NL; ++j) process(buf[j], t0 + j * SUB + tid * EPL, it0 + j, false, hb[j], tg[j]);
     it0 += NL;
   };
   auto process_end = [&](const uint4 (&buf)[NL], int t0) {                     // a tile that the chunk ends in
 #pragma unroll
     for (int j = 0; j < NL; ++j)
-      if (t0 + j * SUB < c1) process(buf[j], t0 + j * SUB + tid * EPL, it0 + j, true, hist_bits(t0, j, true));     // workgroup-uniform condition
+      if (t0 + j * SUB < c1) {               // workgroup-uniform condition
+        const uint32_t hb = hist_bits(t0, j, true);
+        process(buf[j], t0 + j * SUB + tid * EPL, it0 + j, true, hb, sm.tag_words[hb]);
+      }
     it0 += NL;
   };
   // A queue goes out to the segment, behind what other queues have put there so far (in the order in
-  // which the waves get here); what its entries added to the sums is taken out of them again, in
-  // integers.
+  // which the waves get here).
   const uint32_t seg_cap = ROW ? (uint32_t)(a.S * kChunkCap) : (uint32_t)kChunkCap;
   uint2* const seg = a.cand + (size_t)wg * (size_t)seg_cap;
   const int lpp = NL * ((c1 - c0 + TILE - 1) / TILE);                          // load numbers of one piece
-  unsigned long long taken = 0;
   bool lost = false;                        // wave-uniform: the queue overflowed
   // entry i of the queue, as the list has it
   auto taken_out = [&](uint32_t i) -> uint2 {
@@ -725,11 +747,6 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
     if ((bmw[min(bit >> 5, (uint32_t)(Sh::kBits / 32 - 1))] >> (bit & 31u)) & 1u) en.y |= kTagBit;
     return en;
   };
-  auto take_out = [&](const uint2& en) {
-    const float t = bulk_term(bulk_arg(__uint_as_float(en.x), ref));
-    taken += bulk_units(t);
-    if (!SH && plain) atomicAdd(&sm.blk_mass[min(((en.y & ~kTagBit) - (uint32_t)g0) / (uint32_t)kBlkElems, (uint32_t)Sh::kBlocks - 1u)], 0ull - blk_units(t));
-  };
   uint32_t n_flushed = 0;                   // entries that went out ahead of the end
   auto queue_place = [&](uint32_t& n_out) -> uint32_t {
     n_out = min((uint32_t)__builtin_amdgcn_readfirstlane((int)qn), (uint32_t)Sh::kQueue);
@@ -743,7 +760,6 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
     const uint32_t at = queue_place(n_out);
     for (uint32_t i = lane; i < n_out; i += kWave) {
       const uint2 en = taken_out(i);
-      take_out(en);
       if (!ROW || at + i < seg_cap) seg[at + i] = en;
     }
     n_flushed += n_out;
@@ -807,7 +823,6 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
     for (int r = 0; r < kRowRegs; ++r) {
       const uint32_t i = (uint32_t)(r * kWave + lane);
       if (i < n_last) {
-        take_out(hand->list[r]);
         if (at + i < seg_cap) seg[at + i] = hand->list[r];
       } else {
         hand->list[r] = make_uint2(0u, 0xFFFFFFFFu);
@@ -815,13 +830,12 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
     }
     for (uint32_t i = (uint32_t)(kRowRegs * kWave + lane); i < n_last; i += kWave) {
       const uint2 en = taken_out(i);
-      take_out(en);
       if (at + i < seg_cap) seg[at + i] = en;
     }
   } else {
     flush();
   }
-  const unsigned long long wsum = dpp_scan_add_u64(bulk_units(acc) - taken);
+  const unsigned long long wsum = dpp_scan_add_u64(bulk_units(acc));
   // (31: the queue overflowed; 30: part of it went out early; below: its entries at the end)
   if (lane == kWave - 1) { sm.red64[wave] = wsum; sm.red32[wave] = n_last | (n_flushed ? 1u << 30 : 0u) | (lost ? 1u << 31 : 0u); }
   __syncthreads();
@@ -836,10 +850,10 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
   if (tid < n_blk) (reinterpret_cast<unsigned long long*>(seg + seg_cap) - n_blk)[tid] = ref.none ? 0ull : sm.blk_mass[tid];
   if (ROW || tid == 0) {
     ChunkOut o;
-    long long sum = 0;
+    o.bulk = 0;
 #pragma unroll
-    for (int w = 0; w < kStreamWaves; ++w) sum += (long long)sm.red64[w];
-    o.bulk = ref.none || sum < 0 ? 0ull : (unsigned long long)sum;               // (an ulp of the threads' sums below 0)
+    for (int w = 0; w < kStreamWaves; ++w) o.bulk += sm.red64[w];
+    if (ref.none) o.bulk = 0;
     o.Tc = ref.Tc;
     o.off = published_off(ref);
     o.cnt = overflow ? kCntOverflow : tot;
@@ -862,6 +876,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
 template <int DT, bool SH>
 __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void stream_kernel(Args a) {
   __shared__ StreamShared<DT, false> sm;
+  static_assert(sizeof(sm) <= 40 * 1024, "four workgroups per compute unit");
   // Workgroups are handed to the 8 XCDs round-robin by their id.  The chunks of one row read
   // the same sample, so they are renumbered to land on the same XCD (and its L2): id i works
   // on logical chunk (i % 8) * (n / 8) + i / 8 when n, the grid size, is a multiple of 8.
