@@ -1037,9 +1037,10 @@ __device__ __forceinline__ void rescue_row(const Args& a, const int b, unsigned 
 }
 
 // The rows that the kernel before it could not settle (row_why is not 1), one workgroup per row at a
-// time: the i-th of them is workgroup i % grid's.  Launched with a fixed, small grid; every workgroup
-// looks at all the codes, four of a thread at a time, so that nothing has to be counted (and nothing
-// set to zero) ahead of it.  Nothing to rescue, 1024 rows: 4.7 us, as with a queue in memory.
+// time.  Launched with a fixed, small grid; every wave looks at all the codes for itself, so that nothing
+// has to be counted (and nothing set to zero) ahead of it, and no wave waits for another to find that
+// there is nothing to do.  Nothing to rescue, 1024 rows: 4.9 us (6.5 with the codes counted through LDS and a
+// frame of 504 bytes a lane, which also cost the kernel before it 2 us of 111).
 template <int DT, bool SH>
 __global__ __launch_bounds__(kFinalThreads) void rescue_kernel(Args a_by_value) {
   // The arguments are read where they are used, straight from the kernel-argument segment
@@ -1050,38 +1051,41 @@ __global__ __launch_bounds__(kFinalThreads) void rescue_kernel(Args a_by_value) 
   extern __shared__ __align__(16) unsigned char dynraw[];
   __shared__ ExactShared ex;
   __shared__ FastShared fs;
-  constexpr int PER = 4, SPAN = PER * kFinalThreads;
-  __shared__ unsigned short mine[SPAN];                // this workgroup's, from the rows looked at
-  __shared__ int n_mine;
-  __shared__ uint32_t wave_n[kFinalWaves];
-  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-  uint32_t seen = 0;                                   // unsettled rows so far
+  // Every wave looks at the codes for itself, kSpan rows at a time: nothing to share, and nothing to wait for.
+  constexpr int kLook = 16, kSpan = kLook * kWave;
+  const int lane = lane_id();
+  int base = 0;
+  uint32_t seen = 0;                                   // unsettled rows ahead of `base`
+  auto row_of = [&](uint32_t rank) -> int {            // the row with that rank among the unsettled, -1 = none
 #pragma nounroll
-  for (int base = 0; base < a.B; base += SPAN) {
-    uint32_t bad = 0;
+    for (; base < a.B; base += kSpan) {
+      int code[kLook];
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const int r = base + j * kFinalThreads + tid;
-      bad |= (r < a.B && a.row_why[min(r, a.B - 1)] != 1) ? 1u << j : 0u;
+      for (int j = 0; j < kLook; ++j) code[j] = a.row_why[min(base + j * kWave + lane, a.B - 1)];
+      uint32_t before = seen;
+      int row = -1;
+#pragma unroll
+      for (int j = 0; j < kLook; ++j) {
+        const unsigned long long bad = __ballot(code[j] != 1 && base + j * kWave + lane < a.B);
+        const uint32_t n = (uint32_t)__popcll(bad), k = rank - before;
+        if (row < 0 && k < n) {
+          const uint32_t mine = __builtin_amdgcn_mbcnt_hi((uint32_t)(bad >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bad, 0u));
+          const unsigned long long at = __ballot(((bad >> lane) & 1ull) && mine == k);
+          row = base + j * kWave + __ffsll((long long)at) - 1;
+        }
+        before += n;
+      }
+      if (row >= 0) return row;
+      seen = before;
     }
-    if (!__syncthreads_or((int)bad)) continue;         // uniform
-    const uint32_t n = (uint32_t)__popc(bad), incl = wave_incl_scan_u32(n);
-    if (lane == kWave - 1) wave_n[wave] = incl;
-    if (tid == 0) n_mine = 0;
-    __syncthreads();
-    uint32_t i = seen + incl - n;
-    for (int w = 0; w < kFinalWaves; ++w) {
-      if (w < wave) i += wave_n[w];
-      seen += wave_n[w];
-    }
-    for (; bad; bad &= bad - 1, ++i)
-      if (i % gridDim.x == blockIdx.x) mine[atomicAdd(&n_mine, 1)] = (unsigned short)((__ffs((int)bad) - 1) * kFinalThreads + tid);
-    __syncthreads();
+    return -1;
+  };
 #pragma nounroll
-    for (int q = 0; q < n_mine; ++q) {
-      rescue_row<DT, SH>(a, base + (int)mine[q], dynraw, ex, fs);
-      __syncthreads();                                 // done with the tables in LDS
-    }
+  for (uint32_t round = 0;; ++round) {
+    const int b = row_of(round * gridDim.x + blockIdx.x);
+    if (b < 0) return;                                 // uniform: all waves have seen the same codes
+    rescue_row<DT, SH>(a, b, dynraw, ex, fs);
+    __syncthreads();                                   // done with the tables in LDS
   }
 }
 
@@ -1256,7 +1260,8 @@ __device__ __attribute__((noinline)) int whole_row_draw(const char* row, const i
 // first read's 64-bit LDS additions.  One row of V = 213087 bf16 whose cut falls among equal values: 1060 ->
 // 261 us for the call (count and mass bins on each of up to three levels, a read to gather at most 256
 // members, a read for the block masses; more equal members than that went to the exact path); eleven rows
-// of V = 44143 fp32, three wide nuclei among them, 144 -> 127.
+// of V = 44143 fp32, three wide nuclei among them, 144 -> 127.  A flat row of V = 213087 bf16: 264, and 232 since
+// the reads take two loads of eight elements at a time instead of four and nothing is spilled.
 template <int DT>
 __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, const int V, const bool has_pen,
                                                            const uint32_t* bm, const unsigned short* pre,
@@ -1268,12 +1273,12 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
   constexpr int NT = kFinalThreads;
   constexpr int EPL = (DT == SIP_F32) ? 4 : 8;
   constexpr int ESZ = (DT == SIP_F32) ? 4 : 2;
-  constexpr int UNR = 4;                                  // loads in flight per thread
+  constexpr int UNR = 16 / EPL;                           // loads in flight per thread (32 elements at once: 230 bytes of scratch a lane)
   constexpr int kLevels = 3;
   constexpr float kSpan = 28.0f;                          // exp(-28) * 2^40 < 1: nothing below has mass
   constexpr int BLK = UNR * kWave * EPL;                  // elements of a block: one wave's loads
   constexpr uint32_t kList = kBins;                       // members listed (key, block) where the bins were
-  static_assert(262144 / (UNR * kWave * 4) <= kBins / 2, "two sums per block in hd[]");
+  static_assert(262144 / BLK <= kBins / 2, "two sums per block in hd[]");
   const RowDivisor by_tau(inv_tau);
   const int e_last = ((V - 1) / EPL) * EPL;
   auto ldrow = [&](int e0) { return *reinterpret_cast<const uint4*>(row + (size_t)min(e0, e_last) * ESZ); };
@@ -1302,8 +1307,8 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
   };
   auto mass = [&](float sv) { return mass_units(__builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(sv, m), 1.44269504f))); };
   auto kept_minp = [&](float sv) { return !minp_on || __fsub_rn(sv, m) >= t_minp; };
-  float lo[kLevels], sc[kLevels];
-  int pick[kLevels];
+  float lo[kLevels] = {m - kSpan, 0.0f, 0.0f}, sc[kLevels] = {};       // (indexed with constants only)
+  int pick[kLevels] = {};
   auto bin_at = [&](int l, float sv) { return min(kBins - 1, max(0, (int)(__fsub_rn(sv, lo[l]) * sc[l]))); };
   // where s lies against the interval of level n (the picked bins of the levels above it): -1 below, 0 in it, 1 above
   auto side = [&](int n, float sv) {
@@ -1317,9 +1322,19 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
   unsigned long long above = 0;                           // mass of everything larger than the current interval
   const int nblk = (V + BLK - 1) / BLK;
   uint32_t key_cut = 0;
+  // One interval: 1 = the cut is found, 0 = it lies among more than kList members, 11 = nothing qualifies.  (One
+  // copy for the first, which settles most rows, and one for all others, with the level in a register: for the
+  // first, that costs a tenth of the time.)
+  auto interval = [&](auto is_first, const int level) -> int {
+    constexpr bool FIRST = decltype(is_first)::value;
+    const float cur_sc = (float)kBins / cur_w;
+    if constexpr (FIRST) {
+      lo[0] = cur_lo; sc[0] = cur_sc;
+    } else {
 #pragma unroll
-  for (int level = 0; level < kLevels; ++level) {
-    lo[level] = cur_lo; sc[level] = (float)kBins / cur_w; pick[level] = 0;
+      for (int l = 1; l < kLevels; ++l)
+        if (l == level) { lo[l] = cur_lo; sc[l] = cur_sc; }
+    }
     // ---- first read: mass per bin of the current interval
     __syncthreads();
     for (int i = tid; i < kBins; i += NT) { hm[i] = 0; hd[i] = 0; }
@@ -1337,9 +1352,9 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
         for (int i = 0; i < EPL; ++i)
           // (who is in the interval, bin_at() alone says: the interval's rounded lower end can lie an ulp above
           // a value of the bin that it was)
-          if (sv[i] >= lo[0] && side(level, sv[i]) == 0) {
+          if (sv[i] >= lo[0] && (FIRST || side(level, sv[i]) == 0)) {
             const unsigned long long E = mass(sv[i]);
-            if (E) atomicAdd(&hm[bin_at(level, sv[i])], E);
+            if (E) atomicAdd(&hm[min(kBins - 1, max(0, (int)(__fsub_rn(sv[i], cur_lo) * cur_sc)))], E);
           }
       }
     }
@@ -1375,8 +1390,15 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
     }
     __syncthreads();
     const int bp = fs.bin_p;
-    if (bp >= kBins) return 11;                           // uniform: nothing qualifies (limit of 0)
-    pick[level] = bp; above = fs.before_d;
+    if (bp >= kBins) return 11;                           // uniform (limit of 0)
+    if constexpr (FIRST) {
+      pick[0] = bp;
+    } else {
+#pragma unroll
+      for (int l = 1; l < kLevels; ++l)
+        if (l == level) pick[l] = bp;
+    }
+    above = fs.before_d;
     // ---- second read: sums per block, members of the bin
     uint2* const list = reinterpret_cast<uint2*>(hm);     // (the bins are done with)
     const int per_wave = (nblk + kFinalWaves - 1) / kFinalWaves;
@@ -1393,7 +1415,7 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
         svals(q[u], base + (u * kWave + lane) * EPL, sv);
 #pragma unroll
         for (int i = 0; i < EPL; ++i) {
-          const int r = sv[i] >= lo[0] && kept_minp(sv[i]) ? side(level + 1, sv[i]) : -1;
+          const int r = sv[i] >= lo[0] && kept_minp(sv[i]) ? side(FIRST ? 1 : level + 1, sv[i]) : -1;
           const unsigned long long E = r >= 0 ? mass(sv[i]) : 0ull;
           A += r > 0 ? E : 0ull;
           const bool member = r == 0 && E != 0;
@@ -1423,7 +1445,7 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
       key_cut = kmin;
       for (int i = tid; i < nblk; i += NT) hd[i] += hd[kBins / 2 + i];
       __syncthreads();
-      break;
+      return 1;
     }
     if (n <= kList) {
       // the smallest key above which the mass stays short of the limit: bisection, kmax being one
@@ -1448,12 +1470,16 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
       for (uint32_t q = tid; q < n; q += NT)
         if (list[q].x >= key_cut) atomicAdd(&hd[list[q].y], mass(value_of(list[q].x)));
       __syncthreads();
-      break;
+      return 1;
     }
-    if (level + 1 == kLevels) return 11;                  // uniform
     cur_w = cur_w * (1.0f / (float)kBins);
-    cur_lo = lo[level] + (float)bp * cur_w;
-  }
+    cur_lo = cur_lo + (float)bp * cur_w;
+    return 0;
+  };
+  int found_cut = interval(std::true_type{}, 0);
+#pragma nounroll
+  for (int level = 1; level < kLevels && found_cut == 0; ++level) found_cut = interval(std::false_type{}, level);       // uniform
+  if (found_cut != 1) return 11;                          // uniform
   // ---- prefix over the blocks, and the block that holds the crossing
   unsigned long long target;
   {
