@@ -40,6 +40,11 @@ constexpr int kFinBPT = kFinBins / kFinThreads;        // bins per thread in the
 constexpr int kFinList = 4352;                         // entries of the bin-sorted list in LDS
 constexpr int kFinHash = 8192;                         // slots of the multiplicity table
 constexpr int kFinHashMax = 6144;                      // distinct history tokens it takes
+// Buckets looked at for one token before the table counts as full.  At kFinHashMax tokens three quarters of the
+// slots are taken, and the longest search is 30 (random tokens, strides, runs of neighbours); a table with no room
+// left costs the tokens that are not in it this many.  (All 2048 buckets: V = 29599 bf16, 7 rows of 8400 distinct
+// tokens, 976 us a call, so 295.)
+constexpr int kFinProbes = 128;
 constexpr int kFinCountBits = 14;                      // a slot: token << 14 | multiplicity (18 + 14 bits), 0 = free
 constexpr uint32_t kFinCountMax = (1u << kFinCountBits) - 1;
 constexpr uint32_t kFinFold = 4096, kFinFolded = 8192; // histories that could outgrow these bits, see note_fold
@@ -300,7 +305,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
       if (ti < 0 || ti >= V) return;
       const uint32_t t = (uint32_t)ti;
       uint32_t bk = home(t);
-      for (int probe = 0; probe < kFinHash / 4 + 64; ++probe) {                // (a bucket may be looked at again)
+      for (int probe = 0; probe < kFinProbes; ++probe) {                       // (a bucket may be looked at again)
         if ((probe & 31) == 31 && fs.hash_fail) return;                        // given up already
         const uint4 q = hslot4[bk];
         const uint32_t x0 = slot_for(q.x, t), x1 = slot_for(q.y, t), x2 = slot_for(q.z, t), x3 = slot_for(q.w, t);
