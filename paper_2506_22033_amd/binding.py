@@ -270,10 +270,17 @@ def _nbytes(t: torch.Tensor) -> int:
     return t.numel() * t.element_size()
 
 
+# (the handle itself: the Stream object that torch.cuda.current_stream() builds around it takes 1.9 us, twice in a
+# decode iteration, ahead of the launches.  Not part of torch's public interface, hence the other way below.)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(dev, stream):
-    # (the handle itself: the Stream object that torch.cuda.current_stream() builds around it takes 1.9 us, twice
-    # in a decode iteration, ahead of the launches)
-    return torch._C._cuda_getCurrentRawStream(dev.index) if stream is None else stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is None:
+        return torch.cuda.current_stream(dev).cuda_stream
+    return _current_raw_stream(dev.index)
 
 
 def sip_state_init(state: torch.Tensor, slots: int, L_max: int,

@@ -340,3 +340,19 @@ def test_a_workspace_sized_for_the_longest_histories_and_largest_batch_serves_sm
             for nnz in (0, 100_000, 4_000_000, 4_540_000, 5_000_000):
                 sizes = [need(B, nnz) for B in range(1, 257)]
                 assert sizes == sorted(sizes), (nnz, [i + 1 for i in range(1, 256) if sizes[i] < sizes[i - 1]])
+
+
+def test_stream_handle_without_the_private_torch_function(monkeypatch):
+    """The current stream's handle is the one that torch's public interface names where torch has no function
+    that gives it without a Stream object."""
+    class Stream:
+        def __init__(self, handle):
+            self.cuda_stream = handle
+    asked = []
+    monkeypatch.setattr(binding.torch.cuda, "current_stream", lambda dev: asked.append(dev) or Stream(77))
+    monkeypatch.setattr(binding, "_current_raw_stream", None)
+    dev = binding.torch.device("cuda", 3)
+    assert binding._stream_handle(dev, None) == 77 and asked == [dev]
+    assert binding._stream_handle(dev, Stream(5)) == 5 and len(asked) == 1
+    monkeypatch.setattr(binding, "_current_raw_stream", lambda index: 100 + index)
+    assert binding._stream_handle(dev, None) == 103 and len(asked) == 1
