@@ -19,9 +19,9 @@
  *    out-of-bounds access: history offsets are clamped to [0, hist_nnz], token ids
  *    outside [0, V) are skipped.
  *  - Concurrent calls are allowed on different streams if they use different workspaces.
- *  - Same inputs, seed, step and row ids in a call of the same shape (B, V, dtype, sharding)
- *    give the same output bits on every call.  In a call of another shape a row's partial sums
- *    are grouped differently: its token id and best-n ids are still the same unless a decision
+ *  - Same inputs, seed, step and row ids in a call of the same shape (B, V, dtype, sharding, with
+ *    or without a state, number of history tokens or L_max) give the same output bits on every
+ *    call.  In a call of another shape a row's partial sums are grouped differently: its token id and best-n ids are still the same unless a decision
  *    of the row lies within rounding of a boundary (a uniform within 1e-6 of a CDF edge), and
  *    its log-probabilities agree within 1e-5 + 2^-22 * |logprob|.
  */
@@ -97,7 +97,7 @@ typedef struct {
  *   single-pass kernels (why = 1: settled from registers all the same).
  *   why: 1 = the finishing kernel (or the one that holds the row) settled it; else why it passed the
  *   row on: 2 no list was made, 3 a chunk's list overflowed, 4 more distinct history tokens than the
- *   table of multiplicities holds, 5 list too long, 6 maximum not proven, 7 value span not representable,
+ *   table of multiplicities holds, 6 maximum not proven, 7 value span not representable,
  *   8 k-th / n-th largest not in the list, 9 too many equal values in one bin, 10 top_p <= 0,
  *   11 nucleus reaches below the list, 12 min-p cut below the list, 13 no filter at all and no masses
  *   of the row's blocks (a list that left no room for them, or logits in pieces),

@@ -1,6 +1,7 @@
 """Nuclei of tens of thousands of tokens, cut and drawn over the whole row: thousands of equal values at the cut, more
 members of its bin than are listed (a second and third interval), penalties and a min-p in the kept set, a list too
-long for its segment on the way."""
+long for its segment on the way.  (Rows in coarse steps are settled on the first interval, the narrow ones on the others; cuts
+on the rounded end of an interval: test_gpu_nucleus_edges.py.)"""
 import numpy as np
 import pytest
 
