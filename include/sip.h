@@ -21,9 +21,10 @@
  *  - Concurrent calls are allowed on different streams if they use different workspaces.
  *  - Same inputs, seed, step and row ids in a call of the same shape (B, V, dtype, sharding, with
  *    or without a state, number of history tokens or L_max) give the same output bits on every
- *    call.  In a call of another shape a row's partial sums are grouped differently: its token id and best-n ids are still the same unless a decision
- *    of the row lies within rounding of a boundary (a uniform within 1e-6 of a CDF edge), and
- *    its log-probabilities agree within 1e-5 + 2^-22 * |logprob|.
+ *    call.  In a call of another shape a row's partial sums are grouped differently: its token
+ *    id and best-n ids are still the same unless a decision of the row lies within rounding of a
+ *    boundary (a uniform within 1e-6 of a CDF edge), and its log-probabilities agree within
+ *    1e-5 + 2^-22 * |logprob|.
  */
 #ifndef SIP_H_
 #define SIP_H_
