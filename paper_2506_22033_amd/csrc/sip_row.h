@@ -6,9 +6,9 @@
 // chunk.  Two workgroups per compute unit: the finishing tables take 70 KB of LDS, and 128 registers a
 // lane pay for four 16-byte loads in flight per tile instead of two.  (One row per compute unit and less:
 // row_rescue_kernel, sip_fused.h.)
-// Measured against the two kernels, us a call: bf16 V = 129280 x 1024 117 -> 104, fp32 V = 256000 x 2048 572 ->
-// 505; 256 rows, one per compute unit: bf16 V = 151643 without a filter 41 -> 35, fp32 V = 152064 52.4 -> 50.
-// What bounds it: 1024 rows as above, vector issue (66 % of the slots; a row's 42 us are 9 set-up, 14
+// Measured against the two kernels, us a call: bf16 V = 129280 x 1024 115.7 -> 110.3, fp32 V = 256000 x 2048 569
+// -> 504; 256 rows, one per compute unit: bf16 V = 151643 without a filter 40.4 -> 36.5, fp32 V = 152064 53.1 -> 51.2.
+// What bounds it: 1024 rows as above, vector issue (61 % of the slots; a row's 42 us are 9 set-up, 14
 // streaming, 5 queues out, 13 finishing); 2048 rows, HBM while it streams (4.2 TB/s over the whole kernel).
 #pragma once
 #include "sip_finish.h"
