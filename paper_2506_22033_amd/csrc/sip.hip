@@ -206,8 +206,11 @@ Plan plan_for(int32_t B, int32_t V, int dtype, int t, int64_t nnz, size_t gather
 // largest need of the batches up to this one that are cut into chunks of one tile counts, and for a
 // history beyond which they give way the built-in scratch's size, which bounds the need up to there.
 size_t workspace_need(int32_t B, int32_t V, int dtype, int t, int64_t nnz, size_t gather_row_bytes = 0) {
+  // (Batches with the same 256 / b have chunks of the same length, and the need grows with b among them: the
+  // largest of each counts, and below 256 / kMaxChunks they are all alike.  One batch after the other, this
+  // took 16 us where a caller leaves the workspace to the binding, V = 24275 bf16 and 255 rows; now 4.)
   size_t need = 0;
-  for (int32_t b = 1; ; ++b) {
+  for (int32_t b = std::min(B, 256 / sip::kMaxChunks); ; b = std::min(B, b < 256 ? 256 / (256 / (b + 1)) : B)) {
     if (b < B && make_plan(b, V, dtype, t).S == make_plan(b, V, dtype, t, false).S) b = B;   // (from here on they all agree)
     bool coarse = false;
     const size_t own = make_layout(b, plan_for(b, V, dtype, t, nnz, gather_row_bytes, &coarse), nnz, gather_row_bytes).total;
