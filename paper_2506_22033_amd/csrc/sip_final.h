@@ -825,7 +825,7 @@ __device__ __attribute__((noinline)) void restream_row(const Args& a, const int 
   const char* row = reinterpret_cast<const char*>(a.logits) + (size_t)b * (size_t)a.row_stride * ESZ;
   uint2* region = a.cand + (size_t)b * (size_t)a.S * (size_t)a.cap_c;
   const uint32_t cap = (uint32_t)(a.S * a.cap_c);
-  const BulkRef ref = make_bulk_ref(Tc, rp);
+  const BulkRef ref = make_bulk_ref(Tc, log2_scale(rp));
   __syncthreads();
   if (tid == 0) fs.rq_n = 0;
   __syncthreads();

@@ -34,9 +34,8 @@ namespace sip {
 constexpr int kStreamThreads = 512;
 constexpr int kStreamWaves = kStreamThreads / kWave;
 static_assert(kStreamWaves == 8, "a chunk's segment is made of eight wave queues");
-constexpr int kSampleBins = 8192;           // 13-bit keys: sign, exponent, 4 mantissa bits
+constexpr int kSampleBins = 8192;           // see sample_bin()
 constexpr int kSampleSize = 8192;           // elements of a row the threshold is estimated from
-constexpr int kTailKeys = 3 * kStreamThreads;         // the three largest sample keys of every thread
 constexpr int kQueueCap = 480;              // entries of one wave's LDS candidate queue
 constexpr int kChunkCap = kStreamWaves * kQueueCap;   // entries of one chunk's segment in the workspace
 constexpr int kChunkBitsMax = 73728;        // most elements a chunk may have (history bitmap: 9 KB of LDS)
@@ -92,8 +91,10 @@ __device__ __forceinline__ RowParams load_row_params(const Args& a, int b) {
 // sample, j = target * (sample size) / V, so the list comes out at target * (1 +- 1/sqrt(j)).
 // Lists of kWholeFrom entries and more are the ones that may outgrow the 4096 entries of the
 // finishing kernel's faster variants (twice the time for that row), so they are estimated from
-// the whole sample of kSampleSize elements as long as that keeps j small (<= kTailRank: a thread
-// then only tracks its three largest values); every other list from every other sample block.
+// the whole sample of kSampleSize elements as long as that keeps j small (<= kTailRank); every other
+// list from every other sample block.  A thread only tracks its three largest values where that finds
+// the j largest, or all but about one in a hundred of them (j <= 3/2 kTailRank): the list then comes
+// out that much longer.
 constexpr int kTailRank = 256;
 constexpr int kWholeFrom = 2048;
 __device__ __forceinline__ bool whole_sample(int target, int V) {
@@ -156,8 +157,8 @@ struct BulkRef {
 // `Tc`: where the threshold should lie; the result's is where it lies (every reader takes that one).
 // At temperatures so small that whatever lies below the threshold has less than 2^-64 of its mass the
 // multiply-add only tells which side an element is on.
-__device__ __forceinline__ BulkRef make_bulk_ref(float Tc, const RowParams& rp) {
-  const double c = log2_scale(rp);
+// `c`: log2_scale() of the row.
+__device__ __forceinline__ BulkRef make_bulk_ref(float Tc, const double c) {
   BulkRef r;
   r.c = (float)c; r.Tc = Tc;
   double tc = (double)Tc * (double)r.c;
@@ -208,21 +209,85 @@ __device__ __forceinline__ unsigned long long bulk_units(float acc) {
   return acc > 0.0f ? (unsigned long long)(acc * kBulkScale) : 0ull;
 }
 
+// The sample's histogram has a bin per value of sign, exponent and 9 mantissa bits for 1/4 <= |z| < 64, in
+// ascending order; what lies beyond joins the outermost bins of that sign.  (With 8 mantissa bits a row of
+// thousands of elements on each of two neighbouring values had both in its list.)
+constexpr uint32_t kBinBase = 125u << 9;               // of 1/4: exponent and mantissa bits
+constexpr int kGroup = 32;                             // bins of a sixteenth of their values
+// (One level.  13-bit keys first and then the found bin split by 5 bits more, by wave 0 from all threads' largest
+// keys, took 2000 to 3000 cycles longer, 1 us of every call: one row of V = 128256 bf16 20.5 -> 19.6 us.)
+__device__ __forceinline__ uint32_t sample_bin(float z) {
+  const uint32_t b = __float_as_uint(z);
+  const int t = min(max((int)((b >> 14) & 0x1FFFFu) - (int)kBinBase, 0), 4095);
+  return ((uint32_t)t | 4096u) ^ ((uint32_t)((int)b >> 31) & 8191u);
+}
+__device__ __forceinline__ bool outermost_bin(uint32_t i) { return ((i + 1u) & 4095u) <= 1u; }
+// Smallest value of bin i (of one that is not an outermost one).
+__device__ __forceinline__ float sample_floor(uint32_t i) {
+  return i >= 4096u ? __uint_as_float((i - 4096u + kBinBase) << 14) : -__uint_as_float(((4096u - i + kBinBase) << 14) - 1u);
+}
 
-// LDS: first the sample histogram (two 16-bit counters per word, 16 KB) and the threads' largest
-// sample keys (6 KB), then, in their place, the per-wave candidate queues (a chunk's: fp32 30 KB, bf16 15 KB; a row's: 44 or 40 KB); then the history
+// A row that top-p or min-p bounds asks for a list that reaches far down (candidate_target()), which a
+// peaked row does not need.  Its sample says how far down is enough: this looks, from the
+// threshold asked for upwards, for the highest group of bins such that in the sample
+//   - at least `least` values lie in it or above (the maximum and the best-n come from the list), and
+//   - min-p keeps nothing below, or the mass below is at most a half (with a penalty on, a quarter) of the
+//     share that top-p leaves out,
+// values below counting as their group's upper end and those above as its lower end.  A few of the row's
+// largest may be history tokens that a penalty takes away, or be in the sample by chance: the fourth (with
+// a penalty on, eighth) largest sample value stands for the maximum, and those above it count as much as
+// it does.  (3400 simulated rows of normal, Student-t, spiked and Zipf logits, p 0.5 to 0.99, min_p 0.02 to
+// 0.1, half of the top tokens penalised: none lost that the long list settles.)  Returns that group (its lower
+// end is the threshold), or G.
+// What it gives, us a call: Student-t logits, lists of 540 instead of 2830 entries, V = 129280 bf16, 1024 rows
+// 110.0 -> 93.3; V = 152064 bf16 in pieces, 200 rows 38.8 -> 34.2; V = 128256 bf16, 32 rows of 8600 tokens under
+// min-p 32.6 -> 27.3.  A row that keeps the long list pays 0.3 for the question.
+// For one wave.  G: group of bins the threshold lies in; above: sample values above
+// that group; c: log2_scale() of the row.
+__device__ __forceinline__ uint32_t raised_group(const uint32_t G, const uint32_t above, const uint32_t* hist, const RowParams& rp,
+                                                 const float c, const bool has_pen, const uint32_t least, const uint32_t n_smp) {
+  constexpr int kUp = 44;                              // lane l has group G + kUp - l
+  const int lane = lane_id(), g = (int)G + kUp - lane;
+  const bool in = g >= 0 && g < kSampleBins / kGroup;
+  const uint4* const h4 = reinterpret_cast<const uint4*>(hist) + kGroup / 8 * min(max(g, 0), kSampleBins / kGroup - 1);
+  uint32_t both = 0;                                   // (both counters of a word at once: 8192 values at most)
+#pragma unroll
+  for (int i = 0; i < kGroup / 8; ++i) { const uint4 q = h4[i]; both += q.x + q.y + q.z + q.w; }
+  const uint32_t n = in ? (both & 0xFFFFu) + (both >> 16) : 0u;
+  auto floor_of = [](int gr) { return sample_floor((uint32_t)(kGroup * max(gr, 0))); };
+  const float z0 = floor_of((int)G);
+  const float x_lo = fminf((floor_of(g) - z0) * c, 100.0f), x_hi = (floor_of(g + 1) - z0) * c;
+  const uint32_t scan = dpp_scan_add_u32(n);
+  const uint32_t beyond = above - min(above, (uint32_t)__builtin_amdgcn_readlane((int)scan, kUp - 1));     // above the lanes' groups
+  const uint32_t n_from = beyond + scan;               // in this group or above
+  const unsigned long long flat = __ballot(in && n_from >= (has_pen ? 8u : 4u));
+  const int at = flat ? __ffsll((long long)flat) - 1 : kWave - 1;
+  const float x_top = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x_lo), at));
+  const float head = (float)beyond * __builtin_amdgcn_exp2f(x_top) + dpp_scan_add_f32(n ? (float)n * __builtin_amdgcn_exp2f(fminf(x_lo, x_top)) : 0.0f);
+  const float up = dpp_scan_add_f32(lane >= at && n ? (float)n * __builtin_amdgcn_exp2f(x_hi) : 0.0f);
+  const float rest = (float)(n_smp - min(n_smp, last_lane_u32(n_from))) *
+                     __builtin_amdgcn_exp2f(__uint_as_float(last_lane_u32(__float_as_uint(x_lo))));
+  const float tail = rest + (__uint_as_float(last_lane_u32(__float_as_uint(up))) - up);
+  const bool by_p = rp.top_p < 1.0f && tail <= (has_pen ? 0.25f : 0.5f) * (1.0f - rp.top_p) * (tail + head);
+  const bool by_minp = rp.min_p > 0.0f && x_lo <= x_top + __log2f(rp.min_p);
+  const unsigned long long ok = __ballot(in && lane >= at && lane < kUp && n_from >= least && (by_p || by_minp));
+  return ok ? G + (uint32_t)(kUp + 1 - __ffsll((long long)ok)) : G;
+}
+
+// LDS: first the sample histogram (two 16-bit counters per word, 16 KB), then, in its
+// place, the per-wave candidate queues (a chunk's: fp32 30 KB, bf16 15 KB; a row's: 44 or 40 KB); then the history
 // bitmap (9 or 32 KB) and the tag words (fp32 256 bytes, bf16 4 KB).
 template <int DT, bool ROW>
 struct __align__(16) StreamShared {
   typedef StreamShape<DT, ROW> Sh;
   static constexpr int kQueueBytes = kStreamWaves * Sh::kQueue * (int)sizeof(typename Sh::entry_t);
-  static constexpr int kFrontBytes = kSampleBins * 2 + kTailKeys * 4 > kQueueBytes ? kSampleBins * 2 + kTailKeys * 4 : kQueueBytes;
+  static constexpr int kFrontBytes = kSampleBins * 2 > kQueueBytes ? kSampleBins * 2 : kQueueBytes;
   unsigned char front[kFrontBytes];
   uint32_t bmw[Sh::kBits / 32];
   uint4 tag_words[Sh::kTags];              // history bits of a load -> what is or-ed into its four words
   unsigned long long blk_mass[Sh::kBlocks];
   union {
-    uint32_t sub_hist[32];                 // the threshold bin, split by the next 5 key bits (dead once it is found)
+    uint32_t sub_hist[32];                 // a bin of 13-bit keys, split by the next 5 key bits (dead once the threshold is found)
     struct {
       unsigned long long red64[kStreamWaves];
       uint32_t red32[kStreamWaves];
@@ -230,7 +295,7 @@ struct __align__(16) StreamShared {
   };
   BulkRef ref;
   uint32_t seg_cnt;                        // entries of the segment so far
-  uint32_t key_thr;                        // the threshold's key: 13 bits, later 18
+  uint32_t key_thr;                        // how the threshold came about, see there
 };
 
 // What a workgroup that finishes its row itself takes from here to there (ROW; all of it uniform).
@@ -361,8 +426,8 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
     return false;
   }
   // ---- threshold: the same 8192-element sample (1 KB blocks spread evenly over the row) is
-  // read by every chunk of the row, so all chunks agree on Tc = the j-th largest sample value
-  // rounded down to an 18-bit key (found in two levels: 13 bits, then 5 more), j / 8192 = target / V
+  // read by every chunk of the row, so all chunks agree on Tc = the lower end of the bin of the j-th
+  // largest sample value, j / 8192 = target / V
   // (for long lists: half of the blocks, j / 4096 = target / V; see whole_sample())
   // All blocks are requested, whether or not the row's rank calls for the whole sample: a branch
   // around a load makes the compiler wait for that load where the branches meet, one exposed
@@ -453,6 +518,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
     };
     sm.tag_words[tid] = make_uint4(word(0), word(1), word(2), word(3));
   }
+  const double scale = log2_scale(rp);     // (worked out while the sample travels)
   if (tid < 32) sm.sub_hist[tid] = 0;
   if (tid < Sh::kBlocks) sm.blk_mass[tid] = 0ull;
   if (tid == 0) sm.seg_cnt = 0;
@@ -461,14 +527,15 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
   // three largest of its values: far fewer LDS atomics, and hardly any on the same word.
   // (Should one thread hold more than three of the j largest, the threshold comes out a
   // little low, which only lengthens the candidate list.)
+  const bool bounded = !rp.greedy && !(rp.top_k >= 2 && rp.top_k < V) && (rp.top_p < 1.0f || rp.min_p > 0.0f);   // by top-p or min-p alone
   const bool whole = whole_sample(target, V);        // workgroup-uniform, like everything about the threshold
   const int n_smp = whole ? kSampleSize : kSampleSize / 2;
   uint32_t want = ((uint32_t)target * (uint32_t)n_smp + (uint32_t)V - 1u) / (uint32_t)V;     // < 2^32: target <= 2^14
   if (want < 2u) want = 2u;
   if (want > (uint32_t)n_smp) want = (uint32_t)n_smp;
   const uint32_t j = want;
-  const bool tail_only = whole || j <= (uint32_t)(kTailRank / 2);
-  uint32_t* const tail_keys = hist + kSampleBins / 2;          // full keys of the threads' three largest sample values
+  const bool tail_only = whole || j <= (uint32_t)(kTailRank + kTailRank / 2);
+  auto count_in = [&](uint32_t bin) { atomicAdd(&hist[bin >> 1], (bin & 1u) ? 0x10000u : 1u); };
   if (tail_only) {
     // the three largest as floats, one maximum and two medians per value
     float f0 = -INFINITY, f1 = -INFINITY, f2 = -INFINITY;
@@ -485,30 +552,21 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
         f0 = fmaxf(f0, x);
       }
     }
-    const uint32_t t0 = key_of(f0), t1 = key_of(f1), t2 = key_of(f2);
-    atomicAdd(&hist[t0 >> 20], ((t0 >> 19) & 1u) ? 0x10000u : 1u);
-    atomicAdd(&hist[t1 >> 20], ((t1 >> 19) & 1u) ? 0x10000u : 1u);
-    atomicAdd(&hist[t2 >> 20], ((t2 >> 19) & 1u) ? 0x10000u : 1u);
-    tail_keys[tid] = t0; tail_keys[kStreamThreads + tid] = t1; tail_keys[2 * kStreamThreads + tid] = t2;
+    count_in(sample_bin(f0)); count_in(sample_bin(f1)); count_in(sample_bin(f2));
   } else {
 #pragma unroll
     for (int l = 0; l < SLOADS; l += 2) {
       float z[EPL];
       unpack(smp[l], z);
 #pragma unroll
-      for (int i = 0; i < EPL; ++i) {
-        const uint32_t k13 = key_of(z[i]) >> 19;
-        atomicAdd(&hist[k13 >> 1], (k13 & 1u) ? 0x10000u : 1u);
-      }
+      for (int i = 0; i < EPL; ++i) count_in(sample_bin(z[i]));
     }
   }
   __syncthreads();
   // ---- wave 0 alone finds the bin of the j-th largest (between barriers of all eight the same took
-  // twice as long); the threshold bin is as wide as 1/16 of its values (and bf16 logits or a
-  // spike-and-bulk row put hundreds of sample values into it), so it is split by the next 5 key bits
-  // and only as many of its sub-bins are taken as the target asks for.
-  uint32_t K = 0, need = 1;                          // wave 0: the bin, and what is still wanted from inside it
-  if (wave == 0) {
+  // twice as long), `need` being what is still wanted from inside it and `above` the values above its
+  // group of bins.
+  auto find_bin = [&](uint32_t& need, uint32_t& above) -> uint32_t {
     constexpr int WPL = kSampleBins / 2 / kWave;     // words per lane (64), lane 0 owning the highest bins
     const uint4* mine = reinterpret_cast<const uint4*>(hist + kSampleBins / 2 - (lane + 1) * WPL);
     uint32_t s = 0;                                  // (both counters of a word at once: 8192 values at most)
@@ -523,44 +581,24 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
     const unsigned long long at2 = __ballot(incl2 >= j);
     const int src2 = at2 ? __ffsll((long long)at2) - 1 : kWave - 1;
     const uint32_t cw = (uint32_t)__builtin_amdgcn_readlane((int)w, src2);
+    static_assert(WPL % (kGroup / 2) == 0, "a lane's words are whole groups");
+    const int ahead = src2 & ~(kGroup / 2 - 1);
+    above = ahead ? (uint32_t)__builtin_amdgcn_readlane((int)incl2, ahead - 1) : run;
     run = (uint32_t)__builtin_amdgcn_readlane((int)incl2, src2) - (cw & 0xFFFFu) - (cw >> 16);
     const bool upper = run + (cw >> 16) >= j;
-    K = 2u * (uint32_t)(kSampleBins / 2 - 1 - src * WPL - src2) + (upper ? 1u : 0u);
     need = j - run - (upper ? 0u : cw >> 16);
-  }
-  {
-    auto enter = [&](uint32_t kf) {
-      if ((kf >> 19) == K) atomicAdd(&sm.sub_hist[(kf >> 14) & 31u], 1u);
-    };
-    if (!tail_only) {
-      if (tid == 0) sm.key_thr = K;
-      __syncthreads();
-      K = sm.key_thr;
-#pragma unroll
-      for (int l = 0; l < SLOADS; l += 2) {
-        float z[EPL];
-        unpack(smp[l], z);
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) enter(key_of(z[i]));
-      }
-      __syncthreads();
-    } else if (wave == 0) {
-      const uint4* k4 = reinterpret_cast<const uint4*>(tail_keys);
-#pragma unroll 2
-      for (int i = 0; i < kTailKeys / 4 / kWave; ++i) { const uint4 k = k4[i * kWave + lane]; enter(k.x); enter(k.y); enter(k.z); enter(k.w); }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    return 2u * (uint32_t)(kSampleBins / 2 - 1 - src * WPL - src2) + (upper ? 1u : 0u);
+  };
+  if (wave == 0) {
+    uint32_t need, above, K = find_bin(need, above);
+    const bool out = outermost_bin(K);
+    if (!out && bounded) {
+      const uint32_t G = raised_group(K / kGroup, above, hist, rp, (float)scale, has_pen,
+                                      max(2u, (512u * (uint32_t)n_smp + (uint32_t)V - 1u) / (uint32_t)V), (uint32_t)n_smp);
+      if (G != K / kGroup) K = G * kGroup;
     }
-    if (wave == 0) {
-      // lane l: sub-bin 31 - l, descending
-      const uint32_t c = lane < 32 ? sm.sub_hist[31 - min(lane, 31)] : 0u;
-      const uint32_t incl = dpp_scan_add_u32(c);
-      const unsigned long long reach = __ballot(lane < 32 && incl >= need);
-      const uint32_t first = reach ? (uint32_t)__ffsll((long long)reach) - 1u : 31u;
-      const uint32_t k18 = (K << 5) | (31u - first);                           // 18-bit key from here on
-      const BulkRef r = make_bulk_ref(value_of(k18 << 14), rp);
-      if (lane == 0) { sm.key_thr = k18; sm.ref = r; }
-    }
+    const BulkRef r = make_bulk_ref(out ? 0.0f : sample_floor(K), scale);
+    if (lane == 0) { sm.key_thr = out ? 1u : 0u; sm.ref = r; }
   }
   if (has_pen && wave > 0) {
     auto mark = [&](int t) {
@@ -590,32 +628,71 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
     mark_all(a.p_tokens, pen.p_lo, pen.p_hi);                                  // separate prompt
   }
   __syncthreads();                                   // also: the histogram is dead from here on
-  // A row that is masked almost everywhere (-inf for all but a few hundred tokens, as a grammar
-  // constraint leaves it) has fewer finite values in its sample than the list asks for, and the
-  // threshold has landed among the -inf (keys up to 511 in 18 bits: -inf and the negative NaNs).
-  // Then the lowest finite sample value is the threshold: the list takes every finite element
-  // from there up, and what lies below it is bulk as usual.  (No finite sample value at all: the
-  // lowest finite float, which makes the finishing kernel pass the row on.)
-  if (sm.key_thr <= 511u) {                                                       // workgroup-uniform
-    float lo = INFINITY;
+  if (sm.key_thr != 0u) {                                                         // workgroup-uniform
+    // The j-th largest lies among the values that the histogram does not tell apart (|z| below 1/4 or from
+    // 64 on, -inf): the same over 13-bit keys (sign, exponent, 4 mantissa bits), the bin that holds it then
+    // split by the next 5.  (Rarely needed, and read again: held until here, the sample costs registers.)
+    auto each_key = [&](auto&& f) {
 #pragma nounroll
-    for (int l = 0; l < SLOADS; ++l) {                 // (read again: held until here, the sample costs registers)
-      float z[EPL];
-      unpack(load_sample(l), z);
+      for (int l = 0; l < SLOADS; l += whole ? 1 : 2) {
+        float z[EPL];
+        unpack(load_sample(l), z);
 #pragma unroll
-      for (int i = 0; i < EPL; ++i)
-        if (z[i] > -INFINITY && z[i] < lo) lo = z[i];
+        for (int i = 0; i < EPL; ++i) f(key_of(z[i]));
+      }
+    };
+    uint4* const z4 = reinterpret_cast<uint4*>(hist);
+    for (int i = tid; i < kSampleBins * 2 / 16; i += kStreamThreads) z4[i] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    each_key([&](uint32_t k) { count_in(k >> 19); });
+    __syncthreads();
+    uint32_t need = 1, above;
+    if (wave == 0) {
+      const uint32_t K = find_bin(need, above);
+      if (lane == 0) sm.key_thr = K;
     }
-    uint32_t klo = last_lane_u32(dpp_scan_min_u32(lo == INFINITY ? 0xFFFFFFFFu : key_of(lo)));
-    if (lane == 0) sm.red32[wave] = klo;
     __syncthreads();
-    klo = sm.red32[0];
+    const uint32_t K = sm.key_thr;
+    each_key([&](uint32_t k) { if ((k >> 19) == K) atomicAdd(&sm.sub_hist[(k >> 14) & 31u], 1u); });
+    __syncthreads();
+    if (wave == 0) {
+      // lane l: sub-bin 31 - l, descending
+      const uint32_t c = lane < 32 ? sm.sub_hist[31 - min(lane, 31)] : 0u;
+      const uint32_t incl = dpp_scan_add_u32(c);
+      const unsigned long long reach = __ballot(lane < 32 && incl >= need);
+      const uint32_t first = reach ? (uint32_t)__ffsll((long long)reach) - 1u : 31u;
+      const uint32_t k18 = (K << 5) | (31u - first);                           // 18-bit key
+      const BulkRef r = make_bulk_ref(value_of(k18 << 14), scale);
+      if (lane == 0) { sm.key_thr = k18; sm.ref = r; }
+    }
+    __syncthreads();
+    // A row that is masked almost everywhere (-inf for all but a few hundred tokens, as a grammar
+    // constraint leaves it) has fewer finite values in its sample than the list asks for, and the
+    // threshold has landed among the -inf (keys up to 511 in 18 bits: -inf and the negative NaNs).
+    // Then the lowest finite sample value is the threshold: the list takes every finite element
+    // from there up, and what lies below it is bulk as usual.  (No finite sample value at all: the
+    // lowest finite float, which makes the finishing kernel pass the row on.)
+    if (sm.key_thr <= 511u) {                                                     // workgroup-uniform
+      float lo = INFINITY;
+#pragma nounroll
+      for (int l = 0; l < SLOADS; ++l) {
+        float z[EPL];
+        unpack(load_sample(l), z);
 #pragma unroll
-    for (int w = 1; w < kStreamWaves; ++w) klo = min(klo, sm.red32[w]);
-    const uint32_t k18 = klo == 0xFFFFFFFFu ? 512u : max(klo >> 14, 512u);
-    __syncthreads();
-    if (tid == 0) sm.ref = make_bulk_ref(value_of(k18 << 14), rp);
-    __syncthreads();
+        for (int i = 0; i < EPL; ++i)
+          if (z[i] > -INFINITY && z[i] < lo) lo = z[i];
+      }
+      uint32_t klo = last_lane_u32(dpp_scan_min_u32(lo == INFINITY ? 0xFFFFFFFFu : key_of(lo)));
+      if (lane == 0) sm.red32[wave] = klo;
+      __syncthreads();
+      klo = sm.red32[0];
+#pragma unroll
+      for (int w = 1; w < kStreamWaves; ++w) klo = min(klo, sm.red32[w]);
+      const uint32_t k18 = klo == 0xFFFFFFFFu ? 512u : max(klo >> 14, 512u);
+      __syncthreads();
+      if (tid == 0) sm.ref = make_bulk_ref(value_of(k18 << 14), scale);
+      __syncthreads();
+    }
   }
   BulkRef ref = sm.ref;
   auto uniform = [](float x) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x))); };

@@ -1,0 +1,51 @@
+"""The threshold of rows that top-p or min-p alone bounds, raised as far as the row's sample allows: peaked rows, rows on
+both sides of the line, rows whose largest tokens a penalty takes away (the list then ends too high, and a second one
+settles the row), logits far from 0 on either side, where a bin of the sample is wide or the outermost one, and samples with few or equal values."""
+import numpy as np
+import pytest
+
+import workloads
+from tests import sip_harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,V,bf16", [(12, 100003, True), (12, 131072, False), (24, 45001, False), (12, 33001, True),
+                                      (240, 70001, True), (300, 36003, True)])
+def test_raised_threshold(B, V, bf16):
+    rng = np.random.default_rng(V + B)
+    kind = np.arange(B) % 12
+    z = rng.standard_normal((B, V)).astype(np.float32) * 2.5
+    hist = [[] for _ in range(B)]
+    for b, k in enumerate(kind):
+        if k in (0, 1, 7):
+            z[b] = rng.standard_t(3, V) * 2.0
+        elif k in (2, 3):
+            z[b, rng.integers(0, V, 8)] += 9.0
+        elif k == 4:
+            z[b] = z[b] * 4.0 + (300.0 if b < 12 else 700.0)       # a group of bins is several powers of e wide; the outermost bin
+        elif k == 5:
+            z[b] = z[b] * 4.0 - 300.0
+        elif k == 6:
+            z[b] = np.where(rng.random(V) < 0.02, np.round(z[b]) + 12.0, -np.inf)   # masked, and many equal values
+        elif k == 8:
+            z[b] = np.round(z[b]) * 2.0                            # a few dozen values
+        elif k == 11:
+            z[b] *= 1e-3                                           # the bins around 0
+        elif k == 9:
+            z[b, :V // 2] = -1e30
+        if k == 7:
+            hist[b] = np.argsort(-z[b])[:V // 100].tolist()        # every token that could be kept is penalised
+        elif k in (1, 3, 10):
+            hist[b] = rng.integers(0, V, 700).tolist()
+    params = dict(temperature=np.choose(kind, [1.0, 0.8, 0.7, 0.6, 0.9, 0.9, 0.5, 1.0, 0.5, 1.0, 0.4, 1.5]),
+                  top_p=np.choose(kind, [0.9, 0.95, 0.95, 1.0, 0.9, 0.8, 0.9, 0.9, 0.5, 0.99, 0.9, 0.3]),
+                  min_p=np.choose(kind, [0, 0, 0, 0.05, 0, 0.01, 0, 0, 0, 0.02, 0.05, 0]),
+                  repetition_penalty=np.choose(kind, [1, 1.2, 1, 1.1, 1, 1, 1, 1.5, 1, 1, 1, 1]),
+                  presence_penalty=np.choose(kind, [0, 0, 0, 0, 0, 0, 0, 30.0, 0, 0, 0.5, 0]))
+    w = H.custom(f"raised_{V}", workloads.f32_to_bf16_bits(z) if bf16 else z, params, hist, k_logprobs=4)
+    d = H.to_device(w)
+    for step in range(4 if B < 30 else 1):
+        H.compare(w, H.run_gpu(d, 23, step), 23, step)
+        # what the raised list must not lose: peaked rows are settled from it
+        assert (H.last_row_why[np.isin(kind, (0, 1, 3))] == 1).all(), H.last_row_why[:12]
