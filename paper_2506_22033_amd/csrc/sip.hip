@@ -31,12 +31,15 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct Plan {
   bool fast;       // false: vocabulary outside what the single-pass kernels are built for
   int S, cap_c, nc_cap;
+  int room;        // segments of kChunkCap entries a row has in the workspace
   size_t final_lds;
 };
 
 // Rows up to here fit the registers of one workgroup (16 waves x 128; sip_resident.h).
 constexpr int kResidentMaxV = SIP_MAX_RESIDENT_V;
 static_assert(kResidentMaxV == 1024 * 32, "the largest variant launched below");
+// Kernels that use more than the default 64 KB of dynamic LDS have to be told so once per device.
+constexpr int kMaxDynLds = 144 * 1024;
 constexpr int kFastMinV = 16384;
 constexpr int kFastMaxV = 262144;
 constexpr int kFastMinPiece = 8192;      // smallest vocabulary shard: its sample blocks (at most 32 of 256 elements) must fit
@@ -51,12 +54,43 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t, bool small_chunks = true)
   if (!p.fast) return p;
   const int tile = dtype == SIP_F32 ? sip::StreamShape<SIP_F32, false>::kTile : sip::StreamShape<SIP_BF16, false>::kTile;
   const int n_tiles = (Vp + tile - 1) / tile * pieces;
-  // Chunks per row.  Up to 256 rows: as many workgroups as fit on the chip at once (4 per compute
-  // unit), so that there is a single, full round.  Larger batches run in rounds of that many
-  // workgroups, and every workgroup pays a fixed set-up (sample, threshold, history bitmap: about
-  // what streaming 38 elements per lane costs) before it streams its V / (S * 512) elements per
-  // lane: take the S with the cheapest rounds x (set-up + stream).
-  constexpr int kResident = 256 * 4;
+  // `n` chunks a row, as the kernels can have them.
+  auto fit = [&](int n) {
+    // A chunk holds at least two tiles; where the batch is small, one: a short bf16 row would else be one or
+    // two chunks, whose queues overflow under a long history.  (V = 24275 bf16, 61 rows of 3034 tokens on a
+    // state, one chunk: half of the rows took the exact path, 254 us; three: 78.)  The workspace grows with
+    // the chunks, so for at most 256 of them.
+    n = std::max(1, std::min({n, sip::kMaxChunks, std::max({1, n_tiles / 2, small_chunks ? std::min(n_tiles, 256 / B) : 0})}));
+    if (n >= pieces) {
+      n = n / pieces * pieces;                           // a chunk is part of one piece: a multiple of their number
+    } else {
+      // a chunk is several whole pieces: the divisor of their number nearest to `n` (by ratio)
+      int best = pieces;
+      for (int dv = 1; dv <= pieces; ++dv)
+        if (pieces % dv == 0) {
+          const double r0 = std::fabs(std::log((double)best / n)), r1 = std::fabs(std::log((double)dv / n));
+          if (r1 < r0 || (r1 == r0 && dv > best)) best = dv;
+        }
+      n = best;
+    }
+    // the streaming kernel marks a chunk's history tokens in an LDS bitmap of kChunkBitsMax bits:
+    // cut finer (first at the piece boundaries, then inside the pieces) until a chunk fits
+    const int unit = sip::kChunkUnit;
+    const int n_units = (Vp + unit - 1) / unit;
+    auto max_chunk = [&](int S) {
+      return S >= pieces ? (n_units + S / pieces - 1) / (S / pieces) * unit : pieces / S * Vp;
+    };
+    while (max_chunk(n) > sip::kChunkBitsMax) {
+      n = n >= pieces ? n + pieces : pieces;
+      if (n > sip::kMaxChunks) return 0;
+    }
+    return n;                                            // <= n_tiles
+  };
+  // Room in the workspace.  Up to 256 rows: for as many chunks as fit on the chip at once, 4 per compute
+  // unit.  Larger batches run in rounds of that many workgroups, and every workgroup pays a fixed set-up
+  // (sample, threshold, history bitmap: about what streaming 38 elements per lane costs) before it
+  // streams its V / (S * 512) elements per lane: the S with the cheapest rounds x (set-up + stream).
+  constexpr int kUnits = 256, kResident = kUnits * 4;
   int want;
   if (B * 4 <= kResident) {
     want = kResident / B;
@@ -70,42 +104,34 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t, bool small_chunks = true)
       if (S == 2 || cost < best_cost) { best_cost = cost; want = S; }
     }
   }
-  // A chunk holds at least two tiles; where the batch is small, one: a short bf16 row would else be one or
-  // two chunks, whose queues overflow under a long history.  (V = 24275 bf16, 61 rows of 3034 tokens on a
-  // state, one chunk: half of the rows took the exact path, 254 us; three: 78.)  The workspace grows with
-  // the chunks, so for at most 256 of them.
-  want = std::max(1, std::min({want, sip::kMaxChunks, std::max({1, n_tiles / 2, small_chunks ? std::min(n_tiles, 256 / B) : 0})}));
-  if (want >= pieces) {
-    want = want / pieces * pieces;                     // a chunk is part of one piece: a multiple of their number
-  } else {
-    // a chunk is several whole pieces: the divisor of their number nearest to `want` (by ratio)
-    int best = pieces;
-    for (int dv = 1; dv <= pieces; ++dv)
-      if (pieces % dv == 0) {
-        const double r0 = std::fabs(std::log((double)best / want)), r1 = std::fabs(std::log((double)dv / want));
-        if (r1 < r0 || (r1 == r0 && dv > best)) best = dv;
-      }
-    want = best;
-  }
-  // the streaming kernel marks a chunk's history tokens in an LDS bitmap of kChunkBitsMax bits:
-  // cut finer (first at the piece boundaries, then inside the pieces) until a chunk fits
-  {
-    const int unit = sip::kChunkUnit;
-    const int n_units = (Vp + unit - 1) / unit;
-    auto max_chunk = [&](int S) {
-      return S >= pieces ? (n_units + S / pieces - 1) / (S / pieces) * unit : pieces / S * Vp;
-    };
-    while (max_chunk(want) > sip::kChunkBitsMax) {
-      const int next = want >= pieces ? want + pieces : pieces;
-      if (next > sip::kMaxChunks) { p.fast = false; return p; }
-      want = next;
+  p.room = p.S = fit(want);
+  if (p.S == 0) { p.fast = false; return p; }
+  // Chunks per row.  Up to 256 rows the room's worth of chunks is often too many: each pays the set-up, and what
+  // counts is how many a compute unit gets.  With w of them its time grows as w * (set-up + stream), the set-up
+  // being worth 32 KB of the row, and a compute unit that has only one streams at 4/5 of the speed.  us a call, at 1024
+  // workgroups / at 256 / as chosen: V = 128256 fp32, 64 rows 27.5 / 23.2 / 23.2, 128 rows 29.6 / 27.7 / 27.0; bf16, 64
+  // rows 23.1 / 22.1 / 22.1, 128 rows 29.6 / 26.3 / 26.8; V = 200000 fp32, 128 rows 32.8 / - / 31.5; bf16 31.8 / - / 29.5.
+  int load = 4;                                          // chunks of a compute unit
+  if (B <= kUnits) {
+    const double set_up = dtype == SIP_F32 ? 8192.0 : 16384.0;                 // in elements
+    double best_cost = 0.0;
+    const int room = p.room;
+    for (int w = 1; w <= 4; ++w) {
+      const int S = w * kUnits >= B ? fit(w * kUnits / B) : 0;
+      if (S == 0 || S > room) continue;
+      const int per_unit = (B * S + kUnits - 1) / kUnits;
+      const double cost = per_unit * (set_up + (per_unit == 1 ? 1.25 : 1.0) * V / S);
+      if (best_cost == 0.0 || cost < best_cost) { best_cost = cost; p.S = S; load = per_unit; }
     }
   }
-  p.S = want;                                          // <= n_tiles
-  p.cap_c = sip::kChunkCap;
+  // Fewer chunks share the row's room in the workspace and their compute unit's LDS: longer queues and segments.
+  constexpr int kTables = sip::stream_lds_bytes<SIP_F32>(sip::kQueueCap) - sip::kChunkCap * (int)sizeof(uint2);
+  const int lds = std::min(kMaxDynLds, 160 * 1024 / load);
+  const int queue = std::min(sip::kQueueCap * p.room / p.S, (lds - kTables) / (sip::kStreamWaves * (int)sizeof(uint2))) / 32 * 32;
+  p.cap_c = sip::kStreamWaves * std::max(queue, sip::kQueueCap);
   // the longest list a row may have: what the heavier per-row logic holds in registers, and what
   // the row's chunks can hand over
-  p.nc_cap = std::min(sip::kFinalThreads * sip::kCandLong, p.S * sip::kChunkCap);
+  p.nc_cap = std::min(sip::kFinalThreads * sip::kCandLong, p.S * p.cap_c);
   p.final_lds = sip::final_lds_fixed(V);
   return p;
 }
@@ -116,8 +142,6 @@ struct Layout {
 
 thread_local hipEvent_t g_prof[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};   // one-shot, see sip_profile_kernel_events()
 
-// Kernels that use more than the default 64 KB of dynamic LDS have to be told so once per device.
-constexpr int kMaxDynLds = 144 * 1024;
 constexpr int kMaxDevices = 64;
 constexpr int kRescueGrid = 256;         // workgroups of the rescue kernel (one per compute unit)
 
@@ -147,7 +171,9 @@ DeviceSetup* device_setup() {
       reinterpret_cast<const void*>(sip::exact_kernel<SIP_F32, false>), reinterpret_cast<const void*>(sip::exact_kernel<SIP_BF16, false>),
       reinterpret_cast<const void*>(sip::exact_kernel<SIP_F32, true>),  reinterpret_cast<const void*>(sip::exact_kernel<SIP_BF16, true>),
       reinterpret_cast<const void*>(sip::rescue_kernel<SIP_F32, false>), reinterpret_cast<const void*>(sip::rescue_kernel<SIP_BF16, false>),
-      reinterpret_cast<const void*>(sip::rescue_kernel<SIP_F32, true>),  reinterpret_cast<const void*>(sip::rescue_kernel<SIP_BF16, true>)};
+      reinterpret_cast<const void*>(sip::rescue_kernel<SIP_F32, true>),  reinterpret_cast<const void*>(sip::rescue_kernel<SIP_BF16, true>),
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, false>), reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, false>),
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, true>),  reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, true>)};
   for (const void* k : big)
     if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds) != hipSuccess) {
       (void)hipGetLastError();
@@ -180,9 +206,9 @@ Layout make_layout(int32_t B, const Plan& p, int64_t nnz, size_t gather_row_byte
   l.rowinfo = off;
   if (p.fast) off += align_up((size_t)B * sizeof(sip::RowInfo));
   l.chunks = off;
-  if (p.fast) off += align_up((size_t)B * p.S * sizeof(sip::ChunkOut));
+  if (p.fast) off += align_up((size_t)B * p.room * sizeof(sip::ChunkOut));
   l.cand = off;
-  if (p.fast) off += align_up((size_t)B * p.S * (size_t)p.cap_c * sizeof(uint2));
+  if (p.fast) off += align_up((size_t)B * p.room * (size_t)sip::kChunkCap * sizeof(uint2));
   l.gather = off; off += align_up((size_t)B * gather_row_bytes);
   l.total = off ? off : kAlign;
   return l;
@@ -196,7 +222,7 @@ Plan plan_for(int32_t B, int32_t V, int dtype, int t, int64_t nnz, size_t gather
   if (make_layout(B, p, nnz, gather_row_bytes).total <= kNoallocBytes) return p;
   const Plan two = make_plan(B, V, dtype, t, false);
   const bool give_way = make_layout(B, two, nnz, gather_row_bytes).total <= kNoallocBytes;
-  if (coarse) *coarse = give_way && two.S != p.S;
+  if (coarse) *coarse = give_way && two.room != p.room;
   return give_way ? two : p;
 }
 
@@ -211,7 +237,7 @@ size_t workspace_need(int32_t B, int32_t V, int dtype, int t, int64_t nnz, size_
   // took 16 us where a caller leaves the workspace to the binding, V = 24275 bf16 and 255 rows; now 4.)
   size_t need = 0;
   for (int32_t b = std::min(B, 256 / sip::kMaxChunks); ; b = std::min(B, b < 256 ? 256 / (256 / (b + 1)) : B)) {
-    if (b < B && make_plan(b, V, dtype, t).S == make_plan(b, V, dtype, t, false).S) b = B;   // (from here on they all agree)
+    if (b < B && make_plan(b, V, dtype, t).room == make_plan(b, V, dtype, t, false).room) b = B;   // (from here on they all agree)
     bool coarse = false;
     const size_t own = make_layout(b, plan_for(b, V, dtype, t, nnz, gather_row_bytes, &coarse), nnz, gather_row_bytes).total;
     need = std::max(need, coarse ? kNoallocBytes : own);
@@ -272,24 +298,28 @@ bool resident_is_chosen(const sip::Args& a, int32_t B, bool state, int compute_u
 // finishing kernel.  A row to a workgroup pays the set-up once and overlaps one row's finishing with
 // another's streaming, or at least needs no second kernel; but up to one row per compute unit it leaves
 // chip idle that chunks would use, and beyond that the rows come in rounds of two per compute unit.
-// us a call in chunks / a row to a workgroup (256 compute units; nucleus 0.95 or no filter):
-//   V = 40000 bf16 (80 KB): 96 rows 23 / 23, 160 27 / 23, 300 36 / 33, 640 51 / 50, 2048 115 / 108
-//   V = 128256 bf16 (256 KB): 96 28 / 30, 128 31 / 30, 160 32 / 31, 256 34 / 31, 300 44 / 46, 512 49 / 48, 1024 87 / 84, 2048 178 / 159
-//   V = 128256 fp32 (513 KB): 192 35 / 35, 224 39 / 37, 384 56 / 58, 768 114 / 101, 2048 277 / 240
-//   V = 262144 fp32 (1 MB): 128 39 / 47, 224 57 / 54, 300 78 / 90, 512 127 / 120, 2048 486 / 425
-//   V = 100000 and 200000, both types: 420 to 500 rows 0 to 11 % less, 520 8 % more to 4 % less, 600 2 % more
+// us a call in chunks / a row to a workgroup (256 compute units; nucleus 0.95, Student-t, 600 tokens):
+//   V = 40000 bf16 (80 KB): 64 rows 19.7 / 20.1, 96 21.0 / 20.2, 256 25.0 / 20.9; fp32 (160 KB): 96 21.6 / 21.5, 128 22.0 / 21.8
+//   V = 128256 bf16 (256 KB): 128 26.3 / 28.0, 144 28.1 / 28.1, 176 30.0 / 28.3, 256 32.5 / 28.7
+//   V = 128256 fp32 (513 KB): 160 29.3 / 32.4, 192 31.8 / 32.5, 200 33.4 / 33.0, 256 36.8 / 35.6
+//   V = 200000 bf16 (400 KB): 144 31.2 / 33.3, 192 33.4 / 33.7, 224 36.6 / 33.7; fp32 (800 KB): 160 35.9 / 40.1, 192 41.0 / 40.8, 224 49.5 / 45.0
+//   (without a filter 192 rows 38.1 / 39.8 bf16, 44.6 / 50.6 fp32; 224 always a row to a workgroup)
+//   V = 110000 bf16 380 rows 41.2 / 41.2, fp32 53.7 / 52.4; V = 152064 bf16 300 44.5 / 46.6, 380 49.8 / 46.9, fp32 380 72.4 / 65.1; V = 230000
+//   fp32 380 95.4 / 92.6
+//   V = 100000 and 200000, both types: 520 rows 8 % more to 4 % less, 600 2 % more
 //   to 8 % less, 700 and 1030 2 to 17 % less.
-// So up to one row per compute unit from a number of rows on that grows with the row's bytes, to 7/8 of
-// the compute units; above, not in the first half of a round -- unless the row is short -- but in the
-// third and later rounds always.  A state's call would have to take its number in a launch of its own
+// So up to one row per compute unit from a number of rows on that grows with the row's bytes, to 3/4 of
+// the compute units (where three chunks to a compute unit no longer fit the batch); above, not in the first
+// part of a round -- unless the row is short -- but in the third and later rounds always.  A state's call
+// would have to take its number in a launch of its own
 // ahead of it (V = 152064, 256 rows: 74 / 73 bf16, 81 / 82 fp32; 520 rows 108 / 113, 136 / 139; 1030
 // 161 / 155, 220 / 205).
 bool row_is_chosen(int32_t B, int32_t V, int dtype, bool state, int compute_units) {
   const int64_t row_bytes = (int64_t)V * (dtype == SIP_F32 ? 4 : 2), cu = compute_units;
   if (state) return B >= 4 * cu;
-  if (B <= cu) return B >= std::min(cu * 7 / 8, cu * 3 / 8 + row_bytes / 4096);
+  if (B <= cu) return B > std::min(cu * 3 / 4, cu * 3 / 16 + row_bytes / 2200);
   if (row_bytes <= 200 * 1024) return true;
-  return B <= 2 * cu ? B >= cu * 25 / 16 : B >= cu * 75 / 32;
+  return B <= 2 * cu ? B >= cu * 23 / 16 : B >= cu * 75 / 32;
 }
 
 // Argument checks common to the entry points, workspace carving and the kernel launches.
@@ -429,6 +459,8 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
   a.one_seg = row_is_chosen(B, a.V, dtype, state, dev->compute_units);
   if (a.one_seg) {
     // the row's workgroup streams and finishes it, and the rescue kernel is behind it
+    a.S = plan.room; a.cap_c = sip::kChunkCap;       // (one segment of them all)
+    a.nc_cap = std::min(sip::kFinalThreads * sip::kCandLong, a.S * a.cap_c);
     if (state) hipLaunchKernelGGL(sip::state_take_tick_kernel, dim3(1), dim3(64), 0, stream, head, a.call_tick);
     if (fused) {
       auto k_both = dtype == SIP_F32 ? sip::row_rescue_kernel<SIP_F32, SH> : sip::row_rescue_kernel<SIP_BF16, SH>;
@@ -454,8 +486,10 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
     }
     return hipGetLastError() == hipSuccess ? SIP_OK : SIP_ERR_HIP;
   }
-  if (timed) hipExtLaunchKernelGGL(k_stream, dim3(B * plan.S), dim3(sip::kStreamThreads), 0, stream, ev[0], ev[1], 0, a);
-  else hipLaunchKernelGGL(k_stream, dim3(B * plan.S), dim3(sip::kStreamThreads), 0, stream, a);
+  const uint32_t stream_lds = (uint32_t)(dtype == SIP_F32 ? sip::stream_lds_bytes<SIP_F32>(plan.cap_c / sip::kStreamWaves)
+                                                        : sip::stream_lds_bytes<SIP_BF16>(plan.cap_c / sip::kStreamWaves));
+  if (timed) hipExtLaunchKernelGGL(k_stream, dim3(B * plan.S), dim3(sip::kStreamThreads), stream_lds, stream, ev[0], ev[1], 0, a);
+  else hipLaunchKernelGGL(k_stream, dim3(B * plan.S), dim3(sip::kStreamThreads), stream_lds, stream, a);
   if (fused) {
     auto k_fused = dtype == SIP_F32 ? sip::finish_rescue_kernel<SIP_F32, SH> : sip::finish_rescue_kernel<SIP_BF16, SH>;
     if (timed) {             // the events take the dispatches' own begin / end time stamps

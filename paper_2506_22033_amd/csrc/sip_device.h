@@ -77,7 +77,7 @@ struct Args {
   uint2* cand;              // [B * S * cap_c]  (value bits, index | tag): one segment per chunk
   int bf16;                 // the logits' type, for kernels that are not instantiated for each
   int S;                    // chunks per row
-  int cap_c;                // list entries per chunk segment
+  int cap_c;                // list entries per chunk segment: eight wave queues
   int nc_cap;               // longest list any finishing path can hold
   int* row_path;            // [B] diagnostic: 1 = finished by the single-pass path, >1 = exact path (reason)
   int* row_why;             // [B] diagnostic: 1, or why the finishing kernel left the row to the rescue kernel

@@ -22,7 +22,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   const Args& a = *(const Args*)__builtin_amdgcn_kernarg_segment_ptr();
   warm_kernel_arguments();
   static_assert(kStreamThreads == kFinThreads, "one workgroup shape for both parts");
-  __shared__ union __align__(16) Both { StreamShared<DT, true> stream; FinShared fin; __device__ Both() {} } u;
+  __shared__ union __align__(16) Both { RowStreamShared<DT> stream; FinShared fin; __device__ Both() {} } u;
   static_assert(sizeof(u) <= 80 * 1024, "two workgroups per compute unit");
   // Workgroups go to the 8 XCDs round-robin by their id.  Every eight rows are dealt out turned by one
   // against the eight before, so that a batch whose rows alternate (every other one greedy, say) loads
@@ -32,7 +32,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   if (b < (a.B & ~7)) b = (b & ~7) | ((b + (b >> 3)) & 7);
   RowHand hand;
   int code = 2;
-  if (stream_part<DT, SH, true>(a, b, u.stream, &hand)) {                      // uniform
+  if (stream_part<DT, SH, true>(a, b, u.stream.front, u.stream.tables, &hand)) {                      // uniform
     __syncthreads();                       // the list is written, and the tables are free
     code = finish_row<true>(a, b, u.fin, nullptr, &hand);
   }

@@ -36,8 +36,8 @@ constexpr int kStreamWaves = kStreamThreads / kWave;
 static_assert(kStreamWaves == 8, "a chunk's segment is made of eight wave queues");
 constexpr int kSampleBins = 8192;           // see sample_bin()
 constexpr int kSampleSize = 8192;           // elements of a row the threshold is estimated from
-constexpr int kQueueCap = 480;              // entries of one wave's LDS candidate queue
-constexpr int kChunkCap = kStreamWaves * kQueueCap;   // entries of one chunk's segment in the workspace
+constexpr int kQueueCap = 480;              // entries of one wave's LDS candidate queue where four workgroups share a compute unit
+constexpr int kChunkCap = kStreamWaves * kQueueCap;   // entries of such a chunk's segment in the workspace
 constexpr int kChunkBitsMax = 73728;        // most elements a chunk may have (history bitmap: 9 KB of LDS)
 constexpr int kRowBitsMax = 262144;         // and a row that one workgroup streams (32 KB)
 // What differs between a workgroup that streams one chunk of a row for the finishing kernel (ROW =
@@ -49,7 +49,7 @@ struct StreamShape {
   static constexpr int kLoads = ROW ? 4 : 2;                           // 16-byte loads per thread per tile, of which two are held
   static constexpr int kTile = kStreamThreads * kLoads * EPL;
   typedef typename std::conditional<DT == SIP_F32, uint2, uint32_t>::type entry_t;      // of a queue, see `process`
-  static constexpr int kQueue = ROW ? (DT == SIP_F32 ? 704 : 1280) : kQueueCap;         // entries of one wave's queue
+  static constexpr int kQueue = DT == SIP_F32 ? 704 : 1280;             // ROW: entries of one wave's queue (chunks: an eighth of Args::cap_c)
   static constexpr int kTags = 1 << EPL;                               // history bits of one load
   static constexpr int kBits = ROW ? kRowBitsMax : kChunkBitsMax;      // most elements a workgroup streams
   static constexpr int kBlocks = kBits / kBlkElems;
@@ -278,12 +278,9 @@ __device__ __forceinline__ uint32_t raised_group(const uint32_t G, const uint32_
 // place, the per-wave candidate queues (a chunk's: fp32 30 KB, bf16 15 KB; a row's: 44 or 40 KB); then the history
 // bitmap (9 or 32 KB) and the tag words (fp32 256 bytes, bf16 4 KB).
 template <int DT, bool ROW>
-struct __align__(16) StreamShared {
+struct __align__(16) StreamTables {
   typedef StreamShape<DT, ROW> Sh;
-  static constexpr int kQueueBytes = kStreamWaves * Sh::kQueue * (int)sizeof(typename Sh::entry_t);
-  static constexpr int kFrontBytes = kSampleBins * 2 > kQueueBytes ? kSampleBins * 2 : kQueueBytes;
-  unsigned char front[kFrontBytes];
-  uint32_t bmw[Sh::kBits / 32];
+  uint32_t bmw[Sh::kBits / 32];            // (first: a queue that overflows may write up to 4 KB past the last wave's end)
   uint4 tag_words[Sh::kTags];              // history bits of a load -> what is or-ed into its four words
   unsigned long long blk_mass[Sh::kBlocks];
   union {
@@ -297,6 +294,21 @@ struct __align__(16) StreamShared {
   uint32_t seg_cnt;                        // entries of the segment so far
   uint32_t key_thr;                        // how the threshold came about, see there
 };
+// Bytes ahead of them: the histogram, later queues of `cap` entries.
+template <int DT, bool ROW>
+__host__ __device__ constexpr int stream_front_bytes(int cap) {
+  const int q = kStreamWaves * cap * (int)sizeof(typename StreamShape<DT, ROW>::entry_t);
+  return q > kSampleBins * 2 ? q : kSampleBins * 2;
+}
+template <int DT>
+constexpr int stream_lds_bytes(int cap) { return stream_front_bytes<DT, false>(cap) + (int)sizeof(StreamTables<DT, false>); }
+static_assert(stream_lds_bytes<SIP_F32>(kQueueCap) <= 40 * 1024 && stream_lds_bytes<SIP_BF16>(kQueueCap) <= 40 * 1024, "four workgroups per compute unit");
+static_assert(stream_lds_bytes<SIP_F32>(2 * kQueueCap) <= 80 * 1024, "two with queues of twice the length");
+template <int DT>
+struct __align__(16) RowStreamShared {
+  unsigned char front[stream_front_bytes<DT, true>(StreamShape<DT, true>::kQueue)];
+  StreamTables<DT, true> tables;
+};
 
 // What a workgroup that finishes its row itself takes from here to there (ROW; all of it uniform).
 constexpr int kRowRegs = 10;               // list entries a thread holds in registers
@@ -308,9 +320,11 @@ struct RowHand {
   uint2 list[kRowRegs];                    // (per thread)
 };
 
-// Streams chunk wg % S of row wg / S (ROW: row wg).  False: the row cannot be finished from a list.
+// Streams chunk wg % S of row wg / S (ROW: row wg).  False: the row cannot be finished from a list.  `front` and `sm`: LDS,
+// one behind the other.
 template <int DT, bool SH, bool ROW>
-__device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamShared<DT, ROW>& sm, RowHand* hand) {
+__device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigned char* const front, StreamTables<DT, ROW>& sm,
+                                            RowHand* hand) {
   typedef StreamShape<DT, ROW> Sh;
   typedef typename Sh::entry_t entry_t;
   constexpr int EPL = Sh::EPL;
@@ -321,7 +335,8 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
   constexpr int SLOADS = kSampleSize / SUB;         // sample loads per thread (4 fp32, 2 bf16)
   constexpr int NSB = SLOADS * kStreamWaves;        // 1 KB sample blocks spread over the row
   uint32_t* const bmw = sm.bmw;
-  uint32_t* const hist = reinterpret_cast<uint32_t*>(sm.front);
+  uint32_t* const hist = reinterpret_cast<uint32_t*>(front);
+  const int queue_cap = ROW ? Sh::kQueue : a.cap_c / kStreamWaves;
 
   // (the wave's number, and further down r0, in a scalar register: as vector registers they were
   // spilled, and a store to scratch ahead of the loads makes every wait for one of them a wait for
@@ -699,7 +714,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
   ref.Tc = uniform(ref.Tc); ref.c = uniform(ref.c); ref.off = uniform(ref.off);
 
   // ---- stream
-  entry_t* const queue = reinterpret_cast<entry_t*>(sm.front) + wave * Sh::kQueue;   // this wave's LDS queue
+  entry_t* const queue = reinterpret_cast<entry_t*>(front) + wave * queue_cap;       // this wave's LDS queue
   const unsigned char* bm8 = reinterpret_cast<const unsigned char*>(bmw);
   uint32_t qn = 0;                          // wave-uniform: list entries in the queue
   float acc = 0.0f;                         // this thread's bulk mass, fixed order of additions
@@ -740,7 +755,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
     const uint32_t place = DT == SIP_F32 ? (uint32_t)(e0 + EPL - 1) + (SH ? ib : 0u) : ((uint32_t)it << 9) | ((uint32_t)lane << 3) | 7u;
     // (a queue that is full is looked at once per load: what it gets beyond its room lies in the next
     // waves' or in the bitmap, and the chunk is given up)
-    if (__builtin_amdgcn_readfirstlane((int)qn) <= Sh::kQueue) {
+    if (__builtin_amdgcn_readfirstlane((int)qn) <= queue_cap) {
       for (;;) {
         const unsigned long long mask = __ballot(hits != 0);
         if (!mask) break;
@@ -805,7 +820,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
   };
   // A queue goes out to the segment, behind what other queues have put there so far (in the order in
   // which the waves get here).
-  const uint32_t seg_cap = ROW ? (uint32_t)(a.S * kChunkCap) : (uint32_t)kChunkCap;
+  const uint32_t seg_cap = (uint32_t)(ROW ? a.S * a.cap_c : a.cap_c);
   uint2* const seg = a.cand + (size_t)wg * (size_t)seg_cap;
   const int lpp = NL * ((c1 - c0 + TILE - 1) / TILE);                          // load numbers of one piece
   bool lost = false;                        // wave-uniform: the queue overflowed
@@ -826,8 +841,8 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
   };
   uint32_t n_flushed = 0;                   // entries that went out ahead of the end
   auto queue_place = [&](uint32_t& n_out) -> uint32_t {
-    n_out = min((uint32_t)__builtin_amdgcn_readfirstlane((int)qn), (uint32_t)Sh::kQueue);
-    lost |= qn > (uint32_t)Sh::kQueue;
+    n_out = min((uint32_t)__builtin_amdgcn_readfirstlane((int)qn), (uint32_t)queue_cap);
+    lost |= qn > (uint32_t)queue_cap;
     uint32_t at = 0;
     if (lane == 0) at = atomicAdd(&sm.seg_cnt, n_out);
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
@@ -964,14 +979,13 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, StreamS
 
 template <int DT, bool SH>
 __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void stream_kernel(Args a) {
-  __shared__ StreamShared<DT, false> sm;
-  static_assert(sizeof(sm) <= 40 * 1024, "four workgroups per compute unit");
+  extern __shared__ __align__(16) unsigned char stream_lds[];                  // stream_lds_bytes()
   // Workgroups are handed to the 8 XCDs round-robin by their id.  The chunks of one row read
   // the same sample, so they are renumbered to land on the same XCD (and its L2): id i works
   // on logical chunk (i % 8) * (n / 8) + i / 8 when n, the grid size, is a multiple of 8.
   int wg = blockIdx.x;
   if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-  stream_part<DT, SH, false>(a, wg, sm, nullptr);
+  stream_part<DT, SH, false>(a, wg, stream_lds, *reinterpret_cast<StreamTables<DT, false>*>(stream_lds + stream_front_bytes<DT, false>(a.cap_c / kStreamWaves)), nullptr);
 }
 
 }  // namespace sip
