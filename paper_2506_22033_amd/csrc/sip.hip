@@ -172,8 +172,10 @@ DeviceSetup* device_setup() {
       reinterpret_cast<const void*>(sip::exact_kernel<SIP_F32, true>),  reinterpret_cast<const void*>(sip::exact_kernel<SIP_BF16, true>),
       reinterpret_cast<const void*>(sip::rescue_kernel<SIP_F32, false>), reinterpret_cast<const void*>(sip::rescue_kernel<SIP_BF16, false>),
       reinterpret_cast<const void*>(sip::rescue_kernel<SIP_F32, true>),  reinterpret_cast<const void*>(sip::rescue_kernel<SIP_BF16, true>),
-      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, false>), reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, false>),
-      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, true>),  reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, true>)};
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, false, false>), reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, false, false>),
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, true, false>),  reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, true, false>),
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, false, true>),  reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, false, true>),
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, true, true>),   reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, true, true>)};
   for (const void* k : big)
     if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds) != hipSuccess) {
       (void)hipGetLastError();
@@ -446,7 +448,9 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
     return SIP_OK;
   }
   a.call_tick = state ? a.tick_room : nullptr;   // the streaming kernel takes the state's counter and leaves it here
-  auto k_stream = dtype == SIP_F32 ? sip::stream_kernel<SIP_F32, SH> : sip::stream_kernel<SIP_BF16, SH>;
+  const bool ids = a.k_lp < 0;                   // token ids only
+  auto k_stream = dtype == SIP_F32 ? (ids ? sip::stream_kernel<SIP_F32, SH, true> : sip::stream_kernel<SIP_F32, SH, false>)
+                                   : (ids ? sip::stream_kernel<SIP_BF16, SH, true> : sip::stream_kernel<SIP_BF16, SH, false>);
   auto k_rescue = dtype == SIP_F32 ? sip::rescue_kernel<SIP_F32, SH> : sip::rescue_kernel<SIP_BF16, SH>;
   const size_t dyn = std::max(plan.final_lds, 2 * words * sizeof(uint32_t));
   // A row streamed and finished by one workgroup, or the pass over the logits in chunks, then one
@@ -473,7 +477,8 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
       }
       return hipGetLastError() == hipSuccess ? SIP_OK : SIP_ERR_HIP;
     }
-    auto k_row = dtype == SIP_F32 ? sip::row_kernel<SIP_F32, SH> : sip::row_kernel<SIP_BF16, SH>;
+    auto k_row = dtype == SIP_F32 ? (ids ? sip::row_kernel<SIP_F32, SH, true> : sip::row_kernel<SIP_F32, SH, false>)
+                                  : (ids ? sip::row_kernel<SIP_BF16, SH, true> : sip::row_kernel<SIP_BF16, SH, false>);
     const int n_rescue_wg = std::min<int>(B, kRescueGrid);
     if (timed) {
       hipExtLaunchKernelGGL(k_row, dim3(B), dim3(sip::kStreamThreads), 0, stream, ev[0], ev[1], 0, a);

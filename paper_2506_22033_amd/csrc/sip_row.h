@@ -16,7 +16,7 @@
 
 namespace sip {
 
-template <int DT, bool SH>
+template <int DT, bool SH, bool IDS>
 __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void row_kernel(Args a_by_value) {
   (void)a_by_value;
   const Args& a = *(const Args*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -32,7 +32,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   if (b < (a.B & ~7)) b = (b & ~7) | ((b + (b >> 3)) & 7);
   RowHand hand;
   int code = 2;
-  if (stream_part<DT, SH, true>(a, b, u.stream.front, u.stream.tables, &hand)) {                      // uniform
+  if (stream_part<DT, SH, true, IDS>(a, b, u.stream.front, u.stream.tables, &hand)) {                      // uniform
     __syncthreads();                       // the list is written, and the tables are free
     code = finish_row<true>(a, b, u.fin, nullptr, &hand);
   }

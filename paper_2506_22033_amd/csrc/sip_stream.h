@@ -107,6 +107,14 @@ __device__ __forceinline__ bool unfiltered(const RowParams& r, int V) {
   return !(r.top_k >= 2 && r.top_k < V) && !(r.top_p < 1.0f) && !(r.min_p > 0.0f);
 }
 
+// Whether anything is asked for that takes the mass of the whole row: a log-probability, or a share of it that is
+// drawn from or that top-p leaves out.  (Not so the largest element, a draw from the k largest, top-p among
+// these, or a draw from what min-p keeps.)
+__device__ __forceinline__ bool total_is_used(const RowParams& r, const Args& a) {
+  if (a.k_lp >= 0) return true;
+  return !r.greedy && !(r.top_k >= 2 && r.top_k < a.V) && (r.top_p < 1.0f || !(r.min_p > 0.0f));
+}
+
 // How many of the row's largest elements the candidate list should hold; 0 = this row
 // cannot be finished from a candidate list (k is too large) and takes the exact multi-pass
 // path instead.
@@ -321,8 +329,8 @@ struct RowHand {
 };
 
 // Streams chunk wg % S of row wg / S (ROW: row wg).  False: the row cannot be finished from a list.  `front` and `sm`: LDS,
-// one behind the other.
-template <int DT, bool SH, bool ROW>
+// one behind the other.  IDS: a call that asks for token ids only (a kernel of its own, see `masses`).
+template <int DT, bool SH, bool ROW, bool IDS = false>
 __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigned char* const front, StreamTables<DT, ROW>& sm,
                                             RowHand* hand) {
   typedef StreamShape<DT, ROW> Sh;
@@ -726,6 +734,9 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
   // 16 us, streaming kernel 28 us as before, call 99.4 -> 43 us; with the sums in fp32 26.5 + 14.8 us,
   // but fewer bits than the draw by re-reading the row has.
   const bool plain = !SH && !rp.greedy && unfiltered(rp, V);                   // workgroup-uniform
+  // Where nothing takes the row's mass it is not summed, which is a third of what a load costs.  (One more branch a
+  // load for everybody else took 1 to 2 % of bf16 calls, hence a kernel of its own.)
+  const bool masses = !IDS || total_is_used(rp, a);                            // workgroup-uniform
   // Per element a multiply-add, its sign shifted into a mask, a minimum, an exponential and an addition; the
   // elements at or above the threshold and the history tokens (`hb`) are then pushed lane by lane, one
   // of each lane at a time, which takes one or two rounds of a load at the usual list lengths.
@@ -774,6 +785,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
         qn += (uint32_t)__popcll(mask);
       }
     }
+    if (IDS && !masses) return;
     float g = bulk_term(x[0]);
 #pragma unroll
     for (int i = 1; i < EPL; ++i) g += bulk_term(x[i]);
@@ -977,7 +989,9 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
   return true;
 }
 
-template <int DT, bool SH>
+// IDS: for calls that ask for token ids only.  us a call: V = 152064 bf16, 128 greedy rows 19.9 -> 17.9; V = 83007 bf16, 287
+// rows under min-p 39.8 -> 35.8.
+template <int DT, bool SH, bool IDS>
 __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void stream_kernel(Args a) {
   extern __shared__ __align__(16) unsigned char stream_lds[];                  // stream_lds_bytes()
   // Workgroups are handed to the 8 XCDs round-robin by their id.  The chunks of one row read
@@ -985,7 +999,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   // on logical chunk (i % 8) * (n / 8) + i / 8 when n, the grid size, is a multiple of 8.
   int wg = blockIdx.x;
   if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-  stream_part<DT, SH, false>(a, wg, stream_lds, *reinterpret_cast<StreamTables<DT, false>*>(stream_lds + stream_front_bytes<DT, false>(a.cap_c / kStreamWaves)), nullptr);
+  stream_part<DT, SH, false, IDS>(a, wg, stream_lds, *reinterpret_cast<StreamTables<DT, false>*>(stream_lds + stream_front_bytes<DT, false>(a.cap_c / kStreamWaves)), nullptr);
 }
 
 }  // namespace sip
