@@ -91,8 +91,8 @@ typedef struct {
  *   other value = finished after reading the row again (normally from cache): 15 = from a second,
  *   longer candidate list (one more read of that row); 16 = by the row's workgroup over the whole
  *   row (plain temperature sampling without any filter: one block of 1024 entries is read again if
- *   why = 1, the row twice if why = 13; a nucleus that reaches below the candidate list: twice,
- *   and one block for the token); anything else = the exact multi-pass path, the value
+ *   why = 1, the row twice if why = 13; a nucleus that reaches below the candidate list: once, or
+ *   three times, and one block for the token); anything else = the exact multi-pass path, the value
  *   naming the reason (2 top_k too large for any candidate list, 3-13 the candidate list could
  *   not prove the answer, 17-29 nor could the longer one), or 14: vocabulary size outside the
  *   single-pass kernels (why = 1: settled from registers all the same).

@@ -7,9 +7,9 @@
 //     history tokens' multiplicities from a bitmap over the vocabulary, popcount ranks and side
 //     tables in LDS;
 //   - a second, longer list, made by reading the row once more with a lower threshold
-//     (restream_row), and the same logic on that one;
-//   - the continuations over the whole row (whole_row_finish): a nucleus that reaches below any
-//     list is cut and drawn from in two reads of the row, and a row without any filter is drawn
+//     (restream_row), and the same logic on that one (rows under min-p, and lists that lack the k-th or n-th);
+//   - the continuations over the whole row (whole_row_finish): a nucleus that reaches below the
+//     list is cut and drawn from in one read of the row, or two, and a row without any filter is drawn
 //     over all its elements;
 //   - the exact multi-pass path (sip_exact.h).
 //
@@ -65,7 +65,7 @@ struct FastShared {
   unsigned long long limit_out;         // for the whole-row continuation: top-p limit, ln Z, whether penalties apply
   double lnz_out;
   int has_pen_out;
-  int retry_ok_out;                     // a second, longer list can hold the nucleus (lower bound on its length)
+  int second_list_out;                  // min-p bounds the kept set: a second list can be cut there
   uint32_t rq_n;                         // candidates found by the second pass
   const char* shard_row[8];             // sharded logits: this row's piece in every shard
   int ndist_out;                        // distinct history tokens of the row, -1 while not counted (thread 0 only)
@@ -81,6 +81,9 @@ struct FastShared {
   uint32_t n_top;
   uint32_t t_key[kTopList];
   uint32_t t_idx[kTopList];
+  int w_lo[2], w_hi[2];                 // whole_row_window: first and last bin of two windows, elements of the sample
+  uint32_t w_n0[2], w_n1[2];            // below the first and up to the last
+  float w_sq;                           // sum of the squared masses below the place where the cut is expected
 };
 
 // Bytes of dynamic LDS the finishing kernel needs for vocabulary V, before the candidates.
@@ -653,7 +656,7 @@ __device__ __forceinline__ int fast_row(const Args& a, const int b, const RowPar
       if (nm > (uint32_t)kMembers) {                                          // uniform
         if (k_act) return 9;
         // (without top-k what settles a cut below the list settles this one too)
-        if (tid == 0) { fs.limit_out = limit; fs.lnz_out = lnZ; fs.has_pen_out = has_pen; fs.retry_ok_out = 0; }
+        if (tid == 0) { fs.limit_out = limit; fs.lnz_out = lnZ; fs.has_pen_out = has_pen; fs.second_list_out = 0; }
         return kWholeRowCut;
       }
       if (nm <= (uint32_t)kWave) {
@@ -686,17 +689,7 @@ __device__ __forceinline__ int fast_row(const Args& a, const int b, const RowPar
         // whole row by the caller (out of this function: code that is rarely needed slows it down)
         if (tid == 0) {
           fs.limit_out = limit; fs.lnz_out = lnZ; fs.has_pen_out = has_pen;
-          // Every token below the list weighs at most what the completeness threshold weighs, so
-          // the nucleus needs at least (limit - mass of the complete part of the list) / that many
-          // more: if even this bound does not fit a second list, do not try one.
-          const unsigned long long have = hm[0], e_c = mass(s_c);
-          const unsigned long long lack = limit > have ? limit - have : 0ull;
-          // (and a list that holds less than three quarters of the nucleus' mass is taken as a sign
-          // that the rest is far longer than this bound)
-          // With min-p on, the kept set ends at the min-p threshold at the latest, which is known
-          // exactly by now: a second list cut there settles the row if it fits (the caller checks).
-          fs.retry_ok_out = minp_on ||
-                            (e_c > 0 && lack / e_c + total_seg < 10000ull && have >= limit - (limit >> 2));
+          fs.second_list_out = minp_on;
         }
         return kWholeRowCut;
       }
@@ -933,7 +926,6 @@ __device__ __forceinline__ void history_bitmap(const Args& a, const int b, const
 // in the same workgroup), or nothing.
 struct RescueSeen {
   int why = 0;               // finish_row()'s code; 0 = nothing is known
-  bool retry_ok = false;
   float m = 0.0f, zmax = 0.0f, T = 0.0f;
 };
 template <int DT, bool SH>
@@ -962,7 +954,7 @@ __device__ __forceinline__ void rescue_row(const Args& a, const int b, unsigned 
     for (int attempt = 0; attempt < 2; ++attempt) {
       int r;
       bool cut_below = false;
-      const bool skipped = attempt == 0 && (seen.why == 12 || (seen.why == 11 && seen.retry_ok));
+      const bool skipped = attempt == 0 && (seen.why == 12 || (seen.why == 11 && rp.min_p > 0.0f));
       if (skipped) {
         // The first list has been looked at already and is known to be too short for a cut whose
         // place a second list can reach: go straight on to that one.
@@ -973,10 +965,12 @@ __device__ __forceinline__ void rescue_row(const Args& a, const int b, unsigned 
         r = fast_any<DT, SH>(a, b, rp, dynraw, fs, S, cap_c, ndist_ub);
       }
       if (attempt == 0 && r == kWholeRowCut) {
-        // a nucleus somewhat longer than the list is cheaper to settle from a second list than
-        // over the whole row
+        // with min-p on, the kept set ends at the min-p threshold at the latest, which is known exactly by now:
+        // a second list cut there settles the row if it fits.  (Without it the row's one read in
+        // whole_row_window() is no dearer than a second list, which besides may turn out too short: V = 128256
+        // bf16, 256 rows, 244 with nuclei beyond their lists, 247 us a call with second lists, 130 without.)
         __syncthreads();
-        if (fs.retry_ok_out) { r = 11; cut_below = true; }
+        if (fs.second_list_out) { r = 11; cut_below = true; }
       }
       if (attempt == 1) {
         const bool fine = r == 1 || r == kWholeRowCut || r == kWholeRow;
@@ -1540,6 +1534,415 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
   return fs.token == 0x7FFFFFFF ? 13 : 1;
 }
 
+// The same in one read of the row, for rows that no min-p bounds.  A sample of 8192 elements says about where
+// the cut lies: the mass below it is known (total less limit), so the cut lies where the sample's elements
+// from below add up to their share of that, give or take three standard deviations of such a sum (2 to 3 % of
+// it each on flat rows, 8 on rows whose tail is a few hundred elements).  The read then sums, per block of 1024 elements, what lies above that
+// window, and lists what lies in it (some thousand elements, to where the row's candidates were); bins over
+// the window, and the members of one of them, settle the cut; and one block is read again for the token.
+// Every decision is taken on the exact fp32 s; masses of a load are added in fp32, in the order of its
+// elements, and from there on as integers.  Returns 1 (fs.token, fs.token_key), 13 (no mass), or 0: the window
+// is too long for the room, or the cut not in it (whole_row_nucleus() then does without one).
+// What bounds it: vector issue of one compute unit (30 instructions an element).  us a call, against a second list and
+// two reads: 1 row of V = 256000 fp32, flat 269 -> 114, V = 213087 bf16 234 -> 106; V = 200000 fp32, 64 rows, 16 of them flat
+// 267 -> 111; V = 128256 bf16, 256 rows, 244 of them spiked at top-p 0.9 291 -> 98; V = 166557 fp32, 1883 rows, 471 flat 752 -> 436.
+template <int DT>
+__device__ __attribute__((noinline)) int whole_row_window(const char* row_any, const int V_any, const bool has_pen_any,
+                                                          const uint32_t* bm, const unsigned short* pre, const uint32_t* cnt,
+                                                          unsigned long long* hm, unsigned long long* hd, uint32_t* hc,
+                                                          FastShared& fs, uint2* region_any, const uint32_t cap_any, const double inv_tau,
+                                                          const float m, const unsigned long long limit, const float top_p,
+                                                          const unsigned long long j24) {
+  const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
+  constexpr int NT = kFinalThreads;
+  constexpr int EPL = (DT == SIP_F32) ? 4 : 8;
+  constexpr int ESZ = (DT == SIP_F32) ? 4 : 2;
+  constexpr int BLK = 1024;
+  constexpr int UNR = BLK / (kWave * EPL);                // loads of a block per lane
+  constexpr int SL = kSampleSize / (NT * EPL);            // sample loads per thread
+  constexpr float kSpan = 28.0f;                          // exp(-28) * 2^40 < 1: nothing below has mass
+  constexpr float kWide[2] = {3.0f, 1.5f};                // standard deviations on either side
+  // (what a function is handed lies in vector registers, and pointers may be to anything: said to be uniform, and
+  // global, they leave the loop without exec-masked branches and flat accesses: 130 -> 98 us in the fourth of these, together
+  // with barriers alone, no device-wide fences, around the list)
+  typedef __attribute__((address_space(1))) char global_char;
+  typedef __attribute__((address_space(1))) unsigned long long global_u64;
+  auto uniform_at = [](const void* p) {
+    const unsigned long long at = (unsigned long long)(uintptr_t)p;
+    return ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+  };
+  const int V = __builtin_amdgcn_readfirstlane(V_any);
+  const bool has_pen = __builtin_amdgcn_readfirstlane(has_pen_any ? 1 : 0) != 0;
+  const uint32_t cap = (uint32_t)__builtin_amdgcn_readfirstlane((int)cap_any);
+  global_char* const row = (global_char*)uniform_at(row_any);
+  global_u64* const region = (global_u64*)uniform_at(region_any);             // key of s | element << 32
+  const RowDivisor by_tau(inv_tau);
+  const int e_last = ((V - 1) / EPL) * EPL;
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(1))) const u32x4 global_x4;
+  auto ldrow = [&](int e0) {
+    const u32x4 q = *(global_x4*)(row + (uint32_t)min(e0, e_last) * (uint32_t)ESZ);
+    return make_uint4(q.x, q.y, q.z, q.w);
+  };
+  auto raw = [&](const uint4& q, float (&z)[EPL]) {
+    if (DT == SIP_F32) {
+      z[0] = __uint_as_float(q.x); z[1] = __uint_as_float(q.y);
+      z[2] = __uint_as_float(q.z); z[3] = __uint_as_float(q.w);
+    } else {
+      const uint32_t w4[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        z[2 * i] = __uint_as_float(w4[i] << 16);
+        z[2 * i + 1] = __uint_as_float(w4[i] & 0xFFFF0000u);
+      }
+    }
+  };
+  // s of a load's elements; of what carries a penalty, and past the end, -inf
+  auto svals = [&](const uint4& q, int e0, bool end, float (&sv)[EPL]) {
+    float z[EPL];
+    raw(q, z);
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) sv[i] = by_tau.of(z[i]);
+    if (has_pen) {                                        // uniform (the elements of a load share a bitmap word)
+      const uint32_t bits = bm[min(e0, V - 1) >> 5] >> (e0 & 31);
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) sv[i] = (bits >> i) & 1u ? -INFINITY : sv[i];
+    }
+    if (end) {
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) sv[i] = e0 + i < V ? sv[i] : -INFINITY;
+    }
+  };
+  auto rel = [&](float sv) { return __builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(sv, m), 1.44269504f)); };
+  auto mass = [&](float sv) { return mass_units(rel(sv)); };
+  // every penalised token: f(s, token) per lane that has one, all lanes of the wave together
+  auto each_penalised = [&](auto&& f) {
+    if (!has_pen) return;
+    const int W = (V + 31) >> 5;
+    for (int w0 = wave * kWave; w0 < W; w0 += NT) {
+      const int w = w0 + lane;
+      const uint32_t word = w < W ? bm[w] : 0u;
+      uint32_t left = word;
+      while (__any(left != 0u)) {
+        const uint32_t bit = left & (0u - left);
+        f(left != 0u, left ? value_of(cnt[pre[w] + __popc(word & (bit - 1u))]) : 0.0f, (uint32_t)(w << 5) + (uint32_t)__popc(bit - 1u));
+        left &= left - 1u;
+      }
+    }
+  };
+  // ---- the window, from the sample: bins over [m - 28, m], mass and number of elements
+  const float lo0 = m - kSpan, sc0 = (float)kBins / kSpan;
+  __syncthreads();
+  for (int i = tid; i < kBins; i += NT) { hm[i] = 0; hc[i] = 0; }
+  if (tid < 2) { fs.w_lo[tid] = -1; fs.w_hi[tid] = -1; }
+  if (tid == 0) { fs.bin_p = 1 << 30; fs.bin_d = -1; fs.n_memb2 = 0; fs.key_p = 0xFFFFFFFFu; fs.key_k = 0; fs.token = 0x7FFFFFFF; fs.w_sq = -1.0f; }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < SL; ++j) {
+    constexpr uint32_t NSB = (uint32_t)(SL * kFinalWaves), B0 = (uint32_t)(kWave * EPL);
+    const int e0 = (int)((uint32_t)(wave * SL + j) * (uint32_t)V / NSB / B0 * B0) + lane * EPL;           // (V >= 16384: inside the row)
+    float sv[EPL];
+    svals(ldrow(e0), e0, true, sv);
+#pragma unroll
+    for (int i = 0; i < EPL; ++i)
+      if (sv[i] >= lo0) {
+        const int bin = min(kBins - 1, max(0, (int)(__fsub_rn(sv[i], lo0) * sc0)));
+        atomicAdd(&hm[bin], mass(sv[i]));
+        atomicAdd(&hc[bin], 1u);
+      }
+  }
+  __syncthreads();
+  {
+    // thread t has bins 4t .. 4t + 3, ascending
+    unsigned long long w[kBinsPerThread], msum = 0;
+    uint32_t c[kBinsPerThread], csum = 0;
+#pragma unroll
+    for (int j = 0; j < kBinsPerThread; ++j) {
+      w[j] = hm[kBinsPerThread * tid + j]; msum += w[j];
+      c[j] = hc[kBinsPerThread * tid + j]; csum += c[j];
+    }
+    float sq[kBinsPerThread], ssum = 0.0f;                // squares, a bin's elements taken to weigh the same
+#pragma unroll
+    for (int j = 0; j < kBinsPerThread; ++j) { sq[j] = c[j] ? (float)w[j] / (float)c[j] * (float)w[j] : 0.0f; ssum += sq[j]; }
+    const unsigned long long minc = dpp_scan_add_u64(msum);
+    const uint32_t cinc = dpp_scan_add_u32(csum);
+    const float sinc = dpp_scan_add_f32(ssum);
+    if (lane == kWave - 1) { fs.r64[wave] = minc; fs.r32[wave] = cinc; fs.rkey[wave] = __float_as_uint(sinc); }
+    __syncthreads();
+    unsigned long long ex0 = minc - msum;
+    uint32_t n0 = cinc - csum;
+    float sq0 = sinc - ssum;
+#pragma unroll
+    for (int ww = 0; ww < kFinalWaves; ++ww)
+      if (ww < wave) { ex0 += fs.r64[ww]; n0 += fs.r32[ww]; sq0 += __uint_as_float(fs.rkey[ww]); }
+    const double below = (double)limit * (1.0 - (double)top_p) / (double)top_p * ((double)kSampleSize / (double)V);
+    {
+      unsigned long long ex = ex0;
+      float q = sq0;
+#pragma unroll
+      for (int j = 0; j < kBinsPerThread; ++j) {
+        if ((double)ex <= below && below < (double)(ex + w[j])) fs.w_sq = fmaxf(q, 0.0f) + sq[j] * (float)((below - (double)ex) / (double)w[j]);
+        ex += w[j]; q += sq[j];
+      }
+    }
+    __syncthreads();
+    const double dev = sqrt((double)fmaxf(fs.w_sq, 0.0f));
+    unsigned long long ex = ex0;
+    uint32_t n = n0;
+    double ends[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const double wide = fmax((double)kWide[k >> 1] * dev, 0.02 * below);
+      ends[k] = fs.w_sq < 0.0f ? -1.0 : (k & 1) ? below + wide : fmax(below - wide, 0.0);
+    }
+#pragma unroll
+    for (int j = 0; j < kBinsPerThread; ++j) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if ((double)ex <= ends[k] && ends[k] < (double)(ex + w[j])) {
+          if (k & 1) { fs.w_hi[k >> 1] = kBinsPerThread * tid + j; fs.w_n1[k >> 1] = n + c[j]; }
+          else { fs.w_lo[k >> 1] = kBinsPerThread * tid + j; fs.w_n0[k >> 1] = n; }
+        }
+      ex += w[j]; n += c[j];
+    }
+  }
+  __syncthreads();
+  const uint32_t wave_cap = cap / kFinalWaves;
+  int pick = -1;
+#pragma unroll
+  for (int k = 1; k >= 0; --k)                            // the wider one where it fits (an eighth of the room to spare)
+    if (fs.w_lo[k] >= 0 && fs.w_hi[k] >= 0 &&
+        (unsigned long long)(fs.w_n1[k] - fs.w_n0[k]) * (unsigned long long)V < (unsigned long long)(cap - cap / 8) * (unsigned long long)kSampleSize)
+      pick = k;
+  if (pick < 0) return 0;                                 // uniform
+  const float s_lo = lo0 + (float)fs.w_lo[pick] / sc0, s_hi = lo0 + (float)(fs.w_hi[pick] + 1) / sc0;
+  for (int i = tid; i < kBins; i += NT) { hm[i] = 0; hd[i] = 0; }
+  __syncthreads();
+  // ---- the read: sums per block of what lies above, list of what lies in the window
+  const int nblk = (V + BLK - 1) / BLK;
+  const int per_wave = (nblk + kFinalWaves - 1) / kFinalWaves;
+  global_u64* const seg = region + (size_t)wave * wave_cap;
+  uint32_t qn = 0;                                        // wave-uniform: the wave's entries
+  auto part_of = [&](const float (&sv)[EPL], uint32_t& in) -> float {          // mass above the window; bit EPL-1-i: element i lies in it
+    uint32_t not_lo = ~0u, not_hi = ~0u;
+    float part = 0.0f;
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+      const float a_lo = __fsub_rn(sv[i], s_lo), a_hi = __fsub_rn(sv[i], s_hi);               // (a difference has the comparison's sign)
+      not_lo = __builtin_amdgcn_alignbit(not_lo, __float_as_uint(a_lo), 31);
+      not_hi = __builtin_amdgcn_alignbit(not_hi, __float_as_uint(a_hi), 31);
+      part += a_hi >= 0.0f ? rel(sv[i]) : 0.0f;
+    }
+    in = ~not_lo & not_hi & ((1u << EPL) - 1u);
+    return part;
+  };
+  uint4 q[UNR], next[UNR];                                // (a block's loads and the next one's)
+#pragma unroll
+  for (int u = 0; u < UNR; ++u) q[u] = ldrow(wave * per_wave * BLK + (u * kWave + lane) * EPL);
+  for (int blk = wave * per_wave; blk < min(nblk, (wave + 1) * per_wave); ++blk) {
+    const int base = blk * BLK;
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) next[u] = ldrow(base + BLK + (u * kWave + lane) * EPL);
+    unsigned long long A = 0;
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      const int e0 = base + (u * kWave + lane) * EPL;
+      float sv[EPL];
+      svals(q[u], e0, base + BLK > V, sv);                // (uniform)
+      uint32_t in;
+      A += mass_units(part_of(sv, in));
+      unsigned long long mask = __ballot(in != 0u);
+      while (mask) {
+        const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, qn));
+        if (in != 0u && pos < wave_cap) {
+          const int i = EPL - __ffs((int)in);
+          float z[EPL], x = 0.0f;
+          raw(q[u], z);
+#pragma unroll
+          for (int k = 0; k < EPL; ++k) x = k == i ? z[k] : x;
+          seg[pos] = ((unsigned long long)(uint32_t)(e0 + i) << 32) | key_of(by_tau.of(x));
+        }
+        in &= in - 1u;
+        qn += (uint32_t)__popcll(mask);
+        mask = __ballot(in != 0u);
+      }
+    }
+    A = dpp_scan_add_u64(A);
+    if (lane == kWave - 1) hd[blk] = A;
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) q[u] = next[u];
+  }
+  __syncthreads();
+  each_penalised([&](bool have, float sv, uint32_t v) {
+    const bool above = have && sv >= s_hi, in = have && sv >= s_lo && !above;
+    if (above) atomicAdd(&hd[v / BLK], mass(sv));
+    const unsigned long long mask = __ballot(in);
+    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, qn));
+    if (in && pos < wave_cap) seg[pos] = ((unsigned long long)v << 32) | key_of(sv);
+    qn += (uint32_t)__popcll(mask);
+  });
+  if (lane == 0) fs.r32[wave] = qn;
+  __syncthreads();                                        // (a workgroup's own stores are visible to it behind a barrier)
+  bool full = false;
+#pragma unroll
+  for (int ww = 0; ww < kFinalWaves; ++ww) full |= fs.r32[ww] > wave_cap;
+  if (full) return 0;                                     // uniform
+  // ---- the cut: bins over the window, then the members of one
+  const float sc = (float)kBins / __fsub_rn(s_hi, s_lo);
+  auto bin_at = [&](float sv) { return min(kBins - 1, max(0, (int)(__fsub_rn(sv, s_lo) * sc))); };
+  // every entry of the wave, four under way at a time
+  auto each_entry = [&](auto&& f) {
+    for (uint32_t i0 = 0; i0 < qn; i0 += 4 * kWave) {
+      uint2 en[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const unsigned long long w = seg[min(i0 + (uint32_t)(k * kWave + lane), qn - 1u)];
+        en[k] = make_uint2((uint32_t)w, (uint32_t)(w >> 32));
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (i0 + (uint32_t)(k * kWave + lane) < qn) f(en[k]);
+    }
+  };
+  each_entry([&](const uint2& en) {
+    const float sv = value_of(en.x);
+    const unsigned long long E = mass(sv);
+    if (E) atomicAdd(&hm[bin_at(sv)], E);
+  });
+  unsigned long long above = 0;                           // mass above the window, later above the bin
+  {
+    const unsigned long long a2 = dpp_scan_add_u64((tid < nblk ? hd[tid] : 0ull) + (tid + NT < nblk ? hd[tid + NT] : 0ull));
+    if (lane == kWave - 1) fs.r64[wave] = a2;
+    __syncthreads();
+#pragma unroll
+    for (int ww = 0; ww < kFinalWaves; ++ww) above += fs.r64[ww];
+    __syncthreads();
+    // thread t has bins kBins-1-4t .. kBins-4-4t, descending
+    const int b0 = kBins - 1 - kBinsPerThread * tid;
+    unsigned long long w[kBinsPerThread], msum = 0;
+#pragma unroll
+    for (int j = 0; j < kBinsPerThread; ++j) { w[j] = hm[b0 - j]; msum += w[j]; }
+    const unsigned long long minc = dpp_scan_add_u64(msum);
+    if (lane == kWave - 1) fs.r64[wave] = minc;
+    __syncthreads();
+    unsigned long long ex = above + minc - msum;
+#pragma unroll
+    for (int ww = 0; ww < kFinalWaves; ++ww)
+      if (ww < wave) ex += fs.r64[ww];
+#pragma unroll
+    for (int j = 0; j < kBinsPerThread; ++j) {
+      if (ex < limit && limit <= ex + w[j]) { fs.bin_p = b0 - j; fs.before_d = ex; }         // one bin at most
+      ex += w[j];
+    }
+  }
+  __syncthreads();
+  const int bp = fs.bin_p;
+  if (bp >= kBins) return 0;                              // uniform: the cut lies above or below the window
+  above = fs.before_d;
+  __syncthreads();
+  constexpr uint32_t kList = kBins;
+  uint32_t* const list = reinterpret_cast<uint32_t*>(hm); // (the bins are done with)
+  uint32_t kmin = 0xFFFFFFFFu, kmax = 0;
+  each_entry([&](const uint2& en) {
+    const float sv = value_of(en.x);
+    const int bin = bin_at(sv);
+    const unsigned long long E = mass(sv);
+    if (E && bin > bp) atomicAdd(&hd[en.y / BLK], E);
+    if (E && bin == bp) {
+      const uint32_t at = atomicAdd(&fs.n_memb2, 1u);
+      if (at < kList) list[at] = en.x;
+      kmin = min(kmin, en.x); kmax = max(kmax, en.x);
+    }
+  });
+  if (kmax) { atomicMin(&fs.key_p, kmin); atomicMax(&fs.key_k, kmax); }
+  __syncthreads();
+  const uint32_t n = fs.n_memb2;
+  uint32_t k_lo = fs.key_p, k_hi = fs.key_k;              // the smallest key above which the mass stays short of the limit lies in [k_lo, k_hi]
+  if (k_lo != k_hi && n > kList) return 0;                // uniform
+  while (k_lo < k_hi) {                                   // uniform
+    const uint32_t mid = k_lo + ((k_hi - k_lo) >> 1);
+    unsigned long long g = 0;
+    for (uint32_t i = tid; i < n; i += NT)
+      if (list[i] > mid) g += mass(value_of(list[i]));
+    g = dpp_scan_add_u64(g);
+    __syncthreads();
+    if (lane == kWave - 1) fs.r64[wave] = g;
+    __syncthreads();
+    unsigned long long G = above;
+#pragma unroll
+    for (int ww = 0; ww < kFinalWaves; ++ww) G += fs.r64[ww];
+    if (G < limit) k_hi = mid; else k_lo = mid + 1;
+  }
+  const uint32_t key_cut = k_hi;
+  each_entry([&](const uint2& en) {
+    const float sv = value_of(en.x);
+    if (en.x >= key_cut && bin_at(sv) == bp) atomicAdd(&hd[en.y / BLK], mass(sv));
+  });
+  __syncthreads();
+  // ---- prefix over the blocks, and the block that holds the crossing
+  unsigned long long target;
+  {
+    static_assert(262144 / BLK <= NT, "a block per thread");
+    const unsigned long long w = tid < nblk ? hd[tid] : 0ull;
+    const unsigned long long minc = dpp_scan_add_u64(w);
+    if (lane == kWave - 1) fs.r64[wave] = minc;
+    __syncthreads();
+    unsigned long long ex = minc - w, S3 = 0;
+#pragma unroll
+    for (int ww = 0; ww < kFinalWaves; ++ww) {
+      if (ww < wave) ex += fs.r64[ww];
+      S3 += fs.r64[ww];
+    }
+    target = (__umul64hi(j24, S3) << 40) | ((j24 * S3) >> 24);                // floor(j * S3 / 2^24)
+    if (ex <= target && target < ex + w) { fs.bin_d = tid; fs.before_d = ex; }
+  }
+  __syncthreads();
+  const int blk_d = fs.bin_d;
+  if (blk_d < 0) return 13;                                                   // uniform (no mass at all)
+  if (wave == 0) {                                                            // lane prefixes in vocabulary order
+    const int base = blk_d * BLK;
+    unsigned long long running = fs.before_d;
+    bool found = false;
+#pragma nounroll
+    for (int u = 0; u < UNR && !found; ++u) {
+      const int e0 = base + (u * kWave + lane) * EPL;
+      const uint4 q = ldrow(e0);
+      float sv[EPL], pv[EPL];
+      svals(q, e0, true, sv);
+      const uint32_t word = has_pen ? bm[min(e0, V - 1) >> 5] : 0u;
+      // element i: what it adds to the load's fp32 sum, or as an integer
+      auto single = [&](int i) -> unsigned long long {
+        float x = sv[i];
+        if (e0 + i < V && ((word >> ((e0 + i) & 31)) & 1u)) x = value_of(cnt[pre[(e0 + i) >> 5] + __popc(word & ((1u << ((e0 + i) & 31)) - 1u))]);
+        pv[i] = x;
+        return x > -INFINITY && !(sv[i] >= s_hi) && key_of(x) >= key_cut ? mass(x) : 0ull;
+      };
+      float part = 0.0f;
+      unsigned long long ints = 0;
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) { part += sv[i] >= s_hi ? rel(sv[i]) : 0.0f; ints += single(i); }
+      const unsigned long long tot = mass_units(part) + ints;
+      const unsigned long long incl = dpp_scan_add_u64(tot);
+      const unsigned long long before = running + incl - tot;
+      int hit = -1;
+      uint32_t hit_key = 0;
+      part = 0.0f; ints = 0;
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) {
+        part += sv[i] >= s_hi ? rel(sv[i]) : 0.0f; ints += single(i);
+        if (hit < 0 && before + mass_units(part) + ints > target) { hit = e0 + i; hit_key = key_of(pv[i]); }
+      }
+      const unsigned long long ball = __ballot(hit >= 0);
+      found = ball != 0;
+      if (found && lane == __ffsll((long long)ball) - 1) { fs.token = hit; fs.token_key = hit_key; }
+      running += last_lane_u64(incl);
+    }
+  }
+  __syncthreads();
+  return fs.token == 0x7FFFFFFF ? 13 : 1;
+}
+
 // Continuation of fast_row for the two kinds of row that are finished over the whole row
 // (codes kWholeRowCut and kWholeRow): nucleus cut if asked for, draw, token and its logprob.
 // The best-n list is already written.  Returns 1, or a code that sends the row to the exact path.
@@ -1565,7 +1968,11 @@ __device__ __attribute__((noinline)) int whole_row_finish(const Args& a, const i
   const float t_minp = minp_on ? (float)log((double)rp.min_p) : 0.0f;
   const unsigned long long j24 = (unsigned long long)(philox_word0(a.seed, rp.row_id, step_of(a)) >> 8);
   if (cut) {
-    const int r = whole_row_nucleus<DT>(row, V, has_pen, bm, pre, cnt, hm, hd, fs, 1.0 / (double)rp.tau, m, limit, j24,
+    int r = 0;
+    if (!minp_on)
+      r = whole_row_window<DT>(row, V, has_pen, bm, pre, cnt, hm, hd, hc, fs, a.cand + (size_t)b * (size_t)a.S * (size_t)a.cap_c,
+                               (uint32_t)(a.S * a.cap_c), 1.0 / (double)rp.tau, m, limit, rp.top_p, j24);
+    if (r == 0) r = whole_row_nucleus<DT>(row, V, has_pen, bm, pre, cnt, hm, hd, fs, 1.0 / (double)rp.tau, m, limit, j24,
                                         minp_on, t_minp);
     if (r != 1) return r == 11 ? 10 : r;                                      // uniform
   } else if (whole_row_draw<DT>(row, V, has_pen, bm, pre, cnt, hd, fs, rp.tau, rp.greedy, m, zmax, (float)log2_scale(rp), j24) != 1) {

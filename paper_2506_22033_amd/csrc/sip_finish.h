@@ -77,7 +77,6 @@ struct __align__(16) FinShared {
   uint32_t r32[kFinWaves], rkey[kFinWaves], ridx[kFinWaves];
   int bin_k, bin_n, bin_d;
   int code, code_top;
-  int retry_ok;                             // code 11 only: a second, longer list can be expected to hold the nucleus
   uint32_t hash_fail, n_memb, n_fold, key_cut, n_hi;
   uint32_t token, token_key;
   unsigned long long before_d;
@@ -100,7 +99,6 @@ __device__ __forceinline__ void lds_barrier() {
 // What a caller that goes on with a row this function could not settle may reuse (uniform).
 struct FinHint {
   bool valid = false;        // m, zmax and T are the row's
-  bool retry_ok = false;     // code 11: a second, longer list can be expected to hold the nucleus
   float m = 0.0f;            // maximum of s
   float zmax = 0.0f;         // maximum of z'
   float T = 0.0f;            // every element of the row above T is in the list
@@ -249,7 +247,6 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
 
   const bool direct = ROW && hand->direct;                                   // a round is 64 entries of every queue
   const bool any_over = ROW ? hand->co.cnt > (uint32_t)cap_c : __any(my_cnt > (uint32_t)cap_c);   // includes the overflow mark
-  const uint32_t total = ROW ? hand->co.cnt : wave_add_u32(my_cnt);
   const uint32_t longest = ROW ? (direct ? hand->longest * (uint32_t)kFinWaves : hand->co.cnt) : wave_max_u32(my_cnt);
   const unsigned long long bulk = ROW ? hand->co.bulk : wave_add_u64(my_bulk);
   if (any_over || !(Tc == Tc)) { list_is_used(); return 3; }                 // uniform
@@ -768,18 +765,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
         // the cut is proven to lie inside the list if some complete entry fell on its far side
         const bool inside = k_act || others || dropped;
         if (code == 0 && key_p == kFinNone) code = 10;
-        if (code == 0 && !inside && !minp_bounds) {
-          code = 11;                                                           // the nucleus may reach below the list
-          // Every token below the list weighs at most what the completeness threshold weighs, so
-          // the nucleus needs at least (limit - mass of the complete part of the list) / that many
-          // more entries: a second list is worth trying if that bound fits one and the list
-          // already holds three quarters of the nucleus' mass.  With min-p on the kept set ends
-          // at the min-p threshold at the latest, so a list cut there settles the row if it fits.
-          const unsigned long long have = fs.hmass[0], e_c = mass(s_c);
-          const unsigned long long lack = limit > have ? limit - have : 0ull;
-          const bool ok = minp_on || (e_c > 0 && lack / e_c + total < 10000ull && have >= limit - (limit >> 2));
-          if (lane == 0) fs.retry_ok = ok ? 1 : 0;
-        }
+        if (code == 0 && !inside && !minp_bounds) code = 11;                   // the nucleus may reach below the list
         key_cut = max(key_k, key_p);
       }
     } else if (code == 0 && !k_act && !minp_bounds) {
@@ -834,7 +820,6 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   }
   lds_barrier();
   int code = fs.code_top ? fs.code_top : fs.code;                              // a failure of the best-n ranking stands
-  if (hint && code == 11) hint->retry_ok = fs.retry_ok != 0;
   if (code == kFinDrawBig) {
     // ---- (6') kept mass per vocabulary-index bin, prefix, then the crossing inside one bin
     const uint32_t key_cut = fs.key_cut, n_hi = fs.n_hi;

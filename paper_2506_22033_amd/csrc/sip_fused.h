@@ -33,7 +33,7 @@ __global__ __launch_bounds__(kFinalThreads) void finish_rescue_kernel(Args a_by_
   if (code == 1 || code == kFinWholeRow) return;                     // uniform
   __syncthreads();
   RescueSeen seen;
-  if (hint.valid) { seen.why = code; seen.retry_ok = hint.retry_ok; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
+  if (hint.valid) { seen.why = code; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
   rescue_row<DT, SH>(a, b, u.raw, ex, fsr, seen);
 }
 
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
   if (code == 1 || code == kFinWholeRow) return;                     // uniform
   __syncthreads();
   RescueSeen seen;
-  if (hint.valid) { seen.why = code; seen.retry_ok = hint.retry_ok; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
+  if (hint.valid) { seen.why = code; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
   rescue_row<DT, SH>(a, b, u.raw, ex, fsr, seen);
 }
 

@@ -1,0 +1,53 @@
+"""Nuclei cut and drawn in one read of the row with a window from its sample: rows that end at a block, one element short of
+it and past it, flat and peaked tails, cuts far up and far down, coarse values (the window's members all equal), penalised
+tokens above, in and below the window, pieces; and rows that go on to the two reads instead (a min-p beside top-p, more
+elements in the window than there is room for, a sample that most of the tail's mass is missing from)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2506_22033_amd as sip
+import workloads
+from tests import sip_harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,V,bf16,pieces", [(10, 33792, True, 0), (10, 33793, False, 0), (10, 45055, True, 0), (10, 262144, False, 0),
+                                             (10, 99999, True, 0), (10, 65536, True, 4), (270, 35001, False, 0)])
+def test_cut_in_one_read(B, V, bf16, pieces):
+    rng = np.random.default_rng(V + B)
+    kind = np.arange(B) % 10
+    z = rng.standard_normal((B, V)).astype(np.float32)
+    hist = [[] for _ in range(B)]
+    for b, k in enumerate(kind):
+        z[b] *= (1.0, 0.3, 2.0, 1.0, 1.0, 1.5, 1.0, 1.0, 2.5, 0.05)[k]
+        if k == 3:
+            z[b] = np.round(z[b] * 8) / 8
+        elif k == 4:
+            z[b, : V // 8] += 2.0                                  # the kept tokens at the front
+        elif k in (5, 6):
+            hist[b] = rng.integers(0, V, 3000).tolist()
+        elif k == 7:
+            hist[b] = np.argsort(-z[b])[:2500].tolist()
+        elif k == 8:
+            z[b, rng.integers(0, V, 40)] = 9.0                     # tail of little mass beside a few tokens
+    params = dict(temperature=np.choose(kind, [1.0, 1.0, 1.0, 0.8, 1.0, 1.2, 1.0, 1.0, 1.0, 1.0]),
+                  top_p=np.choose(kind, [0.9, 0.5, 0.95, 0.9, 0.9, 0.9, 0.99, 0.8, 0.97, 0.7]),
+                  min_p=np.choose(kind, [0, 0, 0, 0, 0, 0, 0, 0, 0, 1e-4]),
+                  repetition_penalty=np.choose(kind, [1, 1, 1, 1, 1, 1.3, 1.1, 2.0, 1, 1]),
+                  frequency_penalty=np.choose(kind, [0, 0, 0, 0, 0, 0, 0.2, 0, 0, 0]))
+    w = H.custom(f"window_{V}", workloads.f32_to_bf16_bits(z) if bf16 else z, params, hist, k_logprobs=2)
+    d = H.to_device(w)
+    rows = list(range(B)) if B < 30 else list(range(0, B, B // 30))
+    for step in range(3 if B < 30 else 1):
+        if pieces:
+            n = V // pieces
+            shards = [d.logits[:, i * n:(i + 1) * n].contiguous() for i in range(pieces)]
+            out = sip.sip_sample_sharded(shards, d.params, d.indptr, d.tokens, 41, step, 2)
+            torch.cuda.synchronize()
+            out = tuple(x.cpu().numpy() for x in out)
+        else:
+            out = H.run_gpu(d, 41, step)
+            assert (H.last_row_path[np.isin(kind, (0, 1, 4, 6))] == 16).all(), H.last_row_path[:10]
+        H.compare(w, out, 41, step, rows=rows)
