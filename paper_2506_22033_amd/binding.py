@@ -356,10 +356,18 @@ def state_views(state: torch.Tensor, slots: int, L_max: int):
     """(tick, overflow, len [slots], tokens [slots, L_max]) as views of a state buffer, per the
     layout that include/sip.h documents."""
     len_bytes = (4 * slots + 255) // 256 * 256
+    base = 256 + 2 * len_bytes
+    if (slots > 0 and L_max > 0 and state.dtype == torch.uint8 and state.dim() == 1 and state.stride(0) == 1
+            and state.numel() % 4 == 0 and state.numel() >= base + 4 * slots * L_max and state.storage_offset() % 8 == 0):
+        # (the same views from one of 32-bit words, without a slice and a view for each: 5.5 -> 3.7 us of a decode
+        # iteration's 46, which its host thread spends between the ids' arrival and the next call)
+        words = state.view(torch.int32)
+        at = words.storage_offset()
+        return (state[0:8].view(torch.int64), words.as_strided((1,), (1,), at + 2), words.as_strided((slots,), (1,), at + 64),
+                words.as_strided((slots, L_max), (L_max, 1), at + base // 4))
     tick = state[0:8].view(torch.int64)
     overflow = state[8:12].view(torch.int32)
     length = state[256:256 + 4 * slots].view(torch.int32)
-    base = 256 + 2 * len_bytes
     tokens = state[base:base + 4 * slots * L_max].view(torch.int32).view(slots, L_max)
     return tick, overflow, length, tokens
 
