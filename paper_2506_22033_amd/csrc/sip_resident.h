@@ -23,8 +23,12 @@
 // by one wave, parameters that are off take part with their neutral value instead of a branch,
 // temperature and repetition penalty are products with a double reciprocal (RowDivisor), masses
 // become integers through a double's low bits, and bins cost three instructions; with the
-// straightforward forms of these V = 32000 took 34.5 us, now 26 (fp32, 4 rows, one of each kind
-// of filter).  Against exact_kernel, which vocabularies below 16384 used to go through: V = 4096, 64
+// straightforward forms of these V = 32000 took 34.5 us, then 25.0 (fp32, 4 rows, one of each kind
+// of filter); with the block masses of a wave's loads added up together (row_sums_u64(): eight sums over 64 lanes
+// one by one were a fifth of what a thread issues for the draw), min-p taken out of the masses once, and the gathering of a cut's
+// members passing over loads whose largest value is below, 24.0.  Without a filter, V = 16000, 64 rows 13.7 -> 12.7, 1500 rows 81.4 -> 75.5;
+// top-p 97.9 -> 95.3.  (Counting only bins that the k-th or n-th best can be in, by the least of 128 groups' maxima,
+// made everything 1 to 5 % slower: the LDS additions are hidden, the test is not.)  Against exact_kernel, which vocabularies below 16384 used to go through: V = 4096, 64
 // rows, top-k and top-p: 53 -> 11 us; V = 12556, 468 rows, no filter: 99 -> 19 us.  Which of the larger
 // ones come here: resident_is_chosen().
 //
@@ -67,6 +71,32 @@ struct __align__(16) ResShared {
   unsigned long long j24;
   ExactShared ex;
 };
+
+// Sums of N values over the 16 lanes of a DPP row: lane l has that of t[l % N].  Half of the values go to
+// the other lane of a pair at each of the first steps, so that eight take 10 additions, not 32.
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_mov_u64(unsigned long long v) {
+  return ((unsigned long long)dpp_mov<CTRL, 0xf>(0u, (uint32_t)(v >> 32)) << 32) | dpp_mov<CTRL, 0xf>(0u, (uint32_t)v);
+}
+template <int CTRL, int HALF, int N>
+__device__ __forceinline__ void halve_u64(unsigned long long (&t)[N], bool upper) {
+#pragma unroll
+  for (int j = 0; j < HALF; ++j) {
+    const unsigned long long keep = upper ? t[j + HALF] : t[j], give = upper ? t[j] : t[j + HALF];
+    t[j] = keep + dpp_mov_u64<CTRL>(give);
+  }
+}
+template <int N>
+__device__ __forceinline__ unsigned long long row_sums_u64(unsigned long long (&t)[N], int lane) {
+  static_assert(N == 1 || N == 2 || N == 4 || N == 8, "");
+  if constexpr (N >= 8) halve_u64<0x141, 4>(t, lane & 4);                      // from the other end of eight lanes
+  if constexpr (N >= 4) halve_u64<0x4E, 2>(t, lane & 2);                       // lane ^ 2
+  if constexpr (N >= 2) halve_u64<0xB1, 1>(t, lane & 1);                       // lane ^ 1
+  unsigned long long v = t[0] + dpp_mov_u64<0x128>(t[0]);                      // rotations by 8, 4, 2
+  if constexpr (N <= 4) v += dpp_mov_u64<0x124>(v);
+  if constexpr (N <= 2) v += dpp_mov_u64<0x122>(v);
+  return v;
+}
 
 // `NT` threads, `NPT` elements each: V <= NT * NPT.
 template <int DT, int NT, int NPT>
@@ -126,6 +156,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
     z4 = reinterpret_cast<uint4*>(fs.u.cnt);
     if (pen.any)
       for (int i = tid; i < NT * NPT * 2 / 16; i += NT) z4[i] = make_uint4(0, 0, 0, 0);
+    if (NL > 1 && tid < NBLK) fs.blk[tid] = 0;
     if (tid == 0) {
       fs.n_a = 0; fs.n_m = 0; fs.m_lo = kFinNone; fs.m_hi = 0; fs.key_k = 0; fs.key_p = kFinNone; fs.s1_part = 0;
       fs.bin_k = -1; fs.bin_n = -1; fs.bin_p = 1 << 30; fs.arg_max = kFinNone;
@@ -439,6 +470,12 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
 #pragma unroll
       for (int j = 0; j < NL; ++j) {
         if (j * NT * EPL >= V) continue;               // workgroup-uniform
+        if (NPT >= 16 && first > 0) {                  // (a shorter row's loads have one nearly always)
+          float hi = s[j * EPL];
+#pragma unroll
+          for (int i = 1; i < EPL; ++i) hi = fmaxf(hi, s[j * EPL + i]);
+          if (!(__fmaf_rn(hi, scale, shift) >= (float)first)) continue;        // every bin_of() below `first`
+        }
 #pragma unroll
         for (int i = 0; i < EPL; ++i) {
           const int v = (j * NT + tid) * EPL + i;
@@ -563,23 +600,34 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
     float s_cut = -INFINITY;
     if (fs.key_k) s_cut = value_of(fs.key_k);
     if (p_act) s_cut = fmaxf(s_cut, value_of(fs.key_p));
-    auto kept = [&](int r) { return s[r] >= s_cut && __fsub_rn(s[r], m) >= t_minp; };
+    if (minp_on) {                                     // (a mass less costs the other rows nothing)
+#pragma unroll
+      for (int r = 0; r < NPT; ++r) e[r] = __fsub_rn(s[r], m) >= t_minp ? e[r] : 0.0f;
+    }
+    auto kept = [&](int r) { return s[r] >= s_cut; };
     auto lane_mass = [&](int j) -> unsigned long long {
       unsigned long long t = 0;
 #pragma unroll
       for (int i = 0; i < EPL; ++i) t += mass_bits(kept(j * EPL + i) ? e[j * EPL + i] : 0.0f);
       return t - (unsigned long long)EPL * kMagicBits;
     };
+    unsigned long long t_of[NL];
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
-      unsigned long long t = 0;
+      t_of[j] = 0;
       if (j * NT * EPL < V) {                          // workgroup-uniform
         bool some = false;
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) some |= s[j * EPL + i] >= s_cut;
-        if (__any(some)) t = wave_add_u64(lane_mass(j));
+        for (int i = 0; i < EPL; ++i) some |= kept(j * EPL + i);
+        if (__any(some)) t_of[j] = lane_mass(j);
       }
-      if (lane == 0) fs.blk[j * NW + wave] = t;
+    }
+    if (NL == 1) {
+      const unsigned long long t = wave_add_u64(t_of[0]);
+      if (lane == 0) fs.blk[wave] = t;
+    } else {
+      const unsigned long long t = row_sums_u64(t_of, lane);
+      if ((lane & 15) < NL) atomicAdd(&fs.blk[(lane & 15) * NW + wave], t);
     }
     __syncthreads();
     const unsigned long long w0 = 2 * lane < NBLK ? fs.blk[2 * lane] : 0ull;
