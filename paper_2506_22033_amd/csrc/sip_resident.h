@@ -18,7 +18,7 @@
 //       over the blocks, and the wave that holds the crossing finds it in its registers.
 //
 // What bounds it: vector issue of the one compute unit that has the row (16 waves, 4 to a SIMD, so
-// an instruction per element costs V / 1024 x 16 cycles; 59 % of the slots at V = 32000) and the chain of
+// an instruction per element costs V / 1024 x 16 cycles; 58 % of the slots at V = 32000) and the chain of
 // its barriers.  Hence what is done once per row is done
 // by one wave, parameters that are off take part with their neutral value instead of a branch,
 // temperature and repetition penalty are products with a double reciprocal (RowDivisor), masses

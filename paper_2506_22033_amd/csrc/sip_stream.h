@@ -283,7 +283,8 @@ __device__ __forceinline__ uint32_t raised_group(const uint32_t G, const uint32_
 }
 
 // LDS: first the sample histogram (two 16-bit counters per word, 16 KB), then, in its
-// place, the per-wave candidate queues (a chunk's: fp32 30 KB, bf16 15 KB; a row's: 44 or 40 KB); then the history
+// place, the per-wave candidate queues (a chunk's: fp32 30 KB, bf16 15 KB, up to four times
+// that where fewer than four share a compute unit; a row's: 44 or 40 KB); then the history
 // bitmap (9 or 32 KB) and the tag words (fp32 256 bytes, bf16 4 KB).
 template <int DT, bool ROW>
 struct __align__(16) StreamTables {
