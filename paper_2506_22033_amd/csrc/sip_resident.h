@@ -68,6 +68,7 @@ struct __align__(16) ResShared {
   int bin_k, bin_n, bin_p;
   uint32_t arg_max;
   float t_minp;
+  double ln_z;
   unsigned long long j24;
   ExactShared ex;
 };
@@ -364,6 +365,16 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
   __syncthreads();
   const unsigned long long S0 = wave_add_u64(lane < NW ? fs.r64[lane] : 0ull);
   auto ln_total = [&]() -> double { return log((double)S0) - (double)kFixShift * 0.6931471805599453094; };
+  // One wave works it out while the others are at the elements, instead of whoever needs it at the end of the chain
+  // (V = 16000 without a filter 12.7 -> 12.3, everything on 21.2 -> 20.9 us; not with eight waves: 1500 rows of 4096, top-p, 60.8 / 62.0).
+  constexpr bool kAhead = NW == 16;
+  auto note_ln_total = [&]() {
+    if (kAhead && wave == NW / 2) {
+      const double z = ln_total();
+      if (lane == 0) fs.ln_z = z;
+    }
+  };
+  auto noted_ln_total = [&]() -> double { return kAhead ? fs.ln_z : ln_total(); };
 
   // ---- (4) descending scan: thread t owns bins kResBins-1-BPT*t .. kResBins-BPT*(t+1)
   auto limit_of = [&](unsigned long long mass1) -> unsigned long long {
@@ -513,6 +524,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
       }
     };
     if (code == 0) {
+      if (n_top > 0) note_ln_total();
       gather(n_top > 0 ? bin_n : -1, bin_m);
       __syncthreads();
       if (bin_m >= 0) {
@@ -554,7 +566,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
           }
           if (rank < n_top) {
             a.out_lp_ids[(size_t)b * cols + 1 + rank] = (int)v;
-            a.out_lp[(size_t)b * cols + 1 + rank] = (float)((double)value_of(kt) - (double)m - ln_total());
+            a.out_lp[(size_t)b * cols + 1 + rank] = (float)((double)value_of(kt) - (double)m - noted_ln_total());
           }
         }
         for (int o = (int)n_top + tid; o < a.k_lp; o += NT) {                  // vocabulary smaller than k_logprobs
@@ -593,7 +605,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
 
   // ---- (5) draw
   if (code == 0 && rp.greedy) {
-    if (tid == 0) emit(fs.arg_max, m, ln_total());
+    if (tid == 0) emit(fs.arg_max, m, n_top > 0 ? noted_ln_total() : ln_total());
     return;
   }
   if (code == 0) {
@@ -611,6 +623,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
       for (int i = 0; i < EPL; ++i) t += mass_bits(kept(j * EPL + i) ? e[j * EPL + i] : 0.0f);
       return t - (unsigned long long)EPL * kMagicBits;
     };
+    if (n_top == 0 && a.k_lp >= 0) note_ln_total();
     unsigned long long t_of[NL];
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
@@ -664,7 +677,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
             }
           }
         }
-        if (token != kFinNone) emit(token, sv, ln_total());                    // one lane
+        if (token != kFinNone) emit(token, sv, a.k_lp >= 0 ? noted_ln_total() : 0.0);                    // one lane
       }
       return;
     }

@@ -21,5 +21,5 @@ def test_draws_from_every_block(V, bf16):
                   top_p=np.choose(kind, [1.0, 1.0, 0.97, 1.0, 0.3]), min_p=np.choose(kind, [0.0, 0.1, 0.0, 0.0, 0.05]))
     w = H.custom(f"draw_{V}", workloads.f32_to_bf16_bits(z) if bf16 else z, params, [[] for _ in range(B)], k_logprobs=3)
     d = H.to_device(w)
-    for step in range(4):
-        H.compare(w, H.run_gpu(d, 71, step), 71, step)
+    for step, k in enumerate((3, 0, -1, 3)):                  # best three, the sampled token's alone, ids only
+        H.compare(w, H.run_gpu(d, 71, step, k_logprobs=k), 71, step, k_logprobs=k)
