@@ -230,9 +230,12 @@ __device__ __forceinline__ uint32_t sample_bin(float z) {
   return ((uint32_t)t | 4096u) ^ ((uint32_t)((int)b >> 31) & 8191u);
 }
 __device__ __forceinline__ bool outermost_bin(uint32_t i) { return ((i + 1u) & 4095u) <= 1u; }
-// Smallest value of bin i (of one that is not an outermost one).
+// Smallest value of bin i.  (Bin 4096 begins at 0: a threshold raised to it would else lie at 1/4, above values that
+// were counted as kept.  Rows whose largest lie in [0, 1/4) then had an empty list and took the exact path, 210 us a
+// call instead of 24.  Bin 0 has no lower end.)
 __device__ __forceinline__ float sample_floor(uint32_t i) {
-  return i >= 4096u ? __uint_as_float((i - 4096u + kBinBase) << 14) : -__uint_as_float(((4096u - i + kBinBase) << 14) - 1u);
+  if (i == 4096u) return 0.0f;
+  return i > 4096u ? __uint_as_float((i - 4096u + kBinBase) << 14) : -__uint_as_float(((4096u - i + kBinBase) << 14) - 1u);
 }
 
 // A row that top-p or min-p bounds asks for a list that reaches far down (candidate_target()), which a

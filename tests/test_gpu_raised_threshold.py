@@ -49,3 +49,26 @@ def test_raised_threshold(B, V, bf16):
         H.compare(w, H.run_gpu(d, 23, step), 23, step)
         # what the raised list must not lose: peaked rows are settled from it
         assert (H.last_row_why[np.isin(kind, (0, 1, 3))] == 1).all(), H.last_row_why[:12]
+
+
+@pytest.mark.parametrize("B,V,bf16", [(12, 65536, True), (12, 65537, False), (66, 40001, True), (300, 36003, False)])
+def test_largest_values_around_zero(B, V, bf16):
+    """The row's largest in [0, 1/4), on both sides of 0 or just below it, everything else far below: the list reaches
+    down to where they begin, so that it settles the rows."""
+    rng = np.random.default_rng(V)
+    kind = np.arange(B) % 4
+    z = -1.05 - np.abs(rng.standard_normal((B, V)).astype(np.float32)) * 4.0
+    hist = [[] for _ in range(B)]
+    for b, k in enumerate(kind):
+        top = rng.permutation(V)[:V // 100]
+        z[b, top] = (0.24, 0.1, 0.3, -0.2)[k] + (-0.24, 0.1, -0.5, 0.19)[k] * rng.random(top.size)
+        if k == 1:
+            hist[b] = rng.integers(0, V, 300).tolist()
+    params = dict(temperature=np.choose(kind, [0.1, 0.2, 0.15, 0.1]), top_p=np.choose(kind, [0.9, 0.9, 1, 0.9]),
+                  min_p=np.choose(kind, [0, 0, 0.02, 0]), repetition_penalty=np.full(B, 1.1))
+    w = H.custom(f"around0_{V}", workloads.f32_to_bf16_bits(z) if bf16 else z, params, hist, k_logprobs=2)
+    d = H.to_device(w)
+    rows = list(range(B)) if B < 30 else list(range(0, B, B // 24))
+    for step in range(3 if B < 30 else 1):
+        H.compare(w, H.run_gpu(d, 47, step), 47, step, rows=rows)
+        assert (H.last_row_why == 1).all(), H.last_row_why[:12]
