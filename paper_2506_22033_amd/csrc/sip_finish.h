@@ -762,10 +762,11 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
           }
           if (step == kFinKeySteps) code = 9;
         }
-        // the cut is proven to lie inside the list if some complete entry fell on its far side
+        // the cut is proven to lie inside the list if some complete entry fell on its far side, or if all of
+        // them together reach the limit (which has many equal values at the list's end kept, and nothing listed below)
         const bool inside = k_act || others || dropped;
         if (code == 0 && key_p == kFinNone) code = 10;
-        if (code == 0 && !inside && !minp_bounds) code = 11;                   // the nucleus may reach below the list
+        if (code == 0 && !inside && !minp_bounds && fs.hmass[0] < limit) code = 11;     // the nucleus may reach below the list
         key_cut = max(key_k, key_p);
       }
     } else if (code == 0 && !k_act && !minp_bounds) {

@@ -619,12 +619,17 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
   if (wave == 0) {
     uint32_t need, above, K = find_bin(need, above);
     const bool out = outermost_bin(K);
+    float at = out ? 0.0f : sample_floor(K);
     if (!out && bounded) {
       const uint32_t G = raised_group(K / kGroup, above, hist, rp, (float)scale, has_pen,
                                       max(2u, (512u * (uint32_t)n_smp + (uint32_t)V - 1u) / (uint32_t)V), (uint32_t)n_smp);
-      if (G != K / kGroup) K = G * kGroup;
+      // (Put below the group's lower end by as little as still tells the two apart when divided by the temperature: what
+      // equals the threshold counts as outside the list, and logits on coarse values, whole numbers say, lie on that
+      // end by the hundred, having been counted as kept.  64 rows of V = 152064 fp32, whole numbers, top-p 0.99 at 0.3:
+      // 20 of them left their lists.)
+      if (G != K / kGroup) { at = sample_floor(G * kGroup); at -= fmaxf(fabsf(at), 0.25f) * 0x1p-18f; }
     }
-    const BulkRef r = make_bulk_ref(out ? 0.0f : sample_floor(K), scale);
+    const BulkRef r = make_bulk_ref(at, scale);
     if (lane == 0) { sm.key_thr = out ? 1u : 0u; sm.ref = r; }
   }
   if (has_pen && wave > 0) {

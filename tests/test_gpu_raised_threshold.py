@@ -72,3 +72,29 @@ def test_largest_values_around_zero(B, V, bf16):
     for step in range(3 if B < 30 else 1):
         H.compare(w, H.run_gpu(d, 47, step), 47, step, rows=rows)
         assert (H.last_row_why == 1).all(), H.last_row_why[:12]
+
+
+@pytest.mark.parametrize("B,V,bf16", [(60, 50000, True), (60, 65537, False), (300, 40003, True), (600, 50021, False)])
+def test_coarse_values(B, V, bf16):
+    """Whole numbers, halves and ties at 0: a raised threshold lies on a value that many tokens have, which the nucleus
+    may end with, or which may be the largest there is.  The list settles all of them."""
+    rng = np.random.default_rng(V + B)
+    kind = np.arange(B) % 6
+    z = rng.standard_normal((B, V)).astype(np.float32)
+    for b, k in enumerate(kind):
+        if k < 4:
+            z[b] = np.round(z[b] * (2.0, 2.0, 4.0, 3.0)[k]) / (1.0, 1.0, 2.0, 1.0)[k]
+        else:
+            z[b] = -1.05 - np.abs(z[b]) * 4.0
+            top = rng.permutation(V)[:V // 75]
+            z[b, top] = 0.0
+            if k == 5:
+                z[b, top[::2]] = -0.0
+    params = dict(temperature=np.choose(kind, [0.5, 0.3, 0.5, 0.9, 0.1, 0.1]), top_p=np.choose(kind, [0.9, 0.99, 0.9, 1.0, 0.9, 0.9]),
+                  min_p=np.choose(kind, [0, 0, 0, 0.05, 0, 0]))
+    w = H.custom(f"coarse_{V}", workloads.f32_to_bf16_bits(z) if bf16 else z, params, [[] for _ in range(B)], k_logprobs=0)
+    d = H.to_device(w)
+    rows = list(range(0, B, max(1, B // 30)))
+    for step in range(2):
+        H.compare(w, H.run_gpu(d, 53, step), 53, step, rows=rows)
+        assert (H.last_row_why == 1).all(), (H.last_row_why[:12], np.bincount(kind[H.last_row_why != 1]))
