@@ -217,25 +217,33 @@ __device__ __forceinline__ unsigned long long bulk_units(float acc) {
   return acc > 0.0f ? (unsigned long long)(acc * kBulkScale) : 0ull;
 }
 
-// The sample's histogram has a bin per value of sign, exponent and 9 mantissa bits for 1/4 <= |z| < 64, in
-// ascending order; what lies beyond joins the outermost bins of that sign.  (With 8 mantissa bits a row of
-// thousands of elements on each of two neighbouring values had both in its list.)
-constexpr uint32_t kBinBase = 125u << 9;               // of 1/4: exponent and mantissa bits
-constexpr int kGroup = 32;                             // bins of a sixteenth of their values
+// The sample's histogram has a bin per sign, exponent and 9 mantissa bits for 1 <= |z| < 128, in ascending order
+// of z; below 1 the bins are 2^-9 wide, and what lies beyond 128 joins the outermost bin of its sign.  (With 8 mantissa
+// bits a row of thousands of elements on each of two neighbouring values had both in its list.)  A row whose
+// threshold lies in an outermost bin -- nearly always one that is masked with -inf -- or among more values around 0
+// than these bins tell apart has its sample read again: 2 us of a call for the masked, 3 to 4 for logits beyond
+// 128 or all below 0.01.
 // (One level.  13-bit keys first and then the found bin split by 5 bits more, by wave 0 from all threads' largest
 // keys, took 2000 to 3000 cycles longer, 1 us of every call: one row of V = 128256 bf16 20.5 -> 19.6 us.)
+// (The range: with bins of z's own exponent from 1/4 to 64, V = 128256, one row, logits around 100 cost 25.7 us a
+// call bf16, 25.1 fp32, of 1/30 the size 21.7 and 22.1, masked rows 28.4 and 28.9; now 20.0, 19.4, 18.8, 19.5, 20.8 and
+// 21.6.  Bins put around what the row's middle holds cost every call the wait for that, 0.3 us.)
+constexpr float kLow = 0.5f;
+constexpr int kGroup = 32;                             // bins of a sixteenth of their values
 __device__ __forceinline__ uint32_t sample_bin(float z) {
-  const uint32_t b = __float_as_uint(z);
-  const int t = min(max((int)((b >> 14) & 0x1FFFFu) - (int)kBinBase, 0), 4095);
-  return ((uint32_t)t | 4096u) ^ ((uint32_t)((int)b >> 31) & 8191u);
+  // (positive floats, the former the larger one from 1 on, compared as integers)
+  const uint32_t y = max(__float_as_uint(fabsf(z)), __float_as_uint(__fmaf_rn(fabsf(z), 0.5f, kLow)));
+  const uint32_t t = min((y >> 14) - (__float_as_uint(kLow) >> 14), 4095u);
+  return (t | 4096u) ^ ((uint32_t)(__float_as_int(z) >> 31) & 8191u);
 }
-__device__ __forceinline__ bool outermost_bin(uint32_t i) { return ((i + 1u) & 4095u) <= 1u; }
-// Smallest value of bin i.  (Bin 4096 begins at 0: a threshold raised to it would else lie at 1/4, above values that
-// were counted as kept.  Rows whose largest lie in [0, 1/4) then had an empty list and took the exact path, 210 us a
-// call instead of 24.  Bin 0 has no lower end.)
+__device__ __forceinline__ bool outermost_bin(uint32_t i) { return ((i + 1u) & 8191u) <= 1u; }
+__device__ __forceinline__ bool bin_around_0(uint32_t i) { return i - 4064u < 64u; }      // |z| < 1/16
+// Smallest value of bin i (of one that is not an outermost one).  Bin 4096 begins at 0.
 __device__ __forceinline__ float sample_floor(uint32_t i) {
-  if (i == 4096u) return 0.0f;
-  return i > 4096u ? __uint_as_float((i - 4096u + kBinBase) << 14) : -__uint_as_float(((4096u - i + kBinBase) << 14) - 1u);
+  const uint32_t b = __float_as_uint(kLow) >> 14;
+  const float y = __uint_as_float(i >= 4096u ? (i - 4096u + b) << 14 : ((4096u - i + b) << 14) - 1u);
+  const float z = fminf(y, 2.0f * (y - kLow));
+  return i >= 4096u ? z : -z;
 }
 
 // A row that top-p or min-p bounds asks for a list that reaches far down (candidate_target()), which a
@@ -256,7 +264,8 @@ __device__ __forceinline__ float sample_floor(uint32_t i) {
 // For one wave.  G: group of bins the threshold lies in; above: sample values above
 // that group; c: log2_scale() of the row.
 __device__ __forceinline__ uint32_t raised_group(const uint32_t G, const uint32_t above, const uint32_t* hist, const RowParams& rp,
-                                                 const float c, const bool has_pen, const uint32_t least, const uint32_t n_smp) {
+                                                 const float c, const bool has_pen, const uint32_t least,
+                                                 const uint32_t n_smp) {
   constexpr int kUp = 44;                              // lane l has group G + kUp - l
   const int lane = lane_id(), g = (int)G + kUp - lane;
   const bool in = g >= 0 && g < kSampleBins / kGroup;
@@ -546,7 +555,6 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
     sm.tag_words[tid] = make_uint4(word(0), word(1), word(2), word(3));
   }
   const double scale = log2_scale(rp);     // (worked out while the sample travels)
-  if (tid < 32) sm.sub_hist[tid] = 0;
   if (tid < Sh::kBlocks) sm.blk_mass[tid] = 0ull;
   if (tid == 0) sm.seg_cnt = 0;
   __syncthreads();
@@ -563,21 +571,24 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
   const uint32_t j = want;
   const bool tail_only = whole || j <= (uint32_t)(kTailRank + kTailRank / 2);
   auto count_in = [&](uint32_t bin) { atomicAdd(&hist[bin >> 1], (bin & 1u) ? 0x10000u : 1u); };
+  // the three largest as floats, one maximum and two medians per value
+  float f0 = -INFINITY, f1 = -INFINITY, f2 = -INFINITY;
+  auto best = [&](const uint4& q) {
+    float z[EPL];
+    unpack(q, z);
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+      const float x = z[i];
+      f2 = __builtin_amdgcn_fmed3f(f1, f2, x);
+      f1 = __builtin_amdgcn_fmed3f(f0, f1, x);
+      f0 = fmaxf(f0, x);
+    }
+  };
   if (tail_only) {
-    // the three largest as floats, one maximum and two medians per value
-    float f0 = -INFINITY, f1 = -INFINITY, f2 = -INFINITY;
 #pragma unroll
     for (int l = 0; l < SLOADS; ++l) {
       if (!whole && (l & 1)) continue;
-      float z[EPL];
-      unpack(smp[l], z);
-#pragma unroll
-      for (int i = 0; i < EPL; ++i) {
-        const float x = z[i];
-        f2 = __builtin_amdgcn_fmed3f(f1, f2, x);
-        f1 = __builtin_amdgcn_fmed3f(f0, f1, x);
-        f0 = fmaxf(f0, x);
-      }
+      best(smp[l]);
     }
     count_in(sample_bin(f0)); count_in(sample_bin(f1)); count_in(sample_bin(f2));
   } else {
@@ -617,9 +628,11 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
     return 2u * (uint32_t)(kSampleBins / 2 - 1 - src * WPL - src2) + (upper ? 1u : 0u);
   };
   if (wave == 0) {
-    uint32_t need, above, K = find_bin(need, above);
-    const bool out = outermost_bin(K);
-    float at = out ? 0.0f : sample_floor(K);
+    uint32_t need, above;
+    const uint32_t K = find_bin(need, above);
+    bool out = outermost_bin(K);
+    if (__builtin_expect(bin_around_0(K), 0)) out = ((hist[K >> 1] >> (K & 1u) * 16u) & 0xFFFFu) - need > j / 4u + 8u;
+    float at = sample_floor(K);
     if (!out && bounded) {
       const uint32_t G = raised_group(K / kGroup, above, hist, rp, (float)scale, has_pen,
                                       max(2u, (512u * (uint32_t)n_smp + (uint32_t)V - 1u) / (uint32_t)V), (uint32_t)n_smp);
@@ -627,9 +640,9 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
       // equals the threshold counts as outside the list, and logits on coarse values, whole numbers say, lie on that
       // end by the hundred, having been counted as kept.  64 rows of V = 152064 fp32, whole numbers, top-p 0.99 at 0.3:
       // 20 of them left their lists.)
-      if (G != K / kGroup) { at = sample_floor(G * kGroup); at -= fmaxf(fabsf(at), 0.25f) * 0x1p-18f; }
+      if (G != K / kGroup) { at = sample_floor(G * kGroup); at -= fmaxf(fabsf(at), kLow) * 0x1p-18f; }
     }
-    const BulkRef r = make_bulk_ref(at, scale);
+    const BulkRef r = make_bulk_ref(out ? 0.0f : at, scale);
     if (lane == 0) { sm.key_thr = out ? 1u : 0u; sm.ref = r; }
   }
   if (has_pen && wave > 0) {
@@ -660,71 +673,81 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
     mark_all(a.p_tokens, pen.p_lo, pen.p_hi);                                  // separate prompt
   }
   __syncthreads();                                   // also: the histogram is dead from here on
-  if (sm.key_thr != 0u) {                                                         // workgroup-uniform
-    // The j-th largest lies among the values that the histogram does not tell apart (|z| below 1/4 or from
-    // 64 on, -inf): the same over 13-bit keys (sign, exponent, 4 mantissa bits), the bin that holds it then
-    // split by the next 5.  (Rarely needed, and read again: held until here, the sample costs registers.)
-    auto each_key = [&](auto&& f) {
+  if (__builtin_expect(sm.key_thr != 0u, 0)) {                                    // workgroup-uniform
+    // The bins do not tell where the j-th largest lies.  The sample once more (read again, a load at a time: held
+    // until here, it costs registers): its lowest finite value, how many there are in the blocks that count, the
+    // threads' three largest.
+    f0 = f1 = f2 = -INFINITY;
+    float lo = INFINITY;
+    uint32_t n_fin = 0;
 #pragma nounroll
-      for (int l = 0; l < SLOADS; l += whole ? 1 : 2) {
-        float z[EPL];
-        unpack(load_sample(l), z);
+    for (int l = 0; l < SLOADS; ++l) {
+      const bool counts = whole || !(l & 1);
+      const uint4 q = load_sample(l);
+      float z[EPL];
+      unpack(q, z);
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) f(key_of(z[i]));
-      }
-    };
+      for (int i = 0; i < EPL; ++i)
+        if (z[i] > -INFINITY) { lo = fminf(lo, z[i]); n_fin += counts ? 1u : 0u; }
+      if (counts) best(q);
+    }
+    uint32_t klo = last_lane_u32(dpp_scan_min_u32(lo == INFINITY ? 0xFFFFFFFFu : key_of(lo)));
+    n_fin = last_lane_u32(dpp_scan_add_u32(n_fin));
+    if (lane == 0) { sm.red32[wave] = klo; sm.red64[wave] = n_fin; }
     uint4* const z4 = reinterpret_cast<uint4*>(hist);
     for (int i = tid; i < kSampleBins * 2 / 16; i += kStreamThreads) z4[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    each_key([&](uint32_t k) { count_in(k >> 19); });
-    __syncthreads();
-    uint32_t need = 1, above;
-    if (wave == 0) {
-      const uint32_t K = find_bin(need, above);
-      if (lane == 0) sm.key_thr = K;
-    }
-    __syncthreads();
-    const uint32_t K = sm.key_thr;
-    each_key([&](uint32_t k) { if ((k >> 19) == K) atomicAdd(&sm.sub_hist[(k >> 14) & 31u], 1u); });
-    __syncthreads();
-    if (wave == 0) {
-      // lane l: sub-bin 31 - l, descending
-      const uint32_t c = lane < 32 ? sm.sub_hist[31 - min(lane, 31)] : 0u;
-      const uint32_t incl = dpp_scan_add_u32(c);
-      const unsigned long long reach = __ballot(lane < 32 && incl >= need);
-      const uint32_t first = reach ? (uint32_t)__ffsll((long long)reach) - 1u : 31u;
-      const uint32_t k18 = (K << 5) | (31u - first);                           // 18-bit key
-      const BulkRef r = make_bulk_ref(value_of(k18 << 14), scale);
-      if (lane == 0) { sm.key_thr = k18; sm.ref = r; }
-    }
-    __syncthreads();
-    // A row that is masked almost everywhere (-inf for all but a few hundred tokens, as a grammar
-    // constraint leaves it) has fewer finite values in its sample than the list asks for, and the
-    // threshold has landed among the -inf (keys up to 511 in 18 bits: -inf and the negative NaNs).
-    // Then the lowest finite sample value is the threshold: the list takes every finite element
-    // from there up, and what lies below it is bulk as usual.  (No finite sample value at all: the
-    // lowest finite float, which makes the finishing kernel pass the row on.)
-    if (sm.key_thr <= 511u) {                                                     // workgroup-uniform
-      float lo = INFINITY;
-#pragma nounroll
-      for (int l = 0; l < SLOADS; ++l) {
-        float z[EPL];
-        unpack(load_sample(l), z);
+    klo = sm.red32[0]; n_fin = (uint32_t)sm.red64[0];
 #pragma unroll
-        for (int i = 0; i < EPL; ++i)
-          if (z[i] > -INFINITY && z[i] < lo) lo = z[i];
-      }
-      uint32_t klo = last_lane_u32(dpp_scan_min_u32(lo == INFINITY ? 0xFFFFFFFFu : key_of(lo)));
-      if (lane == 0) sm.red32[wave] = klo;
-      __syncthreads();
-      klo = sm.red32[0];
-#pragma unroll
-      for (int w = 1; w < kStreamWaves; ++w) klo = min(klo, sm.red32[w]);
+    for (int w = 1; w < kStreamWaves; ++w) { klo = min(klo, sm.red32[w]); n_fin += (uint32_t)sm.red64[w]; }
+    if (n_fin < j) {                                                              // workgroup-uniform
+      // A row that is masked almost everywhere (-inf for all but a few hundred tokens, as a grammar
+      // constraint leaves it) has fewer finite values in its sample than the list asks for.  Then the
+      // lowest of them is the threshold: the list takes every finite element from there up, and what
+      // lies below it is bulk as usual.  (No finite sample value at all: the lowest finite float,
+      // which makes the finishing kernel pass the row on.)
       const uint32_t k18 = klo == 0xFFFFFFFFu ? 512u : max(klo >> 14, 512u);
-      __syncthreads();
       if (tid == 0) sm.ref = make_bulk_ref(value_of(k18 << 14), scale);
+    } else {
+      // Else over 13-bit keys (sign, exponent, 4 mantissa bits), the bin that holds the j-th largest then split by the
+      // next 5.
+      auto each_key = [&](auto&& f) {
+        if (tail_only) {
+          f(key_of(f0)); f(key_of(f1)); f(key_of(f2));
+        } else {
+#pragma nounroll
+          for (int l = 0; l < SLOADS; l += 2) {
+            float z[EPL];
+            unpack(load_sample(l), z);
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) f(key_of(z[i]));
+          }
+        }
+      };
+      each_key([&](uint32_t k) { count_in(k >> 19); });
       __syncthreads();
+      if (tid < 32) sm.sub_hist[tid] = 0;              // (where the waves' sums were)
+      uint32_t need = 1, above;
+      if (wave == 0) {
+        const uint32_t K = find_bin(need, above);
+        if (lane == 0) sm.key_thr = K;
+      }
+      __syncthreads();
+      const uint32_t K = sm.key_thr;
+      each_key([&](uint32_t k) { if ((k >> 19) == K) atomicAdd(&sm.sub_hist[(k >> 14) & 31u], 1u); });
+      __syncthreads();
+      if (wave == 0) {
+        // lane l: sub-bin 31 - l, descending
+        const uint32_t c = lane < 32 ? sm.sub_hist[31 - min(lane, 31)] : 0u;
+        const uint32_t incl = dpp_scan_add_u32(c);
+        const unsigned long long reach = __ballot(lane < 32 && incl >= need);
+        const uint32_t first = reach ? (uint32_t)__ffsll((long long)reach) - 1u : 31u;
+        const uint32_t k18 = max((K << 5) | (31u - first), 512u);              // 18-bit key, of a finite value
+        const BulkRef r = make_bulk_ref(value_of(k18 << 14), scale);
+        if (lane == 0) sm.ref = r;
+      }
     }
+    __syncthreads();
   }
   BulkRef ref = sm.ref;
   auto uniform = [](float x) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x))); };
