@@ -1302,7 +1302,7 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
       if (v < V && ((word >> (v & 31)) & 1u)) sv[i] = value_of(cnt[pre[v >> 5] + __popc(word & ((1u << (v & 31)) - 1u))]);
     }
   };
-  auto mass = [&](float sv) { return mass_units(__builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(sv, m), 1.44269504f))); };
+  auto mass = [&](float sv) { return mass_units(exp_nonpos(__fsub_rn(sv, m))); };   // as a list's, which the limit is from
   auto kept_minp = [&](float sv) { return !minp_on || __fsub_rn(sv, m) >= t_minp; };
   float lo[kLevels] = {m - kSpan, 0.0f, 0.0f}, sc[kLevels] = {};       // (indexed with constants only)
   int pick[kLevels] = {};
@@ -1540,12 +1540,14 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
 // it each on flat rows, 8 on rows whose tail is a few hundred elements).  The read then sums, per block of 1024 elements, what lies above that
 // window, and lists what lies in it (some thousand elements, to where the row's candidates were); bins over
 // the window, and the members of one of them, settle the cut; and one block is read again for the token.
-// Every decision is taken on the exact fp32 s; masses of a load are added in fp32, in the order of its
-// elements, and from there on as integers.  Returns 1 (fs.token, fs.token_key), 13 (no mass), or 0: the window
-// is too long for the room, or the cut not in it (whole_row_nucleus() then does without one).
-// What bounds it: vector issue of one compute unit (30 instructions an element).  us a call, against a second list and
-// two reads: 1 row of V = 256000 fp32, flat 269 -> 114, V = 213087 bf16 234 -> 106; V = 200000 fp32, 64 rows, 16 of them flat
-// 267 -> 111; V = 128256 bf16, 256 rows, 244 of them spiked at top-p 0.9 291 -> 98; V = 166557 fp32, 1883 rows, 471 flat 752 -> 436.
+// Every decision is taken on the exact fp32 s; masses are exp_nonpos() like a list's, every element's an
+// integer.  (Added up in fp32 over a load first, what weighs less than 2^-24 of its neighbour could not be drawn, and
+// v_exp_f32 of a rounded product is off by 1e-6 some twenty below the maximum: that was 115 us in place of 133 in the
+// first of the calls below, 96 in place of 103 in the fourth.)  Returns 1 (fs.token, fs.token_key), 13 (no mass), or
+// 0: the window is too long for the room, or the cut not in it (whole_row_nucleus() then does without one).
+// What bounds it: vector issue of one compute unit (some 40 instructions an element).  us a call, against a second list and
+// two reads: 1 row of V = 256000 fp32, flat 269 -> 133, V = 213087 bf16 234 -> 125; V = 200000 fp32, 64 rows, 16 of them flat
+// 267 -> 111; V = 128256 bf16, 256 rows, 244 of them spiked at top-p 0.9 291 -> 103; V = 166557 fp32, 1883 rows, 471 flat 752 -> 436.
 template <int DT>
 __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, const int V_any, const bool has_pen_any,
                                                           const uint32_t* bm, const unsigned short* pre, const uint32_t* cnt,
@@ -1614,7 +1616,7 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
       for (int i = 0; i < EPL; ++i) sv[i] = e0 + i < V ? sv[i] : -INFINITY;
     }
   };
-  auto rel = [&](float sv) { return __builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(sv, m), 1.44269504f)); };
+  auto rel = [&](float sv) { return exp_nonpos(__fsub_rn(sv, m)); };
   auto mass = [&](float sv) { return mass_units(rel(sv)); };
   // every penalised token: f(s, token) per lane that has one, all lanes of the wave together
   auto each_penalised = [&](auto&& f) {
@@ -1724,18 +1726,19 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
   const int per_wave = (nblk + kFinalWaves - 1) / kFinalWaves;
   global_u64* const seg = region + (size_t)wave * wave_cap;
   uint32_t qn = 0;                                        // wave-uniform: the wave's entries
-  auto part_of = [&](const float (&sv)[EPL], uint32_t& in) -> float {          // mass above the window; bit EPL-1-i: element i lies in it
+  // mass above the window; bit EPL-1-i of `in`: element i lies in it
+  auto part_of = [&](const float (&sv)[EPL], uint32_t& in) -> unsigned long long {
     uint32_t not_lo = ~0u, not_hi = ~0u;
-    float part = 0.0f;
+    unsigned long long part = 0;
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
       const float a_lo = __fsub_rn(sv[i], s_lo), a_hi = __fsub_rn(sv[i], s_hi);               // (a difference has the comparison's sign)
       not_lo = __builtin_amdgcn_alignbit(not_lo, __float_as_uint(a_lo), 31);
       not_hi = __builtin_amdgcn_alignbit(not_hi, __float_as_uint(a_hi), 31);
-      part += a_hi >= 0.0f ? rel(sv[i]) : 0.0f;
+      part += mass_bits(a_hi >= 0.0f ? rel(sv[i]) : 0.0f);
     }
     in = ~not_lo & not_hi & ((1u << EPL) - 1u);
-    return part;
+    return part - (unsigned long long)EPL * kMagicBits;
   };
   uint4 q[UNR], next[UNR];                                // (a block's loads and the next one's)
 #pragma unroll
@@ -1751,7 +1754,7 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
       float sv[EPL];
       svals(q[u], e0, base + BLK > V, sv);                // (uniform)
       uint32_t in;
-      A += mass_units(part_of(sv, in));
+      A += part_of(sv, in);
       unsigned long long mask = __ballot(in != 0u);
       while (mask) {
         const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, qn));
@@ -1908,30 +1911,25 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
     for (int u = 0; u < UNR && !found; ++u) {
       const int e0 = base + (u * kWave + lane) * EPL;
       const uint4 q = ldrow(e0);
-      float sv[EPL], pv[EPL];
+      float sv[EPL];
       svals(q, e0, true, sv);
       const uint32_t word = has_pen ? bm[min(e0, V - 1) >> 5] : 0u;
-      // element i: what it adds to the load's fp32 sum, or as an integer
-      auto single = [&](int i) -> unsigned long long {
-        float x = sv[i];
-        if (e0 + i < V && ((word >> ((e0 + i) & 31)) & 1u)) x = value_of(cnt[pre[(e0 + i) >> 5] + __popc(word & ((1u << ((e0 + i) & 31)) - 1u))]);
-        pv[i] = x;
-        return x > -INFINITY && !(sv[i] >= s_hi) && key_of(x) >= key_cut ? mass(x) : 0ull;
-      };
-      float part = 0.0f;
-      unsigned long long ints = 0;
-#pragma unroll
-      for (int i = 0; i < EPL; ++i) { part += sv[i] >= s_hi ? rel(sv[i]) : 0.0f; ints += single(i); }
-      const unsigned long long tot = mass_units(part) + ints;
-      const unsigned long long incl = dpp_scan_add_u64(tot);
-      const unsigned long long before = running + incl - tot;
-      int hit = -1;
-      uint32_t hit_key = 0;
-      part = 0.0f; ints = 0;
+      unsigned long long E[EPL], tot = 0;
 #pragma unroll
       for (int i = 0; i < EPL; ++i) {
-        part += sv[i] >= s_hi ? rel(sv[i]) : 0.0f; ints += single(i);
-        if (hit < 0 && before + mass_units(part) + ints > target) { hit = e0 + i; hit_key = key_of(pv[i]); }
+        if (e0 + i < V && ((word >> ((e0 + i) & 31)) & 1u))
+          sv[i] = value_of(cnt[pre[(e0 + i) >> 5] + __popc(word & ((1u << ((e0 + i) & 31)) - 1u))]);
+        E[i] = sv[i] > -INFINITY && key_of(sv[i]) >= key_cut ? mass(sv[i]) : 0ull;
+        tot += E[i];
+      }
+      const unsigned long long incl = dpp_scan_add_u64(tot);
+      unsigned long long c = running + incl - tot;
+      int hit = -1;
+      uint32_t hit_key = 0;
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) {
+        c += E[i];
+        if (hit < 0 && E[i] && c > target) { hit = e0 + i; hit_key = key_of(sv[i]); }
       }
       const unsigned long long ball = __ballot(hit >= 0);
       found = ball != 0;

@@ -8,6 +8,7 @@ import torch
 
 import paper_2506_22033_amd as sip
 import workloads
+from oracle import sip_oracle as O
 from tests import sip_harness as H
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +52,23 @@ def test_cut_in_one_read(B, V, bf16, pieces):
             out = H.run_gpu(d, 41, step)
             assert (H.last_row_path[np.isin(kind, (0, 1, 4, 6))] == 16).all(), H.last_row_path[:10]
         H.compare(w, out, 41, step, rows=rows)
+
+
+@pytest.mark.parametrize("at,top_p,row_id", [(0, 0.9973, 4802487), (131072, 0.9971, 2227849)])
+def test_small_masses_beside_a_large_one(at, top_p, row_id):
+    """One token of mass 1, the three behind it of 0.996 * 2^-24 each, which a sum in fp32 over the four leaves out, and a flat
+    tail of which the nucleus keeps a part.  The rows' ids are such that the draw falls on the middle one of the three: 0.4
+    of a mass from either neighbour's share in float64, where one element more or less in the cut is worth 0.5 and the
+    limit lies a quarter of an element from the nearest."""
+    V = 262144
+    z = np.random.default_rng(5).uniform(-19.0, -16.7, V).astype(np.float32)
+    z[at], z[at + 1:at + 4] = 0.0, -16.64
+    mass = np.exp(z.astype(np.float64))
+    order = np.argsort(-z)
+    n = int(np.searchsorted(np.cumsum(mass[order]), float(np.float32(top_p)) * mass.sum())) + 1
+    kept = np.where(z >= z[order[n - 1]], mass, 0.0)
+    assert int(np.searchsorted(np.cumsum(kept), O.row_uniform(41, row_id, 0) * kept.sum(), side="right")) == at + 2
+    w = H.custom("beside", z[None], dict(top_p=np.array([top_p])), k_logprobs=-1)
+    ids, _, _ = H.run_gpu(H.to_device(w), 41, 0, row_ids=torch.tensor([row_id], dtype=torch.int64, device=H.DEV))
+    assert H.last_row_path[0] == 16
+    assert ids[0] == at + 2
