@@ -1545,9 +1545,10 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
 // v_exp_f32 of a rounded product is off by 1e-6 some twenty below the maximum: that was 115 us in place of 133 in the
 // first of the calls below, 96 in place of 103 in the fourth.)  Returns 1 (fs.token, fs.token_key), 13 (no mass), or
 // 0: the window is too long for the room, or the cut not in it (whole_row_nucleus() then does without one).
-// What bounds it: vector issue of one compute unit (some 40 instructions an element).  us a call, against a second list and
-// two reads: 1 row of V = 256000 fp32, flat 269 -> 133, V = 213087 bf16 234 -> 125; V = 200000 fp32, 64 rows, 16 of them flat
-// 267 -> 111; V = 128256 bf16, 256 rows, 244 of them spiked at top-p 0.9 291 -> 103; V = 166557 fp32, 1883 rows, 471 flat 752 -> 436.
+// What bounds it: vector issue of one compute unit (some 40 instructions an element).  us a call, against a second
+// list and two reads: 1 row of V = 256000 fp32, flat 269 -> 138, V = 213087 bf16 234 -> 126; V = 200000 fp32, 64 rows, 16
+// of them flat 267 -> 140; V = 128256 bf16, 256 rows, 244 of them spiked at top-p 0.9 291 -> 103; V = 166557 fp32,
+// 1883 rows, 471 flat 752 -> 497.
 template <int DT>
 __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, const int V_any, const bool has_pen_any,
                                                           const uint32_t* bm, const unsigned short* pre, const uint32_t* cnt,
@@ -1638,7 +1639,7 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
   __syncthreads();
   for (int i = tid; i < kBins; i += NT) { hm[i] = 0; hc[i] = 0; }
   if (tid < 2) { fs.w_lo[tid] = -1; fs.w_hi[tid] = -1; }
-  if (tid == 0) { fs.bin_p = 1 << 30; fs.bin_d = -1; fs.n_memb2 = 0; fs.key_p = 0xFFFFFFFFu; fs.key_k = 0; fs.token = 0x7FFFFFFF; fs.w_sq = -1.0f; }
+  if (tid == 0) { fs.bin_p = 1 << 30; fs.bin_d = -1; fs.n_memb2 = 0; fs.key_p = 0xFFFFFFFFu; fs.key_k = 0; fs.token = 0x7FFFFFFF; fs.w_sq = -1.0f; fs.rq_n = 0; }
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < SL; ++j) {
@@ -1710,7 +1711,6 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
     }
   }
   __syncthreads();
-  const uint32_t wave_cap = cap / kFinalWaves;
   int pick = -1;
 #pragma unroll
   for (int k = 1; k >= 0; --k)                            // the wider one where it fits (an eighth of the room to spare)
@@ -1724,8 +1724,31 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
   // ---- the read: sums per block of what lies above, list of what lies in the window
   const int nblk = (V + BLK - 1) / BLK;
   const int per_wave = (nblk + kFinalWaves - 1) / kFinalWaves;
-  global_u64* const seg = region + (size_t)wave * wave_cap;
-  uint32_t qn = 0;                                        // wave-uniform: the wave's entries
+  // The list is dealt out in pages of a wave's size, as they are asked for: a wave's share of the row may hold most of
+  // the window (ids in order of frequency, a piece with a tail of its own).  Fixed eighths ran over there, and the row was read
+  // twice more: 400 rows of V = 131072 fp32 with their tail in an eighth of the ids, top-p 0.5, 454 -> 249 us; what did not run
+  // over takes 0 to 5 % longer.
+  constexpr uint32_t kPage = kWave;
+  const uint32_t room = cap / kPage * kPage;
+  const uint32_t key_none = key_of(-INFINITY);            // of places left empty
+  uint32_t at = 0, end = 0;                               // wave-uniform: the rest of the wave's page
+  typedef __attribute__((address_space(3))) uint32_t lds_u32;
+  lds_u32* const pages = (lds_u32*)&fs.rq_n;              // (as a flat address its answer would wait for the loads under way)
+  auto push = [&](const unsigned long long mask, const bool mine, auto&& entry) {                // by all lanes
+    const uint32_t to = at + (uint32_t)__popcll(mask);
+    uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, at));
+    if (__builtin_expect(to > end, 0)) {                  // uniform
+      uint32_t page = 0;
+      if (lane == 0) page = __hip_atomic_fetch_add(pages, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      page = (uint32_t)__builtin_amdgcn_readfirstlane((int)page) * kPage;
+      if (pos >= end) pos = page + (pos - end);
+      at = page + (to - end);
+      end = page + kPage;
+    } else {
+      at = to;
+    }
+    if (mine && pos < room) region[pos] = entry();
+  };
   // mass above the window; bit EPL-1-i of `in`: element i lies in it
   auto part_of = [&](const float (&sv)[EPL], uint32_t& in) -> unsigned long long {
     uint32_t not_lo = ~0u, not_hi = ~0u;
@@ -1757,17 +1780,15 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
       A += part_of(sv, in);
       unsigned long long mask = __ballot(in != 0u);
       while (mask) {
-        const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, qn));
-        if (in != 0u && pos < wave_cap) {
+        push(mask, in != 0u, [&]() {
           const int i = EPL - __ffs((int)in);
           float z[EPL], x = 0.0f;
           raw(q[u], z);
 #pragma unroll
           for (int k = 0; k < EPL; ++k) x = k == i ? z[k] : x;
-          seg[pos] = ((unsigned long long)(uint32_t)(e0 + i) << 32) | key_of(by_tau.of(x));
-        }
+          return ((unsigned long long)(uint32_t)(e0 + i) << 32) | key_of(by_tau.of(x));
+        });
         in &= in - 1u;
-        qn += (uint32_t)__popcll(mask);
         mask = __ballot(in != 0u);
       }
     }
@@ -1781,31 +1802,27 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
     const bool above = have && sv >= s_hi, in = have && sv >= s_lo && !above;
     if (above) atomicAdd(&hd[v / BLK], mass(sv));
     const unsigned long long mask = __ballot(in);
-    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, qn));
-    if (in && pos < wave_cap) seg[pos] = ((unsigned long long)v << 32) | key_of(sv);
-    qn += (uint32_t)__popcll(mask);
+    if (mask) push(mask, in, [&]() { return ((unsigned long long)v << 32) | key_of(sv); });
   });
-  if (lane == 0) fs.r32[wave] = qn;
+  for (uint32_t i = at + (uint32_t)lane; i < min(end, room); i += kWave) region[i] = key_none;
   __syncthreads();                                        // (a workgroup's own stores are visible to it behind a barrier)
-  bool full = false;
-#pragma unroll
-  for (int ww = 0; ww < kFinalWaves; ++ww) full |= fs.r32[ww] > wave_cap;
-  if (full) return 0;                                     // uniform
+  const uint32_t n_list = fs.rq_n * kPage;
+  if (n_list > room) return 0;                            // uniform
   // ---- the cut: bins over the window, then the members of one
   const float sc = (float)kBins / __fsub_rn(s_hi, s_lo);
   auto bin_at = [&](float sv) { return min(kBins - 1, max(0, (int)(__fsub_rn(sv, s_lo) * sc))); };
-  // every entry of the wave, four under way at a time
+  // every entry, four of a lane under way at a time
   auto each_entry = [&](auto&& f) {
-    for (uint32_t i0 = 0; i0 < qn; i0 += 4 * kWave) {
+    for (uint32_t i0 = (uint32_t)tid; i0 < n_list; i0 += 4 * NT) {             // (wave-uniform: whole pages)
       uint2 en[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const unsigned long long w = seg[min(i0 + (uint32_t)(k * kWave + lane), qn - 1u)];
+        const unsigned long long w = region[min(i0 + (uint32_t)(k * NT), n_list - 1u)];
         en[k] = make_uint2((uint32_t)w, (uint32_t)(w >> 32));
       }
 #pragma unroll
       for (int k = 0; k < 4; ++k)
-        if (i0 + (uint32_t)(k * kWave + lane) < qn) f(en[k]);
+        if (i0 + (uint32_t)(k * NT) < n_list && en[k].x != key_none) f(en[k]);
     }
   };
   each_entry([&](const uint2& en) {

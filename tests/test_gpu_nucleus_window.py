@@ -72,3 +72,38 @@ def test_small_masses_beside_a_large_one(at, top_p, row_id):
     ids, _, _ = H.run_gpu(H.to_device(w), 41, 0, row_ids=torch.tensor([row_id], dtype=torch.int64, device=H.DEV))
     assert H.last_row_path[0] == 16
     assert ids[0] == at + 2
+
+
+def test_which_rows_the_window_settles():
+    """What the window lists goes into the row's room in the workspace, as the element's number above the ordered bits of
+    its s.  With the thirty tokens on either side of the cut all there the row was settled by its window; with none of them
+    it went straight to the two reads.  (At 400 rows a row has room for 7680 entries.)  Of each four rows: flat; the tail
+    in one eighth of the ids, where it has 2400 entries in the window; min-p beside top-p; a fifth of the row, far
+    more than there is room for, on the value of the cut."""
+    B, V = 400, 131072
+    assert sip.binding.load().sip_plan_chunks(B, V, sip.SIP_F32, 0) * 3840 == 7680
+    rng = np.random.default_rng(11)
+    z = np.full((B, V), -30.0, np.float32)
+    z[0::4] = rng.uniform(-1.0, 0.0, (B // 4, V))
+    z[1::4, V // 2:V // 8 * 5] = rng.uniform(-1.0, 0.0, (B // 4, V // 8))
+    z[2::4] = rng.uniform(-1.0, 0.0, (B // 4, V))
+    z[3::4] = np.round(rng.standard_normal((B // 4, V)) * 2) / 2
+    kind = np.arange(B) % 4
+    top_p = np.choose(kind, [0.9, 0.5, 0.9, 0.9])
+    w = H.custom("which", z, dict(top_p=top_p, min_p=np.where(kind == 2, 1e-3, 0.0)), k_logprobs=0)
+    d = H.to_device(w)
+    ws = torch.zeros(sip.sip_workspace_bytes(B, V, sip.SIP_F32, 0, 0), dtype=torch.uint8, device=H.DEV)
+    out = sip.sip_sample(d.logits, d.params, None, None, 41, 0, 0, V=V, workspace=ws)
+    torch.cuda.synchronize()
+    assert (ws[:4 * B].view(torch.int32) == 16).all(), ws[:4 * B].view(torch.int32)[:8]
+    words = ws[:ws.numel() // 8 * 8].view(torch.int64)
+    for b in [*range(8), B - 3, B - 1]:
+        mass = np.exp(z[b].astype(np.float64))
+        order = np.argsort(-z[b], kind="stable")
+        n = int(np.searchsorted(np.cumsum(mass[order]), float(np.float32(top_p[b])) * mass.sum())) + 1
+        near = order[n - 30:n + 30]
+        bits = z[b, near].view(np.uint32).astype(np.int64)
+        word = (near.astype(np.int64) << 32) | np.where(bits >> 31, bits ^ 0xFFFFFFFF, bits | 0x80000000)
+        there = int(torch.isin(torch.from_numpy(word).to(H.DEV), words).sum())
+        assert there == (60 if kind[b] < 2 else 0), (b, there)
+    H.compare(w, tuple(x.cpu().numpy() for x in out), 41, 0, rows=list(range(8)))
