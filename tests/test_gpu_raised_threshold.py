@@ -3,7 +3,9 @@ both sides of the line, rows whose largest tokens a penalty takes away (the list
 settles the row), logits far from 0 on either side, where a bin of the sample is wide or the outermost one, and samples with few or equal values."""
 import numpy as np
 import pytest
+import torch
 
+import paper_2506_22033_amd as sip
 import workloads
 from tests import sip_harness as H
 
@@ -98,3 +100,27 @@ def test_coarse_values(B, V, bf16):
     for step in range(2):
         H.compare(w, H.run_gpu(d, 53, step), 53, step, rows=rows)
         assert (H.last_row_why == 1).all(), (H.last_row_why[:12], np.bincount(kind[H.last_row_why != 1]))
+
+
+@pytest.mark.parametrize("B,V", [(12, 131072), (40, 131072)])
+def test_which_lists_are_short(B, V):
+    """A row's list lies in the workspace, a logit's bits with its index above them.  Peaked rows have the 512 tokens that
+    every list holds, give or take three standard deviations of the sample's 32 and a group of bins, which a Student-t
+    tail puts a fifth more into; normal logits of standard deviation 3.8, of which 95 % of the mass are some 2000
+    tokens, half of what is left out being the least that may lie below a list, have more than twice that many."""
+    rng = np.random.default_rng(V + B)
+    z = (rng.standard_normal((B, V)) * 3.8).astype(np.float32)
+    z[::2] = rng.standard_t(3, (B // 2, V)) * 2.0
+    z[::2, 17] = 40.0 + np.arange(B // 2)
+    w = H.custom("lists", z, dict(temperature=np.ones(B), top_p=np.full(B, 0.9)), k_logprobs=0)
+    d = H.to_device(w)
+    ws = torch.zeros(sip.sip_workspace_bytes(B, V, sip.SIP_F32, 0, 0), dtype=torch.uint8, device=H.DEV)
+    sip.sip_sample(d.logits, d.params, None, None, 23, 0, 0, V=V, workspace=ws)
+    torch.cuda.synchronize()
+    assert (ws[:8 * B].view(torch.int32) == 1).all()
+    words = ws[:ws.numel() // 8 * 8].view(torch.int64)
+    place = torch.arange(V, device=H.DEV) << 32
+    for b in range(B):
+        bits = d.logits[b, :V].view(torch.int32).to(torch.int64) & 0xFFFFFFFF
+        n = int(torch.isin(bits | place, words).sum())
+        assert (240 < n < 1000) if b % 2 == 0 else (1100 < n < 4096), (b, n)
