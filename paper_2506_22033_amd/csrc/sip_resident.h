@@ -89,10 +89,10 @@ __device__ __forceinline__ void halve_u64(unsigned long long (&t)[N], bool upper
 }
 template <int N>
 __device__ __forceinline__ unsigned long long row_sums_u64(unsigned long long (&t)[N], int lane) {
-  static_assert(N == 1 || N == 2 || N == 4 || N == 8, "");
+  static_assert(N == 2 || N == 4 || N == 8, "");
   if constexpr (N >= 8) halve_u64<0x141, 4>(t, lane & 4);                      // from the other end of eight lanes
   if constexpr (N >= 4) halve_u64<0x4E, 2>(t, lane & 2);                       // lane ^ 2
-  if constexpr (N >= 2) halve_u64<0xB1, 1>(t, lane & 1);                       // lane ^ 1
+  halve_u64<0xB1, 1>(t, lane & 1);                                             // lane ^ 1
   unsigned long long v = t[0] + dpp_mov_u64<0x128>(t[0]);                      // rotations by 8, 4, 2
   if constexpr (N <= 4) v += dpp_mov_u64<0x124>(v);
   if constexpr (N <= 2) v += dpp_mov_u64<0x122>(v);
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
         if (__any(some)) t_of[j] = lane_mass(j);
       }
     }
-    if (NL == 1) {
+    if constexpr (NL == 1) {
       const unsigned long long t = wave_add_u64(t_of[0]);
       if (lane == 0) fs.blk[wave] = t;
     } else {
