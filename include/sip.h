@@ -91,8 +91,10 @@ typedef struct {
  *   other value = finished after reading the row again (normally from cache): 15 = from a second,
  *   longer candidate list (one more read of that row); 16 = by the row's workgroup over the whole
  *   row (plain temperature sampling without any filter: one block of 1024 entries is read again if
- *   why = 1, the row twice if why = 13; a nucleus that reaches below the candidate list: once, or
- *   three times, and one block for the token); anything else = the exact multi-pass path, the value
+ *   why = 1, the row twice if why = 13; a nucleus that reaches below the candidate list: once, and
+ *   one block for the token; twice under a min_p or where what lies about the cut is more than there
+ *   is room for, three times where the read shows that the cut lies elsewhere, and twice more for every
+ *   further level that thousands of nearly equal values take); anything else = the exact multi-pass path, the value
  *   naming the reason (2 top_k too large for any candidate list, 3-13 the candidate list could
  *   not prove the answer, 17-29 nor could the longer one), or 14: vocabulary size outside the
  *   single-pass kernels (why = 1: settled from registers all the same).

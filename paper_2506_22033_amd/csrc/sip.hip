@@ -90,6 +90,9 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t, bool small_chunks = true)
   // unit.  Larger batches run in rounds of that many workgroups, and every workgroup pays a fixed set-up
   // (sample, threshold, history bitmap: about what streaming 38 elements per lane costs) before it
   // streams its V / (S * 512) elements per lane: the S with the cheapest rounds x (set-up + stream).
+  // (256 units, whatever device the call will run on: how large a workspace is and how a row is cut are the same for
+  // every device, and known without one.  A partition of the chip with fewer units gets as many chunks; only its speed
+  // is not what is said below.)
   constexpr int kUnits = 256, kResident = kUnits * 4;
   int want;
   if (B * 4 <= kResident) {
@@ -110,7 +113,8 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t, bool small_chunks = true)
   // counts is how many a compute unit gets.  With w of them its time grows as w * (set-up + stream), the set-up
   // being worth 32 KB of the row, and a compute unit that has only one streams at 4/5 of the speed.  us a call, at 1024
   // workgroups / at 256 / as chosen: V = 128256 fp32, 64 rows 27.5 / 23.2 / 23.2, 128 rows 29.6 / 27.7 / 27.0; bf16, 64
-  // rows 23.1 / 22.1 / 22.1, 128 rows 29.6 / 26.3 / 26.8; V = 200000 fp32, 128 rows 32.8 / - / 31.5; bf16 31.8 / - / 29.5.
+  // rows 23.1 / 22.1 / 22.1, 128 rows 29.6 / 26.3 / 26.8; V = 200000 fp32, 128 rows 32.8 / - / 31.5; bf16 31.8 / - /
+  // 29.5.
   int load = 4;                                          // chunks of a compute unit
   if (B <= kUnits) {
     const double set_up = dtype == SIP_F32 ? 8192.0 : 16384.0;                 // in elements
@@ -172,10 +176,14 @@ DeviceSetup* device_setup() {
       reinterpret_cast<const void*>(sip::exact_kernel<SIP_F32, true>),  reinterpret_cast<const void*>(sip::exact_kernel<SIP_BF16, true>),
       reinterpret_cast<const void*>(sip::rescue_kernel<SIP_F32, false>), reinterpret_cast<const void*>(sip::rescue_kernel<SIP_BF16, false>),
       reinterpret_cast<const void*>(sip::rescue_kernel<SIP_F32, true>),  reinterpret_cast<const void*>(sip::rescue_kernel<SIP_BF16, true>),
-      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, false, false>), reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, false, false>),
-      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, true, false>),  reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, true, false>),
-      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, false, true>),  reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, false, true>),
-      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, true, true>),   reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, true, true>)};
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, false, false>),
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, false, false>),
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, true, false>),
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, true, false>),
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, false, true>),
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, false, true>),
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_F32, true, true>),
+      reinterpret_cast<const void*>(sip::stream_kernel<SIP_BF16, true, true>)};
   for (const void* k : big)
     if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds) != hipSuccess) {
       (void)hipGetLastError();
@@ -201,7 +209,8 @@ Layout make_layout(int32_t B, const Plan& p, int64_t nnz, size_t gather_row_byte
   Layout l;
   size_t off = 0;
   l.row_path = off; off += align_up((size_t)2 * B * sizeof(int));            // first, so that callers can find it: path
-                                                                             // codes, then the finishing kernel's own codes
+                                                                             // codes, then the finishing kernel's own
+                                                                             // codes
   l.tick = off; off += align_up(sizeof(unsigned long long));                 // the state's call counter as taken by this call
   l.side_z = off; off += align_up((size_t)nnz * sizeof(float));
   l.side_c = off; off += align_up((size_t)nnz * sizeof(unsigned int));
@@ -277,14 +286,19 @@ sip_status launch(const sip::Args& a, int32_t B, int dtype, const Plan& plan, bo
 // compute units takes as many rounds of it.  The streaming and finishing kernels overlap their rows,
 // but pay for a row that its list does not settle: a nucleus that outgrows it, or queues that overflow
 // (bf16 rows of one chunk under a wide min-p).  Which rows are like that, or greedy, is not known here;
-// which parameters the call has is.  us, both ways / in registers (fp32 unless said, 256 compute units):
-//   up to one row per compute unit, V = 32768, 64 rows: greedy 16 / 10; no filter 24 / 14; min-p 20 / 15;
-//   top-k 20 / 18; top-k and top-p 20 / 22.5; top-p, peaked rows 23 / 22.5, flat rows 83 / 25 (bf16 171 /
-//   27); all parameters, 512 tokens of history, best 20: 27 / 32, and V = 24000 bf16, 256 rows 215 / 31.
-//   So: in registers, up to a fifth slower on the rows that a list settles and several times faster
-//   where one of them is not; but greedy rows and best 5, without any filter: 17 / 23, by streaming.
-//   V = 24000, 2048 rows: greedy 78 / 53; no filter 119 / 100; min-p 107 / 105, V = 32000 and 512 tokens
-//   of history 125 / 152, 600 rows of it 56 / 57; top-k and top-p 106 / 158; top-p, peaked 118 / 141.
+// which parameters the call has is.  us, by streaming / in registers (fp32 unless said, 256 compute units,
+// the present kernels on both sides; normal logits of standard deviation 2.5 unless said):
+//   up to one row per compute unit, V = 32768, 64 rows: greedy 16 / 10; no filter 23 / 12.5; min-p 20 / 13.5;
+//   top-k 19 / 18; top-k and top-p 19 / 21.5; top-p, peaked rows 23 / 23, Student-t 19 / 17, flat rows 63 / 28 (bf16
+//   61 / 29); all parameters, 512 tokens of history, best 20: 23 / 28, V = 24000 bf16, 256 rows 22 / 26.
+//   V = 32000, 1 to 64 rows of all four modes (greedy, top-k, top-p 0.9, min-p) with 256 tokens of history: Student-t
+//   21 / 19 from 4 rows on; normal logits, whose nuclei outgrow their lists, 65 to 71 / 26.
+//   So: in registers, up to a quarter slower on the rows that a list settles and several times faster
+//   where one of them is not; but rows without any filter that ask for best-n, which are always settled from
+//   a list, by streaming: V = 32768, 64 rows, best 5, greedy 17 / 15 normal, 17 / 24 Student-t; sampled 23 / 18, 23 /
+//   27.
+//   V = 24000, 2048 rows: greedy 77 / 75; no filter 109 / 93; min-p 95 / 99, V = 32000 and 512 tokens
+//   of history 126 / 143, 600 rows of it 56 / 54; top-k and top-p 91 / 151; top-p, peaked 114 / 153.
 //   So: in registers without a filter, min-p alone up to three rounds.
 bool resident_is_chosen(const sip::Args& a, int32_t B, bool state, int compute_units) {
   // A state's call would have to take its number in a launch of its own before this kernel (the
@@ -301,21 +315,24 @@ bool resident_is_chosen(const sip::Args& a, int32_t B, bool state, int compute_u
 // another's streaming, or at least needs no second kernel; but up to one row per compute unit it leaves
 // chip idle that chunks would use, and beyond that the rows come in rounds of two per compute unit.
 // us a call in chunks / a row to a workgroup (256 compute units; nucleus 0.95, Student-t, 600 tokens):
-//   V = 40000 bf16 (80 KB): 64 rows 19.7 / 20.1, 96 21.0 / 20.2, 256 25.0 / 20.9; fp32 (160 KB): 96 21.6 / 21.5, 128 22.0 / 21.8
+//   V = 40000 bf16 (80 KB): 64 rows 19.7 / 20.1, 96 21.0 / 20.2, 256 25.0 / 20.9; fp32 (160 KB): 96 21.6 / 21.5, 128
+//   22.0 / 21.8
 //   V = 128256 bf16 (256 KB): 128 26.3 / 28.0, 144 28.1 / 28.1, 176 30.0 / 28.3, 256 32.5 / 28.7
 //   V = 128256 fp32 (513 KB): 160 29.3 / 32.4, 192 31.8 / 32.5, 200 33.4 / 33.0, 256 36.8 / 35.6
-//   V = 200000 bf16 (400 KB): 144 31.2 / 33.3, 192 33.4 / 33.7, 224 36.6 / 33.7; fp32 (800 KB): 160 35.9 / 40.1, 192 41.0 / 40.8, 224 49.5 / 45.0
-//   (without a filter 192 rows 38.1 / 39.8 bf16, 44.6 / 50.6 fp32; 224 always a row to a workgroup)
-//   V = 110000 bf16 380 rows 41.2 / 41.2, fp32 53.7 / 52.4; V = 152064 bf16 300 44.5 / 46.6, 380 49.8 / 46.9, fp32 380 72.4 / 65.1; V = 230000
-//   fp32 380 95.4 / 92.6
+//   V = 200000 bf16 (400 KB): 144 31.2 / 33.3, 192 33.4 / 33.7, 224 36.6 / 33.7; fp32 (800 KB): 160 35.9 / 40.1, 192
+//   41.0 / 40.8, 224 49.5 / 45.0 (without a filter 192 rows 38.1 / 39.8 bf16, 44.6 / 50.6 fp32; 224 always a row to a
+//   workgroup)
+//   V = 110000 bf16 380 rows 41.2 / 41.2, fp32 53.7 / 52.4; V = 152064 bf16 300 44.5 / 46.6, 380 49.8 / 46.9, fp32
+//   380 72.4 / 65.1; V = 230000 fp32 380 95.4 / 92.6
 //   V = 100000 and 200000, both types: 520 rows 8 % more to 4 % less, 600 2 % more
 //   to 8 % less, 700 and 1030 2 to 17 % less.
 // So up to one row per compute unit from a number of rows on that grows with the row's bytes, to 3/4 of
 // the compute units (where three chunks to a compute unit no longer fit the batch); above, not in the first
 // part of a round -- unless the row is short -- but in the third and later rounds always.  A state's call
-// would have to take its number in a launch of its own
-// ahead of it (V = 152064, 256 rows: 74 / 73 bf16, 81 / 82 fp32; 520 rows 108 / 113, 136 / 139; 1030
-// 161 / 155, 220 / 205).
+// would have to take its number in a launch of its own ahead of it: with 600 tokens a slot, V = 152064, 128
+// rows 34.6 / 38.9 bf16, 35.2 / 44.2 fp32; 256 41.6 / 40.5, 46.3 / 46.4; 520 76.2 / 77.8, 99.7 / 102.7; 1030 130.9
+// / 120.4, 181.9 / 167.5.  (The line is on the safe side: 700 rows 88.7 / 79.9, 121.4 / 110.3; V = 40000 bf16, 512 rows
+// 43.1 / 40.1.)
 bool row_is_chosen(int32_t B, int32_t V, int dtype, bool state, int compute_units) {
   const int64_t row_bytes = (int64_t)V * (dtype == SIP_F32 ? 4 : 2), cu = compute_units;
   if (state) return B >= 4 * cu;

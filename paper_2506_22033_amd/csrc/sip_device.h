@@ -471,7 +471,11 @@ __device__ __forceinline__ uint32_t dpp_scan_max_u32(uint32_t v) { SIP_DPP_STEPS
 __device__ __forceinline__ uint32_t dpp_scan_min_u32(uint32_t v) { SIP_DPP_STEPS(op_min, 0xFFFFFFFFu) return v; }
 // (a fixed tree of additions)
 __device__ __forceinline__ uint32_t op_addf(uint32_t a, uint32_t b) { return __float_as_uint(__uint_as_float(a) + __uint_as_float(b)); }
-__device__ __forceinline__ float dpp_scan_add_f32(float x) { uint32_t v = __float_as_uint(x); SIP_DPP_STEPS(op_addf, 0u) return __uint_as_float(v); }
+__device__ __forceinline__ float dpp_scan_add_f32(float x) {
+  uint32_t v = __float_as_uint(x);
+  SIP_DPP_STEPS(op_addf, 0u)
+  return __uint_as_float(v);
+}
 #undef SIP_DPP_STEPS
 // Sums of 16 consecutive lanes, in the last of them.
 __device__ __forceinline__ uint32_t row16_sum_u32(uint32_t v) {

@@ -1537,18 +1537,18 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
 // The same in one read of the row, for rows that no min-p bounds.  A sample of 8192 elements says about where
 // the cut lies: the mass below it is known (total less limit), so the cut lies where the sample's elements
 // from below add up to their share of that, give or take three standard deviations of such a sum (2 to 3 % of
-// it each on flat rows, 8 on rows whose tail is a few hundred elements).  The read then sums, per block of 1024 elements, what lies above that
-// window, and lists what lies in it (some thousand elements, to where the row's candidates were); bins over
-// the window, and the members of one of them, settle the cut; and one block is read again for the token.
-// Every decision is taken on the exact fp32 s; masses are exp_nonpos() like a list's, every element's an
+// it each on flat rows, 8 on rows whose tail is a few hundred elements).  The read then sums, per block of 1024
+// elements, what lies above that window, and lists what lies in it (some thousand elements, to where the row's
+// candidates were); bins over the window, and the members of one of them, settle the cut; and one block is read again
+// for the token. Every decision is taken on the exact fp32 s; masses are exp_nonpos() like a list's, every element's an
 // integer.  (Added up in fp32 over a load first, what weighs less than 2^-24 of its neighbour could not be drawn, and
 // v_exp_f32 of a rounded product is off by 1e-6 some twenty below the maximum: that was 115 us in place of 133 in the
 // first of the calls below, 96 in place of 103 in the fourth.)  Returns 1 (fs.token, fs.token_key), 13 (no mass), or
 // 0: the window is too long for the room, or the cut not in it (whole_row_nucleus() then does without one).
 // What bounds it: vector issue of one compute unit (some 40 instructions an element).  us a call, against a second
-// list and two reads: 1 row of V = 256000 fp32, flat 269 -> 138, V = 213087 bf16 234 -> 126; V = 200000 fp32, 64 rows, 16
-// of them flat 267 -> 140; V = 128256 bf16, 256 rows, 244 of them spiked at top-p 0.9 291 -> 103; V = 166557 fp32,
-// 1883 rows, 471 flat 752 -> 497.
+// list and two reads: 1 row of V = 256000 fp32, flat 269 -> 138, V = 213087 bf16 234 -> 126; V = 200000 fp32, 64
+// rows, 16 of them flat 267 -> 140; V = 128256 bf16, 256 rows, 244 of them spiked at top-p 0.9 291 -> 103; V = 166557
+// fp32, 1883 rows, 471 flat 752 -> 497.
 template <int DT>
 __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, const int V_any, const bool has_pen_any,
                                                           const uint32_t* bm, const unsigned short* pre, const uint32_t* cnt,
@@ -1566,8 +1566,8 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
   constexpr float kSpan = 28.0f;                          // exp(-28) * 2^40 < 1: nothing below has mass
   constexpr float kWide[2] = {3.0f, 1.5f};                // standard deviations on either side
   // (what a function is handed lies in vector registers, and pointers may be to anything: said to be uniform, and
-  // global, they leave the loop without exec-masked branches and flat accesses: 130 -> 98 us in the fourth of these, together
-  // with barriers alone, no device-wide fences, around the list)
+  // global, they leave the loop without exec-masked branches and flat accesses: 130 -> 98 us in the fourth of these,
+  // together with barriers alone, no device-wide fences, around the list)
   typedef __attribute__((address_space(1))) char global_char;
   typedef __attribute__((address_space(1))) unsigned long long global_u64;
   auto uniform_at = [](const void* p) {
@@ -1639,7 +1639,10 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
   __syncthreads();
   for (int i = tid; i < kBins; i += NT) { hm[i] = 0; hc[i] = 0; }
   if (tid < 2) { fs.w_lo[tid] = -1; fs.w_hi[tid] = -1; }
-  if (tid == 0) { fs.bin_p = 1 << 30; fs.bin_d = -1; fs.n_memb2 = 0; fs.key_p = 0xFFFFFFFFu; fs.key_k = 0; fs.token = 0x7FFFFFFF; fs.w_sq = -1.0f; fs.rq_n = 0; }
+  if (tid == 0) {
+    fs.bin_p = 1 << 30; fs.bin_d = -1; fs.n_memb2 = 0; fs.key_p = 0xFFFFFFFFu; fs.key_k = 0; fs.token = 0x7FFFFFFF;
+    fs.w_sq = -1.0f; fs.rq_n = 0;
+  }
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < SL; ++j) {
@@ -1685,7 +1688,8 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
       float q = sq0;
 #pragma unroll
       for (int j = 0; j < kBinsPerThread; ++j) {
-        if ((double)ex <= below && below < (double)(ex + w[j])) fs.w_sq = fmaxf(q, 0.0f) + sq[j] * (float)((below - (double)ex) / (double)w[j]);
+        if ((double)ex <= below && below < (double)(ex + w[j]))
+          fs.w_sq = fmaxf(q, 0.0f) + sq[j] * (float)((below - (double)ex) / (double)w[j]);
         ex += w[j]; q += sq[j];
       }
     }
@@ -1715,7 +1719,8 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
 #pragma unroll
   for (int k = 1; k >= 0; --k)                            // the wider one where it fits (an eighth of the room to spare)
     if (fs.w_lo[k] >= 0 && fs.w_hi[k] >= 0 &&
-        (unsigned long long)(fs.w_n1[k] - fs.w_n0[k]) * (unsigned long long)V < (unsigned long long)(cap - cap / 8) * (unsigned long long)kSampleSize)
+        (unsigned long long)(fs.w_n1[k] - fs.w_n0[k]) * (unsigned long long)V <
+            (unsigned long long)(cap - cap / 8) * (unsigned long long)kSampleSize)
       pick = k;
   if (pick < 0) return 0;                                 // uniform
   const float s_lo = lo0 + (float)fs.w_lo[pick] / sc0, s_hi = lo0 + (float)(fs.w_hi[pick] + 1) / sc0;
@@ -1725,9 +1730,9 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
   const int nblk = (V + BLK - 1) / BLK;
   const int per_wave = (nblk + kFinalWaves - 1) / kFinalWaves;
   // The list is dealt out in pages of a wave's size, as they are asked for: a wave's share of the row may hold most of
-  // the window (ids in order of frequency, a piece with a tail of its own).  Fixed eighths ran over there, and the row was read
-  // twice more: 400 rows of V = 131072 fp32 with their tail in an eighth of the ids, top-p 0.5, 454 -> 249 us; what did not run
-  // over takes 0 to 5 % longer.
+  // the window (ids in order of frequency, a piece with a tail of its own).  Fixed eighths ran over there, and the
+  // row was read twice more: 400 rows of V = 131072 fp32 with their tail in an eighth of the ids, top-p 0.5, 454 ->
+  // 249 us; what did not run over takes 0 to 5 % longer.
   constexpr uint32_t kPage = kWave;
   const uint32_t room = cap / kPage * kPage;
   const uint32_t key_none = key_of(-INFINITY);            // of places left empty
@@ -1878,7 +1883,8 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
   if (kmax) { atomicMin(&fs.key_p, kmin); atomicMax(&fs.key_k, kmax); }
   __syncthreads();
   const uint32_t n = fs.n_memb2;
-  uint32_t k_lo = fs.key_p, k_hi = fs.key_k;              // the smallest key above which the mass stays short of the limit lies in [k_lo, k_hi]
+  // the smallest key above which the mass stays short of the limit lies in [k_lo, k_hi]
+  uint32_t k_lo = fs.key_p, k_hi = fs.key_k;
   if (k_lo != k_hi && n > kList) return 0;                // uniform
   while (k_lo < k_hi) {                                   // uniform
     const uint32_t mid = k_lo + ((k_hi - k_lo) >> 1);

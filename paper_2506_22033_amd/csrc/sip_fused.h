@@ -43,7 +43,10 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
   (void)a_by_value;
   const Args& a = *(const Args*)__builtin_amdgcn_kernarg_segment_ptr();
   warm_kernel_arguments();
-  __shared__ union __align__(16) Tables { RowStreamShared<DT> stream; FinShared fin; unsigned char raw[kFusedRawBytes]; __device__ Tables() {} } u;
+  __shared__ union __align__(16) Tables {
+    RowStreamShared<DT> stream; FinShared fin; unsigned char raw[kFusedRawBytes];
+    __device__ Tables() {}
+  } u;
   static_assert(sizeof(u) == kFusedRawBytes, "");
   __shared__ ExactShared ex;
   __shared__ FastShared fsr;

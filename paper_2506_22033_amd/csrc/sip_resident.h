@@ -23,14 +23,15 @@
 // by one wave, parameters that are off take part with their neutral value instead of a branch,
 // temperature and repetition penalty are products with a double reciprocal (RowDivisor), masses
 // become integers through a double's low bits, and bins cost three instructions; with the
-// straightforward forms of these V = 32000 took 34.5 us, then 25.0 (fp32, 4 rows, one of each kind
+// straightforward forms of these V = 32000 took 34.5 us, then 25.3 (fp32, 4 rows, one of each kind
 // of filter); with the block masses of a wave's loads added up together (row_sums_u64(): eight sums over 64 lanes
-// one by one were a fifth of what a thread issues for the draw), min-p taken out of the masses once, and the gathering of a cut's
-// members passing over loads whose largest value is below, 24.0.  Without a filter, V = 16000, 64 rows 13.7 -> 12.7, 1500 rows 81.4 -> 75.5;
-// top-p 97.9 -> 95.3.  (Counting only bins that the k-th or n-th best can be in, by the least of 128 groups' maxima,
-// made everything 1 to 5 % slower: the LDS additions are hidden, the test is not.)  Against exact_kernel, which vocabularies below 16384 used to go through: V = 4096, 64
-// rows, top-k and top-p: 53 -> 11 us; V = 12556, 468 rows, no filter: 99 -> 19 us.  Which of the larger
-// ones come here: resident_is_chosen().
+// one by one were a fifth of what a thread issues for the draw), min-p taken out of the masses once, and the
+// gathering of a cut's members passing over loads whose largest value is below, 24.5.  Without a filter, V = 16000,
+// 64 rows 13.7 -> 12.7, 1500 rows 81.4 -> 75.5; top-p 97.9 -> 95.3.  (Counting only bins that the k-th or n-th best
+// can be in, by the least of 128 groups' maxima, made everything 1 to 5 % slower: the LDS additions are hidden, the
+// test is not.)  Against exact_kernel, which vocabularies below 16384 used to go through: V = 4096, 64 rows, top-k
+// and top-p: 53 -> 11 us; V = 12556, 468 rows, no filter: 99 -> 19 us.  Which of the larger ones come here:
+// resident_is_chosen().
 //
 // What this cannot settle -- more than kResList members in a bin of a cut (all-equal rows), top_p <= 0,
 // no finite maximum -- goes through exact_row() in the same workgroup.
@@ -366,7 +367,8 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
   const unsigned long long S0 = wave_add_u64(lane < NW ? fs.r64[lane] : 0ull);
   auto ln_total = [&]() -> double { return log((double)S0) - (double)kFixShift * 0.6931471805599453094; };
   // One wave works it out while the others are at the elements, instead of whoever needs it at the end of the chain
-  // (V = 16000 without a filter 12.7 -> 12.3, everything on 21.2 -> 20.9 us; not with eight waves: 1500 rows of 4096, top-p, 60.8 / 62.0).
+  // (V = 16000 without a filter 12.7 -> 12.3, everything on 21.2 -> 20.9 us; not with eight waves: 1500 rows of 4096,
+  // top-p, 60.8 / 62.0).
   constexpr bool kAhead = NW == 16;
   auto note_ln_total = [&]() {
     if (kAhead && wave == NW / 2) {

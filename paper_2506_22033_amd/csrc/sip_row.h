@@ -6,11 +6,11 @@
 // chunk.  Two workgroups per compute unit: the finishing tables take 70 KB of LDS, and 128 registers a
 // lane pay for four 16-byte loads in flight per tile instead of two.  (One row per compute unit and less:
 // row_rescue_kernel, sip_fused.h.)
-// Measured against the two kernels, us a call: 256 rows of V = 128256 bf16 32.5 -> 28.7, of V = 200000 fp32 53.6 -> 49.3; 800 rows
-// of V = 152064 bf16 88.2 -> 85.0 (sip.hip has the line between them, and both sides of it).
-// What bounds it: bf16, 1024 rows of V = 129280 (109 us with lists of one length for every nucleus, now 89), vector issue, 65 % of the
-// slots, one row's set-up and finishing beside the other's streaming; fp32, 2048 rows of V = 256000 (493 us), HBM while it streams
-// (4.3 TB/s over the whole kernel).
+// Measured against the two kernels, us a call: 256 rows of V = 128256 bf16 32.5 -> 28.7, of V = 200000 fp32 53.6 ->
+// 49.3; 800 rows of V = 152064 bf16 88.2 -> 85.0 (sip.hip has the line between them, and both sides of it).
+// What bounds it: bf16, 1024 rows of V = 129280 (109 us with lists of one length for every nucleus, now 89), vector
+// issue, 65 % of the slots, one row's set-up and finishing beside the other's streaming; fp32, 2048 rows of V =
+// 256000 (490 us), HBM while it streams (4.3 TB/s over the whole kernel).
 #pragma once
 #include "sip_finish.h"
 #include "sip_stream.h"

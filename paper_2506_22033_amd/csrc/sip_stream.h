@@ -255,9 +255,11 @@ __device__ __forceinline__ float sample_floor(uint32_t i) {
 // values below counting as their group's upper end and those above as its lower end.  A few of the row's
 // largest may be history tokens that a penalty takes away, or be in the sample by chance: the fourth (with
 // a penalty on, eighth) largest sample value stands for the maximum, and those above it count as much as
-// it does.  (3400 simulated rows of normal, Student-t, spiked and Zipf logits, p 0.5 to 0.99, min_p 0.02 to
-// 0.1, half of the top tokens penalised: none lost that the long list settles.)  Returns that group (its lower
-// end is the threshold), or G.
+// it does.  (What a thread's sample holds beyond its three largest counts as at the lowest group, so the mass
+// below is rather too small: a matter of speed, as a row whose list ends too high is settled over the whole row.  Of
+// 72576 rows -- normal, Student-t, spiked and peaked, top-p 0.5, 0.9 and 0.99, V = 50000 to 200000, 16 to 512 of
+// them, both types -- 31561 left their lists; with lists of one length 31590, no fewer at any of the 30 shapes.)
+// Returns that group (its lower end is the threshold), or G.
 // What it gives, us a call: Student-t logits, lists of 540 instead of 2830 entries, V = 129280 bf16, 1024 rows
 // 110.0 -> 93.3; V = 152064 bf16 in pieces, 200 rows 38.8 -> 34.2; V = 128256 bf16, 32 rows of 8600 tokens under
 // min-p 32.6 -> 27.3.  A row that keeps the long list pays 0.3 for the question.
@@ -283,7 +285,8 @@ __device__ __forceinline__ uint32_t raised_group(const uint32_t G, const uint32_
   const unsigned long long flat = __ballot(in && n_from >= (has_pen ? 8u : 4u));
   const int at = flat ? __ffsll((long long)flat) - 1 : kWave - 1;
   const float x_top = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x_lo), at));
-  const float head = (float)beyond * __builtin_amdgcn_exp2f(x_top) + dpp_scan_add_f32(n ? (float)n * __builtin_amdgcn_exp2f(fminf(x_lo, x_top)) : 0.0f);
+  const float head = (float)beyond * __builtin_amdgcn_exp2f(x_top) +
+                     dpp_scan_add_f32(n ? (float)n * __builtin_amdgcn_exp2f(fminf(x_lo, x_top)) : 0.0f);
   const float up = dpp_scan_add_f32(lane >= at && n ? (float)n * __builtin_amdgcn_exp2f(x_hi) : 0.0f);
   const float rest = (float)(n_smp - min(n_smp, last_lane_u32(n_from))) *
                      __builtin_amdgcn_exp2f(__uint_as_float(last_lane_u32(__float_as_uint(x_lo))));
@@ -323,7 +326,8 @@ __host__ __device__ constexpr int stream_front_bytes(int cap) {
 }
 template <int DT>
 constexpr int stream_lds_bytes(int cap) { return stream_front_bytes<DT, false>(cap) + (int)sizeof(StreamTables<DT, false>); }
-static_assert(stream_lds_bytes<SIP_F32>(kQueueCap) <= 40 * 1024 && stream_lds_bytes<SIP_BF16>(kQueueCap) <= 40 * 1024, "four workgroups per compute unit");
+static_assert(stream_lds_bytes<SIP_F32>(kQueueCap) <= 40 * 1024 && stream_lds_bytes<SIP_BF16>(kQueueCap) <= 40 * 1024,
+              "four workgroups per compute unit");
 static_assert(stream_lds_bytes<SIP_F32>(2 * kQueueCap) <= 80 * 1024, "two with queues of twice the length");
 template <int DT>
 struct __align__(16) RowStreamShared {
@@ -341,8 +345,8 @@ struct RowHand {
   uint2 list[kRowRegs];                    // (per thread)
 };
 
-// Streams chunk wg % S of row wg / S (ROW: row wg).  False: the row cannot be finished from a list.  `front` and `sm`: LDS,
-// one behind the other.  IDS: a call that asks for token ids only (a kernel of its own, see `masses`).
+// Streams chunk wg % S of row wg / S (ROW: row wg).  False: the row cannot be finished from a list.  `front` and
+// `sm`: LDS, one behind the other.  IDS: a call that asks for token ids only (a kernel of its own, see `masses`).
 template <int DT, bool SH, bool ROW, bool IDS = false>
 __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigned char* const front, StreamTables<DT, ROW>& sm,
                                             RowHand* hand) {
@@ -636,10 +640,10 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
     if (!out && bounded) {
       const uint32_t G = raised_group(K / kGroup, above, hist, rp, (float)scale, has_pen,
                                       max(2u, (512u * (uint32_t)n_smp + (uint32_t)V - 1u) / (uint32_t)V), (uint32_t)n_smp);
-      // (Put below the group's lower end by as little as still tells the two apart when divided by the temperature: what
-      // equals the threshold counts as outside the list, and logits on coarse values, whole numbers say, lie on that
-      // end by the hundred, having been counted as kept.  64 rows of V = 152064 fp32, whole numbers, top-p 0.99 at 0.3:
-      // 20 of them left their lists.)
+      // (Put below the group's lower end by as little as still tells the two apart when divided by the temperature:
+      // what equals the threshold counts as outside the list, and logits on coarse values, whole numbers say, lie on
+      // that end by the hundred, having been counted as kept.  64 rows of V = 152064 fp32, whole numbers, top-p 0.99
+      // at 0.3: 20 of them left their lists.)
       if (G != K / kGroup) { at = sample_floor(G * kGroup); at -= fmaxf(fabsf(at), kLow) * 0x1p-18f; }
     }
     const BulkRef r = make_bulk_ref(out ? 0.0f : at, scale);
@@ -774,8 +778,8 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
   // of each lane at a time, which takes one or two rounds of a load at the usual list lengths.
   // Bit p of mask and `hb` is element EPL - 1 - p.  A history token's bits are all set for the sum, a NaN,
   // which bulk_term() leaves out: what belongs to the list must not pass through the fp32 sums, not even to be
-  // taken out again (6000 tokens around the threshold, penalised away: 3e-5 of the total was left behind).  `it`: the wave's load
-  // number in its chunk.  A queue entry is the element's value and its place: fp32 (bits, vocabulary
+  // taken out again (6000 tokens around the threshold, penalised away: 3e-5 of the total was left behind).  `it`: the
+  // wave's load number in its chunk.  A queue entry is the element's value and its place: fp32 (bits, vocabulary
   // id); bf16 one word, the value's 16 bits above load number, lane and element (5 or 7 + 6 + 3 bits).
   // Whether it is a history token is looked up again when the queue goes out.
   auto process = [&](const uint4& q, int e0, int it, bool guard, uint32_t hb, const uint4& tg) {
@@ -1021,8 +1025,8 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
   return true;
 }
 
-// IDS: for calls that ask for token ids only.  us a call: V = 152064 bf16, 128 greedy rows 19.9 -> 17.9; V = 83007 bf16, 287
-// rows under min-p 39.8 -> 35.8.
+// IDS: for calls that ask for token ids only.  us a call: V = 152064 bf16, 128 greedy rows 19.9 -> 17.9; V = 83007
+// bf16, 287 rows under min-p 39.8 -> 35.8.
 template <int DT, bool SH, bool IDS>
 __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void stream_kernel(Args a) {
   extern __shared__ __align__(16) unsigned char stream_lds[];                  // stream_lds_bytes()
@@ -1031,7 +1035,8 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   // on logical chunk (i % 8) * (n / 8) + i / 8 when n, the grid size, is a multiple of 8.
   int wg = blockIdx.x;
   if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-  stream_part<DT, SH, false, IDS>(a, wg, stream_lds, *reinterpret_cast<StreamTables<DT, false>*>(stream_lds + stream_front_bytes<DT, false>(a.cap_c / kStreamWaves)), nullptr);
+  unsigned char* const tables = stream_lds + stream_front_bytes<DT, false>(a.cap_c / kStreamWaves);
+  stream_part<DT, SH, false, IDS>(a, wg, stream_lds, *reinterpret_cast<StreamTables<DT, false>*>(tables), nullptr);
 }
 
 }  // namespace sip

@@ -1,6 +1,6 @@
-"""Chunks as a compute unit's share asks for them: one, two and three to a compute unit, with the longer queues that
-come with fewer chunks nearly full, on a few rows with far longer histories than the others (all of them settled from
-their lists), and both sides of the lines between chunks and a row to a workgroup."""
+"""Chunks as a compute unit's share asks for them: one, two and three to a compute unit, on a few rows with far longer
+histories than the others (all of them settled from their lists), both sides of the lines between chunks and a row to a
+workgroup, and the longer queues that come with fewer chunks."""
 import numpy as np
 import pytest
 
