@@ -74,6 +74,13 @@ def test_small_masses_beside_a_large_one(at, top_p, row_id):
     assert ids[0] == at + 2
 
 
+def _listed_about(ws, z, tokens):
+    """How many of the row's tokens (without a penalty, at temperature 1) its window has listed."""
+    bits = z[tokens].view(np.uint32).astype(np.int64)
+    word = (tokens.astype(np.int64) << 32) | np.where(bits >> 31, bits ^ 0xFFFFFFFF, bits | 0x80000000)
+    return int(torch.isin(torch.from_numpy(word).to(H.DEV), ws[:ws.numel() // 8 * 8].view(torch.int64)).sum())
+
+
 def test_which_rows_the_window_settles():
     """What the window lists goes into the row's room in the workspace, as the element's number above the ordered bits of
     its s.  With the thirty tokens on either side of the cut all there the row was settled by its window; with none of them
@@ -96,14 +103,40 @@ def test_which_rows_the_window_settles():
     out = sip.sip_sample(d.logits, d.params, None, None, 41, 0, 0, V=V, workspace=ws)
     torch.cuda.synchronize()
     assert (ws[:4 * B].view(torch.int32) == 16).all(), ws[:4 * B].view(torch.int32)[:8]
-    words = ws[:ws.numel() // 8 * 8].view(torch.int64)
     for b in [*range(8), B - 3, B - 1]:
         mass = np.exp(z[b].astype(np.float64))
         order = np.argsort(-z[b], kind="stable")
         n = int(np.searchsorted(np.cumsum(mass[order]), float(np.float32(top_p[b])) * mass.sum())) + 1
         near = order[n - 30:n + 30]
-        bits = z[b, near].view(np.uint32).astype(np.int64)
-        word = (near.astype(np.int64) << 32) | np.where(bits >> 31, bits ^ 0xFFFFFFFF, bits | 0x80000000)
-        there = int(torch.isin(torch.from_numpy(word).to(H.DEV), words).sum())
+        there = _listed_about(ws, z[b], near)
         assert there == (60 if kind[b] < 2 else 0), (b, there)
     H.compare(w, tuple(x.cpu().numpy() for x in out), 41, 0, rows=list(range(8)))
+
+
+@pytest.mark.parametrize("B,V,n_hist,rest", [(22, 65536, 3500, 1), (300, 40001, 3500, 12), (22, 65536, 1500, 1)])
+def test_window_of_rows_with_long_histories(B, V, n_hist, rest):
+    """Thousands of penalised tokens, which the sample's elements are not: the window lies about the cut all the same.  (It
+    is three standard deviations wide on either side: 0.3 % of the rows may miss it, `rest` is a few times that.)"""
+    rng = np.random.default_rng(V + n_hist)
+    z = rng.standard_normal((B, V)).astype(np.float32)
+    hist = rng.integers(0, V, (B, n_hist))
+    w = H.custom("long", z, dict(top_p=np.full(B, 0.9), repetition_penalty=np.full(B, 1.1), frequency_penalty=np.full(B, 0.5),
+                                 presence_penalty=np.full(B, 0.3)), hist.tolist(), k_logprobs=0)
+    d = H.to_device(w)
+    ws = torch.zeros(sip.sip_workspace_bytes(B, V, sip.SIP_F32, B * n_hist, 0), dtype=torch.uint8, device=H.DEV)
+    out = sip.sip_sample(d.logits, d.params, d.indptr, d.tokens, 41, 0, 0, V=V, workspace=ws)
+    torch.cuda.synchronize()
+    assert (ws[:4 * B].view(torch.int32) == 16).all()
+    missed = 0
+    for b in range(B):
+        c = np.bincount(hist[b], minlength=V)
+        s = z[b].astype(np.float64)
+        s = np.where(c > 0, np.where(s > 0, s / 1.1, s * 1.1) - 0.5 * c - 0.3, s)
+        mass = np.exp(s)
+        order = np.argsort(-s)
+        n = int(np.searchsorted(np.cumsum(mass[order]), 0.9 * mass.sum()))
+        near = order[n - 30:n + 30]
+        near = near[c[near] == 0]
+        missed += _listed_about(ws, z[b], near) < len(near)
+    assert missed <= rest, missed
+    H.compare(w, tuple(x.cpu().numpy() for x in out), 41, 0, rows=list(range(0, B, B // 10)))
