@@ -45,3 +45,18 @@ def test_thresholds_anywhere(B, V, bf16):
         H.compare(w, H.run_gpu(d, 59, step), 59, step, rows=rows)
         why = H.last_row_why[settled]
         assert (why == 1).all(), (kind[settled][why != 1], mode[settled][why != 1], why[why != 1])
+
+
+@pytest.mark.parametrize("B,V,bf16", [(8, 38144, False), (8, 65936, True), (24, 50001, True)])
+def test_largest_in_one_part_of_the_ids(B, V, bf16):
+    """A sixth of the ids holds all that is likely, as where ids follow frequency: some of the sample's threads have
+    far more than their share of the largest values."""
+    rng = np.random.default_rng(V)
+    z = rng.standard_normal((B, V)).astype(np.float32)
+    z[:, :V // 3] -= 8.0
+    z[:, V // 2:] -= 8.0
+    params = dict(temperature=np.full(B, 0.5), top_p=np.full(B, 0.5), repetition_penalty=np.full(B, 1.1))
+    hist = [rng.integers(0, V, 300).tolist() for _ in range(B)]
+    w = H.custom(f"part_{V}", workloads.f32_to_bf16_bits(z) if bf16 else z, params, hist, k_logprobs=1)
+    H.compare(w, H.run_gpu(H.to_device(w), 59, 0), 59, 0)
+    assert (H.last_row_why == 1).all(), H.last_row_why
