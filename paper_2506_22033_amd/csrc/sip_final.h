@@ -1646,8 +1646,12 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < SL; ++j) {
-    constexpr uint32_t NSB = (uint32_t)(SL * kFinalWaves), B0 = (uint32_t)(kWave * EPL);
-    const int e0 = (int)((uint32_t)(wave * SL + j) * (uint32_t)V / NSB / B0 * B0) + lane * EPL;           // (V >= 16384: inside the row)
+    // (Four lanes to a piece of 64 bytes.  In pieces of a wave's load, 16 of a bf16 row, a part of the ids that holds
+    // most of the mass had a piece too many or too few, and the cut lay beside the window: V = 152816 bf16, 50 rows
+    // with all that is likely in a sixth of the ids, 313 us a call, 174 so.)
+    constexpr uint32_t NP = (uint32_t)(SL * NT / 4), P0 = (uint32_t)(4 * EPL);
+    static_assert(16384 / NP >= P0, "the shortest row is that long: every piece lies inside");
+    const int e0 = (int)((uint32_t)(j * NT + tid) / 4u * (uint32_t)V / NP / P0 * P0) + (tid & 3) * EPL;
     float sv[EPL];
     svals(ldrow(e0), e0, true, sv);
 #pragma unroll

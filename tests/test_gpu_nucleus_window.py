@@ -140,3 +140,37 @@ def test_window_of_rows_with_long_histories(B, V, n_hist, rest):
         missed += _listed_about(ws, z[b], near) < len(near)
     assert missed <= rest, missed
     H.compare(w, tuple(x.cpu().numpy() for x in out), 41, 0, rows=list(range(0, B, B // 10)))
+
+
+@pytest.mark.parametrize("B,V,bf16,pieces", [(12, 152816, True, 2), (12, 99999, False, 0), (12, 131072, True, 0)])
+def test_window_where_part_of_the_ids_is_likely(B, V, bf16, pieces):
+    """A sixth of the ids holds nine tenths of the mass, at another place in every row: the sample has its share of them, to
+    within one piece of 43, so that the window lies about the cut."""
+    rng = np.random.default_rng(V)
+    z = rng.standard_normal((B, V)).astype(np.float32) - 4.0
+    for b in range(B):
+        at = V // 20 + b * V // 17
+        z[b, at:at + V // 6] += 4.0
+    if bf16:
+        z = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(z))
+    w = H.custom("part", workloads.f32_to_bf16_bits(z) if bf16 else z, dict(top_p=np.full(B, 0.8)), k_logprobs=0)
+    d = H.to_device(w)
+    code = sip.SIP_BF16 if bf16 else sip.SIP_F32
+    if pieces:
+        n = V // pieces
+        ws = torch.zeros(sip.sip_workspace_bytes_sharded(B, n, pieces, code, 0, 0), dtype=torch.uint8, device=H.DEV)
+        table = sip.ShardTable([d.logits[:, i * n:(i + 1) * n].contiguous() for i in range(pieces)])
+        out = sip.sip_sample_sharded(table, d.params, None, None, 41, 0, 0, workspace=ws)
+    else:
+        ws = torch.zeros(sip.sip_workspace_bytes(B, V, code, 0, 0), dtype=torch.uint8, device=H.DEV)
+        out = sip.sip_sample(d.logits, d.params, None, None, 41, 0, 0, V=V, workspace=ws)
+    torch.cuda.synchronize()
+    assert (ws[:4 * B].view(torch.int32) == 16).all()
+    missed = 0
+    for b in range(B):
+        mass = np.exp(z[b].astype(np.float64))
+        order = np.argsort(-z[b], kind="stable")
+        n = int(np.searchsorted(np.cumsum(mass[order]), 0.8 * mass.sum()))
+        missed += _listed_about(ws, z[b], order[n - 30:n + 30]) < 60
+    assert missed <= 1, missed
+    H.compare(w, tuple(x.cpu().numpy() for x in out), 41, 0, rows=[0, B - 1])
