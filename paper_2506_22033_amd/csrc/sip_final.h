@@ -1634,9 +1634,26 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
       }
     }
   };
-  // ---- the window, from the sample: bins over [m - 28, m], mass and number of elements
-  const float lo0 = m - kSpan, sc0 = (float)kBins / kSpan;
+  // ---- the window, from the sample: bins from the lowest value (or m - 28) to m, mass and number of elements
+  // (Four lanes to a piece of 64 bytes.  In pieces of a wave's load, 16 of a bf16 row, a part of the ids that holds
+  // most of the mass had a piece too many or too few, and the cut lay beside the window: V = 152816 bf16, 50 rows
+  // with all that is likely in a sixth of the ids, 313 us a call, 174 so.  And bins from m - 28 for every row are few
+  // for one whose values are all about the same, and its window too long: V = 180525 bf16, 109 rows of standard
+  // deviation 0.02, 515 us, 174 so.)
+  constexpr uint32_t NP = (uint32_t)(SL * NT / 4), P0 = (uint32_t)(4 * EPL);
+  static_assert(16384 / NP >= P0, "the shortest row is that long: every piece lies inside");
+  float smp[SL][EPL], low = INFINITY;
+#pragma unroll
+  for (int j = 0; j < SL; ++j) {
+    const int e0 = (int)((uint32_t)(j * NT + tid) / 4u * (uint32_t)V / NP / P0 * P0) + (tid & 3) * EPL;
+    svals(ldrow(e0), e0, true, smp[j]);
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) low = smp[j][i] > -INFINITY ? fminf(low, smp[j][i]) : low;
+  }
+  each_penalised([&](bool have, float sv, uint32_t) { low = have && sv > -INFINITY ? fminf(low, sv) : low; });
+  const uint32_t low_key = last_lane_u32(dpp_scan_min_u32(key_of(low)));
   __syncthreads();
+  if (lane == 0) fs.rkey[wave] = low_key;
   for (int i = tid; i < kBins; i += NT) { hm[i] = 0; hc[i] = 0; }
   if (tid < 2) { fs.w_lo[tid] = -1; fs.w_hi[tid] = -1; }
   if (tid == 0) {
@@ -1644,31 +1661,29 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
     fs.w_sq = -1.0f; fs.rq_n = 0;
   }
   __syncthreads();
+  uint32_t lowest = fs.rkey[0];
 #pragma unroll
-  for (int j = 0; j < SL; ++j) {
-    // (Four lanes to a piece of 64 bytes.  In pieces of a wave's load, 16 of a bf16 row, a part of the ids that holds
-    // most of the mass had a piece too many or too few, and the cut lay beside the window: V = 152816 bf16, 50 rows
-    // with all that is likely in a sixth of the ids, 313 us a call, 174 so.)
-    constexpr uint32_t NP = (uint32_t)(SL * NT / 4), P0 = (uint32_t)(4 * EPL);
-    static_assert(16384 / NP >= P0, "the shortest row is that long: every piece lies inside");
-    const int e0 = (int)((uint32_t)(j * NT + tid) / 4u * (uint32_t)V / NP / P0 * P0) + (tid & 3) * EPL;
-    float sv[EPL];
-    svals(ldrow(e0), e0, true, sv);
+  for (int ww = 1; ww < kFinalWaves; ++ww) lowest = min(lowest, fs.rkey[ww]);
+  const float massless = m - kSpan, lo0 = fmaxf(massless, value_of(lowest)), span0 = m - lo0;
+  if (!(span0 > 1e-30f)) return 0;                        // uniform: a sample of one value, or of none
+  const float sc0 = (float)kBins / span0;
+  auto bin0 = [&](float sv) { return min(kBins - 1, max(0, (int)(__fsub_rn(sv, lo0) * sc0))); };
+  __syncthreads();                                        // (rkey is used again)
+#pragma unroll
+  for (int j = 0; j < SL; ++j)
 #pragma unroll
     for (int i = 0; i < EPL; ++i)
-      if (sv[i] >= lo0) {
-        const int bin = min(kBins - 1, max(0, (int)(__fsub_rn(sv[i], lo0) * sc0)));
-        atomicAdd(&hm[bin], mass(sv[i]));
+      if (smp[j][i] >= massless) {
+        const int bin = bin0(smp[j][i]);
+        atomicAdd(&hm[bin], mass(smp[j][i]));
         atomicAdd(&hc[bin], 1u);
       }
-  }
   // The sample's elements carry no penalty.  Those that do are all at hand, so each of them counts for its share
   // of a sample: left out, thousands put the estimate beside the cut, and the row was read twice more (V = 65536
   // fp32, 22 flat rows of 3500 tokens 205 us a call, 130 so; V = 40001, 300 rows 335, 235).
   const double share = (double)kSampleSize / (double)V;
   each_penalised([&](bool have, float sv, uint32_t) {
-    if (have && sv >= lo0)
-      atomicAdd(&hm[min(kBins - 1, max(0, (int)(__fsub_rn(sv, lo0) * sc0)))], (unsigned long long)((double)mass(sv) * share));
+    if (have && sv >= massless) atomicAdd(&hm[bin0(sv)], (unsigned long long)((double)mass(sv) * share));
   });
   __syncthreads();
   {
@@ -1736,6 +1751,7 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
       pick = k;
   if (pick < 0) return 0;                                 // uniform
   const float s_lo = lo0 + (float)fs.w_lo[pick] / sc0, s_hi = lo0 + (float)(fs.w_hi[pick] + 1) / sc0;
+  if (!(s_lo < s_hi)) return 0;                           // uniform
   for (int i = tid; i < kBins; i += NT) { hm[i] = 0; hd[i] = 0; }
   __syncthreads();
   // ---- the read: sums per block of what lies above, list of what lies in the window

@@ -174,3 +174,33 @@ def test_window_where_part_of_the_ids_is_likely(B, V, bf16, pieces):
         missed += _listed_about(ws, z[b], order[n - 30:n + 30]) < 60
     assert missed <= 1, missed
     H.compare(w, tuple(x.cpu().numpy() for x in out), 41, 0, rows=[0, B - 1])
+
+
+@pytest.mark.parametrize("B,V,bf16,n_hist,top_p", [(12, 99999, False, 0, 0.6), (12, 131072, True, 0, 0.6), (270, 50001, False, 0, 0.6),
+                                                     (12, 168448, False, 300, 0.999)])
+def test_window_of_nearly_equal_logits(B, V, bf16, n_hist, top_p):
+    """Logits of standard deviation 0.02: the sample's bins are as narrow as the row asks for.  (In bins of 0.014 the 270 rows'
+    windows were longer than their room.)  And with a cut among penalised tokens, which all lie below the sample."""
+    rng = np.random.default_rng(V)
+    z = rng.standard_normal((B, V)).astype(np.float32) * 0.02
+    if bf16:
+        z = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(z))
+    hist = rng.permuted(np.tile(np.arange(V, dtype=np.int32), (B, 1)), axis=1)[:, :n_hist] if n_hist else np.zeros((B, 0), np.int32)
+    w = H.custom("near", workloads.f32_to_bf16_bits(z) if bf16 else z, dict(top_p=np.full(B, top_p), frequency_penalty=np.full(B, 0.5)),
+                 hist.tolist(), k_logprobs=0)
+    d = H.to_device(w)
+    ws = torch.zeros(sip.sip_workspace_bytes(B, V, sip.SIP_BF16 if bf16 else sip.SIP_F32, B * n_hist, 0), dtype=torch.uint8, device=H.DEV)
+    out = sip.sip_sample(d.logits, d.params, d.indptr, d.tokens, 41, 0, 0, V=V, workspace=ws)
+    torch.cuda.synchronize()
+    assert (ws[:4 * B].view(torch.int32) == 16).all()
+    missed, rows = 0, range(0, B, max(1, B // 24))
+    for b in rows:
+        s = z[b].copy()
+        s[hist[b]] -= np.float32(0.5)
+        mass = np.exp(s.astype(np.float64))
+        order = np.argsort(-s, kind="stable")
+        n = int(np.searchsorted(np.cumsum(mass[order]), float(np.float32(top_p)) * mass.sum()))
+        about = 2 if n_hist else 30                                # (a fiftieth of the mass below either way: six tokens)
+        missed += _listed_about(ws, s, order[n - about:n + about]) < 2 * about
+    assert missed <= 1, missed
+    H.compare(w, tuple(x.cpu().numpy() for x in out), 41, 0, rows=[0, 1, B - 1])
