@@ -484,7 +484,8 @@ def main() -> int:
     single_pass_rows = int((path == 1).sum())       # settled by the streaming + finishing kernels alone
     kernels = {}
     if not bool((path == 14).all()):                # the library launched its single-pass kernels
-        # a batch of at most one row per compute unit is finished by one kernel (finish_rescue_kernel);
+        # a batch of at most 128 rows is one kernel (chunk_rescue_kernel), one of at most one row per compute unit is finished
+        # by one kernel (finish_rescue_kernel) if not streamed by it as well (row_rescue_kernel);
         # a larger one by finish_kernel and, behind it, rescue_kernel (include/sip.h, "Kernels of a call")
         cu = torch.cuda.get_device_properties(dev).multi_processor_count
         one_kernel = w.B <= cu
@@ -494,6 +495,7 @@ def main() -> int:
             row_bytes <= 200 * 1024 or (w.B >= cu * 25 // 16 if w.B <= 2 * cu else w.B >= cu * 75 // 32)
         # (rows of up to SIP_MAX_RESIDENT_V entries, in a batch of one kernel: resident_kernel alone)
         names = (("resident_kernel", (0, 1)),) if w.V <= 32768 and one_kernel else \
+                (("chunk_rescue_kernel", (0, 1)),) if w.B <= 128 else \
                 (("row_rescue_kernel", (0, 1)),) if by_row and one_kernel else \
                 (("row_kernel", (0, 1)), ("rescue_kernel", (4, 5))) if by_row else \
                 (("stream_kernel", (0, 1)), ("finish_rescue_kernel", (2, 3))) if one_kernel else \

@@ -28,9 +28,13 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Launch shape of the single-pass path; a function of (B, V, dtype) only.
+struct Cut {
+  int S, cap_c, nc_cap;                                  // see Args
+};
 struct Plan {
   bool fast;       // false: vocabulary outside what the single-pass kernels are built for
-  int S, cap_c, nc_cap;
+  Cut cut;         // of a row, for the streaming kernel
+  Cut alone;       // the same where no more chunks than compute units are made of the batch, two or more of a row; S = 0: not so
   int room;        // segments of kChunkCap entries a row has in the workspace
   size_t final_lds;
 };
@@ -107,8 +111,8 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t, bool small_chunks = true)
       if (S == 2 || cost < best_cost) { best_cost = cost; want = S; }
     }
   }
-  p.room = p.S = fit(want);
-  if (p.S == 0) { p.fast = false; return p; }
+  p.room = p.cut.S = fit(want);
+  if (p.room == 0) { p.fast = false; return p; }
   // Chunks per row.  Up to 256 rows the room's worth of chunks is often too many: each pays the set-up, and what
   // counts is how many a compute unit gets.  With w of them its time grows as w * (set-up + stream), the set-up
   // being worth 32 KB of the row, and a compute unit that has only one streams at 4/5 of the speed.  us a call, at 1024
@@ -125,17 +129,28 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t, bool small_chunks = true)
       if (S == 0 || S > room) continue;
       const int per_unit = (B * S + kUnits - 1) / kUnits;
       const double cost = per_unit * (set_up + (per_unit == 1 ? 1.25 : 1.0) * V / S);
-      if (best_cost == 0.0 || cost < best_cost) { best_cost = cost; p.S = S; load = per_unit; }
+      if (best_cost == 0.0 || cost < best_cost) { best_cost = cost; p.cut.S = S; load = per_unit; }
     }
   }
   // Fewer chunks share the row's room in the workspace and their compute unit's LDS: longer queues and segments.
   constexpr int kTables = sip::stream_lds_bytes<SIP_F32>(sip::kQueueCap) - sip::kChunkCap * (int)sizeof(uint2);
-  const int lds = std::min(kMaxDynLds, 160 * 1024 / load);
-  const int queue = std::min(sip::kQueueCap * p.room / p.S, (lds - kTables) / (sip::kStreamWaves * (int)sizeof(uint2))) / 32 * 32;
-  p.cap_c = sip::kStreamWaves * std::max(queue, sip::kQueueCap);
-  // the longest list a row may have: what the heavier per-row logic holds in registers, and what
-  // the row's chunks can hand over
-  p.nc_cap = std::min(sip::kFinalThreads * sip::kCandLong, p.S * p.cap_c);
+  auto share = [&](Cut& c, int load) {
+    const int lds = std::min(kMaxDynLds, 160 * 1024 / load);
+    const int queue = std::min(sip::kQueueCap * p.room / c.S, (lds - kTables) / (sip::kStreamWaves * (int)sizeof(uint2))) / 32 * 32;
+    c.cap_c = sip::kStreamWaves * std::max(queue, sip::kQueueCap);
+    // the longest list a row may have: what the heavier per-row logic holds in registers, and what
+    // the row's chunks can hand over
+    c.nc_cap = std::min(sip::kFinalThreads * sip::kCandLong, c.S * c.cap_c);
+  };
+  share(p.cut, load);
+  // Half as many rows as compute units and less: a compute unit for each chunk, and the last of a row's workgroups
+  // finishes it (chunk_rescue_kernel).  That saves a launch and what the second kernel waits for at its start, more
+  // than is lost where the streaming kernel would be cut finer.  us a call, two kernels / one (nucleus 0.95, Student-t, 600 tokens;
+  // greedy, ids only): V = 128256 bf16 40 rows 23.0 / 19.8, 15.2 / 12.5, 64 rows 23.2 / 21.3, 15.6 / 13.6, 100 rows
+  // 25.9 / 24.5, 17.3 / 15.7, 128 rows 26.4 / 26.1, 17.5 / 16.1; fp32 64 rows 24.7 / 23.0, 16.2 / 15.0, 128 rows 27.9 / 27.3, 19.2
+  // / 19.6; V = 40000 fp32 100 rows 24.6 / 20.9; V = 200000 bf16 128 rows 28.7 / 28.5.
+  p.alone.S = B <= kUnits / 2 ? fit(kUnits / B) : 0;
+  if (p.alone.S < 2 || p.alone.S > p.room || B * p.alone.S > kUnits) p.alone.S = 0; else share(p.alone, 1);
   p.final_lds = sip::final_lds_fixed(V);
   return p;
 }
@@ -277,9 +292,30 @@ struct ShardSource {
   int64_t stride = 0;
 };
 
+// A number for a call (Args::call_mark): never 0 in the upper 56 bits.
+uint64_t new_call_mark() {
+  static const uint64_t seed = (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^
+                               (uint64_t)std::chrono::system_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ull ^
+                               (uint64_t)reinterpret_cast<uintptr_t>(&g_dev) << 20;
+  static std::atomic<uint64_t> calls{0};
+  for (;;) {
+    uint64_t x = seed + 0x9E3779B97F4A7C15ull * calls.fetch_add(1, std::memory_order_relaxed);
+    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+    x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+    x = (x ^ (x >> 31)) & ~255ull;
+    if (x) return x;
+  }
+}
+
+void set_cut(sip::Args& a, const Cut& c) {
+  a.S = c.S; a.cap_c = c.cap_c; a.nc_cap = c.nc_cap;
+  a.fin_tps = c.S > 0 ? sip::kFinThreads / c.S : sip::kFinThreads;
+  a.fin_inv = (65536 + a.fin_tps - 1) / a.fin_tps;
+}
+
 template <bool SH>
 sip_status launch(const sip::Args& a, int32_t B, int dtype, const Plan& plan, bool state, sip::StateHeader* head,
-                  hipStream_t stream);
+                  unsigned long long* tick_room, hipStream_t stream);
 
 // Where both ways serve a row (16384 to 32768 entries): whether it is held in registers.  That takes
 // a compute unit for a row and 9 to 34 us, whatever the row's filters keep; a batch of more rows than
@@ -406,24 +442,23 @@ sip_status sample_impl(const void* logits, int32_t B, int32_t V, int64_t row_str
   a.side_z = reinterpret_cast<float*>(ws + lay.side_z);
   a.side_c = reinterpret_cast<unsigned int*>(ws + lay.side_c);
   a.rowinfo = reinterpret_cast<sip::RowInfo*>(ws + lay.rowinfo);
-  a.fin_tps = plan.fast ? sip::kFinThreads / plan.S : sip::kFinThreads;
-  a.fin_inv = (65536 + a.fin_tps - 1) / a.fin_tps;
   a.chunks = reinterpret_cast<sip::ChunkOut*>(ws + lay.chunks);
   a.cand = reinterpret_cast<uint2*>(ws + lay.cand);
   a.bf16 = dtype == SIP_BF16;
-  a.S = plan.S; a.cap_c = plan.cap_c; a.nc_cap = plan.nc_cap;
+  set_cut(a, plan.cut);
   a.row_why = a.row_path + B;
-  a.tick_room = reinterpret_cast<unsigned long long*>(ws + lay.tick);
   a.one_seg = 0;
+  a.call_mark = 0;
 
   sip::StateHeader* head = h.slot ? h.state.head : nullptr;
-  return sh.t ? launch<true>(a, B, (int)dtype, plan, h.slot != nullptr, head, stream)
-              : launch<false>(a, B, (int)dtype, plan, h.slot != nullptr, head, stream);
+  unsigned long long* const tick_room = reinterpret_cast<unsigned long long*>(ws + lay.tick);     // room for a.call_tick
+  return sh.t ? launch<true>(a, B, (int)dtype, plan, h.slot != nullptr, head, tick_room, stream)
+              : launch<false>(a, B, (int)dtype, plan, h.slot != nullptr, head, tick_room, stream);
 }
 
 template <bool SH>
 sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan, bool state, sip::StateHeader* head,
-                  hipStream_t stream) {
+                  unsigned long long* tick_room, hipStream_t stream) {
   const DeviceSetup* dev = device_setup();
   if (!dev) return SIP_ERR_HIP;
   sip::Args a = a_in;
@@ -433,7 +468,7 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
   if (a.V <= kResidentMaxV && (!plan.fast || resident_is_chosen(a, B, state, dev->compute_units))) {
     // a workgroup holds its whole row in registers: one kernel
     if (state) {
-      a.call_tick = a.tick_room;
+      a.call_tick = tick_room;
       hipLaunchKernelGGL(sip::state_take_tick_kernel, dim3(1), dim3(64), 0, stream, head, a.call_tick);
     }
     const bool f32 = dtype == SIP_F32;
@@ -464,7 +499,7 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
     }
     return SIP_OK;
   }
-  a.call_tick = state ? a.tick_room : nullptr;   // the streaming kernel takes the state's counter and leaves it here
+  a.call_tick = state ? tick_room : nullptr;   // the streaming kernel takes the state's counter and leaves it here
   const bool ids = a.k_lp < 0;                   // token ids only
   auto k_stream = dtype == SIP_F32 ? (ids ? sip::stream_kernel<SIP_F32, SH, true> : sip::stream_kernel<SIP_F32, SH, false>)
                                    : (ids ? sip::stream_kernel<SIP_BF16, SH, true> : sip::stream_kernel<SIP_BF16, SH, false>);
@@ -477,6 +512,20 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
   // grid behind it for the rows (normally none) that need more.
   const bool fused = B <= dev->compute_units && (size_t)plan.final_lds <= sip::kFusedRawBytes &&
                      2 * words * sizeof(uint32_t) <= sip::kFusedRawBytes;
+  if (plan.alone.S && fused && !state) {
+    // a compute unit for every chunk: streaming, finishing and the heavier logic in one kernel
+    a.call_mark = new_call_mark();
+    set_cut(a, plan.alone);
+    auto k_alone = dtype == SIP_F32 ? sip::chunk_rescue_kernel<SIP_F32, SH> : sip::chunk_rescue_kernel<SIP_BF16, SH>;
+    if (timed) {
+      hipExtLaunchKernelGGL(k_alone, dim3(B * a.S), dim3(sip::kStreamThreads), 0, stream, ev[0], ev[1], 0, a);
+      for (int i = 2; i < 6; ++i)
+        if (ev[i]) (void)hipEventRecord(ev[i], stream);       // one kernel: empty intervals
+    } else {
+      hipLaunchKernelGGL(k_alone, dim3(B * a.S), dim3(sip::kStreamThreads), 0, stream, a);
+    }
+    return hipGetLastError() == hipSuccess ? SIP_OK : SIP_ERR_HIP;
+  }
   a.one_seg = row_is_chosen(B, a.V, dtype, state, dev->compute_units);
   if (a.one_seg) {
     // the row's workgroup streams and finishes it, and the rescue kernel is behind it
@@ -508,10 +557,10 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
     }
     return hipGetLastError() == hipSuccess ? SIP_OK : SIP_ERR_HIP;
   }
-  const uint32_t stream_lds = (uint32_t)(dtype == SIP_F32 ? sip::stream_lds_bytes<SIP_F32>(plan.cap_c / sip::kStreamWaves)
-                                                        : sip::stream_lds_bytes<SIP_BF16>(plan.cap_c / sip::kStreamWaves));
-  if (timed) hipExtLaunchKernelGGL(k_stream, dim3(B * plan.S), dim3(sip::kStreamThreads), stream_lds, stream, ev[0], ev[1], 0, a);
-  else hipLaunchKernelGGL(k_stream, dim3(B * plan.S), dim3(sip::kStreamThreads), stream_lds, stream, a);
+  const uint32_t stream_lds = (uint32_t)(dtype == SIP_F32 ? sip::stream_lds_bytes<SIP_F32>(a.cap_c / sip::kStreamWaves)
+                                                        : sip::stream_lds_bytes<SIP_BF16>(a.cap_c / sip::kStreamWaves));
+  if (timed) hipExtLaunchKernelGGL(k_stream, dim3(B * a.S), dim3(sip::kStreamThreads), stream_lds, stream, ev[0], ev[1], 0, a);
+  else hipLaunchKernelGGL(k_stream, dim3(B * a.S), dim3(sip::kStreamThreads), stream_lds, stream, a);
   if (fused) {
     auto k_fused = dtype == SIP_F32 ? sip::finish_rescue_kernel<SIP_F32, SH> : sip::finish_rescue_kernel<SIP_BF16, SH>;
     if (timed) {             // the events take the dispatches' own begin / end time stamps
@@ -756,7 +805,7 @@ int32_t sip_plan_chunks(int32_t B, int32_t V, sip_dtype dtype, int32_t t_shards)
   if (B <= 0 || B > SIP_MAX_B || V <= 0 || (dtype != SIP_F32 && dtype != SIP_BF16) || t_shards < 0 || t_shards > SIP_MAX_SHARDS) return -1;
   if (t_shards > 0 && V % t_shards != 0) return -1;
   const Plan p = make_plan(B, V, (int)dtype, t_shards);
-  return p.fast ? p.S : 0;
+  return p.fast ? p.cut.S : 0;
 }
 
 const char* sip_status_string(sip_status status) {

@@ -82,7 +82,7 @@ struct Args {
   int* row_path;            // [B] diagnostic: 1 = finished by the single-pass path, >1 = exact path (reason)
   int* row_why;             // [B] diagnostic: 1, or why the finishing kernel left the row to the rescue kernel
   int one_seg;              // the row's S segments are one: its workgroup made the whole list (sip_row.h)
-  unsigned long long* tick_room;     // room in the workspace for `call_tick`
+  unsigned long long call_mark;      // in the upper 56 bits, a number no other call has; see RowWord
   // Device-resident history (sip_sample_state): `slot` != nullptr replaces the CSR above.  Row b's
   // history is tokens[slot[b] * L_max .. + st_len[slot[b]]); `tokens` then points at the state's
   // token table and nnz = slots * L_max.
@@ -107,6 +107,45 @@ struct Args {
   int smp_bps, smp_inv, smp_step;
   int L_max, slots;
 };
+
+// How the workgroups of a row's chunks tell which of them is the last (chunk_rescue_kernel): a word in the workspace
+// counts them.  Nothing in the workspace need be cleared ahead of a call, so the count carries the call's mark and
+// whoever finds another puts the call's there, at the start; the last one leaves a word without a mark, so that a
+// recorded call can be replayed.  (Marks are 56 bits, from a counter through a mixing function with a seed of the
+// process: what else the memory may hold agrees with one in 1 of 2^56 rows.)
+// For one thread of the workgroup, which does all three.
+struct RowWord {
+  unsigned long long* w;
+  unsigned long long found;
+  __device__ __forceinline__ void look() { found = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+  __device__ __forceinline__ void open(unsigned long long mark) {
+    if ((found ^ mark) >> 8) atomicCAS(w, found, mark);       // (lost: another workgroup of the row was first)
+  }
+  // Everything the workgroup has written is visible to the last to arrive.  (Ahead of it every wave has waited for
+  // its stores, and a barrier.)
+  __device__ __forceinline__ bool arrive(uint32_t n) {
+    const unsigned long long before = __hip_atomic_fetch_add(w, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = (before & 255u) + 1u == n;
+    if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (last) __hip_atomic_store(w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return last;
+  }
+};
+
+// Stores that every workgroup of the device can read once they are done, whatever XCD it is on (past the XCD's L2).
+template <bool SHARED, typename T>
+__device__ __forceinline__ void put(T* at, const T& v) {
+  if constexpr (SHARED) {
+    static_assert(sizeof(T) % 8 == 0, "");
+    unsigned long long w[sizeof(T) / 8];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 8); ++i)
+      __hip_atomic_store(reinterpret_cast<unsigned long long*>(at) + i, w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    *at = v;
+  }
+}
 
 // Extent of row b's history in a.tokens, clamped so that no read leaves the array, and where the
 // row's part of the exact path's side tables starts.

@@ -107,8 +107,8 @@ struct FinHint {
 // Row b, start to finish.  Returns 1 or kFinWholeRow (finished: outputs written) or the reason why the list
 // does not settle the row.  Every return value is workgroup-uniform.
 // ROW: the calling workgroup has made the list itself, as one segment; `hand` holds the row's record and
-// the summary.
-template <bool ROW>
+// the summary.  RECORD: `hand` holds the record alone.
+template <bool ROW, bool RECORD = false>
 __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared& fs, FinHint* hint = nullptr,
                                           const RowHand* hand = nullptr) {
   constexpr int NT = kFinThreads;
@@ -154,7 +154,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     for (int r = 0; r < CR; ++r) asm volatile("" ::"v"(creg[r].x), "v"(creg[r].y));
     asm volatile("" ::"v"((uint32_t)my_bulk), "v"((uint32_t)(my_bulk >> 32)));
   };
-  const RowInfo ri = ROW ? hand->ri : a.rowinfo[b];
+  const RowInfo ri = ROW || RECORD ? hand->ri : a.rowinfo[b];
   const ChunkOut co = ROW ? hand->co : a.chunks[(size_t)b * S + min(lane, S - 1)];
   if constexpr (ROW) {
     if (hand->direct) {                    // uniform

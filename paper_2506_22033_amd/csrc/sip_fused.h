@@ -11,6 +11,7 @@
 
 namespace sip {
 
+constexpr size_t kAloneLds = 144 * 1024;    // sample, queues and tables of a chunk that has a compute unit to itself
 constexpr size_t kFusedRawBytes = 122880;   // final_lds_fixed() of the largest vocabulary of the single-pass kernels
 static_assert(sizeof(FinShared) <= kFusedRawBytes, "the finishing tables lie inside the same LDS");
 
@@ -58,6 +59,53 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
     __syncthreads();                       // the list is written, and the tables are free
     code = finish_row<true>(a, b, u.fin, &hint, &hand);
   }
+  if (threadIdx.x == 0) {
+    a.row_path[b] = code;
+    a.row_why[b] = code == kFinWholeRow ? 1 : code;
+  }
+  if (code == 1 || code == kFinWholeRow) return;                     // uniform
+  __syncthreads();
+  RescueSeen seen;
+  if (hint.valid) { seen.why = code; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
+  rescue_row<DT, SH>(a, b, u.raw, ex, fsr, seen);
+}
+
+// The same where the batch is so small that a row's chunks have a compute unit each: the last of a row's workgroups
+// to be done with its chunk finishes the row.  What a second kernel costs -- 2.4 us until it starts, cold arguments and
+// records -- goes; what the workgroups pay to agree is 1 us: their stores' way to memory (put(): written back from
+// the XCD's L2 by each of them instead, chat_64 took 29.6 us), the addition to the row's word, its answer.  us a call, two
+// kernels / one: one row of V = 128256 bf16 18.7 / 18.5, 32 rows with 8000 prompt tokens 25.9 / 25.0, 64 rows 26.7 /
+// 26.3, 31 rows of V = 64712 fp32 29.8 / 28.4, 9 of V = 65536 in pieces 20.7 / 19.8 (Plan::alone has more).  What bounds
+// it: latency, the set-up's chain of 4.5 us and the finishing's of 13.
+template <int DT, bool SH>
+__global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void chunk_rescue_kernel(Args a_by_value) {
+  (void)a_by_value;
+  const Args& a = *(const Args*)__builtin_amdgcn_kernarg_segment_ptr();
+  warm_kernel_arguments();
+  __shared__ union Tables {
+    uint4 stream[kAloneLds / 16]; FinShared fin; unsigned char raw[kFusedRawBytes];
+    __device__ Tables() {}
+  } u;
+  __shared__ ExactShared ex;
+  __shared__ FastShared fsr;
+  __shared__ bool last;
+  static_assert(sizeof(u) + sizeof(ex) + sizeof(fsr) + 64 <= 160 * 1024, "a compute unit's LDS");
+  // (a row's chunks on one XCD, as in stream_kernel)
+  int wg = blockIdx.x;
+  if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int b = wg / a.S;
+  unsigned char* const front = reinterpret_cast<unsigned char*>(u.stream);
+  RowHand hand;
+  RowWord word{reinterpret_cast<unsigned long long*>(a.rowinfo + b), 0ull};
+  stream_part<DT, SH, false, true, true>(a, wg, front,
+      *reinterpret_cast<StreamTables<DT, false>*>(front + stream_front_bytes<DT, false>(a.cap_c / kStreamWaves)), &hand, &word);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                             // every wave's part of the list is written
+  __syncthreads();
+  if (threadIdx.x == kFinalThreads - kWave) last = word.arrive((uint32_t)a.S);
+  __syncthreads();
+  if (!last) return;                                                 // uniform
+  FinHint hint;
+  const int code = finish_row<false, true>(a, b, u.fin, &hint, &hand);
   if (threadIdx.x == 0) {
     a.row_path[b] = code;
     a.row_why[b] = code == kFinWholeRow ? 1 : code;

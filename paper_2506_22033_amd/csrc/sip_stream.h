@@ -42,18 +42,19 @@ constexpr int kChunkBitsMax = 73728;        // most elements a chunk may have (h
 constexpr int kRowBitsMax = 262144;         // and a row that one workgroup streams (32 KB)
 // What differs between a workgroup that streams one chunk of a row for the finishing kernel (ROW =
 // false: four workgroups per compute unit, 40 KB of LDS and 64 registers each) and one that streams the
-// whole row and finishes it itself (sip_row.h: two, with 80 KB and 128 registers).
-template <int DT, bool ROW>
+// whole row and finishes it itself (sip_row.h: two, with 80 KB and 128 registers).  ALONE: a chunk whose workgroup
+// has a compute unit to itself (sip_fused.h).
+template <int DT, bool ROW, bool ALONE = false>
 struct StreamShape {
   static constexpr int EPL = DT == SIP_F32 ? 4 : 8;                    // elements per 16-byte load
-  static constexpr int kLoads = ROW ? 4 : 2;                           // 16-byte loads per thread per tile, of which two are held
+  static constexpr int kLoads = ROW || ALONE ? 4 : 2;                           // 16-byte loads per thread per tile, of which two are held
   static constexpr int kTile = kStreamThreads * kLoads * EPL;
   typedef typename std::conditional<DT == SIP_F32, uint2, uint32_t>::type entry_t;      // of a queue, see `process`
   static constexpr int kQueue = DT == SIP_F32 ? 704 : 1280;             // ROW: entries of one wave's queue (chunks: an eighth of Args::cap_c)
   static constexpr int kTags = 1 << EPL;                               // history bits of one load
   static constexpr int kBits = ROW ? kRowBitsMax : kChunkBitsMax;      // most elements a workgroup streams
   static constexpr int kBlocks = kBits / kBlkElems;
-  static constexpr int kHistRegs = ROW ? 8 : 4;                         // history tokens a thread requests with the sample
+  static constexpr int kHistRegs = ROW || ALONE ? 8 : 4;                         // history tokens a thread requests with the sample
   // Load numbers of p whole pieces, each rounded up to tiles: they have kLoadBits in a bf16 queue entry.
   static constexpr int kLoadBits = ROW ? 7 : 5;
   static constexpr int load_numbers(int p) { return p * kLoads * ((kBits / p + kTile - 1) / kTile); }
@@ -62,6 +63,7 @@ struct StreamShape {
   }
 };
 static_assert(StreamShape<SIP_BF16, false>::most_load_numbers(SIP_MAX_SHARDS) <= 1 << StreamShape<SIP_BF16, false>::kLoadBits, "see `process`");
+static_assert(StreamShape<SIP_BF16, false, true>::most_load_numbers(SIP_MAX_SHARDS) <= 1 << StreamShape<SIP_BF16, false, true>::kLoadBits, "see `process`");
 static_assert(StreamShape<SIP_BF16, true>::most_load_numbers(SIP_MAX_SHARDS) <= 1 << StreamShape<SIP_BF16, true>::kLoadBits, "see `process`");
 constexpr float kBulkScale = 1073741824.0f; // 2^30
 
@@ -347,11 +349,12 @@ struct RowHand {
 };
 
 // Streams chunk wg % S of row wg / S (ROW: row wg).  False: the row cannot be finished from a list.  `front` and
-// `sm`: LDS, one behind the other.  IDS: a call that asks for token ids only (a kernel of its own, see `masses`).
-template <int DT, bool SH, bool ROW, bool IDS = false>
+// `sm`: LDS, one behind the other.  IDS: a call that may ask for token ids only (a kernel of its own, see `masses`).
+// ALONE: `hand` gets the row's record, whose place has the row's word (opened here by the last wave's first thread).
+template <int DT, bool SH, bool ROW, bool IDS = false, bool ALONE = false>
 __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigned char* const front, StreamTables<DT, ROW>& sm,
-                                            RowHand* hand) {
-  typedef StreamShape<DT, ROW> Sh;
+                                            RowHand* hand, RowWord* word = nullptr) {
+  typedef StreamShape<DT, ROW, ALONE> Sh;
   typedef typename Sh::entry_t entry_t;
   constexpr int EPL = Sh::EPL;
   constexpr int ESZ = (DT == SIP_F32) ? 4 : 2;
@@ -462,8 +465,13 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
   // read: with no store ahead of them in the kernel the compiler reads them through the scalar
   // cache.)
   if (!ROW && a.call_tick && blockIdx.x == 0 && tid == 0) *a.call_tick = atomicAdd(a.st_tick, 1ull);
+  if (ALONE && tid == kStreamThreads - kWave) word->look();
   if (target == 0) {
-    if (!ROW && ch == 0 && tid == 0) a.rowinfo[b].target = 0;                // the finishing kernel looks at nothing else
+    if (ALONE) {
+      hand->ri.target = 0;
+      if (tid == kStreamThreads - kWave) word->open(a.call_mark);
+    }
+    if (!ROW && !ALONE && ch == 0 && tid == 0) a.rowinfo[b].target = 0;                // the finishing kernel looks at nothing else
     return false;
   }
   // ---- threshold: the same 8192-element sample (1 KB blocks spread evenly over the row) is
@@ -537,13 +545,13 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
     if (SH) roll();
   }
 
-  if (ROW || (ch == 0 && tid == 0)) {      // the row's record for the finishing kernel
+  if (ROW || ALONE || (ch == 0 && tid == 0)) {      // the row's record for the finishing kernel
     RowInfo ri;
     ri.tau = rp.tau; ri.top_p = rp.top_p; ri.min_p = rp.min_p; ri.theta = rp.theta; ri.phi = rp.phi; ri.psi = rp.psi;
     ri.top_k = rp.top_k; ri.target = target | (pen.prompt_on ? kPromptFlag : 0);
     ri.row_id = rp.row_id; ri.lo = hr.lo; ri.hi = hr.hi;
     ri.slot = slot; ri.ndist = ndist;
-    if (ROW) hand->ri = ri; else a.rowinfo[b] = ri;
+    if (ROW || ALONE) hand->ri = ri; else a.rowinfo[b] = ri;
   }
   {
     uint4* z4 = reinterpret_cast<uint4*>(hist);
@@ -650,6 +658,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
     const BulkRef r = make_bulk_ref(out ? 0.0f : at, scale);
     if (lane == 0) { sm.key_thr = out ? 1u : 0u; sm.ref = r; }
   }
+  if (ALONE && tid == kStreamThreads - kWave) word->open(a.call_mark);
   if (has_pen && wave > 0) {
     auto mark = [&](int t) {
       const uint32_t r = (uint32_t)(t - g0) ^ (uint32_t)(EPL - 1);             // (last element of a load first, see `process`)
@@ -901,7 +910,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
     const uint32_t at = queue_place(n_out);
     for (uint32_t i = lane; i < n_out; i += kWave) {
       const uint2 en = taken_out(i);
-      if (!ROW || at + i < seg_cap) seg[at + i] = en;
+      if (!ROW || at + i < seg_cap) put<ALONE>(&seg[at + i], en);
     }
     n_flushed += n_out;
     qn = 0;
@@ -1000,7 +1009,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
   overflow |= tot > seg_cap;
   const bool blocks = plain && tot <= seg_cap - (uint32_t)Sh::kBlocks;           // workgroup-uniform
   const int n_blk = blocks ? (c1 - c0 + kBlkElems - 1) / kBlkElems : 0;
-  if (tid < n_blk) (reinterpret_cast<unsigned long long*>(seg + seg_cap) - n_blk)[tid] = ref.none ? 0ull : sm.blk_mass[tid];
+  if (tid < n_blk) put<ALONE>(reinterpret_cast<unsigned long long*>(seg + seg_cap) - n_blk + tid, ref.none ? 0ull : sm.blk_mass[tid]);
   if (ROW || tid == 0) {
     ChunkOut o;
     o.bulk = 0;
@@ -1021,7 +1030,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
       hand->longest = (uint32_t)__builtin_amdgcn_readfirstlane((int)longest);
       hand->direct = __builtin_amdgcn_readfirstlane(!(marks >> 30) && longest <= (uint32_t)(kRowRegs * kWave)) != 0;
     }
-    if (tid == 0) a.chunks[ROW ? (size_t)b * (size_t)a.S : (size_t)wg] = o;
+    if (tid == 0) put<ALONE>(&a.chunks[ROW ? (size_t)b * (size_t)a.S : (size_t)wg], o);
   }
   return true;
 }
