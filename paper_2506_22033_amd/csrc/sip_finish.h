@@ -79,6 +79,8 @@ struct __align__(16) FinShared {
   int code, code_top;
   uint32_t hash_fail, n_memb, n_fold, key_cut, n_hi;
   uint32_t token, token_key;
+  uint32_t uniform;                         // the row's uniform in units of 2^-24, and bit 31 once it is there
+  double ln_total;                          // logarithm of the row's mass, in the maximum's mass
   unsigned long long before_d;
 };
 
@@ -235,13 +237,12 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     }
     if (tid == 0) {
       fs.bin_k = -1; fs.bin_n = -1; fs.bin_d = -1; fs.code = 0; fs.code_top = 0; fs.hash_fail = 0; fs.n_memb = 0; fs.n_fold = 0;
-      fs.token = kFinNone; fs.token_key = 0;
+      fs.token = kFinNone; fs.token_key = 0; fs.uniform = 0;
     }
   }
   // row constants that take long arithmetic, worked out while the loads above travel
   const bool minp_on = !rp.greedy && rp.min_p > 0.0f;
   const float t_minp = minp_on ? (float)log((double)rp.min_p) : 0.0f;
-  const unsigned long long j24 = rp.greedy ? 0ull : (unsigned long long)(philox_word0(a.seed, rp.row_id, step_of(a)) >> 8);
   const bool k_act = !rp.greedy && rp.top_k >= 2 && rp.top_k < V;
   const uint32_t n_top = (uint32_t)max(0, min(a.k_lp, V));
 
@@ -591,6 +592,20 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   }
   lds_barrier();
 
+  // ---- Wave 2, which nothing else occupies from here to the draw: the row's uniform and the logarithm of its mass, which
+  // take 40 multiplications of full length and a chain in double.  (By every wave ahead of the penalties, and by
+  // the thread that stores the outputs, they lay on the row's path.  us a call, so / now: one row of V = 128256 bf16 18.5 /
+  // 18.3, 64 rows 26.3 / 25.7, 32 rows with 8000 prompt tokens 25.0 / 24.4, 1024 rows of V = 129280 bf16 89.1 / 88.4.)
+  constexpr uint32_t kThere = 0x80000000u;
+  if (wave == 2) {
+    if (!rp.greedy) {
+      const uint32_t u = philox_word0(a.seed, rp.row_id, step_of(a)) >> 8;
+      if (lane == 0) __hip_atomic_store(&fs.uniform, u | kThere, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    double lnZ;
+    total_mass(lnZ);
+    if (lane == 0) fs.ln_total = lnZ;
+  }
   // ---- (5) wave 1: best-n.  The range [0, nt) of the sorted list holds every element of the
   // row at or above the bin of the n-th best, so an entry's rank in it is its rank in the row.
   if (wave == 1 && n_top > 0) {
@@ -784,6 +799,9 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
         const uint32_t v = have ? fs.u.list.sidx[lane] : kFinNone;
         const unsigned long long Et = (have && kept_key(kt, key_cut)) ? mass(value_of(kt)) : 0ull;
         const unsigned long long S3 = wave_add_u64(Et);
+        uint32_t u;                                                            // (wave 2 has it by now, or is about to)
+        do u = __hip_atomic_load(&fs.uniform, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); while (!(u & kThere));
+        const unsigned long long j24 = u & ~kThere;
         const unsigned long long target = (__umul64hi(j24, S3) << 40) | ((j24 * S3) >> 24);   // floor(j * S3 / 2^24)
         // The entries are brought into vocabulary order across the lanes: an entry's rank is the
         // number of smaller indices (the indices are distinct), lane `rank` receives its mass and
@@ -821,6 +839,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   }
   lds_barrier();
   int code = fs.code_top ? fs.code_top : fs.code;                              // a failure of the best-n ranking stands
+  const unsigned long long j24 = fs.uniform & ~kThere;
   if (code == kFinDrawBig) {
     // ---- (6') kept mass per vocabulary-index bin, prefix, then the crossing inside one bin
     const uint32_t key_cut = fs.key_cut, n_hi = fs.n_hi;
@@ -1030,11 +1049,7 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     settled = kFinWholeRow;
   }
   if (code != 1) return code;                                                  // uniform
-  if (tid == 0) {
-    double lnZ;
-    total_mass(lnZ);
-    emit(fs.token, fs.token_key, lnZ);
-  }
+  if (tid == 0) emit(fs.token, fs.token_key, fs.ln_total);
   return settled;
 }
 
