@@ -15,6 +15,32 @@ constexpr size_t kAloneLds = 144 * 1024;    // sample, queues and tables of a ch
 constexpr size_t kFusedRawBytes = 122880;   // final_lds_fixed() of the largest vocabulary of the single-pass kernels
 static_assert(sizeof(FinShared) <= kFusedRawBytes, "the finishing tables lie inside the same LDS");
 
+// rescue_row() for the kernels that hardly ever need it, as a function of its own: inlined, its registers made the part
+// that every row goes through keep 540 to 620 scalar registers in lanes of vector registers, now 2 to 28, and 18 to 37
+// vector registers in scratch, now none.  us a call: one row of V = 128256 bf16 18.2 / 17.9, 64 rows 25.8 / 25.5, 200 rows of V
+// = 152064 bf16 in pieces 33.4 / 32.8, 256 rows fp32 with everything on 50.0 / 49.7.  LDS goes along as offsets, the
+// arguments as an address, so that both are reached by the instructions meant for them.
+template <typename T>
+__device__ __forceinline__ uint32_t lds_offset(T& x) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) T*)&x;
+}
+template <typename T>
+__device__ __forceinline__ T& at_lds_offset(uint32_t o) {
+  return *(T*)(__attribute__((address_space(3))) T*)(uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)o);
+}
+template <int DT, bool SH>
+__device__ __attribute__((noinline)) void rescue_apart(unsigned long long args, int b, uint32_t raw, uint32_t ex, uint32_t fs, int why,
+                                                       float m, float zmax, float T) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)args);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(args >> 32));
+  const Args& a = *(const Args*)(const __attribute__((address_space(4))) Args*)(((unsigned long long)hi << 32) | lo);
+  RescueSeen seen;
+  seen.why = __builtin_amdgcn_readfirstlane(why);
+  seen.m = m; seen.zmax = zmax; seen.T = T;
+  rescue_row<DT, SH>(a, __builtin_amdgcn_readfirstlane(b), &at_lds_offset<unsigned char>(raw), at_lds_offset<ExactShared>(ex),
+                     at_lds_offset<FastShared>(fs), seen);
+}
+
 template <int DT, bool SH>
 __global__ __launch_bounds__(kFinalThreads) void finish_rescue_kernel(Args a_by_value) {
   (void)a_by_value;
@@ -35,7 +61,7 @@ __global__ __launch_bounds__(kFinalThreads) void finish_rescue_kernel(Args a_by_
   __syncthreads();
   RescueSeen seen;
   if (hint.valid) { seen.why = code; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
-  rescue_row<DT, SH>(a, b, u.raw, ex, fsr, seen);
+  rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
 }
 
 // The same for a workgroup that has streamed its row itself (sip_row.h).
@@ -67,7 +93,7 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
   __syncthreads();
   RescueSeen seen;
   if (hint.valid) { seen.why = code; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
-  rescue_row<DT, SH>(a, b, u.raw, ex, fsr, seen);
+  rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
 }
 
 // The same where the batch is so small that a row's chunks have a compute unit each: the last of a row's workgroups
@@ -114,7 +140,7 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
   __syncthreads();
   RescueSeen seen;
   if (hint.valid) { seen.why = code; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
-  rescue_row<DT, SH>(a, b, u.raw, ex, fsr, seen);
+  rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
 }
 
 }  // namespace sip
