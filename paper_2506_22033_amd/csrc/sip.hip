@@ -59,7 +59,7 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t, bool small_chunks = true)
   const int tile = dtype == SIP_F32 ? sip::StreamShape<SIP_F32, false>::kTile : sip::StreamShape<SIP_BF16, false>::kTile;
   const int n_tiles = (Vp + tile - 1) / tile * pieces;
   // `n` chunks a row, as the kernels can have them.
-  auto fit = [&](int n) {
+  auto fit = [&](int n, int most = sip::kChunkBitsMax) {
     // A chunk holds at least two tiles; where the batch is small, one: a short bf16 row would else be one or
     // two chunks, whose queues overflow under a long history.  (V = 24275 bf16, 61 rows of 3034 tokens on a
     // state, one chunk: half of the rows took the exact path, 254 us; three: 78.)  The workspace grows with
@@ -77,14 +77,14 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t, bool small_chunks = true)
         }
       n = best;
     }
-    // the streaming kernel marks a chunk's history tokens in an LDS bitmap of kChunkBitsMax bits:
+    // the streaming kernel marks a chunk's history tokens in an LDS bitmap of `most` bits:
     // cut finer (first at the piece boundaries, then inside the pieces) until a chunk fits
     const int unit = sip::kChunkUnit;
     const int n_units = (Vp + unit - 1) / unit;
     auto max_chunk = [&](int S) {
       return S >= pieces ? (n_units + S / pieces - 1) / (S / pieces) * unit : pieces / S * Vp;
     };
-    while (max_chunk(n) > sip::kChunkBitsMax) {
+    while (max_chunk(n) > most) {
       n = n >= pieces ? n + pieces : pieces;
       if (n > sip::kMaxChunks) return 0;
     }
@@ -134,23 +134,33 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t, bool small_chunks = true)
   }
   // Fewer chunks share the row's room in the workspace and their compute unit's LDS: longer queues and segments.
   constexpr int kTables = sip::stream_lds_bytes<SIP_F32>(sip::kQueueCap) - sip::kChunkCap * (int)sizeof(uint2);
-  auto share = [&](Cut& c, int load) {
+  constexpr int kAloneTables = (int)sizeof(sip::StreamTables<SIP_F32, false, true>);
+  static_assert(kAloneTables + 16384 <= (int)sip::kAloneLds && sizeof(sip::StreamTables<SIP_BF16, false, true>) <= kAloneTables + 8192 &&
+                kMaxDynLds <= (int)sip::kAloneLds, "bf16 tables are larger by less than its queues are shorter");
+  auto share = [&](Cut& c, int load, int tables) {
     const int lds = std::min(kMaxDynLds, 160 * 1024 / load);
-    const int queue = std::min(sip::kQueueCap * p.room / c.S, (lds - kTables) / (sip::kStreamWaves * (int)sizeof(uint2))) / 32 * 32;
+    const int queue = std::min(sip::kQueueCap * p.room / c.S, (lds - tables) / (sip::kStreamWaves * (int)sizeof(uint2))) / 32 * 32;
     c.cap_c = sip::kStreamWaves * std::max(queue, sip::kQueueCap);
     // the longest list a row may have: what the heavier per-row logic holds in registers, and what
     // the row's chunks can hand over
     c.nc_cap = std::min(sip::kFinalThreads * sip::kCandLong, c.S * c.cap_c);
   };
-  share(p.cut, load);
+  share(p.cut, load, kTables);
   // Half as many rows as compute units and less: a compute unit for each chunk, and the last of a row's workgroups
   // finishes it (chunk_rescue_kernel).  That saves a launch and what the second kernel waits for at its start, more
   // than is lost where the streaming kernel would be cut finer.  us a call, two kernels / one (nucleus 0.95, Student-t, 600 tokens;
   // greedy, ids only): V = 128256 bf16 40 rows 23.0 / 19.8, 15.2 / 12.5, 64 rows 23.2 / 21.3, 15.6 / 13.6, 100 rows
   // 25.9 / 24.5, 17.3 / 15.7, 128 rows 26.4 / 26.1, 17.5 / 16.1; fp32 64 rows 24.7 / 23.0, 16.2 / 15.0, 128 rows 27.9 / 27.3, 19.2
   // / 19.6; V = 40000 fp32 100 rows 24.6 / 20.9; V = 200000 bf16 128 rows 28.7 / 28.5.
-  p.alone.S = B <= kUnits / 2 ? fit(kUnits / B) : 0;
-  if (p.alone.S < 2 || p.alone.S > p.room || B * p.alone.S > kUnits) p.alone.S = 0; else share(p.alone, 1);
+  // Such chunks may be longer than the streaming kernel's: V = 152064, 128 rows bf16 26.2 / 26.1, fp32 29.1 / 27.8, 86 rows
+  // fp32 27.5 / 26.5; V = 200000 fp32 128 rows 33.6 / 31.4.  But not those beyond 416 KB that leave more than an eighth of the
+  // units without any: V = 256000 fp32, 100 rows 39.1 / 40.8.
+  p.alone.S = B <= kUnits / 2 ? fit(kUnits / B, sip::kAloneBitsMax) : 0;
+  const int64_t chunk_bytes = p.alone.S > 0 ? (int64_t)V / p.alone.S * (dtype == SIP_F32 ? 4 : 2) : 0;
+  if (p.alone.S < 2 || p.alone.S > p.room || B * p.alone.S > kUnits || (chunk_bytes > 416 * 1024 && B * p.alone.S < kUnits * 7 / 8))
+    p.alone.S = 0;
+  else
+    share(p.alone, 1, kAloneTables);
   p.final_lds = sip::final_lds_fixed(V);
   return p;
 }
@@ -516,7 +526,8 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
     // a compute unit for every chunk: streaming, finishing and the heavier logic in one kernel
     a.call_mark = new_call_mark();
     set_cut(a, plan.alone);
-    auto k_alone = dtype == SIP_F32 ? sip::chunk_rescue_kernel<SIP_F32, SH> : sip::chunk_rescue_kernel<SIP_BF16, SH>;
+    auto k_alone = dtype == SIP_F32 ? (ids ? sip::chunk_rescue_kernel<SIP_F32, SH, true> : sip::chunk_rescue_kernel<SIP_F32, SH, false>)
+                                    : (ids ? sip::chunk_rescue_kernel<SIP_BF16, SH, true> : sip::chunk_rescue_kernel<SIP_BF16, SH, false>);
     if (timed) {
       hipExtLaunchKernelGGL(k_alone, dim3(B * a.S), dim3(sip::kStreamThreads), 0, stream, ev[0], ev[1], 0, a);
       for (int i = 2; i < 6; ++i)
@@ -533,7 +544,8 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
     a.nc_cap = std::min(sip::kFinalThreads * sip::kCandLong, a.S * a.cap_c);
     if (state) hipLaunchKernelGGL(sip::state_take_tick_kernel, dim3(1), dim3(64), 0, stream, head, a.call_tick);
     if (fused) {
-      auto k_both = dtype == SIP_F32 ? sip::row_rescue_kernel<SIP_F32, SH> : sip::row_rescue_kernel<SIP_BF16, SH>;
+      auto k_both = dtype == SIP_F32 ? (ids ? sip::row_rescue_kernel<SIP_F32, SH, true> : sip::row_rescue_kernel<SIP_F32, SH, false>)
+                                     : (ids ? sip::row_rescue_kernel<SIP_BF16, SH, true> : sip::row_rescue_kernel<SIP_BF16, SH, false>);
       if (timed) {
         hipExtLaunchKernelGGL(k_both, dim3(B), dim3(sip::kStreamThreads), 0, stream, ev[0], ev[1], 0, a);
         for (int i = 2; i < 6; ++i)

@@ -1053,6 +1053,24 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   return settled;
 }
 
+// Row b of which stream_part() has left the arg max, `best` (uniform).  Returns like finish_row().
+__device__ __forceinline__ int finish_greedy(const Args& a, const int b, const unsigned long long best) {
+  if (best) {
+    if (threadIdx.x == 0) {
+      a.out_ids[b] = (int)~(uint32_t)best;
+      if (a.slot) state_append_row(a, b);
+    }
+    return 1;
+  }
+  // No value above -inf: the general path's, which finds no list.
+  if (threadIdx.x < (uint32_t)a.S) {
+    ChunkOut none{};
+    none.cnt = kCntOverflow;
+    a.chunks[(size_t)b * (size_t)a.S + threadIdx.x] = none;
+  }
+  return 3;
+}
+
 __global__ __launch_bounds__(kFinThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void finish_kernel(Args a_by_value) {
   // The arguments are read where they are used, straight from the kernel-argument segment
   // (the struct is the only parameter, so it starts at offset 0), instead of being held in

@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kFinalThreads) void finish_rescue_kernel(Args a_by_
 }
 
 // The same for a workgroup that has streamed its row itself (sip_row.h).
-template <int DT, bool SH>
+template <int DT, bool SH, bool IDS>
 __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void row_rescue_kernel(Args a_by_value) {
   (void)a_by_value;
   const Args& a = *(const Args*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -81,9 +81,10 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
   RowHand hand;
   FinHint hint;
   int code = 2;
-  if (stream_part<DT, SH, true>(a, b, u.stream.front, u.stream.tables, &hand)) {                      // uniform
+  if (stream_part<DT, SH, true, IDS>(a, b, u.stream.front, u.stream.tables, &hand)) {                      // uniform
     __syncthreads();                       // the list is written, and the tables are free
-    code = finish_row<true>(a, b, u.fin, &hint, &hand);
+    if (IDS && hand.greedy) code = finish_greedy(a, b, hand.best);             // uniform
+    else code = finish_row<true>(a, b, u.fin, &hint, &hand);
   }
   if (threadIdx.x == 0) {
     a.row_path[b] = code;
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
 // kernels / one: one row of V = 128256 bf16 18.7 / 18.5, 32 rows with 8000 prompt tokens 25.9 / 25.0, 64 rows 26.7 /
 // 26.3, 31 rows of V = 64712 fp32 29.8 / 28.4, 9 of V = 65536 in pieces 20.7 / 19.8 (Plan::alone has more).  What bounds
 // it: latency, the set-up's chain of 4.5 us and the finishing's of 13.
-template <int DT, bool SH>
+template <int DT, bool SH, bool IDS>
 __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void chunk_rescue_kernel(Args a_by_value) {
   (void)a_by_value;
   const Args& a = *(const Args*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -123,15 +124,26 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
   unsigned char* const front = reinterpret_cast<unsigned char*>(u.stream);
   RowHand hand;
   RowWord word{reinterpret_cast<unsigned long long*>(a.rowinfo + b), 0ull};
-  stream_part<DT, SH, false, true, true>(a, wg, front,
-      *reinterpret_cast<StreamTables<DT, false>*>(front + stream_front_bytes<DT, false>(a.cap_c / kStreamWaves)), &hand, &word);
+  stream_part<DT, SH, false, IDS, true>(a, wg, front,
+      *reinterpret_cast<StreamTables<DT, false, true>*>(front + stream_front_bytes<DT, false>(a.cap_c / kStreamWaves)), &hand, &word);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                             // every wave's part of the list is written
   __syncthreads();
   if (threadIdx.x == kFinalThreads - kWave) last = word.arrive((uint32_t)a.S);
   __syncthreads();
   if (!last) return;                                                 // uniform
   FinHint hint;
-  const int code = finish_row<false, true>(a, b, u.fin, &hint, &hand);
+  int code;
+  if (IDS && hand.greedy) {                                          // uniform
+    unsigned long long best = 0;
+    for (int i = 0; i < a.S; ++i) {
+      const unsigned long long x = *reinterpret_cast<const unsigned long long*>(a.chunks + (size_t)b * (size_t)a.S + i);
+      best = x > best ? x : best;
+    }
+    __syncthreads();                       // (finish_greedy() may write there)
+    code = finish_greedy(a, b, best);
+  } else {
+    code = finish_row<false, true>(a, b, u.fin, &hint, &hand);
+  }
   if (threadIdx.x == 0) {
     a.row_path[b] = code;
     a.row_why[b] = code == kFinWholeRow ? 1 : code;

@@ -35,7 +35,8 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
   int code = 2;
   if (stream_part<DT, SH, true, IDS>(a, b, u.stream.front, u.stream.tables, &hand)) {                      // uniform
     __syncthreads();                       // the list is written, and the tables are free
-    code = finish_row<true>(a, b, u.fin, nullptr, &hand);
+    if (IDS && hand.greedy) code = finish_greedy(a, b, hand.best);             // uniform
+    else code = finish_row<true>(a, b, u.fin, nullptr, &hand);
   }
   if (threadIdx.x == 0) {
     a.row_path[b] = code;

@@ -39,6 +39,7 @@ constexpr int kSampleSize = 8192;           // elements of a row the threshold i
 constexpr int kQueueCap = 480;              // entries of one wave's LDS candidate queue where four workgroups share a compute unit
 constexpr int kChunkCap = kStreamWaves * kQueueCap;   // entries of such a chunk's segment in the workspace
 constexpr int kChunkBitsMax = 73728;        // most elements a chunk may have (history bitmap: 9 KB of LDS)
+constexpr int kAloneBitsMax = 131072;       // one that has a compute unit to itself (16 KB)
 constexpr int kRowBitsMax = 262144;         // and a row that one workgroup streams (32 KB)
 // What differs between a workgroup that streams one chunk of a row for the finishing kernel (ROW =
 // false: four workgroups per compute unit, 40 KB of LDS and 64 registers each) and one that streams the
@@ -52,11 +53,11 @@ struct StreamShape {
   typedef typename std::conditional<DT == SIP_F32, uint2, uint32_t>::type entry_t;      // of a queue, see `process`
   static constexpr int kQueue = DT == SIP_F32 ? 704 : 1280;             // ROW: entries of one wave's queue (chunks: an eighth of Args::cap_c)
   static constexpr int kTags = 1 << EPL;                               // history bits of one load
-  static constexpr int kBits = ROW ? kRowBitsMax : kChunkBitsMax;      // most elements a workgroup streams
+  static constexpr int kBits = ROW ? kRowBitsMax : ALONE ? kAloneBitsMax : kChunkBitsMax;      // most elements a workgroup streams
   static constexpr int kBlocks = kBits / kBlkElems;
   static constexpr int kHistRegs = ROW || ALONE ? 8 : 4;                         // history tokens a thread requests with the sample
   // Load numbers of p whole pieces, each rounded up to tiles: they have kLoadBits in a bf16 queue entry.
-  static constexpr int kLoadBits = ROW ? 7 : 5;
+  static constexpr int kLoadBits = ROW ? 7 : ALONE ? 6 : 5;
   static constexpr int load_numbers(int p) { return p * kLoads * ((kBits / p + kTile - 1) / kTile); }
   static constexpr int most_load_numbers(int p) {
     return p == 0 ? 0 : load_numbers(p) > most_load_numbers(p - 1) ? load_numbers(p) : most_load_numbers(p - 1);
@@ -304,9 +305,9 @@ __device__ __forceinline__ uint32_t raised_group(const uint32_t G, const uint32_
 // place, the per-wave candidate queues (a chunk's: fp32 30 KB, bf16 15 KB, up to four times
 // that where fewer than four share a compute unit; a row's: 44 or 40 KB); then the history
 // bitmap (9 or 32 KB) and the tag words (fp32 256 bytes, bf16 4 KB).
-template <int DT, bool ROW>
+template <int DT, bool ROW, bool ALONE = false>
 struct __align__(16) StreamTables {
-  typedef StreamShape<DT, ROW> Sh;
+  typedef StreamShape<DT, ROW, ALONE> Sh;
   uint32_t bmw[Sh::kBits / 32];            // (first: a queue that overflows may write up to 4 KB past the last wave's end)
   uint4 tag_words[Sh::kTags];              // history bits of a load -> what is or-ed into its four words
   unsigned long long blk_mass[Sh::kBlocks];
@@ -344,15 +345,17 @@ struct RowHand {
   RowInfo ri;
   ChunkOut co;
   uint32_t longest;                        // entries of the longest queue
+  bool greedy = false;                     // the arg max is all that is asked for, and `best` is it (the chunk's)
+  unsigned long long best;                 // key of the value, complement of the vocabulary id: the larger the better
   bool direct;                             // the queues went to registers, lane l's entry r being entry 64 * r + l of its wave's
   uint2 list[kRowRegs];                    // (per thread)
 };
 
 // Streams chunk wg % S of row wg / S (ROW: row wg).  False: the row cannot be finished from a list.  `front` and
-// `sm`: LDS, one behind the other.  IDS: a call that may ask for token ids only (a kernel of its own, see `masses`).
+// `sm`: LDS, one behind the other.  IDS: a call that asks for token ids only (a kernel of its own, see `masses`).
 // ALONE: `hand` gets the row's record, whose place has the row's word (opened here by the last wave's first thread).
 template <int DT, bool SH, bool ROW, bool IDS = false, bool ALONE = false>
-__device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigned char* const front, StreamTables<DT, ROW>& sm,
+__device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigned char* const front, StreamTables<DT, ROW, ALONE>& sm,
                                             RowHand* hand, RowWord* word = nullptr) {
   typedef StreamShape<DT, ROW, ALONE> Sh;
   typedef typename Sh::entry_t entry_t;
@@ -473,6 +476,80 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
     }
     if (!ROW && !ALONE && ch == 0 && tid == 0) a.rowinfo[b].target = 0;                // the finishing kernel looks at nothing else
     return false;
+  }
+  // ---- A greedy row without penalties of which only the id is asked for: no threshold, no list.  Every thread keeps
+  // the largest of its values, the load that has the first of them and that load's place.  What bounds it: the memory.
+  // us a call, by way of a list / so: one row of V = 128256 bf16 11.9 / 7.9, 64 rows fp32 15.5 / 9.7, 128 rows of V = 152064 bf16
+  // 17.7 / 11.0, 256 rows 22.9 / 14.4, 1024 rows of V = 129280 62.5 / 49.4.
+  if constexpr ((ROW || ALONE) && IDS) {
+    hand->greedy = rp.greedy &&
+                   ((rp.theta == 1.0f && rp.phi == 0.0f && rp.psi == 0.0f) || !(a.slot || csr_on || prompt_csr));
+    if (hand->greedy) {                              // uniform
+      if (ALONE && tid == kStreamThreads - kWave) word->open(a.call_mark);
+      float top = -INFINITY;
+      uint4 top_q = make_uint4(0, 0, 0, 0);
+      uint32_t top_v = 0;                            // vocabulary id of the load's first element
+      auto look = [&](const uint4& q, uint32_t v, int left) {                  // `left`: elements inside the piece
+        float z[EPL];
+        unpack(q, z);
+        if (left < EPL) {
+#pragma unroll
+          for (int i = 0; i < EPL; ++i) z[i] = i < left ? z[i] : -INFINITY;
+        }
+        float x = z[0];
+#pragma unroll
+        for (int i = 1; i < EPL; ++i) x = z[i] > x ? z[i] : x;
+        if (x > top) { top = x; top_q = q; top_v = v; }
+      };
+      for (int pc = 0; pc < np; ++pc) {
+        if (SH) row = shard_base(a, sh + pc) + (size_t)b * (size_t)a.shard_stride * ESZ;
+        const uint32_t v0 = ibase + (uint32_t)(SH ? pc * Vl : 0);
+        uint4 now[2][NL];
+        load_tile(c0, now[0]);
+        load_tile(c0 + TILE, now[1]);
+        auto turn = [&](const uint4 (&q)[NL], int t0) {
+          if (t0 + TILE <= c1) {                     // uniform
+#pragma unroll
+            for (int j = 0; j < NL; ++j) look(q[j], v0 + (uint32_t)(t0 + j * SUB + tid * EPL), EPL);
+          } else {
+#pragma unroll
+            for (int j = 0; j < NL; ++j) {
+              const int e0 = t0 + j * SUB + tid * EPL;
+              if (e0 < c1) look(q[j], v0 + (uint32_t)e0, c1 - e0);
+            }
+          }
+        };
+        for (int t0 = c0;;) {
+          turn(now[0], t0);
+          load_tile(t0 + 2 * TILE, now[0]);
+          if ((t0 += TILE) >= c1) break;
+          turn(now[1], t0);
+          load_tile(t0 + 2 * TILE, now[1]);
+          if ((t0 += TILE) >= c1) break;
+        }
+      }
+      uint32_t at = 0;
+      {
+        float z[EPL];
+        unpack(top_q, z);
+#pragma unroll
+        for (int i = EPL - 1; i >= 0; --i) at = z[i] == top ? (uint32_t)i : at;
+      }
+      // (nothing above -inf: 0)
+      unsigned long long mine = top > -INFINITY ? (unsigned long long)key_of(top) << 32 | (uint32_t)~(top_v + at) : 0ull;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long other = __shfl_xor(mine, o, kWave);
+        mine = other > mine ? other : mine;
+      }
+      if (lane == 0) sm.red64[wave] = mine;
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < kStreamWaves; ++w) mine = sm.red64[w] > mine ? sm.red64[w] : mine;
+      hand->best = mine;
+      if (ALONE && tid == 0) put<ALONE>(reinterpret_cast<unsigned long long*>(a.chunks + wg), mine);
+      return true;
+    }
   }
   // ---- threshold: the same 8192-element sample (1 KB blocks spread evenly over the row) is
   // read by every chunk of the row, so all chunks agree on Tc = the lower end of the bin of the j-th
