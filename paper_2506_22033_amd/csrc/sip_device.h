@@ -409,6 +409,14 @@ __device__ __forceinline__ float penalise_shared(float z, unsigned int count, co
   return count ? x : y;
 }
 
+// A double that is the same for all lanes, in scalar registers.
+__device__ __forceinline__ double uniform_f64(double x) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // ---------------------------------------------------------------- keys
 // Order-preserving map fp32 -> u32 (larger float <=> larger key); -0 and +0 share a key.
 __device__ __forceinline__ uint32_t key_of(float s) {

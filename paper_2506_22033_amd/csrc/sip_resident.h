@@ -71,6 +71,7 @@ struct __align__(16) ResShared {
   float t_minp;
   double ln_z;
   unsigned long long j24;
+  double recip[2];                          // of the temperature and of the repetition penalty
   ExactShared ex;
 };
 
@@ -171,6 +172,10 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
     const unsigned long long u = (unsigned long long)(philox_word0(a.seed, rp.row_id, step_of(a)) >> 8);
     if (lane == 0) { fs.t_minp = t; fs.j24 = u; }
   }
+  if (wave == NW - 2) {
+    const double r = 1.0 / (double)(lane == 0 ? (rp.greedy ? 1.0f : rp.tau) : rp.theta);
+    if (lane < 2) fs.recip[lane] = r;
+  }
   const bool counts = rp.phi != 0.0f;                  // otherwise "occurs" is all that matters
   const bool long_hist = counts && pen.h.hi - pen.h.lo > kResMaxCount;               // uniform
   int code = (pen.any && counts && pen.h.hi - pen.h.lo > (long long)kResFold * kResList) ? 4 : 0;   // uniform, like every `code` below
@@ -232,7 +237,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
   // (parameters that are off take part with the value that changes nothing: no branch per element)
   float s[NPT];
   {
-    const RowDivisor by_theta(rp.theta), by_tau(rp.greedy ? 1.0f : rp.tau);
+    const RowDivisor by_tau(uniform_f64(fs.recip[0])), by_theta(uniform_f64(fs.recip[1]));
     float mx = -INFINITY, mn = INFINITY;
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
