@@ -17,9 +17,11 @@ static_assert(sizeof(FinShared) <= kFusedRawBytes, "the finishing tables lie ins
 
 // rescue_row() for the kernels that hardly ever need it, as a function of its own: inlined, its registers made the part
 // that every row goes through keep 540 to 620 scalar registers in lanes of vector registers, now 2 to 28, and 18 to 37
-// vector registers in scratch, now none.  us a call: one row of V = 128256 bf16 18.2 / 17.9, 64 rows 25.8 / 25.5, 200 rows of V
-// = 152064 bf16 in pieces 33.4 / 32.8, 256 rows fp32 with everything on 50.0 / 49.7.  LDS goes along as offsets, the
-// arguments as an address, so that both are reached by the instructions meant for them.
+// vector registers in scratch, now none.  us a call: one row of V = 128256 bf16 18.2 / 17.9, 64 rows 25.8 / 25.5, 256 rows of
+// V = 152064 fp32 with everything on 50.0 / 49.7.  LDS goes along as offsets, the arguments as an address, so that both are reached by the instructions meant for them.
+// A function has 128 registers: rows that need it are 1 to 2 % slower (20 rows of V = 50000 fp32, a nucleus beyond its list,
+// 69.0 / 70.3).  In pieces, where every row without a filter does, it stays inlined: 50 such rows of V = 60032 bf16 56.6, as a
+// function 63.1.
 template <typename T>
 __device__ __forceinline__ uint32_t lds_offset(T& x) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) T*)&x;
@@ -61,7 +63,8 @@ __global__ __launch_bounds__(kFinalThreads) void finish_rescue_kernel(Args a_by_
   __syncthreads();
   RescueSeen seen;
   if (hint.valid) { seen.why = code; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
-  rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
+  if constexpr (SH) rescue_row<DT, SH>(a, b, u.raw, ex, fsr, seen);
+  else rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
 }
 
 // The same for a workgroup that has streamed its row itself (sip_row.h).
@@ -94,7 +97,8 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
   __syncthreads();
   RescueSeen seen;
   if (hint.valid) { seen.why = code; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
-  rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
+  if constexpr (SH) rescue_row<DT, SH>(a, b, u.raw, ex, fsr, seen);
+  else rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
 }
 
 // The same where the batch is so small that a row's chunks have a compute unit each: the last of a row's workgroups
@@ -152,7 +156,8 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
   __syncthreads();
   RescueSeen seen;
   if (hint.valid) { seen.why = code; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
-  rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
+  if constexpr (SH) rescue_row<DT, SH>(a, b, u.raw, ex, fsr, seen);
+  else rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
 }
 
 }  // namespace sip
