@@ -304,7 +304,7 @@ __device__ __forceinline__ uint32_t raised_group(const uint32_t G, const uint32_
 // LDS: first the sample histogram (two 16-bit counters per word, 16 KB), then, in its
 // place, the per-wave candidate queues (a chunk's: fp32 30 KB, bf16 15 KB, up to four times
 // that where fewer than four share a compute unit; a row's: 44 or 40 KB); then the history
-// bitmap (9 or 32 KB) and the tag words (fp32 256 bytes, bf16 4 KB).
+// bitmap (9, 16 or 32 KB) and the tag words (fp32 256 bytes, bf16 4 KB).
 template <int DT, bool ROW, bool ALONE = false>
 struct __align__(16) StreamTables {
   typedef StreamShape<DT, ROW, ALONE> Sh;
@@ -370,6 +370,12 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
   uint32_t* const hist = reinterpret_cast<uint32_t*>(front);
   const int queue_cap = ROW ? Sh::kQueue : a.cap_c / kStreamWaves;
 
+  // Where several bf16 chunks share a compute unit, the set-up's chain and the queues' way out go ahead of other chunks'
+  // streaming: us a call, without / so, V = 152064, 150 rows 27.9 / 27.2, 300 rows 44.6 / 43.6.  Not for fp32, whose streaming
+  // the memory bounds and which must not stop asking (520 rows of V = 128256 90.0 / 94.9), nor for a row to a workgroup (1024 bf16
+  // rows of V = 129280 88.2 / 89.9, streaming first 88.7; 2048 fp32 rows of V = 256000 502 / 506, 509).
+  constexpr bool CHAIN_FIRST = DT == SIP_BF16 && !ROW && !ALONE;
+  if (CHAIN_FIRST) __builtin_amdgcn_s_setprio(2);
   // (the wave's number, and further down r0, in a scalar register: as vector registers they were
   // spilled, and a store to scratch ahead of the loads makes every wait for one of them a wait for
   // all -- 3 us of the 33 at fp32 V = 152064, 256 rows)
@@ -845,6 +851,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
   ref.Tc = uniform(ref.Tc); ref.c = uniform(ref.c); ref.off = uniform(ref.off);
 
   // ---- stream
+  if (CHAIN_FIRST) __builtin_amdgcn_s_setprio(0);
   entry_t* const queue = reinterpret_cast<entry_t*>(front) + wave * queue_cap;       // this wave's LDS queue
   const unsigned char* bm8 = reinterpret_cast<const unsigned char*>(bmw);
   uint32_t qn = 0;                          // wave-uniform: list entries in the queue
@@ -1048,6 +1055,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
     }
   }
   // ---- the queues go out (ROW = false: only now, all of them), and the chunk's summary
+  if (CHAIN_FIRST) __builtin_amdgcn_s_setprio(2);
   uint32_t n_last = 0;
   if constexpr (ROW) {
     // What is left in the queue also stays in registers, so that finishing need not read it back (it does
