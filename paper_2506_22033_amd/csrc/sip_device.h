@@ -226,6 +226,27 @@ __device__ __forceinline__ const char* shard_base(const Args& a, int sh) {
     if (sh == i) p = a.shard[i];
   return reinterpret_cast<const char*>(p);
 }
+// A pointer into LDS that says so.  The functions that are not inlined take their tables as these: handed plain pointers,
+// they read and write LDS by flat instructions as soon as one of their callers has its own from a number
+// (rescue_apart()), each of which also waits for global memory.  us a call, plain / these, 1024 rows of V = 200000 whose
+// nuclei outgrow their lists 598 / 551 bf16, 715 / 640 fp32.
+template <typename T>
+using lds_ptr = __attribute__((address_space(3))) T*;
+template <typename T>
+__device__ __forceinline__ lds_ptr<T> in_lds(T* x) { return (lds_ptr<T>)x; }
+
+// The same for global memory: a flat load counts as an LDS access too, which the loads of such a function's tables then wait for.
+// One row of V = 200000 fp32 in two pieces, no filter (gather_row(), whole_row_draw()): 101.1 us a call flat, 85.1 so.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint4 load_global(const void* at) {
+  const u32x4 q = *(__attribute__((address_space(1))) const u32x4*)(uintptr_t)at;
+  return make_uint4(q.x, q.y, q.z, q.w);
+}
+__device__ __forceinline__ void store_global(void* at, const uint4& v) {
+  const u32x4 q = {v.x, v.y, v.z, v.w};
+  *(__attribute__((address_space(1))) u32x4*)(uintptr_t)at = q;
+}
+
 // Gather row b of a sharded call into its workspace row (a.logits / a.row_stride describe those
 // rows), for the code paths that walk a whole row.  Called by all threads of the row's workgroup.
 template <int DT>
@@ -242,11 +263,11 @@ __device__ __attribute__((noinline)) void gather_row(const Args& a, int b) {
     for (; i + (N - 1) * blockDim.x < n; i += N * blockDim.x) {
       uint4 q[N];
 #pragma unroll
-      for (int j = 0; j < N; ++j) q[j] = src[i + (uint32_t)j * blockDim.x];
+      for (int j = 0; j < N; ++j) q[j] = load_global(src + i + (uint32_t)j * blockDim.x);
 #pragma unroll
-      for (int j = 0; j < N; ++j) d[i + (uint32_t)j * blockDim.x] = q[j];
+      for (int j = 0; j < N; ++j) store_global(d + i + (uint32_t)j * blockDim.x, q[j]);
     }
-    for (; i < n; i += blockDim.x) d[i] = src[i];
+    for (; i < n; i += blockDim.x) store_global(d + i, load_global(src + i));
   }
   __syncthreads();
 }

@@ -333,7 +333,9 @@ __device__ __forceinline__ T param_or(const T* p, int b, T dflt) { return p ? p[
 // `dyn` is 2 * ceil(V/32) words of LDS.  Not inlined: it is the rarely taken path of the
 // finishing kernel and must not cost that kernel registers or instruction cache.
 template <int DT>
-__device__ __attribute__((noinline)) void exact_row(const Args& a, const int b, uint32_t* dyn, ExactShared& sh) {
+__device__ __attribute__((noinline)) void exact_row(const Args& a, const int b, lds_ptr<uint32_t> dyn_lds, lds_ptr<ExactShared> sh_lds) {
+  uint32_t* const dyn = (uint32_t*)dyn_lds;
+  ExactShared& sh = *(ExactShared*)sh_lds;
   const int tid = threadIdx.x;
   const int V = a.V;
   const int W = (V + 31) >> 5;
@@ -547,7 +549,7 @@ __global__ __launch_bounds__(kExactThreads) void exact_kernel(Args a) {
   extern __shared__ uint32_t dyn[];
   __shared__ ExactShared sh;
   if (SH) gather_row<DT>(a, blockIdx.x);                  // sharded logits: the row is put together first
-  exact_row<DT>(a, blockIdx.x, dyn, sh);
+  exact_row<DT>(a, blockIdx.x, in_lds(dyn), in_lds(&sh));
   if (threadIdx.x == 0) { a.row_path[blockIdx.x] = 14; a.row_why[blockIdx.x] = 14; }   // 14: shape outside the single-pass kernels
   if (a.slot) {                                          // device-resident history: the row's id joins it
     __syncthreads();

@@ -809,7 +809,9 @@ __device__ __forceinline__ int fast_row(const Args& a, const int b, const RowPar
 // bitmap that the first attempt left in LDS: tokens in it stay out of the bulk mass.
 template <int DT>
 __device__ __attribute__((noinline)) void restream_row(const Args& a, const int b, const RowParams rp, const float Tc,
-                                                       FastShared& fs, const uint32_t* bm) {
+                                                       lds_ptr<FastShared> fs_lds, lds_ptr<const uint32_t> bm_lds) {
+  FastShared& fs = *(FastShared*)fs_lds;
+  const uint32_t* const bm = (const uint32_t*)bm_lds;
   constexpr int NT = kFinalThreads;
   constexpr int EPL = (DT == SIP_F32) ? 4 : 8;
   constexpr int ESZ = (DT == SIP_F32) ? 4 : 2;
@@ -884,8 +886,8 @@ __device__ __attribute__((noinline)) void restream_row(const Args& a, const int 
 
 // Rarely needed continuations, defined after the kernel (see there).
 template <int DT>
-__device__ int whole_row_finish(const Args& a, const int b, const RowParams rp, unsigned char* dyn, FastShared& fs,
-                                const bool cut);
+__device__ int whole_row_finish(const Args& a, const int b, const RowParams rp, lds_ptr<unsigned char> dyn_lds,
+                                lds_ptr<FastShared> fs_lds, const bool cut);
 
 // Runs the smallest instantiation of fast_row that can hold the row: the history length bounds
 // the number of distinct tokens; a variant that turns out too small says so early and the next
@@ -948,10 +950,11 @@ __device__ __forceinline__ void rescue_row(const Args& a, const int b, unsigned 
       if (hint >= 0 && hint < ndist_ub) ndist_ub = hint;
     }
     if (threadIdx.x == 0) fs.ndist_out = -1;
-    // At most two attempts, written as a loop so that the kernel holds one copy of the code.
+    // At most two attempts, and a look at the first list again, written as a loop so that the kernel holds one copy
+    // of the code.
     int S = a.one_seg ? 1 : a.S, cap_c = a.one_seg ? a.S * a.cap_c : a.cap_c;
 #pragma nounroll
-    for (int attempt = 0; attempt < 2; ++attempt) {
+    for (int attempt = 0; attempt < 3; ++attempt) {
       int r;
       bool cut_below = false;
       const bool skipped = attempt == 0 && (seen.why == 12 || (seen.why == 11 && rp.min_p > 0.0f));
@@ -972,6 +975,7 @@ __device__ __forceinline__ void rescue_row(const Args& a, const int b, unsigned 
         __syncthreads();
         if (fs.second_list_out) { r = 11; cut_below = true; }
       }
+      if (attempt == 2) { how = r; break; }
       if (attempt == 1) {
         const bool fine = r == 1 || r == kWholeRowCut || r == kWholeRow;
         how = fine ? r : 16 + r;                 // 17..29: failed again after the retry
@@ -996,7 +1000,7 @@ __device__ __forceinline__ void rescue_row(const Args& a, const int b, unsigned 
       const PenaltyPlan pen1 = penalty_plan(a, b, rp.theta, rp.phi, rp.psi);
       const uint32_t* bm1 = pen1.any ? reinterpret_cast<const uint32_t*>(dynraw) : nullptr;
       if (skipped && pen1.any) history_bitmap(a, b, pen1, reinterpret_cast<uint32_t*>(dynraw));   // (else the first attempt left it there)
-      restream_row<DT>(a, b, rp, t_new, fs, bm1);
+      restream_row<DT>(a, b, rp, t_new, in_lds(&fs), in_lds(bm1));
       S = 1; cap_c = a.S * a.cap_c;
       if (cut_below && fs.rq_n > (uint32_t)min(kFinalThreads * kCandLong, a.S * a.cap_c)) {
         // The second list does not fit either: the cut is settled over the whole row, from the
@@ -1004,24 +1008,22 @@ __device__ __forceinline__ void rescue_row(const Args& a, const int b, unsigned 
         // attempt was skipped: then the first list is made again (the second one lies where it
         // was) and looked at now.
         how = kWholeRowCut;
-        if (skipped) {
-          restream_row<DT>(a, b, rp, t_old, fs, bm1);
-          how = fast_any<DT, SH>(a, b, rp, dynraw, fs, S, cap_c, ndist_ub);
-        }
-        break;
+        if (!skipped) break;
+        restream_row<DT>(a, b, rp, t_old, in_lds(&fs), in_lds(bm1));
+        attempt = 1;
       }
     }
   }
   if (how == kWholeRowCut || how == kWholeRow) {
     // rows that are finished over the whole row: nucleus cut below the list, or no filter at all
     if (SH && !gathered) { gather_row<DT>(a, b); gathered = true; }
-    how = whole_row_finish<DT>(a, b, rp, dynraw, fs, how == kWholeRowCut);
+    how = whole_row_finish<DT>(a, b, rp, in_lds(dynraw), in_lds(&fs), how == kWholeRowCut);
     code = how == 1 ? 16 : 0;                    // 16: finished over the whole row by this workgroup
   }
   if (how != 1) {
     __syncthreads();
     if (SH && !gathered) { gather_row<DT>(a, b); gathered = true; }
-    exact_row<DT>(a, b, reinterpret_cast<uint32_t*>(dynraw), ex);
+    exact_row<DT>(a, b, in_lds(reinterpret_cast<uint32_t*>(dynraw)), in_lds(&ex));
   }
   if (threadIdx.x == 0) a.row_path[b] = code ? code : how;
   if (a.slot) {                                  // device-resident history: the row's id joins it
@@ -1086,6 +1088,24 @@ __global__ __launch_bounds__(kFinalThreads) void rescue_kernel(Args a_by_value) 
   }
 }
 
+// Where fast_row() leaves its tables in LDS, for what continues over the whole row.
+struct WholeRowTables {
+  const uint32_t* bm;                       // the row's history, one bit per token
+  const unsigned short* pre;                // history tokens ahead of a word of it
+  unsigned long long *hm, *hd;              // kBins each
+  uint32_t* hc;                             // kBins
+  const uint32_t* cnt;                      // keys of the history tokens' values, in the order of their ids
+  __device__ __forceinline__ WholeRowTables(unsigned char* dyn, const int V) {
+    const int W = (V + 31) >> 5;
+    bm = reinterpret_cast<const uint32_t*>(dyn);
+    pre = reinterpret_cast<const unsigned short*>(dyn + (size_t)W * 4);
+    hm = reinterpret_cast<unsigned long long*>(dyn + (((size_t)W * 6 + 15) / 16) * 16);
+    hd = hm + kBins;
+    hc = reinterpret_cast<uint32_t*>(hd + kBins);
+    cnt = hc + kBins;
+  }
+};
+
 // Draw over the whole row, for a row without any filter (plain temperature sampling).  Maximum,
 // total mass and best-n came from the list; the draw itself needs every element's mass in
 // vocabulary order, so the row is read once more here (it is still in the last-level cache),
@@ -1094,18 +1114,21 @@ __global__ __launch_bounds__(kFinalThreads) void rescue_kernel(Args a_by_value) 
 // token and its key in fs; returns 1, or 13 if there is no mass to draw from.
 template <int DT>
 __device__ __attribute__((noinline)) int whole_row_draw(const char* row, const int V, const bool has_pen,
-                                                        const uint32_t* bm, const unsigned short* pre,
-                                                        const uint32_t* cnt, unsigned long long* hd, FastShared& fs,
+                                                        lds_ptr<unsigned char> dyn_lds, lds_ptr<FastShared> fs_lds,
                                                         const float tau, const bool greedy, const float m,
                                                         const float zmax, const float c_row,
                                                         const unsigned long long j24) {
+  const WholeRowTables tables((unsigned char*)dyn_lds, V);
+  const uint32_t* const bm = tables.bm; const unsigned short* const pre = tables.pre; const uint32_t* const cnt = tables.cnt;
+  unsigned long long* const hd = tables.hd;
+  FastShared& fs = *(FastShared*)fs_lds;
   const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   auto scaled_s = [&](float z) { return greedy ? z : __fdiv_rn(z, tau); };
   constexpr int EPL = (DT == SIP_F32) ? 4 : 8;
   constexpr int ESZ = (DT == SIP_F32) ? 4 : 2;
   const int e_last = ((V - 1) / EPL) * EPL;
   auto ldrow = [&](int e0) {                            // clamped: always a valid address
-    return *reinterpret_cast<const uint4*>(row + (size_t)min(e0, e_last) * ESZ);
+    return load_global(row + (size_t)min(e0, e_last) * ESZ);
   };
   // Masses as fp32, relative to the maximum; a lane adds those of one 16-byte load in a fixed
   // order and only the sum becomes an integer (units of 2^-40), so that both reads of the row
@@ -1261,11 +1284,13 @@ __device__ __attribute__((noinline)) int whole_row_draw(const char* row, const i
 // the reads take two loads of eight elements at a time instead of four and nothing is spilled.
 template <int DT>
 __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, const int V, const bool has_pen,
-                                                           const uint32_t* bm, const unsigned short* pre,
-                                                           const uint32_t* cnt, unsigned long long* hm,
-                                                           unsigned long long* hd, FastShared& fs, const double inv_tau,
-                                                           const float m, const unsigned long long limit,
+                                                           lds_ptr<unsigned char> dyn_lds, lds_ptr<FastShared> fs_lds,
+                                                           const double inv_tau, const float m, const unsigned long long limit,
                                                            const unsigned long long j24, const bool minp_on, const float t_minp) {
+  const WholeRowTables tables((unsigned char*)dyn_lds, V);
+  const uint32_t* const bm = tables.bm; const unsigned short* const pre = tables.pre; const uint32_t* const cnt = tables.cnt;
+  unsigned long long* const hm = tables.hm; unsigned long long* const hd = tables.hd;
+  FastShared& fs = *(FastShared*)fs_lds;
   const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   constexpr int NT = kFinalThreads;
   constexpr int EPL = (DT == SIP_F32) ? 4 : 8;
@@ -1551,9 +1576,8 @@ __device__ __attribute__((noinline)) int whole_row_nucleus(const char* row, cons
 // fp32, 1883 rows, 471 flat 752 -> 497.
 template <int DT>
 __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, const int V_any, const bool has_pen_any,
-                                                          const uint32_t* bm, const unsigned short* pre, const uint32_t* cnt,
-                                                          unsigned long long* hm, unsigned long long* hd, uint32_t* hc,
-                                                          FastShared& fs, uint2* region_any, const uint32_t cap_any, const double inv_tau,
+                                                          lds_ptr<unsigned char> dyn_lds, lds_ptr<FastShared> fs_lds,
+                                                          uint2* region_any, const uint32_t cap_any, const double inv_tau,
                                                           const float m, const unsigned long long limit, const float top_p,
                                                           const unsigned long long j24) {
   const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(wave_id());
@@ -1576,13 +1600,17 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
            (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
   };
   const int V = __builtin_amdgcn_readfirstlane(V_any);
+  const WholeRowTables tables((unsigned char*)dyn_lds, V);
+  const uint32_t* const bm = tables.bm; const unsigned short* const pre = tables.pre; const uint32_t* const cnt = tables.cnt;
+  unsigned long long* const hm = tables.hm; unsigned long long* const hd = tables.hd;
+  uint32_t* const hc = tables.hc;
+  FastShared& fs = *(FastShared*)fs_lds;
   const bool has_pen = __builtin_amdgcn_readfirstlane(has_pen_any ? 1 : 0) != 0;
   const uint32_t cap = (uint32_t)__builtin_amdgcn_readfirstlane((int)cap_any);
   global_char* const row = (global_char*)uniform_at(row_any);
   global_u64* const region = (global_u64*)uniform_at(region_any);             // key of s | element << 32
   const RowDivisor by_tau(inv_tau);
   const int e_last = ((V - 1) / EPL) * EPL;
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(1))) const u32x4 global_x4;
   auto ldrow = [&](int e0) {
     const u32x4 q = *(global_x4*)(row + (uint32_t)min(e0, e_last) * (uint32_t)ESZ);
@@ -1997,16 +2025,9 @@ __device__ __attribute__((noinline)) int whole_row_window(const char* row_any, c
 // The best-n list is already written.  Returns 1, or a code that sends the row to the exact path.
 template <int DT>
 __device__ __attribute__((noinline)) int whole_row_finish(const Args& a, const int b, const RowParams rp,
-                                                          unsigned char* dyn, FastShared& fs, const bool cut) {
+                                                          lds_ptr<unsigned char> dyn_lds, lds_ptr<FastShared> fs_lds, const bool cut) {
+  FastShared& fs = *(FastShared*)fs_lds;
   const int V = a.V;
-  const int W = (V + 31) >> 5;
-  const uint32_t* bm = reinterpret_cast<const uint32_t*>(dyn);
-  const unsigned short* pre = reinterpret_cast<const unsigned short*>(dyn + (size_t)W * 4);
-  unsigned char* p2 = dyn + (((size_t)W * 6 + 15) / 16) * 16;
-  unsigned long long* hm = reinterpret_cast<unsigned long long*>(p2);
-  unsigned long long* hd = hm + kBins;
-  uint32_t* hc = reinterpret_cast<uint32_t*>(hd + kBins);
-  const uint32_t* cnt = hc + kBins;
   const char* row = reinterpret_cast<const char*>(a.logits) + (size_t)b * (size_t)a.row_stride * (DT == SIP_F32 ? 4 : 2);
   __syncthreads();
   const float m = fs.m_out, zmax = fs.zmax_out;
@@ -2019,12 +2040,12 @@ __device__ __attribute__((noinline)) int whole_row_finish(const Args& a, const i
   if (cut) {
     int r = 0;
     if (!minp_on)
-      r = whole_row_window<DT>(row, V, has_pen, bm, pre, cnt, hm, hd, hc, fs, a.cand + (size_t)b * (size_t)a.S * (size_t)a.cap_c,
+      r = whole_row_window<DT>(row, V, has_pen, dyn_lds, fs_lds, a.cand + (size_t)b * (size_t)a.S * (size_t)a.cap_c,
                                (uint32_t)(a.S * a.cap_c), 1.0 / (double)rp.tau, m, limit, rp.top_p, j24);
-    if (r == 0) r = whole_row_nucleus<DT>(row, V, has_pen, bm, pre, cnt, hm, hd, fs, 1.0 / (double)rp.tau, m, limit, j24,
+    if (r == 0) r = whole_row_nucleus<DT>(row, V, has_pen, dyn_lds, fs_lds, 1.0 / (double)rp.tau, m, limit, j24,
                                         minp_on, t_minp);
     if (r != 1) return r == 11 ? 10 : r;                                      // uniform
-  } else if (whole_row_draw<DT>(row, V, has_pen, bm, pre, cnt, hd, fs, rp.tau, rp.greedy, m, zmax, (float)log2_scale(rp), j24) != 1) {
+  } else if (whole_row_draw<DT>(row, V, has_pen, dyn_lds, fs_lds, rp.tau, rp.greedy, m, zmax, (float)log2_scale(rp), j24) != 1) {
     return 13;                                                                // uniform
   }
   if (threadIdx.x == 0) {

@@ -18,10 +18,14 @@ static_assert(sizeof(FinShared) <= kFusedRawBytes, "the finishing tables lie ins
 // rescue_row() for the kernels that hardly ever need it, as a function of its own: inlined, its registers made the part
 // that every row goes through keep 540 to 620 scalar registers in lanes of vector registers, now 2 to 28, and 18 to 37
 // vector registers in scratch, now none.  us a call: one row of V = 128256 bf16 18.2 / 17.9, 64 rows 25.8 / 25.5, 256 rows of
-// V = 152064 fp32 with everything on 50.0 / 49.7.  LDS goes along as offsets, the arguments as an address, so that both are reached by the instructions meant for them.
-// A function has 128 registers: rows that need it are 1 to 2 % slower (20 rows of V = 50000 fp32, a nucleus beyond its list,
-// 69.0 / 70.3).  In pieces, where every row without a filter does, it stays inlined: 50 such rows of V = 60032 bf16 56.6, as a
-// function 63.1.
+// V = 152064 fp32 with everything on 50.0 / 49.7.  LDS goes along as offsets, the arguments as an address, so that both
+// are reached by the instructions meant for them.
+// Not marked as a tail call, which a call at a kernel's end otherwise is: a function that may be one has to save 108 of
+// the 256 registers it uses, 432 bytes a lane, for nobody.  That frame costs more than its traffic: it sets the distance between
+// the waves' scratch for every kernel of the queue, and at 32 KB (500 bytes a lane) the small frames of others collide in
+// the caches (1024 rows of V = 128256 fp32, ids only, 113 / 117).  us a call, inlined / with the registers saved / so: rows of
+// V = 40000 whose nuclei outgrow their lists 128 fp32 70.2 / 71.9 / 66.1, 256 bf16 69.0 / 78.9 / 67.4; in pieces, inlined / so: 200
+// rows of V = 152064 in four, nucleus, bf16 33.4 / 32.7, no filter 99.0 / 96.8, fp32 137.8 / 120.0.
 template <typename T>
 __device__ __forceinline__ uint32_t lds_offset(T& x) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) T*)&x;
@@ -31,7 +35,7 @@ __device__ __forceinline__ T& at_lds_offset(uint32_t o) {
   return *(T*)(__attribute__((address_space(3))) T*)(uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)o);
 }
 template <int DT, bool SH>
-__device__ __attribute__((noinline)) void rescue_apart(unsigned long long args, int b, uint32_t raw, uint32_t ex, uint32_t fs, int why,
+__device__ __attribute__((noinline, not_tail_called)) void rescue_apart(unsigned long long args, int b, uint32_t raw, uint32_t ex, uint32_t fs, int why,
                                                        float m, float zmax, float T) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)args);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(args >> 32));
@@ -63,8 +67,7 @@ __global__ __launch_bounds__(kFinalThreads) void finish_rescue_kernel(Args a_by_
   __syncthreads();
   RescueSeen seen;
   if (hint.valid) { seen.why = code; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
-  if constexpr (SH) rescue_row<DT, SH>(a, b, u.raw, ex, fsr, seen);
-  else rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
+  rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
 }
 
 // The same for a workgroup that has streamed its row itself (sip_row.h).
@@ -97,8 +100,7 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
   __syncthreads();
   RescueSeen seen;
   if (hint.valid) { seen.why = code; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
-  if constexpr (SH) rescue_row<DT, SH>(a, b, u.raw, ex, fsr, seen);
-  else rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
+  rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
 }
 
 // The same where the batch is so small that a row's chunks have a compute unit each: the last of a row's workgroups
@@ -156,8 +158,7 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
   __syncthreads();
   RescueSeen seen;
   if (hint.valid) { seen.why = code; seen.m = hint.m; seen.zmax = hint.zmax; seen.T = hint.T; }
-  if constexpr (SH) rescue_row<DT, SH>(a, b, u.raw, ex, fsr, seen);
-  else rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
+  rescue_apart<DT, SH>((unsigned long long)&a, b, lds_offset(u.raw[0]), lds_offset(ex), lds_offset(fsr), seen.why, seen.m, seen.zmax, seen.T);
 }
 
 }  // namespace sip

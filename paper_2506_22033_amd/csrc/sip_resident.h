@@ -696,7 +696,7 @@ __global__ __launch_bounds__(NT) void resident_kernel(Args a_by_value) {
   // ---- the general multi-pass path for what the above could not settle
   __syncthreads();
   if (sharded) { if (DT == SIP_F32) gather_row<SIP_F32>(a, b); else gather_row<SIP_BF16>(a, b); }
-  exact_row<DT>(a, b, fs.u.dyn, fs.ex);
+  exact_row<DT>(a, b, in_lds(&fs.u.dyn[0]), in_lds(&fs.ex));
   if (tid == 0) { a.row_path[b] = a.S > 0 ? code : 14; a.row_why[b] = code; }
   if (a.slot) {
     __syncthreads();
