@@ -484,22 +484,13 @@ def main() -> int:
     single_pass_rows = int((path == 1).sum())       # settled by the streaming + finishing kernels alone
     kernels = {}
     if not bool((path == 14).all()):                # the library launched its single-pass kernels
-        # a batch of at most 128 rows is one kernel (chunk_rescue_kernel), one of at most one row per compute unit is finished
-        # by one kernel (finish_rescue_kernel) if not streamed by it as well (row_rescue_kernel);
-        # a larger one by finish_kernel and, behind it, rescue_kernel (include/sip.h, "Kernels of a call")
         cu = torch.cuda.get_device_properties(dev).multi_processor_count
-        one_kernel = w.B <= cu
-        # a row to a workgroup that streams and finishes it: the rule of row_is_chosen() in csrc/sip.hip
-        row_bytes = w.V * esz
-        by_row = w.B >= min(cu * 7 // 8, cu * 3 // 8 + row_bytes // 4096) if one_kernel else \
-            row_bytes <= 200 * 1024 or (w.B >= cu * 25 // 16 if w.B <= 2 * cu else w.B >= cu * 75 // 32)
-        # (rows of up to SIP_MAX_RESIDENT_V entries, in a batch of one kernel: resident_kernel alone)
-        names = (("resident_kernel", (0, 1)),) if w.V <= 32768 and one_kernel else \
-                (("chunk_rescue_kernel", (0, 1)),) if w.B <= 128 else \
-                (("row_rescue_kernel", (0, 1)),) if by_row and one_kernel else \
-                (("row_kernel", (0, 1)), ("rescue_kernel", (4, 5))) if by_row else \
-                (("stream_kernel", (0, 1)), ("finish_rescue_kernel", (2, 3))) if one_kernel else \
-                (("stream_kernel", (0, 1)), ("finish_kernel", (2, 3)), ("rescue_kernel", (4, 5)))
+        route = sip.sip_call_route(w.B, w.V, dt_code, 0, False, d.params, nnz, w.k_logprobs, cu)[0]
+        first, finish, rescue = (0, 1), (2, 3), (4, 5)
+        names = {1: (("resident_kernel", first),), 2: (("chunk_rescue_kernel", first),), 3: (("row_rescue_kernel", first),),
+                 4: (("row_kernel", first), ("rescue_kernel", rescue)),
+                 5: (("stream_kernel", first), ("finish_rescue_kernel", finish)),
+                 6: (("stream_kernel", first), ("finish_kernel", finish), ("rescue_kernel", rescue))}[route]
         for name, (i0, i1) in names:
             kernels[name] = float(np.median([q[i0].elapsed_time(q[i1]) for q in marks[4:]]))
     dominant = max(kernels, key=kernels.get) if kernels else "exact_kernel"

@@ -42,15 +42,35 @@ sip_status sip_probe_read(const void* src, size_t bytes, int32_t workgroups, voi
                           size_t workspace_bytes, void* start_event, void* stop_event, void* hip_stream);
 
 /*
- * Diagnostic, HOST only: into how many chunks (workgroups of the streaming kernel) a row of this
- * shape is cut; t_shards = 0 for logits in one matrix, else V = t_shards * V_shard.  0 = no chunks: rows
- * are held in registers or take the exact multi-pass path, -1 = invalid arguments.  A row's chunks are
- * whole units of 1024 elements, dealt out evenly (to each vocabulary piece, if there are
- * pieces); none is empty.  (Up to SIP_MAX_RESIDENT_V entries a call may not launch them at all, see
- * "Kernels of a call" in sip.h; the workspace holds them either way.  A call with millions of history
- * tokens may cut its rows into fewer where the workspace would else exceed sip_noalloc_scratch_bytes().)
+ * Diagnostic, HOST only: into how many chunks the streaming kernel (stream_kernel) cuts a row of this
+ * shape, in the calls that launch it; t_shards = 0 for logits in one matrix, else V = t_shards * V_shard.
+ * 0 = no chunks: rows are held in registers or take the exact multi-pass path, -1 = invalid arguments.  A
+ * row's chunks are whole units of 1024 elements, dealt out evenly (to each vocabulary piece, if there are
+ * pieces); none is empty.  (sip_call_route() says which calls launch it, and how the others cut a row;
+ * the workspace holds the chunks either way.  A call with millions of history tokens may cut its rows
+ * into fewer where the workspace would else exceed sip_noalloc_scratch_bytes().)
  */
 int32_t sip_plan_chunks(int32_t B, int32_t V, sip_dtype dtype, int32_t t_shards);
+
+/* Kernels of a call ("Kernels of a call" in sip.h), one value for each way. */
+typedef enum sip_route {
+  SIP_ROUTE_EXACT = 0,          /* exact_kernel */
+  SIP_ROUTE_RESIDENT = 1,       /* resident_kernel */
+  SIP_ROUTE_CHUNKS_ALONE = 2,   /* chunk_rescue_kernel */
+  SIP_ROUTE_ROW_FUSED = 3,      /* row_rescue_kernel */
+  SIP_ROUTE_ROW = 4,            /* row_kernel, rescue_kernel */
+  SIP_ROUTE_CHUNKS_FUSED = 5,   /* stream_kernel, finish_rescue_kernel */
+  SIP_ROUTE_CHUNKS = 6          /* stream_kernel, finish_kernel, rescue_kernel */
+} sip_route;
+
+/*
+ * Diagnostic, HOST only: the sip_route of a call with these arguments, or -1 where they are invalid.  on_state: whether it
+ * is on a device-resident state; params: only which of its arrays are there counts, NULL = none; hist_nnz:
+ * history tokens, and prompt tokens, of all rows (on a state slots * L_max); compute_units: of the device, 0 = 256.  *chunks
+ * (unless NULL): how many chunks each row is cut into, 1 where a workgroup has whole rows.
+ */
+int32_t sip_call_route(int32_t B, int32_t V, sip_dtype dtype, int32_t t_shards, int32_t on_state, const sip_params* params,
+                       int64_t hist_nnz, int32_t k_logprobs, int32_t compute_units, int32_t* chunks);
 
 #ifdef __cplusplus
 }

@@ -109,6 +109,10 @@ def load() -> ctypes.CDLL:
         lib.sip_sample_call.argtypes = [ctypes.POINTER(SipCall)]
         lib.sip_plan_chunks.restype = ctypes.c_int32
         lib.sip_plan_chunks.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int, ctypes.c_int32]
+        lib.sip_call_route.restype = ctypes.c_int32
+        lib.sip_call_route.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int, ctypes.c_int32, ctypes.c_int32,
+                                       ctypes.POINTER(SipParams), ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
+                                       ctypes.POINTER(ctypes.c_int32)]
         lib.sip_state_bytes.restype = ctypes.c_size_t
         lib.sip_state_bytes.argtypes = [ctypes.c_int32, ctypes.c_int32]
         lib.sip_state_init.restype = ctypes.c_int
@@ -550,3 +554,19 @@ def sip_sample_call(*, logits: Optional[torch.Tensor] = None, shards=None, V: Op
     if status != SIP_OK:
         raise SipError(status)
     return out_ids, out_lp_ids, out_lp
+
+
+def sip_call_route(B: int, V: int, dtype: int, t_shards: int = 0, on_state: bool = False, params=(), hist_nnz: int = 0,
+                   k_logprobs: int = 0, compute_units: int = 0) -> tuple:
+    """(sip_route, chunks of a row) of a call with these arguments (see include/sip_diag.h).  ``params``: the names of the
+    per-row arrays that are handed in, or a dict of them (entries that are None are not)."""
+    sp = SipParams()
+    for name in params:
+        if not isinstance(params, dict) or params[name] is not None:
+            setattr(sp, name, 16)                        # only which of them are there counts
+    chunks = ctypes.c_int32(0)
+    route = load().sip_call_route(B, V, dtype, t_shards, int(on_state), ctypes.byref(sp), hist_nnz, k_logprobs, compute_units,
+                                  ctypes.byref(chunks))
+    if route < 0:
+        raise ValueError("no call has these arguments")
+    return route, chunks.value

@@ -346,14 +346,14 @@ sip_status launch(const sip::Args& a, int32_t B, int dtype, const Plan& plan, bo
 //   V = 24000, 2048 rows: greedy 77 / 75; no filter 109 / 93; min-p 95 / 99, V = 32000 and 512 tokens
 //   of history 126 / 143, 600 rows of it 56 / 54; top-k and top-p 91 / 151; top-p, peaked 114 / 153.
 //   So: in registers without a filter, min-p alone up to three rounds.
-bool resident_is_chosen(const sip::Args& a, int32_t B, bool state, int compute_units) {
+bool resident_is_chosen(const sip_params& params, int32_t k_lp, int32_t B, bool state, int compute_units) {
   // A state's call would have to take its number in a launch of its own before this kernel (the
   // streaming kernel does it in passing): bf16 V = 28532, 4 rows, hand-off: 56.8 us an iteration
   // against 53.4; V = 28092, 13 rows: 59.3 against 53.7.
   if (state) return false;
-  const bool top = a.p.top_k || a.p.top_p, best = a.k_lp > 0;
-  if (B <= compute_units) return top || a.p.min_p || !best;
-  return !top && !best && (!a.p.min_p || B <= 3 * compute_units);
+  const bool top = params.top_k || params.top_p, best = k_lp > 0;
+  if (B <= compute_units) return top || params.min_p || !best;
+  return !top && !best && (!params.min_p || B <= 3 * compute_units);
 }
 
 // Whether a row's workgroup streams and finishes it (sip_row.h) or the row is streamed in chunks for the
@@ -385,6 +385,24 @@ bool row_is_chosen(int32_t B, int32_t V, int dtype, bool state, int compute_unit
   if (B <= cu) return B > std::min(cu * 3 / 4, cu * 3 / 16 + row_bytes / 2200);
   if (row_bytes <= 200 * 1024) return true;
   return B <= 2 * cu ? B >= cu * 23 / 16 : B >= cu * 75 / 32;
+}
+
+// The kernels of a call, and how its rows are cut where they are cut at all.
+struct Way {
+  sip_route route;
+  const Cut* cut = nullptr;
+};
+// A batch of no more rows than the device has compute units, in chunks or a row to a workgroup: the workgroup that finishes
+// a row also takes it through the heavier logic if the list does not settle it (sip_fused.h).  Larger batches: the lean kernel,
+// two workgroups per compute unit, and a small fixed grid behind it for the rows (normally none) that need more.
+Way choose_way(const Plan& plan, const sip_params& params, int32_t k_lp, int32_t B, int32_t V, int dtype, bool state, int compute_units) {
+  if (V <= kResidentMaxV && (!plan.fast || resident_is_chosen(params, k_lp, B, state, compute_units))) return {SIP_ROUTE_RESIDENT};
+  if (!plan.fast) return {SIP_ROUTE_EXACT};
+  const bool fused = B <= compute_units && (size_t)plan.final_lds <= sip::kFusedRawBytes &&
+                     2 * (((size_t)V + 31) / 32) * sizeof(uint32_t) <= sip::kFusedRawBytes;
+  if (plan.alone.S && fused && !state) return {SIP_ROUTE_CHUNKS_ALONE, &plan.alone};
+  if (row_is_chosen(B, V, dtype, state, compute_units)) return {fused ? SIP_ROUTE_ROW_FUSED : SIP_ROUTE_ROW};
+  return {fused ? SIP_ROUTE_CHUNKS_FUSED : SIP_ROUTE_CHUNKS, &plan.cut};
 }
 
 // Argument checks common to the entry points, workspace carving and the kernel launches.
@@ -475,7 +493,8 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
   hipEvent_t ev[6];
   for (int i = 0; i < 6; ++i) { ev[i] = g_prof[i]; g_prof[i] = nullptr; }
   const bool timed = ev[0] || ev[1] || ev[2] || ev[3] || ev[4] || ev[5];
-  if (a.V <= kResidentMaxV && (!plan.fast || resident_is_chosen(a, B, state, dev->compute_units))) {
+  const Way way = choose_way(plan, a.p, a.k_lp, B, a.V, dtype, state, dev->compute_units);
+  if (way.route == SIP_ROUTE_RESIDENT) {
     // a workgroup holds its whole row in registers: one kernel
     if (state) {
       a.call_tick = tick_room;
@@ -497,7 +516,7 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
     return hipGetLastError() == hipSuccess ? SIP_OK : SIP_ERR_HIP;
   }
   const size_t words = ((size_t)a.V + 31) / 32;
-  if (!plan.fast) {
+  if (way.route == SIP_ROUTE_EXACT) {
     // every row takes the exact multi-pass path
     const size_t dyn = 2 * words * sizeof(uint32_t);
     auto kern = dtype == SIP_F32 ? sip::exact_kernel<SIP_F32, SH> : sip::exact_kernel<SIP_BF16, SH>;
@@ -516,16 +535,11 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
   auto k_rescue = dtype == SIP_F32 ? sip::rescue_kernel<SIP_F32, SH> : sip::rescue_kernel<SIP_BF16, SH>;
   const size_t dyn = std::max(plan.final_lds, 2 * words * sizeof(uint32_t));
   // A row streamed and finished by one workgroup, or the pass over the logits in chunks, then one
-  // workgroup per row on what it left.  A batch of no more rows than the device has compute units: the
-  // workgroup also takes its row through the heavier logic if the list does not settle it
-  // (sip_fused.h).  Larger batches: the lean kernel, two workgroups per compute unit, and a small fixed
-  // grid behind it for the rows (normally none) that need more.
-  const bool fused = B <= dev->compute_units && (size_t)plan.final_lds <= sip::kFusedRawBytes &&
-                     2 * words * sizeof(uint32_t) <= sip::kFusedRawBytes;
-  if (plan.alone.S && fused && !state) {
+  // workgroup per row on what it left.
+  if (way.route == SIP_ROUTE_CHUNKS_ALONE) {
     // a compute unit for every chunk: streaming, finishing and the heavier logic in one kernel
     a.call_mark = new_call_mark();
-    set_cut(a, plan.alone);
+    set_cut(a, *way.cut);
     auto k_alone = dtype == SIP_F32 ? (ids ? sip::chunk_rescue_kernel<SIP_F32, SH, true> : sip::chunk_rescue_kernel<SIP_F32, SH, false>)
                                     : (ids ? sip::chunk_rescue_kernel<SIP_BF16, SH, true> : sip::chunk_rescue_kernel<SIP_BF16, SH, false>);
     if (timed) {
@@ -537,13 +551,13 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
     }
     return hipGetLastError() == hipSuccess ? SIP_OK : SIP_ERR_HIP;
   }
-  a.one_seg = row_is_chosen(B, a.V, dtype, state, dev->compute_units);
+  a.one_seg = way.route == SIP_ROUTE_ROW_FUSED || way.route == SIP_ROUTE_ROW;
   if (a.one_seg) {
     // the row's workgroup streams and finishes it, and the rescue kernel is behind it
     a.S = plan.room; a.cap_c = sip::kChunkCap;       // (one segment of them all)
     a.nc_cap = std::min(sip::kFinalThreads * sip::kCandLong, a.S * a.cap_c);
     if (state) hipLaunchKernelGGL(sip::state_take_tick_kernel, dim3(1), dim3(64), 0, stream, head, a.call_tick);
-    if (fused) {
+    if (way.route == SIP_ROUTE_ROW_FUSED) {
       auto k_both = dtype == SIP_F32 ? (ids ? sip::row_rescue_kernel<SIP_F32, SH, true> : sip::row_rescue_kernel<SIP_F32, SH, false>)
                                      : (ids ? sip::row_rescue_kernel<SIP_BF16, SH, true> : sip::row_rescue_kernel<SIP_BF16, SH, false>);
       if (timed) {
@@ -573,7 +587,7 @@ sip_status launch(const sip::Args& a_in, int32_t B, int dtype, const Plan& plan,
                                                         : sip::stream_lds_bytes<SIP_BF16>(a.cap_c / sip::kStreamWaves));
   if (timed) hipExtLaunchKernelGGL(k_stream, dim3(B * a.S), dim3(sip::kStreamThreads), stream_lds, stream, ev[0], ev[1], 0, a);
   else hipLaunchKernelGGL(k_stream, dim3(B * a.S), dim3(sip::kStreamThreads), stream_lds, stream, a);
-  if (fused) {
+  if (way.route == SIP_ROUTE_CHUNKS_FUSED) {
     auto k_fused = dtype == SIP_F32 ? sip::finish_rescue_kernel<SIP_F32, SH> : sip::finish_rescue_kernel<SIP_BF16, SH>;
     if (timed) {             // the events take the dispatches' own begin / end time stamps
       hipExtLaunchKernelGGL(k_fused, dim3(B), dim3(sip::kFinalThreads), 0, stream, ev[2], ev[3], 0, a);
@@ -818,6 +832,17 @@ int32_t sip_plan_chunks(int32_t B, int32_t V, sip_dtype dtype, int32_t t_shards)
   if (t_shards > 0 && V % t_shards != 0) return -1;
   const Plan p = make_plan(B, V, (int)dtype, t_shards);
   return p.fast ? p.cut.S : 0;
+}
+
+int32_t sip_call_route(int32_t B, int32_t V, sip_dtype dtype, int32_t t_shards, int32_t on_state, const sip_params* params,
+                       int64_t hist_nnz, int32_t k_logprobs, int32_t compute_units, int32_t* chunks) {
+  if (!shape_ok(B, V, (int)dtype, hist_nnz, k_logprobs) || B > SIP_MAX_B || V > SIP_MAX_V || k_logprobs > SIP_MAX_K_LOGPROBS) return -1;
+  if (t_shards < 0 || t_shards > SIP_MAX_SHARDS || (t_shards > 0 && V % t_shards != 0) || compute_units < 0) return -1;
+  const size_t gather = t_shards ? (size_t)V * (dtype == SIP_F32 ? 4 : 2) : 0;
+  const Plan p = plan_for(B, V, (int)dtype, t_shards, hist_nnz, gather);
+  const Way way = choose_way(p, params ? *params : sip_params{}, k_logprobs, B, V, (int)dtype, on_state != 0, compute_units ? compute_units : 256);
+  if (chunks) *chunks = way.cut ? way.cut->S : 1;
+  return way.route;
 }
 
 const char* sip_status_string(sip_status status) {

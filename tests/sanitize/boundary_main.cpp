@@ -38,6 +38,9 @@ int main() {
           (void)sip_workspace_bytes_sharded(B, V, t, (sip_dtype)dt, 1000, 5);
           const int32_t S = sip_plan_chunks(B, V, (sip_dtype)dt, t);
           EXPECT(S >= -1 && S <= 16);
+          int32_t chunks = 0;
+          const int32_t route = sip_call_route(B, V, (sip_dtype)dt, t, t & 1, nullptr, 1000, t - 1, 0, &chunks);
+          EXPECT(route == -1 || (route <= 6 && chunks >= 1 && chunks <= 16));
         }
       }
   for (int32_t slots : {-1, 0, 1, 256, 1 << 20, INT32_MAX})

@@ -304,6 +304,55 @@ def test_every_chunk_of_every_plan_is_non_empty():
     assert lib.sip_plan_chunks(4, 20000, sip.SIP_F32, 9) == -1
 
 
+ROUTE_RESIDENT, ROUTE_CHUNKS_ALONE, ROUTE_CHUNKS_FUSED, ROUTE_CHUNKS = 1, 2, 5, 6
+
+
+@pytest.mark.parametrize("on_state,params,k", [(False, ("temperature", "top_p"), 0), (False, ("temperature",), -1), (True, (), 1)])
+def test_no_call_cuts_a_row_into_empty_chunks(on_state, params, k):
+    """As above, over the cuts that calls take: with a compute unit to each chunk, and on a state."""
+    seen = dict.fromkeys((ROUTE_CHUNKS_ALONE, ROUTE_CHUNKS_FUSED, ROUTE_CHUNKS), 0)
+    for dtype in (sip.SIP_F32, sip.SIP_BF16):
+        for t in range(9):
+            for V_piece in (8192, 8200, 9000, 16032, 19008, 32768, 43000, 66560, 131072, 262144):
+                V = V_piece * max(t, 1)
+                if V > 262144:
+                    continue
+                for B in (1, 2, 3, 5, 8, 13, 16, 21, 29, 32, 37, 43, 64, 65, 85, 86, 100, 127, 128, 129, 200, 300):
+                    route, S = sip.sip_call_route(B, V, dtype, t, on_state, params, 0, k)
+                    if route not in seen:
+                        assert S == 1
+                        continue
+                    seen[route] += 1
+                    if route != ROUTE_CHUNKS_ALONE:
+                        assert S == sip.load().sip_plan_chunks(B, V, dtype, t)
+                    pieces = max(t, 1)
+                    most = 131072 if route == ROUTE_CHUNKS_ALONE else 73728       # elements that a chunk's bitmap holds
+                    if S >= pieces:
+                        assert S % pieces == 0
+                        edges = [_chunk_begin(i, V_piece, S // pieces, 1024) for i in range(S // pieces + 1)]
+                        assert edges[-1] == V_piece and all(0 < b - a <= most for a, b in zip(edges, edges[1:])), (B, V, dtype, t, S)
+                    else:
+                        assert pieces % S == 0 and pieces // S * V_piece <= most
+                    if route == ROUTE_CHUNKS_ALONE:
+                        assert S >= 2 and B * S <= 256 and not on_state
+    assert seen[ROUTE_CHUNKS_FUSED] > 50 and seen[ROUTE_CHUNKS] > 50 and (seen[ROUTE_CHUNKS_ALONE] > 50) == (not on_state)
+
+
+@pytest.mark.parametrize("B,V,dtype,state,k,route", [
+    (1, 128256, sip.SIP_BF16, False, 0, 2), (64, 4096, sip.SIP_F32, False, 0, 1), (64, 32768, sip.SIP_F32, False, 0, 1),
+    (64, 300000, sip.SIP_F32, False, 0, 0), (150, 128256, sip.SIP_BF16, False, 1, 5), (200, 152064, sip.SIP_F32, False, 1, 3),
+    (256, 152064, sip.SIP_F32, False, 20, 3), (64, 128256, sip.SIP_BF16, True, 0, 5), (300, 152064, sip.SIP_F32, False, 0, 6),
+    (1024, 129280, sip.SIP_BF16, False, 20, 4), (600, 152064, sip.SIP_BF16, True, 0, 6)])
+def test_kernels_of_a_call(B, V, dtype, state, k, route):
+    assert sip.sip_call_route(B, V, dtype, 0, state, ("temperature", "top_p"), 0, k)[0] == route
+
+
+def test_route_of_no_call():
+    for bad in (dict(B=0), dict(V=0), dict(dtype=3), dict(t_shards=9), dict(V=20001, t_shards=2), dict(k_logprobs=-2), dict(hist_nnz=-1)):
+        with pytest.raises(ValueError):
+            sip.sip_call_route(**{**dict(B=4, V=20000, dtype=sip.SIP_F32), **bad})
+
+
 def test_binding_refuses_host_tensors():
     import torch
     with pytest.raises(TypeError):
