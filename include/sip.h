@@ -111,14 +111,16 @@ typedef struct {
  * 16384 (on a state behind state_take_tick_kernel), and, without a state, up to SIP_MAX_RESIDENT_V
  * for batches of no more rows than the device has compute units, unless nothing but best-n is asked
  * for; for larger batches only if params names no top_k, top_p or min_p and k_logprobs <= 0 (min_p
- * alone: up to three times as many rows).  Else, without a state, chunk_rescue_kernel alone for batches
- * of up to 128 rows (two chunks of a row or more on a compute unit each, the last of a row's workgroups
- * finishing it).  Else either one workgroup streams and finishes a row --
+ * alone: up to three times as many rows).  Else, without a state, chunk_rescue_kernel alone (two chunks of
+ * a row or more on a compute unit each, the last of a row's workgroups finishing it) for batches of up to
+ * 35 rows whose chunks are short enough for that, and, of up to 128 rows, where nothing but token ids is
+ * asked for and params names no top_k, top_p or min_p.  Else either one workgroup streams and finishes a row --
  * row_rescue_kernel for batches of no more rows than the device has compute units, else row_kernel
  * followed by rescue_kernel (which returns at once when no row was passed on), on a state behind
  * state_take_tick_kernel -- or stream_kernel (the one pass over the logits, in chunks of rows), then
  * finish_rescue_kernel or, for more rows than compute units, finish_kernel followed by rescue_kernel;
- * row_is_chosen() in sip.hip says which, from B, the bytes of a row and whether there is a state;
+ * row_is_chosen() in sip.hip says which, from B, the bytes of a row and whether there is a state, and
+ * sip_call_route() (sip_diag.h) tells it for given arguments;
  * exact_kernel alone for vocabulary sizes outside the single-pass kernels.
  */
 size_t sip_workspace_bytes(int32_t B, int32_t V, sip_dtype dtype, int64_t hist_nnz, int32_t k_logprobs);

@@ -34,7 +34,8 @@ struct Cut {
 struct Plan {
   bool fast;       // false: vocabulary outside what the single-pass kernels are built for
   Cut cut;         // of a row, for the streaming kernel
-  Cut alone;       // the same where no more chunks than compute units are made of the batch, two or more of a row; S = 0: not so
+  Cut beside;      // the same for chunks that have a compute unit each, with room on the chip beside them; S = 0: not so
+  Cut alone;       // and on all of the chip
   int room;        // segments of kChunkCap entries a row has in the workspace
   size_t final_lds;
 };
@@ -146,21 +147,30 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t, bool small_chunks = true)
     c.nc_cap = std::min(sip::kFinalThreads * sip::kCandLong, c.S * c.cap_c);
   };
   share(p.cut, load, kTables);
-  // Half as many rows as compute units and less: a compute unit for each chunk, and the last of a row's workgroups
-  // finishes it (chunk_rescue_kernel).  That saves a launch and what the second kernel waits for at its start, more
-  // than is lost where the streaming kernel would be cut finer.  us a call, two kernels / one (nucleus 0.95, Student-t, 600 tokens;
-  // greedy, ids only): V = 128256 bf16 40 rows 23.0 / 19.8, 15.2 / 12.5, 64 rows 23.2 / 21.3, 15.6 / 13.6, 100 rows
-  // 25.9 / 24.5, 17.3 / 15.7, 128 rows 26.4 / 26.1, 17.5 / 16.1; fp32 64 rows 24.7 / 23.0, 16.2 / 15.0, 128 rows 27.9 / 27.3, 19.2
-  // / 19.6; V = 40000 fp32 100 rows 24.6 / 20.9; V = 200000 bf16 128 rows 28.7 / 28.5.
-  // Such chunks may be longer than the streaming kernel's: V = 152064, 128 rows bf16 26.2 / 26.1, fp32 29.1 / 27.8, 86 rows
-  // fp32 27.5 / 26.5; V = 200000 fp32 128 rows 33.6 / 31.4.  But not those beyond 416 KB that leave more than an eighth of the
-  // units without any: V = 256000 fp32, 100 rows 39.1 / 40.8.
-  p.alone.S = B <= kUnits / 2 ? fit(kUnits / B, sip::kAloneBitsMax) : 0;
-  const int64_t chunk_bytes = p.alone.S > 0 ? (int64_t)V / p.alone.S * (dtype == SIP_F32 ? 4 : 2) : 0;
-  if (p.alone.S < 2 || p.alone.S > p.room || B * p.alone.S > kUnits || (chunk_bytes > 416 * 1024 && B * p.alone.S < kUnits * 7 / 8))
-    p.alone.S = 0;
-  else
-    share(p.alone, 1, kAloneTables);
+  // A compute unit for each chunk, and the last of a row's workgroups finishes it (chunk_rescue_kernel).  That saves a launch and
+  // what the second kernel waits for at its start.  But such a workgroup leaves its compute unit no room for another one (the
+  // heavier logic's 256 registers a lane), where the streaming kernel's chunks of two batches in flight lie side by side.
+  // With 176 workgroups the finishing ones of another batch, and some of its chunks, find room.  us a call, two kernels / as many
+  // chunks as compute units / 176 (nucleus 0.95, Student-t, 600 tokens), one batch at a time; two batches in flight, each
+  // on a stream:
+  //   V = 60000 bf16 16 rows 18.4 / 17.7 / 17.7; 10.0 / 9.1 / 9.1, 32 rows 18.6 / 17.7 / 18.3; 10.7 / 12.3 / 9.9
+  //   V = 128256 bf16 16 rows 18.6 / 17.7 / 18.1; 10.8 / 12.2 / 9.6, 32 rows 19.3 / 18.5 / 19.4; 11.4 / 13.2 / 10.7, 40 rows 20.1 /
+  //   19.0 / 20.2; 12.1 / 13.6 / 12.2, 64 rows (192 workgroups) 20.9 / 20.0 / 21.0; 13.2 / 17.7 / 14.2
+  //   V = 128256 fp32 16 rows 18.6 / 18.1 / 18.4; 11.1 / 12.6 / 9.5, 32 rows 19.7 / 18.9 / 19.9; 12.1 / 13.7 / 11.1, 40 rows 20.3 /
+  //   19.7 / 20.7; 14.2 / 14.3 / 13.3
+  //   V = 200000 bf16 24 rows 19.6 / 18.6 / 19.6; 11.7 / 12.9 / 10.6, 32 rows 20.4 / 19.3 / 20.6; fp32 24 rows 20.2 / 19.3 / 20.1;
+  //   12.4 / 13.8 / 11.2, 32 rows 20.7 / 20.0 / 21.6
+  // So with 176, up to 35 rows and chunks of 36 K elements.
+  auto alone = [&](Cut& c, int units, int fewest, int most) {
+    c.S = B * fewest <= units ? fit(units / B, most) : 0;
+    if (c.S < 2 || c.S > p.room || B * c.S > units) c.S = 0;
+    else share(c, 1, kAloneTables);
+  };
+  alone(p.beside, 176, 5, 36 * 1024);
+  // Greedy rows of which only the ids are wanted have next to nothing to finish, and gain from every compute unit
+  // also with two batches in flight.  us a call, two kernels / one, one batch; two: V = 128256 64 rows bf16 14.1 / 6.9; 9.1 / 5.6, 128 rows
+  // 10.9 / 8.3; 7.6 / 7.1, fp32 15.8 / 14.7; 12.3 / 10.9; V = 262144 fp32 100 rows 26.6 / 18.9.
+  alone(p.alone, kUnits, 2, sip::kAloneBitsMax);
   p.final_lds = sip::final_lds_fixed(V);
   return p;
 }
@@ -387,6 +397,12 @@ bool row_is_chosen(int32_t B, int32_t V, int dtype, bool state, int compute_unit
   return B <= 2 * cu ? B >= cu * 23 / 16 : B >= cu * 75 / 32;
 }
 
+// Whether a call's rows are greedy ones of which only the ids are wanted, as far as can be told here: no filter is handed in, and
+// no log-probabilities are asked for.  (Rows sampled without any filter look the same, and pay with two batches in flight for what
+// greedy ones gain: us a call, two kernels / one, one batch; two: 64 rows of V = 128256 bf16 24.5 / 23.7; 14.7 / 20.5, fp32 26.9
+// / 26.4; 18.2 / 21.3.)
+bool greedy_ids(const sip_params& params, int32_t k_lp) { return k_lp < 0 && !params.top_k && !params.top_p && !params.min_p; }
+
 // The kernels of a call, and how its rows are cut where they are cut at all.
 struct Way {
   sip_route route;
@@ -400,7 +416,8 @@ Way choose_way(const Plan& plan, const sip_params& params, int32_t k_lp, int32_t
   if (!plan.fast) return {SIP_ROUTE_EXACT};
   const bool fused = B <= compute_units && (size_t)plan.final_lds <= sip::kFusedRawBytes &&
                      2 * (((size_t)V + 31) / 32) * sizeof(uint32_t) <= sip::kFusedRawBytes;
-  if (plan.alone.S && fused && !state) return {SIP_ROUTE_CHUNKS_ALONE, &plan.alone};
+  const Cut& each = greedy_ids(params, k_lp) ? plan.alone : plan.beside;
+  if (each.S && fused && !state) return {SIP_ROUTE_CHUNKS_ALONE, &each};
   if (row_is_chosen(B, V, dtype, state, compute_units)) return {fused ? SIP_ROUTE_ROW_FUSED : SIP_ROUTE_ROW};
   return {fused ? SIP_ROUTE_CHUNKS_FUSED : SIP_ROUTE_CHUNKS, &plan.cut};
 }

@@ -14,6 +14,7 @@ constexpr float kFixScale = 1099511627776.0f;   // 2^40
 // Bit 31 of a list entry's index: the token occurs in the row's history and the row has a penalty
 // switched on, so the entry's value is the raw logit that the penalty still has to be applied to.
 constexpr uint32_t kTagBit = 0x80000000u;
+constexpr int kArgMaxOnly = -1;                      // RowInfo::target: the chunks' largest values are all that the row's record says
 constexpr int kPromptFlag = 1 << 30;             // RowInfo::target: tokens of a separate prompt are tagged too
 constexpr uint32_t kCntOverflow = 0xFFFFFFFFu;   // ChunkOut::cnt of a chunk whose queue overflowed
 

@@ -106,6 +106,24 @@ struct FinHint {
   float T = 0.0f;            // every element of the row above T is in the list
 };
 
+// Row b of which stream_part() has left the arg max, `best` (uniform).  Returns like finish_row().
+__device__ __forceinline__ int finish_greedy(const Args& a, const int b, const unsigned long long best) {
+  if (best) {
+    if (threadIdx.x == 0) {
+      a.out_ids[b] = (int)~(uint32_t)best;
+      if (a.slot) state_append_row(a, b);
+    }
+    return 1;
+  }
+  // No value above -inf: the general path's, which finds no list.
+  if (threadIdx.x < (uint32_t)a.S) {
+    ChunkOut none{};
+    none.cnt = kCntOverflow;
+    a.chunks[(size_t)b * (size_t)a.S + threadIdx.x] = none;
+  }
+  return 3;
+}
+
 // Row b, start to finish.  Returns 1 or kFinWholeRow (finished: outputs written) or the reason why the list
 // does not settle the row.  Every return value is workgroup-uniform.
 // ROW: the calling workgroup has made the list itself, as one segment; `hand` holds the row's record and
@@ -177,6 +195,18 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
     Tc = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(co.Tc)));   // the chunks of a row share
     off_c = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(co.off)));   // both
     bulk_unit = __longlong_as_double((long long)readlane_u64((unsigned long long)__double_as_longlong(co.unit), 0));
+  }
+  if constexpr (!ROW && !RECORD) {
+    if (ri.target == kArgMaxOnly) {                                            // uniform
+      list_is_used();
+      unsigned long long best = 0;
+      for (int c = 0; c < S; ++c) {
+        const unsigned long long x = readlane_u64(my_bulk, c);
+        best = x > best ? x : best;
+      }
+      __syncthreads();                       // (finish_greedy() may write over the summaries)
+      return finish_greedy(a, b, best);
+    }
   }
   if ((ri.target & ~kPromptFlag) == 0) { list_is_used(); return 2; }          // uniform: k beyond any list
   const bool prompt_on = (ri.target & kPromptFlag) != 0;                     // tokens of a separate prompt are tagged too
@@ -1051,24 +1081,6 @@ __device__ __forceinline__ int finish_row(const Args& a, const int b, FinShared&
   if (code != 1) return code;                                                  // uniform
   if (tid == 0) emit(fs.token, fs.token_key, fs.ln_total);
   return settled;
-}
-
-// Row b of which stream_part() has left the arg max, `best` (uniform).  Returns like finish_row().
-__device__ __forceinline__ int finish_greedy(const Args& a, const int b, const unsigned long long best) {
-  if (best) {
-    if (threadIdx.x == 0) {
-      a.out_ids[b] = (int)~(uint32_t)best;
-      if (a.slot) state_append_row(a, b);
-    }
-    return 1;
-  }
-  // No value above -inf: the general path's, which finds no list.
-  if (threadIdx.x < (uint32_t)a.S) {
-    ChunkOut none{};
-    none.cnt = kCntOverflow;
-    a.chunks[(size_t)b * (size_t)a.S + threadIdx.x] = none;
-  }
-  return 3;
 }
 
 __global__ __launch_bounds__(kFinThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void finish_kernel(Args a_by_value) {

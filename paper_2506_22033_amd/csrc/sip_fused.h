@@ -106,10 +106,9 @@ __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2
 // The same where the batch is so small that a row's chunks have a compute unit each: the last of a row's workgroups
 // to be done with its chunk finishes the row.  What a second kernel costs -- 2.4 us until it starts, cold arguments and
 // records -- goes; what the workgroups pay to agree is 1 us: their stores' way to memory (put(): written back from
-// the XCD's L2 by each of them instead, chat_64 took 29.6 us), the addition to the row's word, its answer.  us a call, two
-// kernels / one: one row of V = 128256 bf16 18.7 / 18.5, 32 rows with 8000 prompt tokens 25.9 / 25.0, 64 rows 26.7 /
-// 26.3, 31 rows of V = 64712 fp32 29.8 / 28.4, 9 of V = 65536 in pieces 20.7 / 19.8 (Plan::alone has more).  What bounds
-// it: latency, the set-up's chain of 4.5 us and the finishing's of 13.
+// the XCD's L2 by each of them instead, 64 rows of V = 128256 bf16 took 29.6 us for 26.3), the addition to the row's word, its
+// answer.  Times and the rule for it are at make_plan().  What bounds it: latency, the set-up's chain of 5 us, 4 us from the
+// last chunk to the finishing and 11 us of that.
 template <int DT, bool SH, bool IDS>
 __global__ __launch_bounds__(kFinalThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void chunk_rescue_kernel(Args a_by_value) {
   (void)a_by_value;

@@ -39,7 +39,7 @@ constexpr int kSampleSize = 8192;           // elements of a row the threshold i
 constexpr int kQueueCap = 480;              // entries of one wave's LDS candidate queue where four workgroups share a compute unit
 constexpr int kChunkCap = kStreamWaves * kQueueCap;   // entries of such a chunk's segment in the workspace
 constexpr int kChunkBitsMax = 73728;        // most elements a chunk may have (history bitmap: 9 KB of LDS)
-constexpr int kAloneBitsMax = 131072;       // one that has a compute unit to itself (16 KB)
+constexpr int kAloneBitsMax = 131072;       // one that has a compute unit to itself (16 KB; only where ids alone are asked for that long)
 constexpr int kRowBitsMax = 262144;         // and a row that one workgroup streams (32 KB)
 // What differs between a workgroup that streams one chunk of a row for the finishing kernel (ROW =
 // false: four workgroups per compute unit, 40 KB of LDS and 64 registers each) and one that streams the
@@ -486,11 +486,14 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
   // ---- A greedy row without penalties of which only the id is asked for: no threshold, no list.  Every thread keeps
   // the largest of its values, the load that has the first of them and that load's place.  What bounds it: the memory.
   // us a call, by way of a list / so: one row of V = 128256 bf16 11.9 / 7.9, 64 rows fp32 15.5 / 9.7, 128 rows of V = 152064 bf16
-  // 17.7 / 11.0, 256 rows 22.9 / 14.4, 1024 rows of V = 129280 62.5 / 49.4.
-  if constexpr ((ROW || ALONE) && IDS) {
-    hand->greedy = rp.greedy &&
-                   ((rp.theta == 1.0f && rp.phi == 0.0f && rp.psi == 0.0f) || !(a.slot || csr_on || prompt_csr));
-    if (hand->greedy) {                              // uniform
+  // 17.7 / 11.0, 256 rows 22.9 / 14.4, 1024 rows of V = 129280 62.5 / 49.4; in chunks that a second kernel compares 128 rows of V = 152064
+  // 18.1 / 12.6, 150 rows 19.1 / 13.6, 300 rows of V = 60000 fp32 30.8 / 21.2, on a state 64 rows of V = 60000 bf16 37.5 / 30.9.
+  if constexpr (IDS) {
+    const bool arg_max = rp.greedy &&
+                         ((rp.theta == 1.0f && rp.phi == 0.0f && rp.psi == 0.0f) || !(a.slot || csr_on || prompt_csr));
+    if (ROW || ALONE) hand->greedy = arg_max;
+    if (arg_max) {                                   // uniform
+      if (CHAIN_FIRST) __builtin_amdgcn_s_setprio(0);
       if (ALONE && tid == kStreamThreads - kWave) word->open(a.call_mark);
       float top = -INFINITY;
       uint4 top_q = make_uint4(0, 0, 0, 0);
@@ -552,8 +555,9 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
       __syncthreads();
 #pragma unroll
       for (int w = 0; w < kStreamWaves; ++w) mine = sm.red64[w] > mine ? sm.red64[w] : mine;
-      hand->best = mine;
-      if (ALONE && tid == 0) put<ALONE>(reinterpret_cast<unsigned long long*>(a.chunks + wg), mine);
+      if (ROW || ALONE) hand->best = mine;
+      if (!ROW && tid == 0) put<ALONE>(&a.chunks[wg].bulk, mine);
+      if (!ROW && !ALONE && ch == 0 && tid == 0) a.rowinfo[b].target = kArgMaxOnly;
       return true;
     }
   }

@@ -405,3 +405,21 @@ def test_stream_handle_without_the_private_torch_function(monkeypatch):
     assert binding._stream_handle(dev, Stream(5)) == 5 and len(asked) == 1
     monkeypatch.setattr(binding, "_current_raw_stream", lambda index: 100 + index)
     assert binding._stream_handle(dev, None) == 103 and len(asked) == 1
+
+
+@pytest.mark.parametrize("k,params", [(0, ("temperature", "top_p")), (5, ()), (-1, ("temperature", "top_k"))])
+def test_chunks_with_a_compute_unit_each_leave_room_for_another_batch(k, params):
+    """A workgroup of such a chunk fills its compute unit: with more of them than this, two batches in flight took turns
+    instead of running side by side (64 rows of V = 128256 bf16 17.7 us a call for 13.2).  Calls that look like greedy rows of which
+    only ids are wanted may take all of the chip."""
+    seen = 0
+    for dtype in (sip.SIP_F32, sip.SIP_BF16):
+        for t in (0, 2, 4, 8):
+            for V in (33000, 40000, 65536, 100000, 128256, 200000, 262144):
+                for B in range(1, 129):
+                    route, S = sip.sip_call_route(B, V // 64 * 64 if t else V, dtype, t, False, params, 1000 * B, k)
+                    if route == ROUTE_CHUNKS_ALONE:
+                        seen += 1
+                        assert B * S <= 176 and B <= 35, (B, V, dtype, t, S)
+    assert seen > 500
+    assert sip.sip_call_route(128, 152064, sip.SIP_BF16, 0, False, ("temperature",), 0, -1) == (ROUTE_CHUNKS_ALONE, 2)

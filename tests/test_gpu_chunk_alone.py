@@ -21,8 +21,8 @@ def _inputs(B, V, bf16, n_hist, seed, k):
     return H.custom(f"alone_{B}_{V}", workloads.f32_to_bf16_bits(z) if bf16 else z, params, hist, k_logprobs=k)
 
 
-# one row; rows in odd numbers, a grid that is no multiple of the XCDs; the smallest rows of two chunks; chunks of the most
-# elements (V = 131073 and more in two); the last batch size of two chunks and the first beyond it; ids only
+# one row; rows in odd numbers, a grid that is no multiple of the XCDs; the smallest rows of several chunks; batches beyond 35
+# rows, which two kernels serve, or a row to a workgroup; ids only
 @pytest.mark.parametrize("B,V,bf16,n_hist,k", [(1, 40001, False, 50, 3), (1, 262144, True, 3000, 0), (7, 33000, True, 700, 5), (37, 50003, False, 300, 20),
                                                (85, 66001, False, 200, 1), (86, 66001, True, 200, -1), (127, 34567, True, 2500, 2),
                                                (128, 131073, True, 300, 1), (129, 40000, False, 100, 1)])
@@ -84,7 +84,7 @@ def test_recorded_call_replayed():
 
 
 def test_pieces():
-    """Chunks that are whole pieces, parts of one, and as many as there are pieces."""
+    """As many chunks as there are pieces, and several of a piece."""
     rng = np.random.default_rng(4)
     for t, B in ((2, 3), (4, 60), (8, 20)):
         V = 16384 * t
@@ -94,3 +94,47 @@ def test_pieces():
         p = {k: None if v is None else torch.from_numpy(v).to(H.DEV) for k, v in w.params.items()}
         out = sip.sip_sample_sharded(pieces, p, None, None, 3, 1, 3)
         H.compare(w, [x.cpu().numpy() for x in out], 3, 1, rows=range(0, B, 4))
+
+
+# the most rows and, in 36 units of 1024 elements, the longest chunks that go this way; eleven and sixteen chunks; the second to
+# last and the last element of every chunk in a history
+@pytest.mark.parametrize("B,V,bf16,k", [(35, 184320, True, 5), (35, 184317, False, 0), (22, 262142, True, 0), (16, 262144, False, 5), (11, 70003, True, 3)])
+def test_longest_chunks(B, V, bf16, k):
+    rng = np.random.default_rng(V + B)
+    z = (rng.standard_normal((B, V)) * 2.0).astype(np.float32)
+    kind = np.arange(B) % 5                  # no filter, top-p, min-p, top-k, greedy
+    params = dict(temperature=np.choose(kind, [0.8, 0.7, 1.0, 0.9, 0.0]), top_p=np.choose(kind, [1, 0.3, 1, 1, 1]),
+                  min_p=np.choose(kind, [0, 0, 0.05, 0, 0]), top_k=np.choose(kind, [0, 0, 0, 60, 0]), repetition_penalty=np.full(B, 1.3))
+    w = H.custom(f"longest_{V}", workloads.f32_to_bf16_bits(z) if bf16 else z, params, None, k_logprobs=k)
+    route, S = sip.sip_call_route(B, V, sip.SIP_BF16 if bf16 else sip.SIP_F32, 0, False, w.params, 0, k)
+    assert route == 2 and 1 < S and B * S <= 176
+    n = -(-V // 1024)
+    ends = sorted({min((c + 1) * n // S * 1024, V) - i for c in range(S) for i in (1, 2)})
+    w = H.custom(f"longest_{V}", w.logits, params, [ends + rng.integers(0, V, 100).tolist() for _ in range(B)], k_logprobs=k)
+    H.compare(w, H.run_gpu(H.to_device(w), 5, 1), 5, 1, rows=range(0, B, 2))
+    assert (H.last_row_why == 1).all(), H.last_row_why
+
+
+# ids only and no filter: chunks of up to 131072 elements (128 blocks), and of several whole pieces (three of 43000 elements have
+# load numbers of six bits)
+@pytest.mark.parametrize("B,V,bf16,t,S", [(128, 262144, False, 0, 2), (128, 262142, True, 0, 2), (86, 200001, True, 0, 2), (37, 262143, False, 0, 6),
+                                          (128, 258000, True, 6, 2), (66, 258000, False, 6, 3), (100, 131072, True, 8, 2), (100, 100000, False, 4, 2)])
+def test_ids_of_rows_without_a_filter(B, V, bf16, t, S):
+    rng = np.random.default_rng(V + B)
+    z = (rng.standard_normal((B, V)) * 2.0).astype(np.float32)
+    z[0, V - 1] = z[3, V // 2 - 1] = z[4, V // 2] = 30.0
+    kind = np.arange(B) % 3
+    params = dict(temperature=np.choose(kind, [0.0, 0.8, 0.0]), repetition_penalty=np.choose(kind, [1.0, 1.2, 1.2]))
+    hist = [np.concatenate(([V - 1, V // S - 1, 0], rng.integers(0, V, 50))).tolist() for _ in range(B)]
+    w = H.custom(f"no_filter_{V}", workloads.f32_to_bf16_bits(z) if bf16 else z, params, hist, k_logprobs=-1)
+    assert sip.sip_call_route(B, V, sip.SIP_BF16 if bf16 else sip.SIP_F32, t, False, w.params, 53 * B, -1) == (2, S)
+    d = H.to_device(w)
+    rows = sorted(set(range(0, B, max(1, B // 24))) | {3, 4, B - 1})
+    if t:
+        n = V // t
+        ids, _, _ = sip.sip_sample_sharded([d.logits[:, i * n:(i + 1) * n].contiguous() for i in range(t)], d.params, d.indptr, d.tokens, 3, 1, -1)
+        out = (ids.cpu().numpy(), None, None)
+    else:
+        out = H.run_gpu(d, 3, 1, k_logprobs=-1)
+        assert (H.last_row_why == 1).all(), H.last_row_why
+    H.compare(w, out, 3, 1, rows=rows, k_logprobs=-1)

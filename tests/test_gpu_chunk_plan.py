@@ -35,6 +35,7 @@ def test_history_in_one_chunk(B, V, bf16, S, n):
     """Three rows' histories lie in the first of the row's S chunks: more of them for each of its eight queues than the 480
     entries that a queue has where four workgroups share a compute unit."""
     assert sip.binding.load().sip_plan_chunks(B, V, sip.SIP_BF16 if bf16 else sip.SIP_F32, 0) == S
+    assert sip.sip_call_route(B, V, sip.SIP_BF16 if bf16 else sip.SIP_F32, 0, False, ("top_k", "min_p"), 3 * n, 2) == (5, S)
     assert n > 1.5 * 8 * 480
     rng = np.random.default_rng(V + B)
     z = (rng.standard_normal((B, V)) * 2.0).astype(np.float32)
