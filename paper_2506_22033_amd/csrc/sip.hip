@@ -343,18 +343,20 @@ sip_status launch(const sip::Args& a, int32_t B, int dtype, const Plan& plan, bo
 // but pay for a row that its list does not settle: a nucleus that outgrows it, or queues that overflow
 // (bf16 rows of one chunk under a wide min-p).  Which rows are like that, or greedy, is not known here;
 // which parameters the call has is.  us, by streaming / in registers (fp32 unless said, 256 compute units,
-// the present kernels on both sides; normal logits of standard deviation 2.5 unless said):
-//   up to one row per compute unit, V = 32768, 64 rows: greedy 16 / 10; no filter 23 / 12.5; min-p 20 / 13.5;
-//   top-k 19 / 18; top-k and top-p 19 / 21.5; top-p, peaked rows 23 / 23, Student-t 19 / 17, flat rows 63 / 28 (bf16
-//   61 / 29); all parameters, 512 tokens of history, best 20: 23 / 28, V = 24000 bf16, 256 rows 22 / 26.
-//   V = 32000, 1 to 64 rows of all four modes (greedy, top-k, top-p 0.9, min-p) with 256 tokens of history: Student-t
-//   21 / 19 from 4 rows on; normal logits, whose nuclei outgrow their lists, 65 to 71 / 26.
-//   So: in registers, up to a quarter slower on the rows that a list settles and several times faster
-//   where one of them is not; but rows without any filter that ask for best-n, which are always settled from
-//   a list, by streaming: V = 32768, 64 rows, best 5, greedy 17 / 15 normal, 17 / 24 Student-t; sampled 23 / 18, 23 /
-//   27.
-//   V = 24000, 2048 rows: greedy 77 / 75; no filter 109 / 93; min-p 95 / 99, V = 32000 and 512 tokens
-//   of history 126 / 143, 600 rows of it 56 / 54; top-k and top-p 91 / 151; top-p, peaked 114 / 153.
+// the present kernels on both sides; normal logits of standard deviation 2.5 unless said; "Student-t" has a spike a row):
+//   up to one row per compute unit, V = 32768, 64 rows: greedy 15 / 10; no filter 22 / 12.5; min-p 20 / 13;
+//   top-k and top-p 18.5 / 21; top-p, peaked rows 22 / 22, Student-t 18 / 16; all parameters, 512 tokens of history,
+//   best 20: 25 / 32, V = 24000 bf16, 256 rows 25 / 28.  16 rows, whose chunks one kernel streams and finishes: greedy 13.5 / 10,
+//   no filter 20 / 12, min-p 17.5 / 13, top-k and top-p 17 / 21, top-p, peaked 20 / 22, Student-t 17 / 16, all parameters
+//   23.5 / 32.
+//   V = 32000, rows of all four modes (greedy, top-k, top-p 0.9, min-p), 256 tokens of history, best 5: normal logits, whose
+//   nuclei outgrow their lists, 4 to 64 rows 65 to 73 / 27; Student-t 17 to 19 / 30.
+//   So: in registers, up to a third slower on rows that a list settles (up to three quarters with best-n
+//   beside a spike) and several times faster where one of them is not; but rows without any filter that ask for best-n,
+//   which are always settled from a list, by streaming: V = 32768, 64 rows, best 5, greedy 16 / 15 normal, 16 / 24 Student-t;
+//   sampled 22 / 17.5, 22 / 27.
+//   V = 24000, 2048 rows: greedy 74 / 75; no filter 106 / 93; min-p 93.5 / 99, V = 32000 and 512 tokens
+//   of history 111 / 143, 600 rows of it 49 / 54; top-k and top-p 87 / 150; top-p, peaked 107 / 144.
 //   So: in registers without a filter, min-p alone up to three rounds.
 bool resident_is_chosen(const sip_params& params, int32_t k_lp, int32_t B, bool state, int compute_units) {
   // A state's call would have to take its number in a launch of its own before this kernel (the
@@ -370,7 +372,7 @@ bool resident_is_chosen(const sip_params& params, int32_t k_lp, int32_t B, bool 
 // finishing kernel.  A row to a workgroup pays the set-up once and overlaps one row's finishing with
 // another's streaming, or at least needs no second kernel; but up to one row per compute unit it leaves
 // chip idle that chunks would use, and beyond that the rows come in rounds of two per compute unit.
-// us a call in chunks / a row to a workgroup (256 compute units; nucleus 0.95, Student-t, 600 tokens):
+// us a call in chunks for two kernels / a row to a workgroup (256 compute units; nucleus 0.95, Student-t, 600 tokens):
 //   V = 40000 bf16 (80 KB): 64 rows 19.7 / 20.1, 96 21.0 / 20.2, 256 25.0 / 20.9; fp32 (160 KB): 96 21.6 / 21.5, 128
 //   22.0 / 21.8
 //   V = 128256 bf16 (256 KB): 128 26.3 / 28.0, 144 28.1 / 28.1, 176 30.0 / 28.3, 256 32.5 / 28.7

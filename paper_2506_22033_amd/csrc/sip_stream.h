@@ -878,7 +878,7 @@ __device__ __forceinline__ bool stream_part(const Args& a, const int wg, unsigne
   // which bulk_term() leaves out: what belongs to the list must not pass through the fp32 sums, not even to be
   // taken out again (6000 tokens around the threshold, penalised away: 3e-5 of the total was left behind).  `it`: the
   // wave's load number in its chunk.  A queue entry is the element's value and its place: fp32 (bits, vocabulary
-  // id); bf16 one word, the value's 16 bits above load number, lane and element (5 or 7 + 6 + 3 bits).
+  // id); bf16 one word, the value's 16 bits above load number, lane and element (5, 6 or 7 + 6 + 3 bits).
   // Whether it is a history token is looked up again when the queue goes out.
   auto process = [&](const uint4& q, int e0, int it, bool guard, uint32_t hb, const uint4& tg) {
     float z[EPL];
