@@ -418,9 +418,13 @@ Way choose_way(const Plan& plan, const sip_params& params, int32_t k_lp, int32_t
   if (!plan.fast) return {SIP_ROUTE_EXACT};
   const bool fused = B <= compute_units && (size_t)plan.final_lds <= sip::kFusedRawBytes &&
                      2 * (((size_t)V + 31) / 32) * sizeof(uint32_t) <= sip::kFusedRawBytes;
+  // (Where a row would have a workgroup of its own if it were not for chunks on a compute unit each -- 80 to 128 short rows of
+  // which the ids are asked for --, it has: greedy ones, chunks / a row to a workgroup, recorded calls, one batch; two in flight, V = 33000
+  // bf16 86 rows 7.0 / 5.1; 4.5 / 2.8, V = 40000 128 rows bf16 6.8 / 5.3; 5.2 / 3.1, fp32 6.9 / 5.4; 6.1 / 4.0, V = 60000 bf16 7.1 / 5.9; 5.5 / 3.4;
+  // sampled ones V = 40000 fp32 23.8 / 24.8; 20.2 / 13.8.)
+  if (row_is_chosen(B, V, dtype, state, compute_units)) return {fused ? SIP_ROUTE_ROW_FUSED : SIP_ROUTE_ROW};
   const Cut& each = greedy_ids(params, k_lp) ? plan.alone : plan.beside;
   if (each.S && fused && !state) return {SIP_ROUTE_CHUNKS_ALONE, &each};
-  if (row_is_chosen(B, V, dtype, state, compute_units)) return {fused ? SIP_ROUTE_ROW_FUSED : SIP_ROUTE_ROW};
   return {fused ? SIP_ROUTE_CHUNKS_FUSED : SIP_ROUTE_CHUNKS, &plan.cut};
 }
 

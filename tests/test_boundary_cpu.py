@@ -347,6 +347,12 @@ def test_kernels_of_a_call(B, V, dtype, state, k, route):
     assert sip.sip_call_route(B, V, dtype, 0, state, ("temperature", "top_p"), 0, k)[0] == route
 
 
+@pytest.mark.parametrize("B,V,dtype,route", [(128, 152064, sip.SIP_BF16, 2), (128, 40000, sip.SIP_BF16, 3), (128, 40000, sip.SIP_F32, 3),
+                                             (64, 40000, sip.SIP_BF16, 2), (100, 262144, sip.SIP_F32, 2), (129, 152064, sip.SIP_BF16, 5)])
+def test_kernels_of_a_call_that_greedy_rows_make(B, V, dtype, route):
+    assert sip.sip_call_route(B, V, dtype, 0, False, ("temperature",), 0, -1)[0] == route
+
+
 def test_route_of_no_call():
     for bad in (dict(B=0), dict(V=0), dict(dtype=3), dict(t_shards=9), dict(V=20001, t_shards=2), dict(k_logprobs=-2), dict(hist_nnz=-1)):
         with pytest.raises(ValueError):
