@@ -31,11 +31,12 @@ def _rows(B, V, bf16, seed):
     return workloads.f32_to_bf16_bits(z) if bf16 else z
 
 
-# one row in many chunks; odd numbers of rows and elements; the most elements of a chunk that has a compute unit to itself, in two; two
-# kernels; a row to a workgroup, one round and several; pieces
+# one row in many chunks; odd numbers of rows and elements; chunks that the finishing kernels compare, with the heavier logic in the
+# same kernel and behind it; a row to a workgroup, one round and several; pieces
 @pytest.mark.parametrize("B,V,bf16,t", [(1, 152064, True, 0), (13, 33001, False, 0), (37, 40003, True, 0), (86, 150001, True, 0),
                                         (128, 262144, False, 0), (128, 262142, True, 0), (140, 100000, True, 0), (230, 33333, False, 0),
-                                        (300, 40001, True, 0), (24, 8192 * 8, False, 8), (100, 40000, True, 2), (230, 32768, True, 4)])
+                                        (300, 40001, True, 0), (260, 52003, False, 0), (24, 8192 * 8, False, 8), (100, 40000, True, 2), (230, 32768, True, 4),
+                                        (260, 52000, False, 4)])
 def test_arg_max(B, V, bf16, t):
     z = _rows(B, V, bf16, V + B)
     kind = np.arange(B) % 12
@@ -58,7 +59,7 @@ def test_arg_max(B, V, bf16, t):
     H.compare(w, out, 3, 1, rows=rows, k_logprobs=-1)
 
 
-@pytest.mark.parametrize("B,V", [(3, 50001), (200, 40001), (1100, 33001)])
+@pytest.mark.parametrize("B,V", [(3, 50001), (200, 40001), (300, 60001), (1100, 33001)])
 def test_nothing_above_minus_infinity(B, V):
     """The general path's, beside rows that have something: no list is there for it.  And a state gets the ids."""
     z = torch.randn(B, (V + 3) // 4 * 4, device=H.DEV)
