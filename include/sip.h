@@ -113,7 +113,7 @@ typedef struct {
  * for; for larger batches only if params names no top_k, top_p or min_p and k_logprobs <= 0 (min_p
  * alone: up to three times as many rows).  Else, without a state, chunk_rescue_kernel alone (two chunks of
  * a row or more on a compute unit each, the last of a row's workgroups finishing it) for batches of up to
- * 35 rows whose chunks are short enough for that, and, of up to 128 rows that are not so short that each has
+ * 32 rows whose chunks are short enough for that, and, of up to 128 rows that are not so short that each has
  * a workgroup, where nothing but token ids is asked for and params names no top_k, top_p or min_p.  Else
  * either one workgroup streams and finishes a row --
  * row_rescue_kernel for batches of no more rows than the device has compute units, else row_kernel

@@ -160,17 +160,20 @@ Plan make_plan(int32_t B, int32_t V, int dtype, int t, bool small_chunks = true)
   //   19.7 / 20.7; 14.2 / 14.3 / 13.3
   //   V = 200000 bf16 24 rows 19.6 / 18.6 / 19.6; 11.7 / 12.9 / 10.6, 32 rows 20.4 / 19.3 / 20.6; fp32 24 rows 20.2 / 19.3 / 20.1;
   //   12.4 / 13.8 / 11.2, 32 rows 20.7 / 20.0 / 21.6
-  // So with 176, up to 35 rows and chunks of 36 K elements.
-  auto alone = [&](Cut& c, int units, int fewest, int most) {
-    c.S = B * fewest <= units ? fit(units / B, most) : 0;
+  //   V = 128256 bf16 35 rows without a filter 23.1 / 23.0 / 23.8; 13.5 / 17.2 / 15.1, V = 40000 21.8 / 21.8 / 21.8; 11.5 / 13.5 / 13.4
+  // So with 176, up to 32 rows and chunks of 36 K elements.
+  auto alone = [&](Cut& c, int units, int rows, int most) {
+    c.S = B <= rows ? fit(units / B, most) : 0;
     if (c.S < 2 || c.S > p.room || B * c.S > units) c.S = 0;
     else share(c, 1, kAloneTables);
   };
-  alone(p.beside, 176, 5, 36 * 1024);
-  // Greedy rows of which only the ids are wanted have next to nothing to finish, and gain from every compute unit
-  // also with two batches in flight.  us a call, two kernels / one, one batch; two: V = 128256 64 rows bf16 14.1 / 6.9; 9.1 / 5.6, 128 rows
-  // 10.9 / 8.3; 7.6 / 7.1, fp32 15.8 / 14.7; 12.3 / 10.9; V = 262144 fp32 100 rows 26.6 / 18.9.
-  alone(p.alone, kUnits, 2, sip::kAloneBitsMax);
+  alone(p.beside, 176, 32, 36 * 1024);
+  // Greedy rows of which only the ids are wanted have next to nothing to finish, and where that does not serve them gain from
+  // every compute unit, also with two batches in flight.  us a call, two kernels / one, one batch; two: V = 128256 64 rows bf16 8.0 /
+  // 7.0; 5.6 / 5.6, fp32 9.4 / 7.4; 9.4 / 7.5, 128 rows bf16 10.9 / 8.4; 7.7 / 7.1, fp32 15.8 / 14.7; 12.1 / 10.8; V = 262144 fp32 100 rows 21.5
+  // / 19.5; 17.5 / 13.9.  (16 rows of V = 128256 bf16 two kernels / 256 workgroups / 176: 7.5 / 8.2 / 7.5; 4.3 / 5.7 / 4.2, fp32 7.6 / 8.0 / 7.7; 4.4 / 5.9 /
+  // 4.4; 32 rows bf16 7.5 / 6.9 / 7.0; 4.4 / 5.3 / 4.1.)
+  alone(p.alone, kUnits, kUnits / 2, sip::kAloneBitsMax);
   p.final_lds = sip::final_lds_fixed(V);
   return p;
 }
@@ -423,7 +426,7 @@ Way choose_way(const Plan& plan, const sip_params& params, int32_t k_lp, int32_t
   // bf16 86 rows 7.0 / 5.1; 4.5 / 2.8, V = 40000 128 rows bf16 6.8 / 5.3; 5.2 / 3.1, fp32 6.9 / 5.4; 6.1 / 4.0, V = 60000 bf16 7.1 / 5.9; 5.5 / 3.4;
   // sampled ones V = 40000 fp32 23.8 / 24.8; 20.2 / 13.8.)
   if (row_is_chosen(B, V, dtype, state, compute_units)) return {fused ? SIP_ROUTE_ROW_FUSED : SIP_ROUTE_ROW};
-  const Cut& each = greedy_ids(params, k_lp) ? plan.alone : plan.beside;
+  const Cut& each = greedy_ids(params, k_lp) && !plan.beside.S ? plan.alone : plan.beside;
   if (each.S && fused && !state) return {SIP_ROUTE_CHUNKS_ALONE, &each};
   return {fused ? SIP_ROUTE_CHUNKS_FUSED : SIP_ROUTE_CHUNKS, &plan.cut};
 }

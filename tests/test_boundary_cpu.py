@@ -426,6 +426,6 @@ def test_chunks_with_a_compute_unit_each_leave_room_for_another_batch(k, params)
                     route, S = sip.sip_call_route(B, V // 64 * 64 if t else V, dtype, t, False, params, 1000 * B, k)
                     if route == ROUTE_CHUNKS_ALONE:
                         seen += 1
-                        assert B * S <= 176 and B <= 35, (B, V, dtype, t, S)
+                        assert B * S <= 176 and B <= 32, (B, V, dtype, t, S)
     assert seen > 500
     assert sip.sip_call_route(128, 152064, sip.SIP_BF16, 0, False, ("temperature",), 0, -1) == (ROUTE_CHUNKS_ALONE, 2)
