@@ -403,9 +403,9 @@ bool row_is_chosen(int32_t B, int32_t V, int dtype, bool state, int compute_unit
 }
 
 // Whether a call's rows are greedy ones of which only the ids are wanted, as far as can be told here: no filter is handed in, and
-// no log-probabilities are asked for.  (Rows sampled without any filter look the same, and pay with two batches in flight for what
-// greedy ones gain: us a call, two kernels / one, one batch; two: 64 rows of V = 128256 bf16 24.5 / 23.7; 14.7 / 20.5, fp32 26.9
-// / 26.4; 18.2 / 21.3.)
+// no log-probabilities are asked for.  (Rows sampled without any filter look the same, and beyond 32 of them pay with two batches in
+// flight for what greedy ones gain: us a call, two kernels / one, one batch; two: 64 rows of V = 128256 bf16 24.5 / 23.7; 15.1 / 20.5, fp32
+// 26.7 / 26.1; 18.0 / 21.8.)
 bool greedy_ids(const sip_params& params, int32_t k_lp) { return k_lp < 0 && !params.top_k && !params.top_p && !params.min_p; }
 
 // The kernels of a call, and how its rows are cut where they are cut at all.
